@@ -107,6 +107,20 @@ int check_r(int64_t r) {
 
 static hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s); }
 
+// Plans a call's `work` (an int(Arena &)).  A workspace below the plan's
+// size, but large enough for the lean plan (fewer partial results: slower,
+// the same sums in another grouping), is still accepted: plan.lean is set.
+template <class F>
+static int plan_work(Arena &plan, size_t ws_bytes, F work) {
+  Arena lean = plan;
+  lean.lean = true;
+  int rc = work(plan);
+  if (rc || ws_bytes >= plan.peak) return rc;
+  if ((rc = work(lean))) return rc;
+  plan = lean;
+  return 0;
+}
+
 // plan + run helpers shared by the entry points, psk_workspace_size and the
 // request server
 int do_sketch_cs(const psk_mat &A, int64_t r, uint64_t seed, void *SA, Arena &ws,
@@ -412,12 +426,16 @@ int sketch_gcs(const psk_mat *A, int64_t m, int64_t r, uint64_t seed, int prec,
   if (!C) return fail(PSK_EINVAL, "C is NULL");
   Arena plan;
   if ((rc = validate_csr(*A, plan, nullptr))) return rc;
-  if ((rc = do_sketch_gcs(*A, m, r, seed, prec, nullptr, plan, nullptr))) return rc;
+  auto work = [&](Arena &ws) {
+    return do_sketch_gcs(*A, m, r, seed, prec, C, ws, as_stream(stream));
+  };
+  if ((rc = plan_work(plan, ws_bytes, work))) return rc;
   if (!wsp || ws_bytes < plan.peak)
     return fail(PSK_ENOMEM, "workspace smaller than psk_workspace_size(PSK_OP_SKETCH_GCS)");
   Arena ws = Arena::over(wsp, ws_bytes);
   if ((rc = validate_csr(*A, ws, as_stream(stream)))) return rc;
-  return do_sketch_gcs(*A, m, r, seed, prec, C, ws, as_stream(stream));
+  ws.lean = plan.lean;
+  return work(ws);
 }
 
 int osnap_hash(int64_t row0, int64_t count, int64_t s, int64_t r, uint64_t seed, int32_t *h,
@@ -444,12 +462,16 @@ int sketch_osnap(const psk_mat *A, int64_t s, int64_t m, int64_t r, uint64_t see
   if (!C) return fail(PSK_EINVAL, "C is NULL");
   Arena plan;
   if ((rc = validate_csr(*A, plan, nullptr))) return rc;
-  if ((rc = do_sketch_osnap(*A, s, m, r, seed, prec, nullptr, plan, nullptr))) return rc;
+  auto work = [&](Arena &ws) {
+    return do_sketch_osnap(*A, s, m, r, seed, prec, C, ws, as_stream(stream));
+  };
+  if ((rc = plan_work(plan, ws_bytes, work))) return rc;
   if (!wsp || ws_bytes < plan.peak)
     return fail(PSK_ENOMEM, "workspace smaller than psk_workspace_size(PSK_OP_SKETCH_OSNAP)");
   Arena ws = Arena::over(wsp, ws_bytes);
   if ((rc = validate_csr(*A, ws, as_stream(stream)))) return rc;
-  return do_sketch_osnap(*A, s, m, r, seed, prec, C, ws, as_stream(stream));
+  ws.lean = plan.lean;
+  return work(ws);
 }
 
 int sketch_g(const psk_mat *A, int64_t m, uint64_t seed, int prec, double *C, void *wsp,
@@ -462,12 +484,16 @@ int sketch_g(const psk_mat *A, int64_t m, uint64_t seed, int prec, double *C, vo
   if (!C) return fail(PSK_EINVAL, "C is NULL");
   Arena plan;
   if ((rc = validate_csr(*A, plan, nullptr))) return rc;
-  if ((rc = do_sketch_g(*A, m, seed, prec, nullptr, plan, nullptr))) return rc;
+  auto work = [&](Arena &ws) {
+    return do_sketch_g(*A, m, seed, prec, C, ws, as_stream(stream));
+  };
+  if ((rc = plan_work(plan, ws_bytes, work))) return rc;
   if (!wsp || ws_bytes < plan.peak)
     return fail(PSK_ENOMEM, "workspace smaller than psk_workspace_size(PSK_OP_SKETCH_G)");
   Arena ws = Arena::over(wsp, ws_bytes);
   if ((rc = validate_csr(*A, ws, as_stream(stream)))) return rc;
-  return do_sketch_g(*A, m, seed, prec, C, ws, as_stream(stream));
+  ws.lean = plan.lean;
+  return work(ws);
 }
 
 int leverage_gram(const psk_mat *A, double *theta, void *wsp, size_t ws_bytes, void *stream) {
@@ -511,13 +537,16 @@ int lsq_sketch_solve(const psk_mat *A, const double *b, double *x, int64_t m, in
   if (!b || !x) return fail(PSK_EINVAL, "b and x must be non-NULL");
   Arena plan;
   if ((rc = validate_csr(*A, plan, nullptr))) return rc;
-  if ((rc = lsq_sketch_solve_impl(*A, nullptr, nullptr, m, r, seed, prec, plan, nullptr)))
-    return rc;
+  auto work = [&](Arena &ws) {
+    return lsq_sketch_solve_impl(*A, b, x, m, r, seed, prec, ws, as_stream(stream));
+  };
+  if ((rc = plan_work(plan, ws_bytes, work))) return rc;
   if (!wsp || ws_bytes < plan.peak)
     return fail(PSK_ENOMEM, "workspace smaller than psk_workspace_size(PSK_OP_LSQ_SKETCH)");
   Arena ws = Arena::over(wsp, ws_bytes);
   if ((rc = validate_csr(*A, ws, as_stream(stream)))) return rc;
-  return lsq_sketch_solve_impl(*A, b, x, m, r, seed, prec, ws, as_stream(stream));
+  ws.lean = plan.lean;
+  return work(ws);
 }
 
 int leverage_sketch(const psk_mat *A, int64_t m, int64_t r, int64_t t, uint64_t seed, int prec,
@@ -528,13 +557,16 @@ int leverage_sketch(const psk_mat *A, int64_t m, int64_t r, int64_t t, uint64_t 
   if (!theta) return fail(PSK_EINVAL, "theta is NULL");
   Arena plan;
   if ((rc = validate_csr(*A, plan, nullptr))) return rc;
-  if ((rc = leverage_sketch_impl(*A, m, r, t, seed, prec, nullptr, true, plan, nullptr)))
-    return rc;
+  auto work = [&](Arena &ws) {
+    return leverage_sketch_impl(*A, m, r, t, seed, prec, theta, true, ws, as_stream(stream));
+  };
+  if ((rc = plan_work(plan, ws_bytes, work))) return rc;
   if (!wsp || ws_bytes < plan.peak)
     return fail(PSK_ENOMEM, "workspace smaller than psk_workspace_size(PSK_OP_LEVERAGE_SKETCH)");
   Arena ws = Arena::over(wsp, ws_bytes);
   if ((rc = validate_csr(*A, ws, as_stream(stream)))) return rc;
-  return leverage_sketch_impl(*A, m, r, t, seed, prec, theta, true, ws, as_stream(stream));
+  ws.lean = plan.lean;
+  return work(ws);
 }
 
 int css_select(const psk_mat *A, int64_t m, int64_t r, int64_t k, uint64_t seed, int prec,
@@ -545,12 +577,16 @@ int css_select(const psk_mat *A, int64_t m, int64_t r, int64_t k, uint64_t seed,
   if (!cols) return fail(PSK_EINVAL, "cols is NULL");
   Arena plan;
   if ((rc = validate_csr(*A, plan, nullptr))) return rc;
-  if ((rc = css_select_impl(*A, m, r, k, seed, prec, nullptr, plan, nullptr))) return rc;
+  auto work = [&](Arena &ws) {
+    return css_select_impl(*A, m, r, k, seed, prec, cols, ws, as_stream(stream));
+  };
+  if ((rc = plan_work(plan, ws_bytes, work))) return rc;
   if (!wsp || ws_bytes < plan.peak)
     return fail(PSK_ENOMEM, "workspace smaller than psk_workspace_size(PSK_OP_CSS)");
   Arena ws = Arena::over(wsp, ws_bytes);
   if ((rc = validate_csr(*A, ws, as_stream(stream)))) return rc;
-  return css_select_impl(*A, m, r, k, seed, prec, cols, ws, as_stream(stream));
+  ws.lean = plan.lean;
+  return work(ws);
 }
 
 int leverage_css(const psk_mat *A, int64_t m, int64_t r, int64_t k, uint64_t seed, int prec,
@@ -562,13 +598,17 @@ int leverage_css(const psk_mat *A, int64_t m, int64_t r, int64_t k, uint64_t see
   Arena plan;
   if ((rc = validate_csr(*A, plan, nullptr))) return rc;
   // planned without the caller's cols, so the bound covers both forms
-  if ((rc = leverage_css_impl(*A, m, r, k, seed, prec, nullptr, nullptr, plan, nullptr)))
-    return rc;
+  auto work = [&](Arena &ws) {
+    return leverage_css_impl(*A, m, r, k, seed, prec, theta, ws.dry() ? nullptr : cols, ws,
+                             as_stream(stream));
+  };
+  if ((rc = plan_work(plan, ws_bytes, work))) return rc;
   if (!wsp || ws_bytes < plan.peak)
     return fail(PSK_ENOMEM, "workspace smaller than psk_workspace_size(PSK_OP_LEVERAGE_CSS)");
   Arena ws = Arena::over(wsp, ws_bytes);
   if ((rc = validate_csr(*A, ws, as_stream(stream)))) return rc;
-  return leverage_css_impl(*A, m, r, k, seed, prec, theta, cols, ws, as_stream(stream));
+  ws.lean = plan.lean;
+  return work(ws);
 }
 
 int gram(double alpha, const psk_mat *A, double beta, void *C, void *wsp,
@@ -666,12 +706,16 @@ int lsq_solve(const psk_mat *A, const double *b, double *x, const psk_lsq_opts *
     return fail(PSK_EDTYPE, "opts->prec must be PSK_PREC_F64, PSK_PREC_BF16 or PSK_PREC_FP8");
   Arena plan;
   if ((rc = validate_csr(*A, plan, nullptr))) return rc;
-  if ((rc = lsq_impl(*A, nullptr, nullptr, o, nullptr, plan, nullptr))) return rc;
+  auto work = [&](Arena &ws) {
+    return lsq_impl(*A, b, x, o, info, ws, as_stream(stream));
+  };
+  if ((rc = plan_work(plan, ws_bytes, work))) return rc;
   if (!wsp || ws_bytes < plan.peak)
     return fail(PSK_ENOMEM, "workspace smaller than psk_workspace_size(PSK_OP_LSQ)");
   Arena ws = Arena::over(wsp, ws_bytes);
   if ((rc = validate_csr(*A, ws, as_stream(stream)))) return rc;
-  return lsq_impl(*A, b, x, o, info, ws, as_stream(stream));
+  ws.lean = plan.lean;
+  return work(ws);
 }
 
 }  // extern "C"

@@ -18,6 +18,7 @@ struct Arena {
   size_t off = 0;
   size_t peak = 0;      // high-water mark (regions may be reused, see mark())
   bool measure = true;  // planning pass: hand out nothing, launch nothing
+  bool lean = false;    // keep the scratch small (the workspace holds no more)
   static Arena over(void *p, size_t bytes) {
     Arena a;
     a.base = (char *)p;

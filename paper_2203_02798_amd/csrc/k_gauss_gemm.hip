@@ -10,8 +10,9 @@
 // in a fixed order by a second kernel, which also applies 1/sqrt(m).
 //
 // Tiling: 512 threads = 8 wavefronts; workgroup tile 128 (rows of G / C) x
-// 256 (columns of C); each wavefront owns 16 rows x 256 columns = 16 MFMA
-// blocks (64 FP64 accumulators per lane).  Generating a Gaussian value costs
+// 256 (columns of C; 128, 64 or 32 for a C that leaves most of 256 empty);
+// each wavefront owns 16 rows x 256 columns = 16 MFMA blocks (64 FP64
+// accumulators per lane).  Generating a Gaussian value costs
 // about as much FP64 vector work as a few matrix instructions, so the wide
 // column tile matters: each value feeds 256 output columns.  K advances 16
 // buckets per chunk: the lane with quad kq = lane/16 draws one Philox block
@@ -21,6 +22,8 @@
 // The S*A chunk is staged through double-buffered LDS with a register
 // prefetch of the next chunk; the LDS row stride (272 doubles) puts the four
 // k rows of one read into two distinct bank halves.
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace psk {
@@ -31,11 +34,7 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
 constexpr int kBM = 16 * kWaves;  // 128
-constexpr int kBN = 256;
-constexpr int kNB = kBN / 16;      // 16 MFMA blocks per wavefront
 constexpr int kBK = 16;
-constexpr int kLdsStride = kBN + 16;
-constexpr int kPf = kBK * kBN / kThreads;  // 8 prefetched values per thread
 
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
 
@@ -46,11 +45,21 @@ typedef __attribute__((address_space(3))) void *lds_ptr_t;
 // slice read as zero (hardware range check); columns past d of a row read
 // the next row's values, which only reach output columns >= d (discarded).
 // Otherwise S*A goes through registers (converted to FP64, masked).
-template <typename T, bool DIRECT>
+// NB: 16-column MFMA blocks per wavefront (a workgroup's tile is 16 NB
+// columns wide).
+template <typename T, bool DIRECT, int NB>
 __global__ __launch_bounds__(kThreads) void k_gauss_gemm_f64(
     int64_t m, int64_t r, int64_t d, uint64_t seed, const T *__restrict__ SA,
     int tiles_m, int tiles_n, int splits, int64_t kper,
     double *__restrict__ out /* [splits][m][d] */) {
+  constexpr int kBN = 16 * NB;
+  constexpr int kNB = NB;
+  constexpr int kLdsStride = kBN + 16;
+  constexpr int kCols = kBN < 256 ? kBN : 256;     // staging: columns a pass covers
+  constexpr int kRows = kThreads / kCols;          // rows a pass covers
+  constexpr int kPf = kBK / kRows;                 // passes
+  static_assert(!DIRECT || kBN == 256, "the direct copy moves 256-column rows");
+  static_assert(kThreads % kCols == 0 && kBK % kRows == 0, "whole staging passes");
   __shared__ __align__(16) double tile[2][kBK][kLdsStride];
 
   // XCD-aware order: blocks are dealt round-robin to the 8 XCDs; renumber so
@@ -80,9 +89,9 @@ __global__ __launch_bounds__(kThreads) void k_gauss_gemm_f64(
 #pragma unroll
   for (int b = 0; b < kNB; ++b) acc[b] = v4d{0.0, 0.0, 0.0, 0.0};
 
-  // S*A staging: thread covers column n0 + (tid % 256), rows tid/256 + 2p
-  const int lcol = tid & (kBN - 1);
-  const int lrow = tid >> 8;
+  // S*A staging: thread covers column n0 + tid % kCols, rows tid / kCols + kRows p
+  const int lcol = tid % kCols;
+  const int lrow = tid / kCols;
   const bool col_ok = (n0 + lcol) < d;
   double pf[kPf];
 
@@ -93,7 +102,7 @@ __global__ __launch_bounds__(kThreads) void k_gauss_gemm_f64(
   auto load_chunk = [&](int64_t k0) {
 #pragma unroll
     for (int p = 0; p < kPf; ++p) {
-      const int64_t k = k0 + lrow + 2 * p;
+      const int64_t k = k0 + lrow + kRows * p;
       const int64_t kc = k < ke ? k : ke - 1;
       const double v = (double)SA[kc * d + ccol];
       pf[p] = (col_ok && k < ke) ? v : 0.0;
@@ -101,7 +110,7 @@ __global__ __launch_bounds__(kThreads) void k_gauss_gemm_f64(
   };
   auto store_chunk = [&](int buf) {
 #pragma unroll
-    for (int p = 0; p < kPf; ++p) tile[buf][lrow + 2 * p][lcol] = pf[p];
+    for (int p = 0; p < kPf; ++p) tile[buf][lrow + kRows * p][lcol] = pf[p];
   };
 
   // direct path: wave w copies rows 2w, 2w+1 of a chunk, 128 doubles per
@@ -187,7 +196,10 @@ __global__ __launch_bounds__(kThreads) void k_gauss_gemm_f64(
   }
 }
 
-// C[i] = scale * sum_s part[s][i], s in increasing order
+// C[i] = scale * sum_s part[s][i], s in increasing order; eight partials are
+// loaded at once (a short C has few wavefronts, so its sums are bound by the
+// latency of one load after another: 200 x 50: 4.5 us for 39 partials, 4.6 for two one
+// by one)
 __global__ __launch_bounds__(256) void k_reduce_splits(const double *__restrict__ part,
                                                        int64_t len, int splits,
                                                        double scale,
@@ -195,8 +207,41 @@ __global__ __launch_bounds__(256) void k_reduce_splits(const double *__restrict_
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= len) return;
   double acc = part[i];
-  for (int s = 1; s < splits; ++s) acc += part[(int64_t)s * len + i];
+  int s = 1;
+  for (; s + 8 <= splits; s += 8) {
+    double v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = part[(int64_t)(s + q) * len + i];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) acc += v[q];
+  }
+  for (; s < splits; ++s) acc += part[(int64_t)s * len + i];
   C[i] = acc * scale;
+}
+
+// Column blocks of a workgroup: the width that costs least over all of C's
+// columns.  A chunk costs about one unit per 16-column block and three to
+// draw its Gaussian values (256 columns: about 5.4 us a chunk, 1 us of it the
+// draw), so 16 blocks unless narrower tiles leave out enough padding.
+int pick_nb(int64_t d) {
+  int best = 16;
+  int64_t least = INT64_MAX;
+  for (int nb : {16, 8, 4, 2}) {
+    const int64_t cost = ceil_div(d, (int64_t)16 * nb) * (nb + 3);
+    if (cost < least) {
+      least = cost;
+      best = nb;
+    }
+  }
+  return best;
+}
+
+template <typename T, bool DIRECT, int NB>
+void launch_f64(int64_t nblk, int64_t m, int64_t r, int64_t d, uint64_t seed, const void *SA,
+                int tiles_m, int tiles_n, int64_t splits, int64_t kper, double *part,
+                hipStream_t st) {
+  k_gauss_gemm_f64<T, DIRECT, NB><<<(unsigned)nblk, kThreads, 0, st>>>(
+      m, r, d, seed, (const T *)SA, tiles_m, tiles_n, (int)splits, kper, part);
 }
 
 }  // namespace
@@ -207,14 +252,28 @@ int gauss_gemm(int64_t m, int64_t r, int64_t d, uint64_t seed, int prec,
   if (prec == PSK_PREC_BF16) return gauss_gemm_bf16(m, r, d, seed, SA, sa_dtype, C, ws, st);
   if (prec == PSK_PREC_FP8) return gauss_gemm_fp8(m, r, d, seed, SA, sa_dtype, C, ws, st);
   if (prec != PSK_PREC_F64) return fail(PSK_EDTYPE, "unknown Gaussian GEMM precision");
+  const int nb = pick_nb(d);
   const int tiles_m = (int)ceil_div(m, kBM);
-  const int tiles_n = (int)ceil_div(d, kBN);
+  const int tiles_n = (int)ceil_div(d, (int64_t)16 * nb);
   const int64_t tiles = (int64_t)tiles_m * tiles_n;
-  // about two rounds of resident workgroups (one 512-thread workgroup per
-  // CU), whole 16-bucket batches, at least 64 batches per split
+  // whole 16-bucket chunks, at most two rounds of resident workgroups (one
+  // 512-thread workgroup per CU; the narrow tiles fit twice) and at least
+  // four chunks a split: a short K is one serial chain of chunks, a few us
+  // each, and most of the chip idles (m = 256, r = 1024, d = 32, with at
+  // least 64 chunks a split and 256-column tiles: 308 us on two workgroups;
+  // now 13 us; m = 200, r = 2500, d = 50: 378 -> 19 us).  A lean workspace keeps the 64.
   const int64_t kchunks = ceil_div(r, kBK);
-  int64_t splits = ceil_div(512, tiles);
-  const int64_t max_splits = kchunks / 64 > 0 ? kchunks / 64 : 1;
+  int64_t splits = (nb == 16 ? 512 : 1024) / tiles;
+  const int64_t whole = kchunks / 64 > 0 ? kchunks / 64 : 1;
+  int64_t max_splits = whole;
+  if (!ws.lean) {
+    // more than 64 chunks' worth only while the partials stay small: 16 of
+    // them, 4 MiB, or half of S*A
+    max_splits = 16;
+    max_splits = std::max(max_splits, ((int64_t)1 << 22) / (m * d * 8));
+    max_splits = std::max(max_splits, r / (2 * m));
+    max_splits = std::max(whole, std::min(max_splits, std::max(kchunks / 4, (int64_t)1)));
+  }
   if (splits > max_splits) splits = max_splits;
   if (splits < 1) splits = 1;
   const int64_t kper = ceil_div(kchunks, splits) * kBK;
@@ -230,15 +289,21 @@ int gauss_gemm(int64_t m, int64_t r, int64_t d, uint64_t seed, int prec,
     const bool direct = sa_dtype == PSK_F64 && (d % 2) == 0 &&
                         ((uintptr_t)SA % 16) == 0 &&
                         (kper + kBK) * d * (int64_t)sizeof(double) + 65536 < ((int64_t)1 << 31);
-    if (direct)
-      k_gauss_gemm_f64<double, true><<<(unsigned)nblk, kThreads, 0, st>>>(
-          m, r, d, seed, (const double *)SA, tiles_m, tiles_n, (int)splits, kper, part);
-    else if (sa_dtype == PSK_F64)
-      k_gauss_gemm_f64<double, false><<<(unsigned)nblk, kThreads, 0, st>>>(
-          m, r, d, seed, (const double *)SA, tiles_m, tiles_n, (int)splits, kper, part);
-    else
-      k_gauss_gemm_f64<float, false><<<(unsigned)nblk, kThreads, 0, st>>>(
-          m, r, d, seed, (const float *)SA, tiles_m, tiles_n, (int)splits, kper, part);
+#define PSK_GG(T, D, NB) \
+  launch_f64<T, D, NB>(nblk, m, r, d, seed, SA, tiles_m, tiles_n, splits, kper, part, st)
+    if (sa_dtype == PSK_F64) {
+      if (nb == 16 && direct) PSK_GG(double, true, 16);
+      else if (nb == 16) PSK_GG(double, false, 16);
+      else if (nb == 8) PSK_GG(double, false, 8);
+      else if (nb == 4) PSK_GG(double, false, 4);
+      else PSK_GG(double, false, 2);
+    } else {
+      if (nb == 16) PSK_GG(float, false, 16);
+      else if (nb == 8) PSK_GG(float, false, 8);
+      else if (nb == 4) PSK_GG(float, false, 4);
+      else PSK_GG(float, false, 2);
+    }
+#undef PSK_GG
   }
   const int64_t len = m * d;
   {

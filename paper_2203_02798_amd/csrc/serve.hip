@@ -42,6 +42,7 @@ struct Job {
   int64_t ticket = 0;
   size_t ws_bytes = 0;
   size_t ws_off = SIZE_MAX;
+  bool lean = false;  // planned lean: its full plan exceeds the whole pool
   double t_submit = 0, t_start = 0, t_end = 0;
   int status = PSK_OK;
   psk_lsq_info info{};
@@ -55,8 +56,9 @@ int leverage_run(const psk_request &q, Arena &ws, hipStream_t st) {
                               false, ws, st);
 }
 
-int plan_request(const psk_request &q, size_t *bytes) {
+int plan_request(const psk_request &q, bool lean, size_t *bytes) {
   Arena plan;
+  plan.lean = lean;
   int rc = validate_csr(q.A, plan, nullptr);
   if (rc) return rc;
   if (q.op == PSK_REQ_LSQ) {
@@ -109,6 +111,7 @@ struct Server {
       lk.unlock();
       cv_work.notify_all();  // the next request may fit as well
       Arena ws = Arena::over(pool + job->ws_off, job->ws_bytes);
+      ws.lean = job->lean;
       // a malformed CSR A ends the request before any kernel walks it
       int rc = validate_csr(job->req.A, ws, st);
       if (!rc)
@@ -191,12 +194,15 @@ int psk_server_submit(psk_server *srv, const psk_request *q, int64_t *ticket) {
   if (o.prec != PSK_PREC_F64 && o.prec != PSK_PREC_BF16 && o.prec != PSK_PREC_FP8)
     return fail(PSK_EDTYPE, "opts.prec must be PSK_PREC_F64, PSK_PREC_BF16 or PSK_PREC_FP8");
   size_t bytes = 0;
-  if ((rc = plan_request(*q, &bytes))) return rc;
+  if ((rc = plan_request(*q, false, &bytes))) return rc;
+  const bool lean = bytes > s->pool_bytes;
+  if (lean && (rc = plan_request(*q, true, &bytes))) return rc;
   if (bytes > s->pool_bytes)
     return fail(PSK_ENOMEM, "request workspace exceeds the whole server pool");
   Job *job = new Job();
   job->req = *q;
   job->ws_bytes = bytes;
+  job->lean = lean;
   {
     std::lock_guard<std::mutex> lk(s->mu);
     if (s->stop) {
