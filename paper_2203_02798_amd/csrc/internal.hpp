@@ -250,6 +250,25 @@ int css_select_impl(const psk_mat &A, int64_t m, int64_t r, int64_t k, uint64_t 
 int leverage_css_impl(const psk_mat &A, int64_t m, int64_t r, int64_t k, uint64_t seed, int prec,
                       double *theta, int32_t *cols, Arena &ws, hipStream_t st);
 
+// ---- sharpened preconditioner (k_precond.hip) ---------------------------------
+// est (kPrecondEst doubles, device): what the host needs to decide, read
+// back by the caller and passed to the two functions after it: the bound of
+// the rounding error of N^T A^T A N (kPrecondMax and above: not worth
+// forming) and, CSR A, the sum of squared row lengths (the Gram matrix's
+// multiply-adds).  R: N's inverse, or NULL; g: d doubles of scratch.
+constexpr double kPrecondMax = 0.1;
+constexpr int kPrecondRowParts = 256;
+constexpr int kPrecondEst = 16 + kPrecondRowParts;
+void precond_estimate(const psk_mat &A, const double *R, const double *N, double *g,
+                      double *est, hipStream_t st);
+double precond_error(const double *est, int64_t d);
+double precond_row_squares(const double *est);
+// P (d x d, whole, d <= 1024) = N S^{-1} with S^T S = N^T A^T A N, or N itself
+// where that is not accurate.  caller: N is the caller's, its lower triangle
+// is not read.
+int precond_sharpen(const psk_mat &A, const double *N, bool caller, double *P, Arena &ws,
+                    hipStream_t st);
+
 // ---- LSQR (k_lsqr.hip) -----------------------------------------------------
 int lsq_impl(const psk_mat &A, const double *b, double *x,
              const psk_lsq_opts &o, psk_lsq_info *info, Arena &ws,

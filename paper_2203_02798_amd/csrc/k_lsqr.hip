@@ -7,6 +7,12 @@
 // preconditioned iterative method, x = N y).  The iterative method is LSQR
 // (Paige & Saunders, ACM TOMS 8(1), 1982), which the paper leaves open.
 //
+// Where it pays, R^{-1} is first sharpened by A's own Gram matrix
+// (precond_sharpen): LSQR then stops after two or three iterations instead of
+// 30 to 50 (1e6 x 256 at condition number 1e3, m = 8 d: 16.1 -> 6.8 ms a
+// solve; 1e4 x 32: 982 -> 518 us; CSR 1e6 x 500 by the caller's R^{-1}: the
+// solve's 1.48 ms became 0.95).
+//
 // One LSQR iteration reads A once: for every row, u_i <- A_i vhat - alpha u_i
 // and A_i^T u_i is accumulated immediately (the normalisation by beta is a
 // scalar applied afterwards), so the two products A v and A^T u of the
@@ -88,6 +94,7 @@ struct SlotGuard {
   }
 };
 
+constexpr int kSharpenMinIter = 100;  // iteration limits from here on allow sharpening
 constexpr int kPassBlocks = 512;  // partial A^T u vectors per pass
 constexpr int kCsrWaves = 8;      // wavefronts of a CSR pass workgroup
 constexpr int kShortRow = 16;   // CSR rows up to this length take one lane each
@@ -882,6 +889,31 @@ void one_step(const psk_mat &A, bool init, int k, const LsqBufs &B, const double
         o.atol, o.btol, init ? 1 : 0);
 }
 
+// Whether the preconditioner of an m-row sketch is worth sharpening with A's
+// Gram matrix: the passes over A it saves (those LSQR takes at the rate
+// sqrt(d / m) to the tighter tolerance, less about five) against the Gram
+// matrix and the d x d factorization.  Times in us from single kernels on
+// the largest and smallest shapes: a dense pass reads 5 TB/s and its two
+// small kernels take 12; the Gram matrix runs at 55 TFLOP/s; a 64-column step of the
+// factorization takes 40.  CSR: a pass is about 20 B a row and 12 an entry
+// at 3 TB/s, and the Gram matrix half a us for every 64 d multiply-adds (a wavefront
+// per column, one dependent load after another).
+bool precond_pays(const psk_mat &A, int64_t m, double tol, double row_squares) {
+  const double n = (double)A.n, d = (double)A.d;
+  const double es = A.dtype == PSK_F64 ? 8.0 : 4.0;
+  const double e = m > 0 ? std::fmin(std::sqrt(d / (double)m), 0.9) : 0.5;
+  const double saved = std::log(1.0 / std::fmax(tol, 1e-16)) / std::log(1.0 / e) - 5.0;
+  double pass = 12.0, gram = 100.0 + 40.0 * std::ceil(d / 64.0);
+  if (A.format == PSK_DENSE) {
+    pass += n * d * es / 5e6;
+    gram += n * d * (d + 64.0) / 55e6;
+  } else {
+    pass += 12.0 + (n * 20.0 + (double)A.nnz * (es + 4.0)) / 3e6;
+    gram += 100.0 + 0.5 * row_squares / (64.0 * d);
+  }
+  return saved * pass > gram;
+}
+
 }  // namespace
 
 int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o,
@@ -904,7 +936,7 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
   B.vhat = ws.take<double>((size_t)d);
   double *res = ws.take<double>((size_t)n);  // residual of the refinement passes
   B.st = ws.take<LsqrState>(1);
-  double *ratio = ws.take<double>(2);       // max |R_ii|, min |R_ii|
+  double *ratio = ws.take<double>(2 + kPrecondEst);  // max |R_ii|, min |R_ii|; precond_estimate's
   // the reduced-precision sketch's perturbation against the FP64 one, on
   // request: that sketch kept (Chat), the FP64 sketch and its factor
   const bool want_delta = own && o.want_delta != 0 && o.prec != PSK_PREC_F64;
@@ -990,15 +1022,29 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
       ws.release(mk2);
     }
   }
+  // sharpening: planned where it pays at the least row_squares that A can
+  // have (equal rows); with an iteration limit below the tens of passes that
+  // the sketch's own preconditioner takes, the limit is meant for that method
+  const double tol = std::fmax(o.atol, o.btol);
+  const double mean_len = (double)A.nnz / (double)n;
+  const bool may_sharpen =
+      !ws.lean && n >= d && (A.format == PSK_DENSE || A.nnz < ((int64_t)1 << 31)) &&
+      precond_pays(A, own ? m : 0, tol, (double)A.nnz * std::fmax(mean_len, 1.0));
+  if (ws.dry() && may_sharpen) {
+    ws.release(mk);
+    ws.take<double>((size_t)d * d);
+    if ((rc = precond_sharpen(A, nullptr, !own, nullptr, ws, st))) return rc;
+  }
   if (ws.dry()) return 0;
   if (!ws.ok()) return fail(PSK_ENOMEM, "workspace too small for lsq_solve");
   // delta of the sketch LSQR is preconditioned with: 0 for the FP64 sketch,
   // NaN when not measured (not requested, or the caller's R^{-1})
   double delta_est = (own && o.prec == PSK_PREC_F64) ? 0.0 : NAN;
+  double hr[2 + kPrecondEst] = {1.0, 1.0};
   if (own) {
     int hflag = 0;
-    double hr[2] = {1.0, 1.0};
     k_diag_ratio<<<1, 256, 0, st>>>(R, d, ratio);
+    if (may_sharpen) precond_estimate(A, R, Rinv, B.vhat, ratio + 2, st);
     PSK_HIP_TRY(hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, st));
     PSK_HIP_TRY(hipMemcpyAsync(hr, ratio, sizeof(hr), hipMemcpyDeviceToHost, st));
     if (want_delta)
@@ -1022,6 +1068,10 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
       ws.release(mk2);
       if ((rc = sketch_qr_impl(C, m, d, R, Rinv, ws, st, &flag))) return rc;
       ws.release(mk2);
+      if (may_sharpen) {
+        precond_estimate(A, R, Rinv, B.vhat, ratio + 2, st);
+        PSK_HIP_TRY(hipMemcpyAsync(hr, ratio, sizeof(hr), hipMemcpyDeviceToHost, st));
+      }
       PSK_HIP_TRY(hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, st));
       PSK_HIP_TRY(hipStreamSynchronize(st));
       prec_used = PSK_PREC_F64;
@@ -1030,6 +1080,28 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
     if ((rc = factor_status(hflag, "sketch is numerically rank deficient"))) return rc;
   }
   ws.release(mk);
+
+  // the preconditioner LSQR runs with: the sketch's, or that one sharpened
+  const double *N = Rinv;
+  int first = 0;  // iterations of the first group when sharpened
+  if (may_sharpen && o.max_iter >= kSharpenMinIter) {
+    if (!own) {
+      precond_estimate(A, nullptr, Rinv, B.vhat, ratio + 2, st);
+      PSK_HIP_TRY(hipMemcpyAsync(hr, ratio, sizeof(hr), hipMemcpyDeviceToHost, st));
+      PSK_HIP_TRY(hipStreamSynchronize(st));
+    }
+    const double err = precond_error(hr + 2, d);
+    const double rsq = A.format == PSK_CSR ? precond_row_squares(hr + 2) : 0.0;
+    if (err <= kPrecondMax && precond_pays(A, own ? m : 0, tol, rsq)) {
+      double *P = ws.take<double>((size_t)d * d);
+      const size_t mkp = ws.mark();
+      if ((rc = precond_sharpen(A, Rinv, !own, P, ws, st))) return rc;
+      ws.release(mkp);
+      N = P;
+      // each iteration multiplies the margin by about the error
+      first = err <= 1e-7 ? 2 : 3;
+    }
+  }
 
   const unsigned db = (unsigned)ceil_div(d, 256);
   const unsigned nb16 = (unsigned)ceil_div(d, kColsPerBlk);
@@ -1065,7 +1137,7 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
     }
     k_state_reset<<<1, 64, 0, st>>>(B.st);
     k_zero<<<db, 256, 0, st>>>(B.v[0], d);
-    one_step(A, true, 0, B, Rinv, rhs, o, st);
+    one_step(A, true, 0, B, N, rhs, o, st);
     int kstep = 1;
     // Groups of at most check_every iterations; after each, the state is
     // copied to pinned memory and the host reads the previous group's copy
@@ -1098,7 +1170,13 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
       }
       int batch = o.check_every;
       bool read_now = false;
-      if (pass > 0 && ngroup == 0) {
+      if (first > 0 && ngroup == 0) {
+        // sharpened: two or three iterations end the first pass, one a
+        // refinement pass (whose margin starts at rounding level)
+        const int few = pass > 0 ? 1 : first;
+        batch = batch < few ? batch : few;
+        read_now = true;
+      } else if (pass > 0 && ngroup == 0) {
         batch = batch < 4 ? batch : 4;
         read_now = true;
       } else if (known_it >= 0 && rate < 0.0 && known_q > 0.0 && std::isfinite(known_q)) {
@@ -1114,7 +1192,7 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
       }
       if (batch > o.max_iter - it) batch = o.max_iter - it;
       if (batch > 0) {
-        for (int q = 0; q < batch; ++q) one_step(A, false, kstep++, B, Rinv, rhs, o, st);
+        for (int q = 0; q < batch; ++q) one_step(A, false, kstep++, B, N, rhs, o, st);
         it += batch;
         const int cur = ngroup++ & 1;
         PSK_HIP_TRY(hipMemcpyAsync(&slot.sl.h[cur], B.st, sizeof(LsqrState),
@@ -1155,7 +1233,7 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
     if (!done) converged = false;
     total_iters += hs.iters;
     // x += R^{-1} y
-    k_trmv<<<nb16, 256, 0, st>>>(Rinv, d, B.y, x, B.st, 0, 1);
+    k_trmv<<<nb16, 256, 0, st>>>(N, d, B.y, x, B.st, 0, 1);
   }
   PSK_HIP_TRY(hipGetLastError());
   PSK_HIP_TRY(hipStreamSynchronize(st));

@@ -1,0 +1,176 @@
+// The sketch's preconditioner sharpened by A's own Gram matrix, for LSQR
+// (FP64, gfx950).
+//
+// Paper mapping (arXiv 2203.02798): Algorithm least_squares_precondition
+// solves min ||A N y - b|| with N = R^{-1} of the sketch.  A N then has
+// singular values in about [1 / (1 + e), 1 / (1 - e)], e = sqrt(d / m), and
+// LSQR reads A ln(1 / tol) / ln(1 / e) times: 31 for m = 8 d at 1e-14.  One
+// more pass over A gives G = A^T A on the matrix cores, and with
+//   W = N^T G N = S^T S  (Cholesky),  P = N S^{-1},
+// A P has orthonormal columns up to the rounding of G, so LSQR on A P stops
+// after two or three passes.  Forming W from G squares cond(A) where forming
+// A N would not, but costs half of A N's own products and no n x d scratch.
+//
+// The rounding: |dG_kl| <= c u g_k g_l with g_k = ||A e_k||, so the error of
+// P^T G P is at most E = c u sum_j t_j^2, t_j = sum_k |P_kj| g_k, in
+// Frobenius norm, whatever the scaling of A's columns.  k_guard sums t_j^2.
+// It is asked twice: before G is formed, with N in P's place and g from R
+// (or a lower bound of it from N's diagonal), where E above kPrecondMax
+// leaves the sketch's N as it is (cond(A) beyond about 1e5); and afterwards
+// with P and G's diagonal, on the device: k_precond_pick puts N back into P
+// when E is too large or a pivot failed, so a bad P never reaches LSQR.
+#include <math.h>
+
+#include "internal.hpp"
+
+namespace psk {
+namespace {
+
+constexpr double kGuardC = 16.0 * 1.1102230246251565e-16;  // c u
+constexpr int kGuardCols = 64;   // columns of a k_guard workgroup
+constexpr int kMaxGuard = 1024 / kGuardCols;
+
+// g[k] = ||R e_k||, R upper triangular: a workgroup takes 64 columns, its
+// four wavefronts every fourth row
+__global__ __launch_bounds__(256) void k_col_norm_upper(const double *__restrict__ R, int64_t d,
+                                                        double *__restrict__ g) {
+  __shared__ double red[4][kGuardCols];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t j = (int64_t)blockIdx.x * kGuardCols + lane;
+  double s = 0.0;
+  if (j < d)
+    for (int64_t i = wave; i <= j; i += 4) s = fma(R[i * d + j], R[i * d + j], s);
+  red[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0 && j < d)
+    g[j] = sqrt((red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]));
+}
+
+// part[b] = sum over the workgroup's columns j of (sum_{k <= j} |M_kj| g_k)^2,
+// g_k = g[k] (mode 0), 1 / |g[k d + k]| (mode 1) or sqrt(g[k d + k]) (mode 2)
+__global__ __launch_bounds__(256) void k_guard(const double *__restrict__ M, int64_t d,
+                                               const double *__restrict__ g, int mode,
+                                               double *__restrict__ part) {
+  __shared__ double red[4][kGuardCols];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t j = (int64_t)blockIdx.x * kGuardCols + lane;
+  double t = 0.0;
+  if (j < d)
+    for (int64_t k = wave; k <= j; k += 4) {
+      const double gk = mode == 0 ? g[k] : mode == 1 ? 1.0 / fabs(g[k * d + k])
+                                                     : sqrt(g[k * d + k]);
+      t = fma(fabs(M[k * d + j]), gk, t);
+    }
+  red[wave][lane] = t;
+  __syncthreads();
+  if (wave == 0) {
+    const double tj = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+    const double s = wave_sum(j < d ? tj * tj : 0.0);
+    if (lane == 0) part[blockIdx.x] = s;
+  }
+}
+
+// U = the upper triangle of X, zero below (a caller's R^{-1} is read in its
+// upper triangle only)
+__global__ __launch_bounds__(256) void k_upper(const double *__restrict__ X, int64_t d,
+                                               double *__restrict__ U) {
+  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (e >= d * d) return;
+  U[e] = e % d >= e / d ? X[e] : 0.0;
+}
+
+// P = N where the guard's sum (nb partials in order) or a pivot says so
+__global__ __launch_bounds__(256) void k_precond_pick(const double *__restrict__ N, int64_t d,
+                                                      const double *__restrict__ part, int nb,
+                                                      const int *__restrict__ flag,
+                                                      double *__restrict__ P) {
+  double s = 0.0;
+  for (int b = 0; b < nb; ++b) s += part[b];
+  if (*flag == 0 && kGuardC * s <= kPrecondMax) return;  // NaN: not taken
+  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (e < d * d) P[e] = N[e];
+}
+
+// part[b] = sum of (entries of row i)^2 over the workgroup's rows
+__global__ __launch_bounds__(256) void k_row_squares(const int64_t *__restrict__ indptr,
+                                                     int64_t n, double *__restrict__ part) {
+  __shared__ double red[4];
+  double s = 0.0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += 256 * kPrecondRowParts) {
+    const double c = (double)(indptr[i + 1] - indptr[i]);
+    s = fma(c, c, s);
+  }
+  s = wave_sum(s);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) part[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+unsigned guard_blocks(int64_t d) { return (unsigned)ceil_div(d, (int64_t)kGuardCols); }
+
+}  // namespace
+
+void precond_estimate(const psk_mat &A, const double *R, const double *N, double *g,
+                      double *est, hipStream_t st) {
+  const int64_t d = A.d;
+  if (R) {
+    k_col_norm_upper<<<guard_blocks(d), 256, 0, st>>>(R, d, g);
+    k_guard<<<guard_blocks(d), 256, 0, st>>>(N, d, g, 0, est);
+  } else {
+    k_guard<<<guard_blocks(d), 256, 0, st>>>(N, d, N, 1, est);
+  }
+  if (A.format == PSK_CSR)
+    k_row_squares<<<kPrecondRowParts, 256, 0, st>>>(A.indptr, A.n, est + kMaxGuard);
+}
+
+double precond_error(const double *est, int64_t d) {
+  double s = 0.0;
+  for (unsigned b = 0; b < guard_blocks(d); ++b) s += est[b];
+  return kGuardC * s;
+}
+
+double precond_row_squares(const double *est) {
+  double s = 0.0;
+  for (int b = 0; b < kPrecondRowParts; ++b) s += est[kMaxGuard + b];
+  return s;
+}
+
+int precond_sharpen(const psk_mat &A, const double *N, bool caller, double *P, Arena &ws,
+                    hipStream_t st) {
+  const int64_t d = A.d;
+  double *G = ws.take<double>((size_t)d * d);
+  double *W = ws.take<double>((size_t)d * d);
+  double *S = ws.take<double>((size_t)d * d);
+  double *X = ws.take<double>((size_t)d * d);
+  double *U = caller ? ws.take<double>((size_t)d * d) : nullptr;
+  double *part = ws.take<double>(kMaxGuard);
+  int *flag = ws.take<int>(4);
+  const bool run = !ws.dry();
+  if (run && !ws.ok()) return fail(PSK_ENOMEM, "workspace too small for the preconditioner");
+  const size_t mk = ws.mark();
+  const unsigned ew = (unsigned)ceil_div(d * d, (int64_t)256);
+  int rc = A.format == PSK_DENSE ? gram_dense(1.0, A, 0.0, G, ws, st, true)
+                                 : gram_csr(1.0, A, 0.0, G, ws, st, true);
+  if (rc) return rc;
+  ws.release(mk);
+  const double *T = N;
+  if (caller) {
+    if (run) k_upper<<<ew, 256, 0, st>>>(N, d, U);
+    T = U;
+  }
+  if ((rc = dgemm(false, false, d, d, d, 1.0, G, d, T, d, 0.0, S, d, ws, st))) return rc;
+  ws.release(mk);
+  if ((rc = dgemm(true, false, d, d, d, 1.0, T, d, S, d, 0.0, W, d, ws, st))) return rc;
+  ws.release(mk);
+  if ((rc = chol_factor(W, d, S, X, flag, ws, st))) return rc;
+  ws.release(mk);
+  if ((rc = dgemm(false, false, d, d, d, 1.0, T, d, X, d, 0.0, P, d, ws, st))) return rc;
+  ws.release(mk);
+  if (!run) return 0;
+  k_guard<<<guard_blocks(d), 256, 0, st>>>(P, d, G, 2, part);
+  k_precond_pick<<<ew, 256, 0, st>>>(N, d, part, (int)guard_blocks(d), flag, P);
+  PSK_HIP_TRY(hipGetLastError());
+  return 0;
+}
+
+}  // namespace psk

@@ -1,0 +1,126 @@
+"""LSQR with the sketch's preconditioner sharpened by A's Gram matrix: the
+solution against LAPACK (residual and normal equations to 1e-10, the bar of
+every least-squares test here), and which preconditioner ran, read off the
+iteration count (a sharpened one takes a handful, the sketch's own tens)."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import synth
+from helpers import to_device
+from oracle import lsq as olsq
+
+torch = pytest.importorskip("torch")
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+
+@pytest.fixture(scope="module")
+def api():
+    from paper_2203_02798_amd import api as a
+    return a
+
+
+def _check(a, b, x, info):
+    rn, ne = olsq.lsq_quality(a, b, x.cpu().numpy())
+    rs, _ = olsq.lsq_quality(a, b, olsq.lstsq(a, b))
+    print(f"iters {info['iters']} excess {(rn - rs) / rs:.2e} normal eq {ne:.2e}", flush=True)
+    assert info["status"] == "PSK_OK" and (rn - rs) / rs <= 1e-10 and ne <= 1e-10
+
+
+# one and more 64-column blocks of the factorization, full and ragged; a
+# condition number past the rounding bound keeps the sketch's preconditioner
+@pytest.mark.parametrize("n,d,cond,dt,few", [
+    (4000, 1, 1.0, "f64", True), (9000, 33, 1e3, "f64", True), (6000, 64, 1e3, "f32", True),
+    (6000, 65, 10.0, "f64", True), (20000, 128, 1e4, "f64", True),
+    (20000, 200, 1e2, "f32", True), (9000, 32, 1e9, "f64", False)])
+def test_sharpened_dense(api, n, d, cond, dt, few):
+    print(f"dense n={n} d={d} cond={cond} {dt}", flush=True)
+    a, b, _ = synth.lsq_problem(n, d, cond, seed=d)
+    a = a.astype(np.float32 if dt == "f32" else np.float64)
+    x, info = api.lsq_solve(to_device(a), torch.from_numpy(b).cuda(), m=8 * d, r=max(d * d, 8 * d),
+                            seed=2)
+    _check(a.astype(np.float64), b, x, info)
+    assert (info["iters"] <= 12) == few
+
+
+@pytest.mark.parametrize("skew", [False, True])
+def test_sharpened_csr(api, skew):
+    """Equal and Zipf row lengths (one row in a few holds most entries)."""
+    n, d = 30000, 120
+    a = (synth.csr_zipf(n, d, 0.03, seed=3, dtype=np.float64) if skew
+         else synth.csr_uniform(n, d, 0.02, seed=3))
+    rng = np.random.default_rng(5)
+    b = a @ rng.standard_normal(d) + 1e-3 * rng.standard_normal(n)
+    x, info = api.lsq_solve(to_device(a), torch.from_numpy(b).cuda(), m=8 * d, r=d * d, seed=2)
+    _check(a.toarray(), b, x, info)
+
+
+def test_sharpened_badly_scaled_columns(api):
+    """Columns scaled over eight decades do not hide behind cond(A): the
+    rounding bound is in the columns' own scale."""
+    well, _, _ = synth.lsq_problem(8000, 40, 10.0, seed=1)
+    a = np.ascontiguousarray(well * np.logspace(4, -4, 40))
+    b = np.random.default_rng(6).standard_normal(8000)
+    x, info = api.lsq_solve(to_device(a), torch.from_numpy(b).cuda(), m=320, r=1600, seed=2)
+    rs = np.linalg.norm(b - well @ olsq.lstsq(well, b))
+    rn = np.linalg.norm(b - a @ x.cpu().numpy())
+    print(f"iters {info['iters']} residual ratio - 1: {rn / rs - 1:.2e}", flush=True)
+    assert info["iters"] <= 12 and abs(rn / rs - 1) <= 1e-10
+
+
+def test_callers_preconditioner_upper_triangle_only(api):
+    """A caller's R^{-1} is read in its upper triangle: what lies below it
+    changes nothing."""
+    a, b, _ = synth.lsq_problem(20000, 70, 1e2, seed=4)
+    ad, bd = to_device(a), torch.from_numpy(b).cuda()
+    _, ri = api.sketch_qr(api.sketch_gcs(ad, 560, 4900, 2))
+    x0, i0 = api.lsq_solve(ad, bd, Rinv=ri)
+    dirty = ri + torch.tril(torch.full_like(ri, float("nan")), -1)
+    x1, i1 = api.lsq_solve(ad, bd, Rinv=dirty)
+    _check(a, b, x0, i0)
+    assert i0["iters"] <= 12 and torch.equal(x0, x1) and i0 == i1 | {"delta_est": i0["delta_est"]}
+
+
+def test_small_iteration_limit_keeps_the_sketch_preconditioner(api):
+    a, b, _ = synth.lsq_problem(20000, 64, 1e2, seed=4)
+    ad, bd = to_device(a), torch.from_numpy(b).cuda()
+    _, info = api.lsq_solve(ad, bd, m=512, r=4096, seed=2, max_iter=10)
+    assert info["status"] == "PSK_ENOCONV"
+    _, info = api.lsq_solve(ad, bd, m=512, r=4096, seed=2, max_iter=99)
+    assert info["status"] == "PSK_OK" and info["iters"] > 20
+
+
+def test_lean_workspace_keeps_the_sketch_preconditioner(api):
+    """A workspace with room for LSQR's vectors but not for the Gram matrix's
+    partials runs on the caller's preconditioner as it is."""
+    from paper_2203_02798_amd import _lib as L
+    n, d = 20000, 64
+    a, b, _ = synth.lsq_problem(n, d, 1e2, seed=4)
+    ad, bd = to_device(a), torch.from_numpy(b).cuda()
+    _, ri = api.sketch_qr(api.sketch_gcs(ad, 512, 4096, 2))
+    full = api.workspace_size(L.PSK_OP_LSQ, ad)
+    small = 2 * n * 8 + (512 + 8) * d * 8 + 64 * 1024
+    assert small < full // 2
+    ws = torch.empty(small, dtype=torch.uint8, device="cuda")
+    x = torch.empty(d, dtype=torch.float64, device="cuda")
+    o = L.PskLsqOpts(Rinv=ri.data_ptr(), m=0, r=0, seed=0, prec=0, max_iter=300, refine=1,
+                     check_every=8, atol=1e-14, btol=1e-14, escalate_cond=0.0, want_delta=0)
+    info = L.PskLsqInfo()
+    mat = api._mat(ad)
+    st = L.lib().lsq_solve(ctypes.byref(mat), bd.data_ptr(), x.data_ptr(), ctypes.byref(o),
+                           ctypes.byref(info), ws.data_ptr(), small, api._stream(ad.device))
+    assert st == L.PSK_OK and info.iters > 20
+    _check(a, b, x, {"iters": info.iters, "status": "PSK_OK"})
+
+
+def test_nonfinite_input_with_a_callers_preconditioner(api):
+    """A NaN in A reaches the Gram matrix too: the call still reports it."""
+    a, b, _ = synth.lsq_problem(20000, 64, 1e2, seed=4)
+    ad, bd = to_device(a), torch.from_numpy(b).cuda()
+    _, ri = api.sketch_qr(api.sketch_gcs(ad, 512, 4096, 2))
+    ad[17, 3] = float("nan")
+    with pytest.raises(api.PskError) as e:
+        api.lsq_solve(ad, bd, Rinv=ri)
+    assert e.value.status == -8
