@@ -647,7 +647,9 @@ int bres_launch(const psk_mat &Am, const double *B, int64_t k, double *part, int
   if (groups < 8) groups = 8;
   groups = (groups / 8) * 8;
   const int64_t need = ceil_div(tiles, (int64_t)kBresWaves);  // row tiles per wavefront round
-  while (groups > 8 && groups / 2 >= need) groups /= 2;
+  // fewer groups for few rows, still whole eights (the kernel deals groups to
+  // XCDs by linear id mod 8; 80 halved to 20 or 10 left rows without a group)
+  while (groups > 8 && groups / 16 * 8 >= need) groups = groups / 16 * 8;
   const unsigned nblk = (unsigned)(groups * tn);
   KTimer timer("rownorm", st);
   k_rownorm_bres<TA, PAIR, VEC><<<nblk, kBresThreads, lds, st>>>(
