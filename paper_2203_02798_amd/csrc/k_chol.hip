@@ -65,26 +65,30 @@ __global__ __launch_bounds__(256) void k_shift_diag(double *__restrict__ W, int6
 // order) and finished one launch after its partials, and one extra launch
 // finishes the last column.  Block 0 is factored by k_chol_first.  W is read
 // in its upper block triangle and destroyed.
+//
+// What bounds a step is the one workgroup that ends in a factorization, a
+// chain of 64 pivots; the other tiles of the launch hide behind it.  The 64 x 64
+// products run on the matrix cores, operands in LDS; inside the factorization
+// one wavefront factors a 16 x 16 block while the other three update the
+// rest, and the inverse is carried along with the updates instead of being
+// formed after them.
 // ---------------------------------------------------------------------------
+typedef double v4d __attribute__((ext_vector_type(4)));
 constexpr int kLd = 68;      // LDS row stride of 64-wide tiles (doubles)
-constexpr int kUt = 66;      // LDS row stride of the transposed factor
 constexpr int kTh = 256;
+constexpr int kVb = 16 * 17;  // one 16 x 16 block inverse in LDS (row stride 17)
 
 struct CholSmem {
-  double As[16 * kLd];
-  double Bs[16 * kLd];
-  double PI[64 * kLd];       // also the diagonal tile to factor
+  double X[64 * kLd];        // an operand tile; the inverse of the factored tile
+  double PI[64 * kLd];       // operand tiles; PJ also the tile to factor
   double PJ[64 * kLd];
-  double Ut[64 * kUt];       // block inverses of the diagonal factor
-  double rowbuf[2][64];
-  double rinv[64];
+  double V[4 * kVb];         // block inverses of the diagonal factor
 };
 
-__device__ __forceinline__ double readlane_f64(double v, int l) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, l);
-  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), l);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+// lane L of each row of 16 lanes, to all of that row (one DPP move)
+template <int L>
+__device__ __forceinline__ double row_bcast(double v) {
+  return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + L, 0xf, 0xf, true);
 }
 
 __device__ __forceinline__ void wave_sync_lds() {
@@ -92,318 +96,303 @@ __device__ __forceinline__ void wave_sync_lds() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// 1/sqrt(x) to about one ulp: the hardware estimate, then one third-order
-// and one Newton correction, each from the residual e = 1 - x y^2 taken with
-// an FMA.
-__device__ __forceinline__ double rsqrt_acc(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  double e = fma(-(x * y), y, 1.0);
-  y = fma(y * e, fma(e, 0.375, 0.5), y);
-  e = fma(-(x * y), y, 1.0);
-  return fma(y * e, 0.5, y);
+__device__ __forceinline__ v4d mfma16(double a, double b, v4d c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-constexpr int kVb = 16 * 17;  // one 16 x 16 block inverse in LDS (row stride 17)
+// 1/sqrt(x) to about an ulp: the hardware estimate (about 2^-24) and one
+// third-order correction from the residual e = 1 - x y^2 taken with an FMA.
+__device__ __forceinline__ double rsqrt_acc(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-(x * y), y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
+}
 
-// Wavefront 0: Cholesky of the 16 x 16 block at (o, o) of the LDS tile T
-// (its upper triangle is read), right-looking with lane l % 16 holding
-// column l % 16: step k takes the pivot from lane k, scales row k, publishes
-// it through LDS and applies the rank-1 update to its column.  The same row
-// operations (scale row k by 1/U_kk, subtract U_ki times row k from row i)
-// applied to the identity leave L^{-1} = U^{-T} in z, lane l holding its
-// column l, i.e. row l of V = U^{-1}.  U overwrites the block's upper
-// triangle and V goes to Vb (row-major, stride 17).  Lanes 16..63 repeat
-// lanes 0..15 and store nothing.  Returns bit 1 when a pivot was not
-// positive (it is then replaced by 1), bit 2 when one was NaN or infinite.
+// x_r -= U_kr u and z_r -= U_kr zk for N consecutive rows r of a step, U_kr
+// being u's element in lane r of the row of 16: one FMA each, its DPP operand
+// doing the broadcast (the compiler makes a move and a dependent FMA of it, 32
+// cycles a row against 8.5).  The s_nop gives the two wait states a DPP operand
+// needs after the VALU has written it.
+#define PSK_ROW_UPDATE(X, Z, U, ZK, R)                                                  \
+  "v_fmac_f64_dpp %" X ", -%" U ", %" U " row_newbcast:%" R " row_mask:0xf bank_mask:0xf\n\t" \
+  "v_fmac_f64_dpp %" Z ", -%" U ", %" ZK " row_newbcast:%" R " row_mask:0xf bank_mask:0xf\n\t"
+
+template <int R, int N>
+__device__ __forceinline__ void update_rows(double (&x)[16], double (&z)[16], double u,
+                                            double zk) {
+  if constexpr (N >= 5) {
+    asm("s_nop 1\n\t" PSK_ROW_UPDATE("0", "5", "10", "11", "12")
+            PSK_ROW_UPDATE("1", "6", "10", "11", "13") PSK_ROW_UPDATE("2", "7", "10", "11", "14")
+                PSK_ROW_UPDATE("3", "8", "10", "11", "15")
+                    PSK_ROW_UPDATE("4", "9", "10", "11", "16")
+        : "+v"(x[R]), "+v"(x[R + 1]), "+v"(x[R + 2]), "+v"(x[R + 3]), "+v"(x[R + 4]),
+          "+v"(z[R]), "+v"(z[R + 1]), "+v"(z[R + 2]), "+v"(z[R + 3]), "+v"(z[R + 4])
+        : "v"(u), "v"(zk), "n"(R), "n"(R + 1), "n"(R + 2), "n"(R + 3), "n"(R + 4));
+    update_rows<R + 5, N - 5>(x, z, u, zk);
+  } else if constexpr (N >= 2) {
+    asm("s_nop 1\n\t" PSK_ROW_UPDATE("0", "2", "4", "5", "6")
+            PSK_ROW_UPDATE("1", "3", "4", "5", "7")
+        : "+v"(x[R]), "+v"(x[R + 1]), "+v"(z[R]), "+v"(z[R + 1])
+        : "v"(u), "v"(zk), "n"(R), "n"(R + 1));
+    update_rows<R + 2, N - 2>(x, z, u, zk);
+  } else if constexpr (N == 1) {
+    asm("s_nop 1\n\t" PSK_ROW_UPDATE("0", "1", "2", "3", "4")
+        : "+v"(x[R]), "+v"(z[R])
+        : "v"(u), "v"(zk), "n"(R));
+  }
+}
+
+// Step k of factor16 and those after it.
+template <int K>
+__device__ __forceinline__ void factor16_step(double (&x)[16], double (&z)[16], double &dg,
+                                              int &bad) {
+  const double piv = row_bcast<K>(dg);
+  double rs = rsqrt_acc(piv);
+  bad |= !(piv > 0.0) ? 1 : 0;
+  bad |= !(fabs(piv) <= 1.7976931348623157e308) ? 2 : 0;  // NaN or infinite
+  rs = piv > 0.0 ? rs : 1.0;
+  const double u = x[K] * rs, zk = z[K] * rs;
+  x[K] = u;
+  z[K] = zk;
+  if constexpr (K < 15) {
+    dg = fma(-u, u, dg);
+    update_rows<K + 1, 15 - K>(x, z, u, zk);
+    factor16_step<K + 1>(x, z, dg, bad);
+  }
+}
+
+// One wavefront: Cholesky of the symmetric 16 x 16 block at (o, o) of the LDS
+// tile T; every row of 16 lanes does the same work, lane l % 16 holding column
+// l % 16 of the block in x and of the identity in z.  The row operations that
+// turn the block into U (scale row k by 1/U_kk, subtract U_ki times row k
+// from row i) turn the identity into U^{-T}, so lane l ends with row l of V =
+// U^{-1} in z.  U overwrites the block's upper triangle (what is left below
+// the diagonal means nothing) and V goes to Vb (row-major, stride 17).  A
+// step's chain is pivot, reciprocal square root, scaled row, next pivot; each
+// lane keeps its column's diagonal entry apart, whose update needs only the
+// lane's own element of the row.  With the multipliers through LDS (a write
+// and up to seven 16-byte reads a step) a block took 5100 cycles, now
+// 3300.  Returns bit 1 when a pivot was not positive (its row is then not
+// scaled), bit 2 when one was NaN or infinite.
 __device__ __forceinline__ int factor16(double *__restrict__ T, int o,
-                                         double *__restrict__ rowbuf,
-                                         double *__restrict__ Vb) {
-  const int l = threadIdx.x & 15;
-  const bool st = threadIdx.x < 16;
-  double c[16], z[16];
+                                        double *__restrict__ Vb) {
+  const int lane = threadIdx.x & 63, l = lane & 15;
+  double x[16], z[16], dg = T[(o + l) * kLd + o + l];
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
-    c[i] = T[(o + i) * kLd + o + l];
-    z[i] = (i == l) ? 1.0 : 0.0;
+    x[i] = T[(o + i) * kLd + o + l];
+    z[i] = i == l ? 1.0 : 0.0;
   }
   int bad = 0;
+  factor16_step<0>(x, z, dg, bad);
+  if (lane < 16) {
 #pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    double piv = readlane_f64(c[k], k);
-    bad |= !(piv > 0.0) ? 1 : 0;
-    bad |= !(fabs(piv) <= 1.7976931348623157e308) ? 2 : 0;  // NaN or infinite
-    piv = piv > 0.0 ? piv : 1.0;
-    const double rs = rsqrt_acc(piv);
-    const double u = (l >= k) ? c[k] * rs : 0.0;
-    z[k] *= rs;
-    double *rb = rowbuf + (k & 1) * 16;
-    if (st) {
-      rb[l] = u;
-      if (l >= k) T[(o + k) * kLd + o + l] = u;
-    }
-    wave_sync_lds();
-    double rbv[16];
-#pragma unroll
-    for (int i = k + 1; i < 16; ++i) rbv[i] = rb[i];
-#pragma unroll
-    for (int i = k + 1; i < 16; ++i) {
-      c[i] -= rbv[i] * u;
-      z[i] -= rbv[i] * z[k];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  if (st) {
+    for (int i = 0; i < 16; ++i) T[(o + i) * kLd + o + l] = x[i];
+  } else if (lane < 32) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) Vb[l * 17 + i] = z[i];
   }
   return bad;
 }
 
-// All 256 threads.  T = S.PI: the 64 x 64 tile (row-major, stride kLd), of
-// which the leading nb x nb block is used (the rest is taken as identity).
-// Blocked right-looking Cholesky over four 16-column blocks: block kb is
-// factored by wavefront 0 (factor16, which also gives the block's inverse),
-// then the panel right of it is solved (U[kb, J] = V_kb^T T[kb, J]) and the
-// trailing block updated (T[I, J] -= U[kb, I]^T U[kb, J]) by the whole
-// workgroup, each thread owning a small register tile of outputs with its
-// operands loaded ahead.  The inverse X = U^{-1} is built block column by
-// block column: X[I, J] = -(sum_{K = I..J-1} X[I, K] U[K, J]) V_J.  Writes
-// the nb x nb blocks of R (= U, zero below the diagonal) and X at (j0, j0).
-template <int TR>
-__device__ __forceinline__ void trailing_update(double *__restrict__ T, int o) {
-  // rows / columns o + 16 + t + 16 a (a < TR) of thread (ti, tj)
-  const int ti = threadIdx.x >> 4, tj = threadIdx.x & 15;
-  const int b0 = o + 16;
-  double acc[TR][TR];
+// 16 x 16 tiles in LDS, one wavefront.  The accumulator's element e of lane
+// (kq, li) = (lane / 16, lane % 16) is row kq + 4 e, column li.
+__device__ __forceinline__ v4d tile_get(const double *__restrict__ T, int ld) {
+  const int li = threadIdx.x & 15, kq = (threadIdx.x >> 4) & 3;
+  v4d c;
 #pragma unroll
-  for (int a = 0; a < TR; ++a)
+  for (int e = 0; e < 4; ++e) c[e] = T[(kq + 4 * e) * ld + li];
+  return c;
+}
+__device__ __forceinline__ void tile_put(double *__restrict__ T, int ld, v4d c) {
+  const int li = threadIdx.x & 15, kq = (threadIdx.x >> 4) & 3;
 #pragma unroll
-    for (int b = 0; b < TR; ++b) acc[a][b] = 0.0;
+  for (int e = 0; e < 4; ++e) T[(kq + 4 * e) * ld + li] = c[e];
+}
+// c + sign * P^T Q (TN) or c + sign * P Q, all 16 x 16
+template <bool TN>
+__device__ __forceinline__ v4d tile_mul(const double *__restrict__ P, int ldp,
+                                        const double *__restrict__ Q, int ldq, double sign,
+                                        v4d c) {
+  const int li = threadIdx.x & 15, kq = (threadIdx.x >> 4) & 3;
+  double a[4], b[4];
 #pragma unroll
-  for (int m = 0; m < 16; ++m) {
-    const double *row = T + (o + m) * kLd;
-    double ri[TR], cj[TR];
-#pragma unroll
-    for (int a = 0; a < TR; ++a) {
-      ri[a] = row[b0 + ti + 16 * a];
-      cj[a] = row[b0 + tj + 16 * a];
-    }
-#pragma unroll
-    for (int a = 0; a < TR; ++a)
-#pragma unroll
-      for (int b = 0; b < TR; ++b) acc[a][b] = fma(ri[a], cj[b], acc[a][b]);
+  for (int s = 0; s < 4; ++s) {
+    a[s] = TN ? P[(4 * s + kq) * ldp + li] : P[li * ldp + 4 * s + kq];
+    b[s] = Q[(4 * s + kq) * ldq + li];
   }
+  // two chains: a product waits for two matrix instructions, not four
+  v4d c2 = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int a = 0; a < TR; ++a)
-#pragma unroll
-    for (int b = 0; b < TR; ++b) T[(b0 + ti + 16 * a) * kLd + b0 + tj + 16 * b] -= acc[a][b];
+  for (int s = 0; s < 2; ++s) {
+    c = mfma16(sign * a[s], b[s], c);
+    c2 = mfma16(sign * a[2 + s], b[2 + s], c2);
+  }
+  return c + c2;
 }
 
-__device__ __forceinline__ void factor_diag(CholSmem &S, int nb, int64_t d, int64_t j0,
+// All 256 threads.  T: the 64 x 64 tile (row-major, stride kLd), of which the
+// leading nb x nb block's upper triangle is used (the rest is taken as
+// identity); XT: LDS for the inverse.  Right-looking Cholesky over four
+// 16-column blocks.  Once block kb is factored (U_kb, V_kb = U_kb^{-1}):
+//   panel     U[kb, J] = V_kb^T T[kb, J] (J > kb),
+//             X[I, kb] = Y[I, kb] V_kb   (I < kb), X[kb, kb] = V_kb
+//   trailing  T[I, J] -= U[kb, I]^T U[kb, J]  (kb < I <= J)
+//             Y[I, J] -= X[I, kb] U[kb, J]    (I <= kb < J; Y starts as 0)
+// so the inverse's sums ride along with the updates.  Wavefront 0 updates and
+// factors the next diagonal block while the others do the rest.  Writes the nb x nb
+// blocks of R (= U, zero below the diagonal) and X at (j0, j0).
+// A 64 x 64 tile takes 24,000 cycles (10 us): 3300 a diagonal block, 1900 the panel and update
+// between two, 2800 writing R and X.  With VALU products and the inverse formed afterwards it took
+// 62,000; a step (m = 2000, d = 500) 18 us instead of 37.
+__device__ __forceinline__ void factor_diag(double *__restrict__ T, double *__restrict__ XT,
+                                            CholSmem &S, int nb, int64_t d, int64_t j0,
                                             double *__restrict__ R, double *__restrict__ X,
                                             int *__restrict__ flag) {
-  double *T = S.PI;
-  double *XT = S.PJ;
-  double *V = S.Ut;   // four block inverses, kVb doubles each
-  double *P = S.As;   // up to three 16 x 16 partial products (stride 17)
-  const int tid = threadIdx.x;
-  for (int e = tid; e < 64 * 64; e += kTh) {
-    const int i = e >> 6, j = e & 63;
-    if (i >= nb || j >= nb) T[i * kLd + j] = (i == j) ? 1.0 : 0.0;
+  const int tid = threadIdx.x, wave = tid >> 6;
+  if (nb < 64) {
+    for (int e = tid; e < 64 * 64; e += kTh) {
+      const int i = e >> 6, j = e & 63;
+      if (i >= nb || j >= nb) T[i * kLd + j] = (i == j) ? 1.0 : 0.0;
+    }
+    __syncthreads();
   }
-  __syncthreads();
+  auto tb = [&](double *M, int I, int J) { return M + 16 * I * kLd + 16 * J; };
   int bad = 0;
+  // one copy of the code for all four blocks: straight-line code run once is
+  // fetched once, and the fetch, not the arithmetic, then sets its pace
 #pragma unroll 1
   for (int kb = 0; kb < 4; ++kb) {
-    const int o = 16 * kb;
-    if (tid < 64) bad |= factor16(T, o, S.rowbuf[0], V + kb * kVb);
-    __syncthreads();
-    const int rest = 48 - o;  // columns right of the block
-    if (rest == 0) break;
-    {
-      // panel rows o..o+15, columns o+16..63: U[o+r][j] = sum_{m<=r} V[m][r] T[o+m][j]
-      const double *Vk = V + kb * kVb;
-      const int r = tid & 15, jg = tid >> 4;
-      double vc[16];
-#pragma unroll
-      for (int m = 0; m < 16; ++m) vc[m] = (m <= r) ? Vk[m * 17 + r] : 0.0;
-      double pv[3];
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        const int j = o + 16 + jg + 16 * q;
-        const int jc = j < 64 ? j : 63;
-        double tc[16];
-#pragma unroll
-        for (int m = 0; m < 16; ++m) tc[m] = T[(o + m) * kLd + jc];
-        double a0 = 0.0, a1 = 0.0;
-#pragma unroll
-        for (int m = 0; m < 16; m += 2) {
-          a0 = fma(vc[m], tc[m], a0);
-          a1 = fma(vc[m + 1], tc[m + 1], a1);
-        }
-        pv[q] = a0 + a1;
+    // V_{kb-1} is at hand; update what block kb - 1 leaves to update
+    if (wave == 0) {
+      double *t = tb(T, kb, kb);
+      if (kb > 0) {
+        const double *u = tb(T, kb - 1, kb);
+        tile_put(t, kLd, tile_mul<true>(u, kLd, u, kLd, -1.0, tile_get(t, kLd)));
+        wave_sync_lds();
       }
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        const int j = o + 16 + jg + 16 * q;
-        if (j < 64) T[(o + r) * kLd + j] = pv[q];
-      }
-      __syncthreads();
-    }
-    // trailing block rows / columns o+16..63
-    if (rest == 48) trailing_update<3>(T, o);
-    else if (rest == 32) trailing_update<2>(T, o);
-    else trailing_update<1>(T, o);
-    __syncthreads();
-  }
-  // X: diagonal blocks from the block inverses, zero below them
-  for (int e = tid; e < 64 * 64; e += kTh) {
-    const int i = e >> 6, j = e & 63;
-    const int bi = i >> 4, bj = j >> 4;
-    XT[i * kLd + j] = (bi == bj) ? V[bi * kVb + (i & 15) * 17 + (j & 15)]
-                                 : 0.0;
-  }
-  __syncthreads();
-  {
-    const int r = tid >> 4, c = tid & 15;
+      bad |= factor16(T, 16 * kb, S.V + kb * kVb);
+    } else if (kb > 0) {
+      // the other products of block row kb - 1, dealt to wavefronts 1 .. 3
+      int n = 0;
 #pragma unroll 1
-    for (int J = 1; J < 4; ++J) {
-      // P[I] = sum_{K=I}^{J-1} X[I, K] U[K, J] for every I < J at once:
-      // thread (r, c) keeps one accumulator per I
-      double acc[3] = {0.0, 0.0, 0.0};
-      for (int K = 0; K < J; ++K) {
-        double tcol[16];
-#pragma unroll
-        for (int m = 0; m < 16; ++m) tcol[m] = T[(16 * K + m) * kLd + 16 * J + c];
-#pragma unroll
-        for (int I = 0; I < 3; ++I) {
-          if (I <= K) {
-            double xr[16];
-#pragma unroll
-            for (int m = 0; m < 16; ++m) xr[m] = XT[(16 * I + r) * kLd + 16 * K + m];
-#pragma unroll
-            for (int m = 0; m < 16; ++m) acc[I] = fma(xr[m], tcol[m], acc[I]);
+      for (int J = kb; J < 4; ++J) {
+#pragma unroll 1
+        for (int I = 0; I <= J; ++I) {
+          if ((I == kb && J == kb) || n++ % 3 != wave - 1) continue;
+          const double *q = tb(T, kb - 1, J);
+          if (I >= kb) {
+            double *t = tb(T, I, J);
+            tile_put(t, kLd,
+                     tile_mul<true>(tb(T, kb - 1, I), kLd, q, kLd, -1.0, tile_get(t, kLd)));
+          } else {
+            double *y = tb(XT, I, J);  // its first product when I = kb - 1
+            v4d c = {0.0, 0.0, 0.0, 0.0};
+            if (I < kb - 1) c = tile_get(y, kLd);
+            tile_put(y, kLd, tile_mul<false>(tb(XT, I, kb - 1), kLd, q, kLd, -1.0, c));
           }
         }
       }
-#pragma unroll
-      for (int I = 0; I < 3; ++I)
-        if (I < J) P[I * kVb + r * 17 + c] = acc[I];
-      __syncthreads();
-      // X[I, J] = -P[I] V_J (V_J upper triangular)
-      const double *VJ = V + J * kVb;
-      double vcol[16];
-#pragma unroll
-      for (int m = 0; m < 16; ++m) vcol[m] = (m <= c) ? VJ[m * 17 + c] : 0.0;
-#pragma unroll
-      for (int I = 0; I < 3; ++I) {
-        if (I < J) {
-          double pr[16];
-#pragma unroll
-          for (int m = 0; m < 16; ++m) pr[m] = P[I * kVb + r * 17 + m];
-          double a0 = 0.0, a1 = 0.0;
-#pragma unroll
-          for (int m = 0; m < 16; m += 2) {
-            a0 = fma(pr[m], vcol[m], a0);
-            a1 = fma(pr[m + 1], vcol[m + 1], a1);
-          }
-          XT[(16 * I + r) * kLd + 16 * J + c] = -(a0 + a1);
-        }
-      }
-      __syncthreads();
     }
+    __syncthreads();
+    // panel: three products whatever kb, one each for wavefronts 0 .. 2;
+    // wavefront 3 copies V_kb
+    const double *V = S.V + kb * kVb;
+    if (wave < 3 - kb) {
+      double *t = tb(T, kb, kb + 1 + wave);
+      tile_put(t, kLd, tile_mul<true>(V, 17, t, kLd, 1.0, v4d{0.0, 0.0, 0.0, 0.0}));
+    } else if (wave < 3) {
+      double *y = tb(XT, wave - (3 - kb), kb);
+      tile_put(y, kLd, tile_mul<false>(y, kLd, V, 17, 1.0, v4d{0.0, 0.0, 0.0, 0.0}));
+    } else {
+      tile_put(tb(XT, kb, kb), kLd, tile_get(V, 17));
+    }
+    __syncthreads();
   }
-  for (int e = tid; e < 64 * 64; e += kTh) {
-    const int i = e >> 6, j = e & 63;
+  const int j = tid & 63;
+  double rv[16], xv[16];
+#pragma unroll
+  for (int p = 0; p < 16; ++p) {
+    const int i = wave + 4 * p;
+    const bool up = (i >> 4) <= (j >> 4);  // the blocks below hold nothing
+    const double a = T[i * kLd + j], b = XT[i * kLd + j];
+    rv[p] = i <= j ? a : 0.0;
+    xv[p] = up ? b : 0.0;
+  }
+#pragma unroll
+  for (int p = 0; p < 16; ++p) {
+    const int i = wave + 4 * p;
     if (i < nb && j < nb) {
-      R[(j0 + i) * d + j0 + j] = (i <= j) ? T[i * kLd + j] : 0.0;
-      X[(j0 + i) * d + j0 + j] = XT[i * kLd + j];
+      R[(j0 + i) * d + j0 + j] = rv[p];
+      X[(j0 + i) * d + j0 + j] = xv[p];
     }
   }
   if (bad) atomicOr(flag, bad);
 }
 
-// acc (this thread's 4 x 4 of a 64 x 64 tile: rows 4*ty.., columns 4*tx..)
-// += op(A) op(B) over K, staged through LDS 16 k at a time with the next
-// chunk prefetched into registers.  fa(i, k) = op(A)[i][k], fb(k, j) =
-// op(B)[k][j]; both return 0 outside the operand.  KCONTIG_A tells which
-// index of A is contiguous in memory (coalesced staging).
-template <bool KCONTIG_A, class FA, class FB>
-__device__ __forceinline__ void tile_mm(double acc[4][4], FA fa, FB fb, int K, CholSmem &S) {
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;
-  double pa[4], pb[4];
-  auto fetch = [&](int k0) {
+// a 64 x 64 tile of a row-major d-wide matrix at (r0, c0), rows < rows and
+// columns < cols of it, zero outside: loaded into registers, then stored
+struct Tile64 {
+  double v[16];
+  __device__ __forceinline__ void load(const double *__restrict__ M, int64_t d, int64_t r0,
+                                       int64_t c0, int rows, int cols) {
+    const int j = threadIdx.x & 63, i0 = threadIdx.x >> 6;
+    const bool jin = j < cols;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int idx = tid + kTh * e;  // 0..1023
-      int i, kk;
-      if (KCONTIG_A) { kk = idx & 15; i = idx >> 4; } else { i = idx & 63; kk = idx >> 6; }
-      pa[e] = (k0 + kk < K) ? fa(i, k0 + kk) : 0.0;
-      const int jj = idx & 63, kb = idx >> 6;
-      pb[e] = (k0 + kb < K) ? fb(k0 + kb, jj) : 0.0;
+    for (int p = 0; p < 16; ++p) {
+      const int i = i0 + 4 * p;
+      const bool in = jin && i < rows;
+      const double x = M[in ? (r0 + i) * d + c0 + j : 0];
+      v[p] = in ? x : 0.0;
     }
-  };
-  fetch(0);
-  for (int k0 = 0; k0 < K; k0 += 16) {
+  }
+  __device__ __forceinline__ void store(double *__restrict__ T) const {
+    const int j = threadIdx.x & 63, i0 = threadIdx.x >> 6;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int idx = tid + kTh * e;
-      int i, kk;
-      if (KCONTIG_A) { kk = idx & 15; i = idx >> 4; } else { i = idx & 63; kk = idx >> 6; }
-      S.As[kk * kLd + i] = pa[e];
-      S.Bs[(idx >> 6) * kLd + (idx & 63)] = pb[e];
+    for (int p = 0; p < 16; ++p) T[(i0 + 4 * p) * kLd + j] = v[p];
+  }
+};
+
+// This wavefront's 16-column strip w of a 64 x 64 product, four 16 x 16
+// blocks down it.  TN: acc[a] += sign * P^T Q with P, Q in LDS by rows of the
+// summed index; else acc[a] += sign * P Q.  TRI 1: P^T is lower triangular,
+// 2: Q is upper triangular (products with their zero blocks left out).
+template <bool TN, int TRI>
+__device__ __forceinline__ void strip_mul(v4d (&acc)[4], const double *__restrict__ P,
+                                          const double *__restrict__ Q, int w, double sign) {
+  const int li = threadIdx.x & 15, kq = (threadIdx.x >> 4) & 3;
+#pragma unroll
+  for (int K = 0; K < 4; ++K) {
+    if (TRI == 2 && K > w) break;  // uniform over the wavefront
+#pragma unroll
+    for (int s = 4 * K; s < 4 * K + 4; ++s) {
+      const double b = Q[(4 * s + kq) * kLd + 16 * w + li];
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        if (TRI == 1 && K > a) continue;
+        const double p = TN ? P[(4 * s + kq) * kLd + 16 * a + li]
+                            : P[(16 * a + li) * kLd + 4 * s + kq];
+        acc[a] = mfma16(sign * p, b, acc[a]);
+      }
     }
-    __syncthreads();
-    if (k0 + 16 < K) fetch(k0 + 16);
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      const double4 a = *reinterpret_cast<const double4 *>(S.As + kk * kLd + 4 * ty);
-      const double4 bq = *reinterpret_cast<const double4 *>(S.Bs + kk * kLd + 4 * tx);
-      const double av[4] = {a.x, a.y, a.z, a.w};
-      const double bv[4] = {bq.x, bq.y, bq.z, bq.w};
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc[r][q] = fma(av[r], bv[q], acc[r][q]);
-    }
-    __syncthreads();
   }
 }
 
-__device__ __forceinline__ void zero_acc(double acc[4][4]) {
+__device__ __forceinline__ void strip_zero(v4d (&acc)[4]) {
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) acc[r][q] = 0.0;
+  for (int a = 0; a < 4; ++a) acc[a] = v4d{0.0, 0.0, 0.0, 0.0};
 }
 
-// acc -> LDS tile (row-major, stride kLd)
-__device__ __forceinline__ void acc_to_lds(const double acc[4][4], double *T) {
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+// P = X^T W in place of W: a wavefront reads and writes its own columns of P
+__device__ __forceinline__ void panel_in_place(const double *__restrict__ X,
+                                               double *__restrict__ P) {
+  const int w = threadIdx.x >> 6;
+  v4d acc[4];
+  strip_zero(acc);
+  strip_mul<true, 1>(acc, X, P, w, 1.0);
+  wave_sync_lds();
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
-    *reinterpret_cast<double4 *>(T + (4 * ty + r) * kLd + 4 * tx) =
-        double4{acc[r][0], acc[r][1], acc[r][2], acc[r][3]};
-}
-
-// P = X_jj^T W[j, K] (64 x 64) into the LDS tile P.
-__device__ __forceinline__ void panel_tile(const double *__restrict__ W, const double *__restrict__ X,
-                           int64_t d, int64_t j0, int nbj, int64_t c0, double *P,
-                           CholSmem &S) {
-  double acc[4][4];
-  zero_acc(acc);
-  // op(A)[i][k] = X[j0+k][j0+i] (i, k < nbj): contiguous in i
-  auto fa = [&](int i, int k) {
-    return (i < nbj && k < nbj) ? X[(j0 + k) * d + j0 + i] : 0.0;
-  };
-  auto fb = [&](int k, int jj) {
-    return (k < nbj && c0 + jj < d) ? W[(j0 + k) * d + c0 + jj] : 0.0;
-  };
-  tile_mm<false>(acc, fa, fb, nbj, S);
-  acc_to_lds(acc, P);
-  __syncthreads();
+  for (int a = 0; a < 4; ++a) tile_put(P + 16 * a * kLd + 16 * w, kLd, acc[a]);
 }
 
 __global__ __launch_bounds__(kTh) void k_chol_first(const double *__restrict__ W, int64_t d,
@@ -412,12 +401,11 @@ __global__ __launch_bounds__(kTh) void k_chol_first(const double *__restrict__ W
                                                     int *__restrict__ flag) {
   __shared__ CholSmem S;
   const int nb = (int)(d < 64 ? d : 64);
-  for (int e = threadIdx.x; e < 64 * 64; e += kTh) {
-    const int i = e >> 6, jj = e & 63;
-    S.PI[i * kLd + jj] = (i < nb && jj < nb) ? W[(int64_t)i * d + jj] : 0.0;
-  }
+  Tile64 t;
+  t.load(W, d, 0, 0, nb, nb);
+  t.store(S.PJ);
   __syncthreads();
-  factor_diag(S, nb, d, 0, R, X, flag);
+  factor_diag(S.PJ, S.X, S, nb, d, 0, R, X, flag);
 }
 
 __global__ __launch_bounds__(kTh) void k_chol_step(double *__restrict__ W, int64_t d,
@@ -435,52 +423,94 @@ __global__ __launch_bounds__(kTh) void k_chol_step(double *__restrict__ W, int64
   int t = blockIdx.x;
   const int64_t j0 = (int64_t)j * 64;
   const int nbj = (int)((d - j0) < 64 ? (d - j0) : 64);
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+  const int w = threadIdx.x >> 6, li = threadIdx.x & 15, kq = (threadIdx.x >> 4) & 3;
+  auto width = [&](int64_t c0) { return (int)(d - c0 < 64 ? d - c0 : 64); };
   if (t < ntrail) {
     // trailing tile (I, J), enumerated row by row of the upper block triangle
     int I = j + 1, rem = t;
     while (rem >= nblk - I) { rem -= nblk - I; ++I; }
     const int J = I + rem;
     const int64_t r0 = (int64_t)I * 64, c0 = (int64_t)J * 64;
-    panel_tile(W, X, d, j0, nbj, r0, S.PI, S);
-    if (J != I) panel_tile(W, X, d, j0, nbj, c0, S.PJ, S);
-    const double *PJ = (J != I) ? S.PJ : S.PI;
-    double acc[4][4];
-    zero_acc(acc);
-#pragma unroll 4
-    for (int k = 0; k < 64; ++k) {
-      const double4 a = *reinterpret_cast<const double4 *>(S.PI + k * kLd + 4 * ty);
-      const double4 bq = *reinterpret_cast<const double4 *>(PJ + k * kLd + 4 * tx);
-      const double av[4] = {a.x, a.y, a.z, a.w};
-      const double bv[4] = {bq.x, bq.y, bq.z, bq.w};
+    Tile64 tx, ti, tj;
+    tx.load(X, d, j0, j0, nbj, nbj);
+    ti.load(W, d, j0, r0, nbj, width(r0));
+    if (I == J) {
+      // a diagonal tile: the ten 16 x 16 blocks of its upper triangle, two
+      // or three a wavefront
+      constexpr int kA[4][3] = {{0, 0, 1}, {0, 1, 2}, {0, 1, 0}, {2, 3, 0}};
+      constexpr int kB[4][3] = {{0, 1, 1}, {2, 2, 2}, {3, 3, 3}, {3, 3, 3}};
+      const int cnt = w < 2 ? 3 : 2;
+      int ba[3], bb[3];
+      v4d acc[3];
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
+      for (int q = 0; q < 3; ++q) {
+        ba[q] = w == 0 ? kA[0][q] : w == 1 ? kA[1][q] : w == 2 ? kA[2][q] : kA[3][q];
+        bb[q] = w == 0 ? kB[0][q] : w == 1 ? kB[1][q] : w == 2 ? kB[2][q] : kB[3][q];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) acc[r][q] = fma(av[r], bv[q], acc[r][q]);
-    }
-    if (I == j + 1 && J == j + 1) {
-      // the next diagonal tile: update in LDS and factor it here
+        for (int e = 0; e < 4; ++e) {
+          const int64_t gi = r0 + 16 * ba[q] + kq + 4 * e, gj = c0 + 16 * bb[q] + li;
+          const bool in = gi < d && gj < d;
+          const double x = W[in ? gi * d + gj : 0];
+          acc[q][e] = in ? x : 0.0;
+        }
+      }
+      tx.store(S.X);
+      ti.store(S.PI);
+      __syncthreads();
+      panel_in_place(S.X, S.PI);
       __syncthreads();
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
+      for (int s = 0; s < 16; ++s) {
+        const double *row = S.PI + (4 * s + kq) * kLd + li;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int64_t gi = r0 + 4 * ty + r, gj = c0 + 4 * tx + q;
-          const double w = (gi < d && gj < d) ? W[gi * d + gj] : 0.0;
-          S.PI[(4 * ty + r) * kLd + 4 * tx + q] = w - acc[r][q];
-        }
-      __syncthreads();
-      const int nb1 = (int)((d - r0) < 64 ? (d - r0) : 64);
-      factor_diag(S, nb1, d, r0, R, X, flag);
-    } else {
+        for (int q = 0; q < 3; ++q)
+          if (q < cnt) acc[q] = mfma16(-row[16 * ba[q]], row[16 * bb[q]], acc[q]);
+      }
+      if (I == j + 1) {
+        // the next diagonal tile, whose last update this is: factored here
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
+        for (int q = 0; q < 3; ++q)
+          if (q < cnt) tile_put(S.PJ + 16 * ba[q] * kLd + 16 * bb[q], kLd, acc[q]);
+        __syncthreads();
+        factor_diag(S.PJ, S.X, S, width(r0), d, r0, R, X, flag);
+      } else {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int64_t gi = r0 + 4 * ty + r, gj = c0 + 4 * tx + q;
-          if (gi < d && gj < d) W[gi * d + gj] -= acc[r][q];
-        }
+        for (int q = 0; q < 3; ++q)
+          if (q < cnt) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const int64_t gi = r0 + 16 * ba[q] + kq + 4 * e, gj = c0 + 16 * bb[q] + li;
+              if (gi < d && gj < d) W[gi * d + gj] = acc[q][e];
+            }
+          }
+      }
+      return;
     }
+    tj.load(W, d, j0, c0, nbj, width(c0));
+    v4d acc[4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t gi = r0 + 16 * a + kq + 4 * e, gj = c0 + 16 * w + li;
+        const double x = W[gj < d ? gi * d + gj : 0];  // rows of block I < J are in range
+        acc[a][e] = gj < d ? x : 0.0;
+      }
+    tx.store(S.X);
+    ti.store(S.PI);
+    tj.store(S.PJ);
+    __syncthreads();
+    panel_in_place(S.X, S.PI);
+    panel_in_place(S.X, S.PJ);
+    __syncthreads();
+    strip_mul<true, 0>(acc, S.PI, S.PJ, w, -1.0);
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t gi = r0 + 16 * a + kq + 4 * e, gj = c0 + 16 * w + li;
+        if (gj < d) W[gi * d + gj] = acc[a][e];
+      }
     return;
   }
   t -= ntrail;
@@ -490,17 +520,18 @@ __global__ __launch_bounds__(kTh) void k_chol_step(double *__restrict__ W, int64
     int K = 0;
     while ((K + 1) * (K + 2) / 2 <= t) ++K;
     const int I = t - K * (K + 1) / 2;
-    const int64_t r0 = (int64_t)I * 64, k0 = (int64_t)K * 64;
-    double acc[4][4];
-    zero_acc(acc);
-    auto fa = [&](int i, int k) { return X[(r0 + i) * d + k0 + k]; };  // in range
-    auto fb = [&](int k, int jj) { return jj < nbj ? R[(k0 + k) * d + j0 + jj] : 0.0; };
-    tile_mm<true>(acc, fa, fb, 64, S);
+    Tile64 tx, tr;
+    tx.load(X, d, (int64_t)I * 64, (int64_t)K * 64, 64, 64);
+    tr.load(R, d, (int64_t)K * 64, j0, 64, nbj);
+    tx.store(S.PI);
+    tr.store(S.PJ);
+    __syncthreads();
+    v4d acc[4];
+    strip_zero(acc);
+    strip_mul<false, 0>(acc, S.PI, S.PJ, w, 1.0);
     double *P = xpart + (j & 1) * half + (int64_t)t * 4096;
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) P[(4 * ty + r) * 64 + 4 * tx + q] = acc[r][q];
+    for (int a = 0; a < 4; ++a) tile_put(P + 16 * a * 64 + 16 * w, 64, acc[a]);
     return;
   }
   t -= npart;
@@ -508,45 +539,37 @@ __global__ __launch_bounds__(kTh) void k_chol_step(double *__restrict__ W, int64
     // X[I, c] = -(sum_{K=I}^{c-2} P_c[I][K] + X[I, c-1] R[c-1, c]) X_cc, c = cfin
     const int I = t, c = cfin;
     const int64_t r0 = (int64_t)I * 64, cm0 = (int64_t)(c - 1) * 64, c0 = (int64_t)c * 64;
-    const int nbc = (int)((d - c0) < 64 ? (d - c0) : 64);
-    double acc[4][4];
-    zero_acc(acc);
-    auto fa = [&](int i, int k) { return X[(r0 + i) * d + cm0 + k]; };  // in range
-    auto fb = [&](int k, int jj) { return jj < nbc ? R[(cm0 + k) * d + c0 + jj] : 0.0; };
-    tile_mm<true>(acc, fa, fb, 64, S);
+    const int nbc = width(c0);
+    Tile64 ta, tr, tx;
+    ta.load(X, d, r0, cm0, 64, 64);
+    tr.load(R, d, cm0, c0, 64, nbc);
+    tx.load(X, d, c0, c0, nbc, nbc);
     const double *Pc = xpart + (c & 1) * half;
-    double sum[4][4];
-    zero_acc(sum);
+    v4d acc[4];
+    strip_zero(acc);
 #pragma unroll 4
     for (int K = I; K <= c - 2; ++K) {
-      const double *pk = Pc + (int64_t)(K * (K + 1) / 2 + I) * 4096 + 4 * tx;
+      const double *pk = Pc + (int64_t)(K * (K + 1) / 2 + I) * 4096 + 16 * w;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const double4 v = *reinterpret_cast<const double4 *>(pk + (4 * ty + r) * 64);
-        sum[r][0] += v.x;
-        sum[r][1] += v.y;
-        sum[r][2] += v.z;
-        sum[r][3] += v.w;
-      }
+      for (int a = 0; a < 4; ++a) acc[a] += tile_get(pk + 16 * a * 64, 64);
     }
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) acc[r][q] = sum[r][q] + acc[r][q];
-    acc_to_lds(acc, S.PI);
+    ta.store(S.PI);
+    tr.store(S.PJ);
+    tx.store(S.X);
     __syncthreads();
-    zero_acc(acc);
-    auto ga = [&](int i, int k) { return S.PI[i * kLd + k]; };
-    auto gb = [&](int k, int jj) {
-      return (k < nbc && jj < nbc) ? X[(c0 + k) * d + c0 + jj] : 0.0;
-    };
-    tile_mm<true>(acc, ga, gb, nbc, S);
+    strip_mul<false, 0>(acc, S.PI, S.PJ, w, 1.0);
+    __syncthreads();  // PI is read by every wavefront
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int a = 0; a < 4; ++a) tile_put(S.PI + 16 * a * kLd + 16 * w, kLd, acc[a]);
+    __syncthreads();
+    strip_zero(acc);
+    strip_mul<false, 2>(acc, S.PI, S.X, w, -1.0);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int64_t gi = r0 + 4 * ty + r, gj = c0 + 4 * tx + q;
-        if (gj < d) X[gi * d + gj] = -acc[r][q];
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t gi = r0 + 16 * a + kq + 4 * e, gj = c0 + 16 * w + li;
+        if (gj < d) X[gi * d + gj] = acc[a][e];
       }
     return;
   }
@@ -554,13 +577,22 @@ __global__ __launch_bounds__(kTh) void k_chol_step(double *__restrict__ W, int64
   if (t < p) {
     // panel tile R[j, J] = X_jj^T W[j, J]
     const int64_t c0 = (int64_t)(j + 1 + t) * 64;
-    panel_tile(W, X, d, j0, nbj, c0, S.PI, S);
+    Tile64 tx, tj;
+    tx.load(X, d, j0, j0, nbj, nbj);
+    tj.load(W, d, j0, c0, nbj, width(c0));
+    tx.store(S.X);
+    tj.store(S.PI);
+    __syncthreads();
+    v4d acc[4];
+    strip_zero(acc);
+    strip_mul<true, 1>(acc, S.X, S.PI, w, 1.0);
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int64_t gi = j0 + 4 * ty + r, gj = c0 + 4 * tx + q;
-        if (4 * ty + r < nbj && gj < d) R[gi * d + gj] = S.PI[(4 * ty + r) * kLd + 4 * tx + q];
+      for (int e = 0; e < 4; ++e) {
+        const int i = 16 * a + kq + 4 * e;
+        const int64_t gj = c0 + 16 * w + li;
+        if (i < nbj && gj < d) R[(j0 + i) * d + gj] = acc[a][e];
       }
   }
 }

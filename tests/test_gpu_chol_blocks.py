@@ -1,0 +1,50 @@
+"""The blocked Cholesky (64-column blocks, 16-column blocks inside) at the
+edges of both, through sketch_qr and leverage_gram; and its flags for a pivot
+that is not positive or not finite in the first, an inner and the last
+column."""
+import numpy as np
+import pytest
+
+import synth
+from helpers import U64, to_device
+from oracle import leverage as olev
+
+torch = pytest.importorskip("torch")
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+
+@pytest.mark.parametrize("d", [1, 2, 15, 16, 17, 48, 63, 64, 65, 80, 127, 128, 129, 193, 320])
+def test_factor_block_edges(d):
+    """R of a well-conditioned C against LAPACK's, R R^{-1} = I and C R^{-1}
+    orthonormal, each to 50 cond u sqrt(d) (cond about 3 here)."""
+    from paper_2203_02798_amd import api
+    print(f"sketch_qr d={d}", flush=True)
+    c = synth.dense_gaussian(4 * d + 8, d, seed=d)
+    r, ri = (t.cpu().numpy() for t in api.sketch_qr(to_device(c)))
+    ref = np.linalg.qr(c, mode="r")
+    ref *= np.sign(np.diag(ref))[:, None]
+    tol = 50 * 4 * U64 * np.sqrt(d)
+    assert np.linalg.norm(r - ref) <= tol * np.linalg.norm(ref)
+    assert not np.tril(r, -1).any() and not np.tril(ri, -1).any()
+    eye = np.eye(d)
+    assert np.linalg.norm(r @ ri - eye) <= tol * np.sqrt(d)
+    q = c @ ri
+    assert np.linalg.norm(q.T @ q - eye) <= tol * np.sqrt(d)
+
+
+@pytest.mark.parametrize("d,col", [(40, 0), (40, 39), (130, 20), (130, 64), (130, 129)])
+def test_factor_flags(d, col):
+    from paper_2203_02798_amd import api
+    a = synth.dense_gaussian(1000, d, seed=2)
+    th = api.leverage_gram(to_device(a)).cpu().numpy()
+    assert np.abs(th - olev.leverage_exact(a)).max() <= 1e-12
+    zero = a.copy()
+    zero[:, col] = 0.0
+    with pytest.raises(api.PskError) as e:
+        api.leverage_gram(to_device(zero))
+    assert e.value.status == -6  # PSK_ERANK
+    a[5, col] = np.inf
+    with pytest.raises(api.PskError) as e:
+        api.leverage_gram(to_device(a))
+    assert e.value.status == -8  # PSK_ENONFINITE
