@@ -86,68 +86,131 @@ __host__ __device__ __forceinline__ void osnap_hash_nz(uint64_t i, uint32_t k, u
 
 // ---------------------------------------------------------------------------
 // Lean FP64 elementary functions for Box-Muller, on the ranges it needs.
-// Accuracy about 1e-16 relative; no branches.
+// Accuracy about 1e-16 relative; no branches.  Drawing G in FP64 is bound by
+// the vector ALUs (an FP64 or integer instruction takes a SIMD 4 to 5 cycles,
+// a conversion or comparison 8, rcp and rsq 16), so the polynomials are
+// near-minimax (Chebyshev economisation of the series, in place of two terms
+// more each), exponent and quarter turn are taken on the integers, and the
+// quotient and the root keep only the corrections that their ranges need.
 // ---------------------------------------------------------------------------
-// ln(x) for x in (0, 1]: x = f 2^e with f in [1/sqrt2, sqrt2),
-// ln f = 2 atanh(s), s = (f-1)/(f+1), |s| <= 0.1716, atanh by its power
-// series s + s^3/3 + ... + s^19/19 (truncation below 1e-17); ln 2 is split so
-// that e * ln2_hi is exact.
-__host__ __device__ __forceinline__ double bm_log(double x) {
-  int e;
-  double f = frexp(x, &e);  // f in [1/2, 1)
-  const bool lo = f < 0.70710678118654752440;
-  f = lo ? 2.0 * f : f;
-  e = lo ? e - 1 : e;
-  const double s = (f - 1.0) / (f + 1.0);
-  const double s2 = s * s;
-  double p = 1.0 / 19.0;
-  p = fma(p, s2, 1.0 / 17.0);
-  p = fma(p, s2, 1.0 / 15.0);
-  p = fma(p, s2, 1.0 / 13.0);
-  p = fma(p, s2, 1.0 / 11.0);
-  p = fma(p, s2, 1.0 / 9.0);
-  p = fma(p, s2, 1.0 / 7.0);
-  p = fma(p, s2, 1.0 / 5.0);
-  p = fma(p, s2, 1.0 / 3.0);
-  const double lnf = fma(2.0 * s * s2, p, 2.0 * s);
-  const double ln2_hi = 0.6931467056274414;       // ln 2 to 21 bits
-  const double ln2_lo = 4.7493250390316726e-07;   // ln 2 - ln2_hi
-  return fma((double)e, ln2_hi, fma((double)e, ln2_lo, lnf));
+// p t + c with the coefficient c read from scalar registers: the compiler's
+// own choice moves every coefficient into the vector register that a
+// two-operand FMA accumulates in, one more vector instruction per term.
+__host__ __device__ __forceinline__ double bm_horner(double p, double t, double c) {
+#ifdef __HIP_DEVICE_COMPILE__
+  double r;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(p), "v"(t), "s"(c));
+  return r;
+#else
+  return fma(p, t, c);
+#endif
 }
 
-// sin(pi z) and cos(pi z) for z in [0, 2]: z = k/2 + y with |y| <= 1/4 (exact
-// split), Taylor series of sin(pi y) (9 terms) and cos(pi y) (10 terms),
-// truncation below 1e-19, then the quarter-turn k mod 4 picks and signs.
+// num / den for den in [1, 4], |num| <= 1, to about half an ulp: the hardware
+// reciprocal (2^-24), one Newton step, and the quotient corrected by its
+// exact residual.
+__host__ __device__ __forceinline__ double bm_div(double num, double den) {
+#ifdef __HIP_DEVICE_COMPILE__
+  double y = __builtin_amdgcn_rcp(den);
+  y = fma(y, fma(-den, y, 1.0), y);
+  const double q = num * y;
+  return fma(fma(-den, q, num), y, q);
+#else
+  return num / den;
+#endif
+}
+
+// sqrt(w) for normal w > 0: w times the hardware reciprocal root (2^-24) and
+// one third-order correction.
+__host__ __device__ __forceinline__ double bm_sqrt(double w) {
+#ifdef __HIP_DEVICE_COMPILE__
+  const double y = __builtin_amdgcn_rsq(w);
+  const double g = w * y;
+  const double e = fma(-g, y, 1.0);
+  return fma(g * e, fma(e, 0.375, 0.5), g);
+#else
+  return sqrt(w);
+#endif
+}
+
+// -2 ln(x) for normal x in (0, 1]: x = f 2^e with f in about [1/sqrt2,
+// sqrt2), ln f = 2 atanh(s), s = (f-1)/(f+1), |s| <= 0.1716, atanh(s) = s +
+// s^3 P(s^2), P of degree 6 on [0, 0.02944] (error of ln f below 5e-18
+// relative); ln 2 is split so that e times its high part is exact.
+__host__ __device__ __forceinline__ double bm_m2log(double x) {
+  const uint64_t xb = __builtin_bit_cast(uint64_t, x);
+  const int32_t hi = (int32_t)(xb >> 32);
+  const int32_t e = (hi - 0x3fe6a09e) >> 20;  // sqrt(1/2) is 0x3fe6a09e 667f3bcd
+  const uint32_t fh = (uint32_t)hi - ((uint32_t)e << 20);
+  const double f = __builtin_bit_cast(double, ((uint64_t)fh << 32) | (uint32_t)xb);
+  const double s = bm_div(f - 1.0, f + 1.0);
+  const double s2 = s * s;
+  double p = 0.073082927124443114;
+  p = bm_horner(p, s2, 0.076658553091053863);
+  p = bm_horner(p, s2, 0.090914447278374735);
+  p = bm_horner(p, s2, 0.11111105565129939);
+  p = bm_horner(p, s2, 0.14285714313001635);
+  p = bm_horner(p, s2, 0.19999999999949722);
+  p = bm_horner(p, s2, 0.33333333333333348);
+  const double m4s = -4.0 * s;
+  const double lnf = fma(m4s * s2, p, m4s);
+  const double ln2_hi = 0.6931467056274414;       // ln 2 to 21 bits
+  const double ln2_lo = 4.7493250390316726e-07;   // ln 2 - ln2_hi
+  const double ed = (double)e;
+  return fma(ed, -2.0 * ln2_hi, fma(ed, -2.0 * ln2_lo, lnf));
+}
+
+__host__ __device__ __forceinline__ double bm_log(double x) { return -0.5 * bm_m2log(x); }
+
+// sin(pi z) and cos(pi z), z = k/2 + y with |y| <= 1/4, from y and the quarter
+// turns in the top two bits of turn (k 2^30): polynomials in y^2 of degree 6
+// for sin(pi y) / y (error below 1e-17) and (cos(pi y) - 1) / y^2 (2e-18).
+__host__ __device__ __forceinline__ void bm_sincos_quarter(double y, uint32_t turn, double &sn,
+                                                           double &cs) {
+  const double y2 = y * y;
+  double ps = 0.00046153185538358102;
+  ps = bm_horner(ps, y2, -0.0073700215869077707);
+  ps = bm_horner(ps, y2, 0.082145869180001746);
+  ps = bm_horner(ps, y2, -0.59926452893964488);
+  ps = bm_horner(ps, y2, 2.5501640398733763);
+  ps = bm_horner(ps, y2, -5.1677127800499543);
+  ps = bm_horner(ps, y2, 3.1415926535897931);
+  const double sp = ps * y;
+  double pc = -0.00010370082971594627;
+  pc = bm_horner(pc, y2, 0.001929493874894941);
+  pc = bm_horner(pc, y2, -0.025806887964701878);
+  pc = bm_horner(pc, y2, 0.23533063028399223);
+  pc = bm_horner(pc, y2, -1.3352627688538095);
+  pc = bm_horner(pc, y2, 4.0587121264167649);
+  pc = bm_horner(pc, y2, -4.934802200544679);
+  const double cp = bm_horner(pc, y2, 1.0);
+  // sin(pi(k/2 + y)) = sp, cp, -sp, -cp ; cos(...) = cp, -sp, -cp, sp
+  const bool odd = (turn & 0x40000000u) != 0u;
+  const uint64_t a = __builtin_bit_cast(uint64_t, odd ? cp : sp);
+  const uint64_t b = __builtin_bit_cast(uint64_t, odd ? sp : cp);
+  sn = __builtin_bit_cast(double, a ^ ((uint64_t)(turn & 0x80000000u) << 32));
+  cs = __builtin_bit_cast(double,
+                          b ^ ((uint64_t)((turn + 0x40000000u) & 0x80000000u) << 32));
+}
+
+// sin(pi z) and cos(pi z) for z in [0, 2]
 __host__ __device__ __forceinline__ void bm_sincospi(double z, double &sn, double &cs) {
   const double k = rint(2.0 * z);
-  const double y = fma(-0.5, k, z);
-  const double y2 = y * y;
-  double ps = 7.952054001475513e-07;
-  ps = fma(ps, y2, -2.1915353447830217e-05);
-  ps = fma(ps, y2, 0.00046630280576761255);
-  ps = fma(ps, y2, -0.0073704309457143504);
-  ps = fma(ps, y2, 0.08214588661112823);
-  ps = fma(ps, y2, -0.5992645293207921);
-  ps = fma(ps, y2, 2.5501640398773455);
-  ps = fma(ps, y2, -5.16771278004997);
-  ps = fma(ps, y2, 3.141592653589793);
-  const double sp = ps * y;
-  double pc = -1.3878952462213771e-07;
-  pc = fma(pc, y2, 4.303069587032947e-06);
-  pc = fma(pc, y2, -0.0001046381049248457);
-  pc = fma(pc, y2, 0.0019295743094039231);
-  pc = fma(pc, y2, -0.02580689139001406);
-  pc = fma(pc, y2, 0.2353306303588932);
-  pc = fma(pc, y2, -1.3352627688545895);
-  pc = fma(pc, y2, 4.0587121264167685);
-  pc = fma(pc, y2, -4.934802200544679);
-  const double cp = fma(pc, y2, 1.0);
-  const int q = ((int)k) & 3;
-  // sin(pi(k/2 + y)) = sp, cp, -sp, -cp ; cos(...) = cp, -sp, -cp, sp
-  const double a = (q & 1) ? cp : sp;
-  const double b = (q & 1) ? sp : cp;
-  sn = (q & 2) ? -a : a;
-  cs = ((q + 1) & 2) ? -b : b;
+  bm_sincos_quarter(fma(-0.5, k, z), (uint32_t)(int)k << 30, sn, cs);
+}
+
+// sin(2 pi u) and cos(2 pi u) for u = (x + 1/2) 2^-32: k = round(4 u) and
+// y = 2 u - k/2, both exact, on the integer
+__host__ __device__ __forceinline__ void bm_sincos_turns(uint32_t x, double &sn, double &cs) {
+  const uint32_t turn = (x + 0x20000000u) & 0xc0000000u;
+  const double y = fma((double)(int32_t)(x - turn), 4.656612873077393e-10,
+                       2.3283064365386963e-10);  // (x - turn + 1/2) 2^-31
+  bm_sincos_quarter(y, turn, sn, cs);
+}
+
+// sqrt(-2 ln u) for u = (x + 1/2) 2^-32 (one exact FMA)
+__host__ __device__ __forceinline__ double bm_radius(uint32_t x) {
+  return bm_sqrt(bm_m2log(fma((double)x, 2.3283064365386963e-10, 1.1641532182693481e-10)));
 }
 
 // Four unscaled standard normals z0..z3 for buckets 4q .. 4q+3 of Gaussian
@@ -155,16 +218,11 @@ __host__ __device__ __forceinline__ void bm_sincospi(double z, double &sn, doubl
 // is the stream: 1 for G, 2 for the JL matrix of the leverage estimate (the
 // hash uses 0).
 __host__ __device__ __forceinline__ void box_muller_f64(const u32x4 &x, double z[4]) {
-  const double s = 2.3283064365386963e-10;  // 2^-32
-  const double u0 = ((double)x.x0 + 0.5) * s;
-  const double u1 = ((double)x.x1 + 0.5) * s;
-  const double u2 = ((double)x.x2 + 0.5) * s;
-  const double u3 = ((double)x.x3 + 0.5) * s;
-  const double r0 = sqrt(-2.0 * bm_log(u0));
-  const double r2 = sqrt(-2.0 * bm_log(u2));
+  const double r0 = bm_radius(x.x0);
+  const double r2 = bm_radius(x.x2);
   double s1, c1, s3, c3;
-  bm_sincospi(2.0 * u1, s1, c1);
-  bm_sincospi(2.0 * u3, s3, c3);
+  bm_sincos_turns(x.x1, s1, c1);
+  bm_sincos_turns(x.x3, s3, c3);
   z[0] = r0 * c1;
   z[1] = r0 * s1;
   z[2] = r2 * c3;
@@ -343,11 +401,9 @@ __device__ __forceinline__ uint32_t gauss4_bf16_fast(const u32x4 &x, float out[4
 
 // Normal k (0 .. 3) of Philox words x in FP64, alone (as box_muller_f64)
 __device__ __forceinline__ double normal_f64_k(const u32x4 &x, int k) {
-  const double s = 2.3283064365386963e-10;  // 2^-32
-  const uint32_t xr = k < 2 ? x.x0 : x.x2, xa = k < 2 ? x.x1 : x.x3;
-  const double rad = sqrt(-2.0 * bm_log(((double)xr + 0.5) * s));
+  const double rad = bm_radius(k < 2 ? x.x0 : x.x2);
   double sn, cs;
-  bm_sincospi(2.0 * (((double)xa + 0.5) * s), sn, cs);
+  bm_sincos_turns(k < 2 ? x.x1 : x.x3, sn, cs);
   return rad * ((k & 1) ? sn : cs);
 }
 

@@ -440,21 +440,28 @@ constexpr int kStageMax = 4 * kSThreads;
 constexpr int kHeavy = 32;
 constexpr int kHeavyMax = 128;
 static_assert(kStageMax / (kHeavy + 1) < kHeavyMax, "heavy list capacity");
+// Lanes that share a column, each with its share of the tile's rows.  A
+// wavefront walks as many entries as the fullest of its columns has, so fewer
+// columns to a wavefront waste fewer lanes, but every lane then walks more
+// columns.  CSR 1e6 x 500, m = 2000 / Zipf 1e7 x 1000, m = 4000 (about one and
+// three entries a column and block), FP64: 1 lane 1.41 / 2.55 ms, 2 lanes
+// 1.32 / 2.56, 4 lanes 1.40 / 2.88.
+constexpr int kLanesPerCol = 2;
 
 // Workgroup (row tile mt, K split ks), 1024 threads: rows a0 .. a0 + MT of
 // C (MT = 16 1024 / DP) and the G blocks ks bper .. ks bper + bper - 1, a
 // block being QB = BLK / 4 occupied quads of buckets (BLK = 512 with G in
 // FP32, 256 with G in FP64; bper from the number of blocks, read here).
-// Thread (h, j) = (tid / DP, tid % DP) holds C[a0 + 16 h + i, j], i < 16, in
-// FP64 registers.  Per block: every thread draws its share of
+// kLanesPerCol threads share a column and hold its MT rows, 16 accumulators
+// a thread over its columns.  Per block: every thread draws its share of
 // the block of G into LDS (bucket-major, so one bucket's MT values are
 // contiguous); the block's entries, sorted by (column, bucket), are staged
-// in LDS with, per column, the range of its entries; thread (h, j) then
-// adds G[a, b] s for the entries (b, j, s) of its column in bucket order
+// in LDS with, per column, the range of its entries; a thread then
+// adds G[a, b] s for the entries (b, j, s) of its columns in bucket order
 // (FP64, or FP32 when G is drawn in FP32).
 // So each element of C is summed by one thread, over buckets in ascending
-// order, with no atomics.  Entries are fetched two blocks ahead, the block
-// bounds three; a block of more than KS entries is staged in turns.
+// order, with no atomics.  Entries are fetched a block ahead, the block
+// bounds two; a block of more than KS entries is staged in turns.
 template <int GP, int DP, int BLK>
 __global__ __launch_bounds__(kSThreads) void k_gauss_sparse(
     int64_t m, int64_t d, int64_t r, uint64_t seed, const uint32_t *__restrict__ be,
@@ -465,8 +472,12 @@ __global__ __launch_bounds__(kSThreads) void k_gauss_sparse(
   typedef GT AT;  // accumulator and staged value: FP64, or FP32 with G in FP32
   constexpr int KS = sizeof(AT) == 4 ? kStageMax : kStageMax / 2;
   const AT *__restrict__ sv = reinterpret_cast<const AT *>(sv_raw);  // the sorted values
-  constexpr int RG = kSThreads / DP;                // row groups
-  constexpr int MT = 16 * RG;                       // tile rows
+  constexpr int MT = 16 * kSThreads / DP;           // tile rows
+  constexpr int LPC = kLanesPerCol;
+  constexpr int CPT = DP * LPC / kSThreads;         // columns per thread
+  constexpr int CR = 16 / (int)sizeof(GT);          // rows of a 16-byte chunk
+  constexpr int NCH = MT / (LPC * CR);              // chunks per thread and column
+  static_assert(CPT >= 1 && NCH >= 1 && CPT * NCH * CR == 16, "16 accumulators a thread");
   constexpr int GS = MT + 16 / (int)sizeof(GT);     // LDS stride of a bucket of G
   constexpr int kQ = BLK / 4;                       // quads (Philox blocks) per G block
   constexpr int NIT = MT * kQ / kSThreads;          // G items per thread
@@ -492,12 +503,17 @@ __global__ __launch_bounds__(kSThreads) void k_gauss_sparse(
   const int64_t bper = ceil_div(nblk, splits);
   const int64_t k0 = ks * bper < nblk ? ks * bper : nblk;
   const int64_t k1 = k0 + bper < nblk ? k0 + bper : nblk;
-  const int j = tid % DP, h = tid / DP;
+  // columns j0 + c kSThreads / LPC, rows CR (LPC i + rl) + t of chunk i
+  const int j0 = tid / LPC, rl = tid % LPC;
   for (int i = tid; i < DP; i += kSThreads) crng[i] = make_uint2(kHole, 0u);
   if (tid < 2) hcnt[tid] = 0u;
-  AT acc[16];
+  AT acc[CPT][NCH][CR];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = AT(0);
+  for (int c = 0; c < CPT; ++c)
+#pragma unroll
+    for (int i = 0; i < NCH; ++i)
+#pragma unroll
+      for (int t = 0; t < CR; ++t) acc[c][i][t] = AT(0);
   uint32_t tag = 0;  // one per staged turn, never kHole
   // block bounds, loaded per lane (through vz, a zero the compiler cannot
   // see) so that they join the entries in the in-order vector load counter
@@ -566,18 +582,26 @@ __global__ __launch_bounds__(kSThreads) void k_gauss_sparse(
     }
   };
   auto consume = [&]() __attribute__((always_inline)) {
-    const uint2 cr = crng[j];
-    if (cr.x == tag) {
-      const int s0 = (int)(cr.y & 0xffffu), s1 = s0 + (int)(cr.y >> 16);
-      for (int i = s0; i < s1; ++i) {
-        const uint32_t pv = stp[i];
-        const AT v = stv[i];
-        const GT *gp = Gb + ((pv >> 10) & 511u) * GS + 16 * h;
-        GT gv[16];
 #pragma unroll
-        for (int t = 0; t < 16; ++t) gv[t] = gp[t];
+    for (int c = 0; c < CPT; ++c) {
+      const uint2 cr = crng[j0 + c * (kSThreads / LPC)];
+      if (cr.x == tag) {
+        const int s0 = (int)(cr.y & 0xffffu), s1 = s0 + (int)(cr.y >> 16);
+#pragma unroll 1
+        for (int i = s0; i < s1; ++i) {
+          const uint32_t pv = stp[i];
+          const AT v = stv[i];
+          const GT *gp = Gb + ((pv >> 10) & 511u) * GS + CR * rl;
+          GT gv[NCH][CR];
 #pragma unroll
-        for (int t = 0; t < 16; ++t) acc[t] = fma(gv[t], v, acc[t]);
+          for (int q = 0; q < NCH; ++q)
+#pragma unroll
+            for (int t = 0; t < CR; ++t) gv[q][t] = gp[CR * LPC * q + t];
+#pragma unroll
+          for (int q = 0; q < NCH; ++q)
+#pragma unroll
+            for (int t = 0; t < CR; ++t) acc[c][q][t] = fma(gv[q][t], v, acc[c][q][t]);
+        }
       }
     }
     // heavy columns: thread (stream st, row a) takes the column's entries
@@ -598,54 +622,61 @@ __global__ __launch_bounds__(kSThreads) void k_gauss_sparse(
       }
       hred[hs * MT + ha] = part;
       __syncthreads();
-      if ((uint32_t)j == hv.x) {
 #pragma unroll
-        for (int t = 0; t < 16; ++t) {
-          AT sum = AT(0);
+      for (int c = 0; c < CPT; ++c) {
+        if ((uint32_t)(j0 + c * (kSThreads / LPC)) != hv.x) continue;
+#pragma unroll
+        for (int q = 0; q < NCH; ++q)
+#pragma unroll
+          for (int t = 0; t < CR; ++t) {
+            AT sum = AT(0);
 #pragma unroll 4
-          for (int q2 = 0; q2 < NSTR; ++q2) sum += hred[q2 * MT + 16 * h + t];
-          acc[t] += sum;
-        }
+            for (int q2 = 0; q2 < NSTR; ++q2) sum += hred[q2 * MT + CR * (LPC * q + rl) + t];
+            acc[c][q][t] += sum;
+          }
       }
       __syncthreads();
     }
     ++tag;
   };
-  auto step = [&](int64_t kb, ESet &X, Bnd &BX, Bnd &BY) __attribute__((always_inline)) {
-    // Block kb: the occupied quads kQ kb .. kQ kb + kQ - 1 of the list
-    // (fewer in the last block); item it of the block is row it % MT of its
-    // (it / MT)-th quad, drawn into the G slots 4 (it / MT) .. + 3; thread
-    // tid takes items tid, tid + 1024, ...
+  // row, slot quad and first bucket of item u of a block whose quads are qr
+  // (r < 2^31: 32-bit); item it is row it % MT of the block's (it / MT)-th
+  // quad, drawn into the G slots 4 (it / MT) .. + 3, thread tid taking items
+  // tid, tid + 1024, ...
+  auto item_of = [&](const uint32_t *qr, int u, int &a, int &q, uint32_t &bq)
+                     __attribute__((always_inline)) {
+    const int it = tid + kSThreads * u;
+    a = it % MT;
+    q = it / MT;
+    bq = 4u * qr[q];
+  };
+  const uint32_t ru = (uint32_t)r;
+  const int mi = (int)m, a0i = (int)a0;
+  // the drawn values: FP64, or (BF16, FP8: exact in bfloat16) two
+  // bfloat16 per register
+  constexpr int GW = GP == kG64 ? 4 : 2;
+  typedef typename std::conditional<GP == kG64, double, uint32_t>::type GR;
+  GR g[NIT][GW];
+  // values within the window of a rounding midpoint (4 bits per item):
+  // redrawn in FP64 after the store, when g is no longer live
+  uint32_t nearm = 0;
+  // items of block kb: its occupied quads kQ kb .. kQ kb + kQ - 1 of the list
+  // (fewer in the last block, none past the split)
+  auto items_of = [&](int64_t kb) -> int {
     const int64_t qleft = nq - kb * kQ;
-    const int nqb = kb < k1 ? (int)(qleft < kQ ? qleft : kQ) : 0;
-    // the quads of block kb + 3, stored into the ring after the draw
-    uint32_t qnext = 0;
-    if (tid < kQ) qnext = quad_of(kb + 3);
-    const int nitems = nqb * MT;
+    return MT * (kb < k1 ? (int)(qleft < kQ ? qleft : kQ) : 0);
+  };
+  // block kb's normals into g
+  auto draw = [&](int64_t kb) __attribute__((always_inline)) {
+    const int nitems = items_of(kb);
     const uint32_t *qr = qring[kb & 3];
-    // row, slot quad and first bucket of item u (r < 2^31: 32-bit)
-    auto item_of = [&](int u, int &a, int &q, uint32_t &bq) __attribute__((always_inline)) {
-      const int it = tid + kSThreads * u;
-      a = it % MT;
-      q = it / MT;
-      bq = 4u * qr[q];
-    };
-    const uint32_t ru = (uint32_t)r;
-    const int mi = (int)m, a0i = (int)a0;
-    // the drawn values: FP64, or (BF16, FP8: exact in bfloat16) two
-    // bfloat16 per register
-    constexpr int GW = GP == kG64 ? 4 : 2;
-    typedef typename std::conditional<GP == kG64, double, uint32_t>::type GR;
-    GR g[NIT][GW];
-    // values within the window of a rounding midpoint (4 bits per item):
-    // redrawn in FP64 after the store, when g is no longer live
-    uint32_t nearm = 0;
+    nearm = 0;
 #pragma unroll
     for (int u = 0; u < NIT; ++u) {
       if (tid + kSThreads * u < nitems) {
         int a, q;
         uint32_t bq;
-        item_of(u, a, q, bq);
+        item_of(qr, u, a, q, bq);
         const int ga = a0i + a;
         if constexpr (GP == kG64) {
           double z[4] = {0.0, 0.0, 0.0, 0.0};
@@ -675,15 +706,19 @@ __global__ __launch_bounds__(kSThreads) void k_gauss_sparse(
           g[u][1] = (__float_as_uint(z[2]) >> 16) | (__float_as_uint(z[3]) & 0xFFFF0000u);
         }
       }
+      __builtin_amdgcn_sched_barrier(0);  // one item's temporaries at a time (128 registers)
     }
-    if (tid < kQ) qring[(kb + 3) & 3][tid] = qnext;  // ring slot of block kb - 1, read
-    __syncthreads();  // the previous block is done with Gb, the stage and crng
+  };
+  // block kb's normals from g into Gb
+  auto store = [&](int64_t kb) __attribute__((always_inline)) {
+    const int nitems = items_of(kb);
+    const uint32_t *qr = qring[kb & 3];
 #pragma unroll
     for (int u = 0; u < NIT; ++u)
       if (tid + kSThreads * u < nitems) {
         int a, q;
         uint32_t bq;
-        item_of(u, a, q, bq);
+        item_of(qr, u, a, q, bq);
         GT gv[4];
         if constexpr (GP == kG64) {
 #pragma unroll
@@ -707,7 +742,7 @@ __global__ __launch_bounds__(kSThreads) void k_gauss_sparse(
           if (nb == 0u) continue;
           int a, q;
           uint32_t bq;
-          item_of(u, a, q, bq);
+          item_of(qr, u, a, q, bq);
           const int ga = a0i + a;
           const u32x4 x = philox_g((uint64_t)(bq >> 2), (uint32_t)ga, seed);
           float z[4];
@@ -724,12 +759,44 @@ __global__ __launch_bounds__(kSThreads) void k_gauss_sparse(
         }
       }
     }
+  };
+  // Between the barriers of a step a wavefront contracts block kb and draws
+  // block kb + 1 (in registers): the even wavefronts of a SIMD in this order,
+  // the odd ones in the other, so that the vector ALUs draw while LDS, which
+  // bounds the contraction, serves the others (CSR 1e6 x 500, m = 2000: FP64
+  // 1.63 ms against 1.70 with all of them contracting first).
+  const int late = __builtin_amdgcn_readfirstlane(tid >> 8) & 1;  // wavefronts w, w + 4, .. share a SIMD
+  if (tid < kQ) {  // ring slots are block index mod 4
+    qring[k0 & 3][tid] = quad_of(k0);
+    qring[(k0 + 1) & 3][tid] = quad_of(k0 + 1);
+    qring[(k0 + 2) & 3][tid] = quad_of(k0 + 2);
+  }
+  __syncthreads();
+  ESet X;  // block kb's entries, then block kb + 1's
+  Bnd B;   // the bounds of the block after those
+  bounds(k0, B);
+  fetch(B, X);
+  bounds(k0 + 1, B);
+  draw(k0);
+#pragma unroll 1
+  for (int64_t kb = k0; kb < k1; ++kb) {
+    __syncthreads();  // the previous block is done with Gb, the stage and crng
+    store(kb);
     const uint32_t lo = X.lo, hi = X.hi;
     stage(X.p, X.v, hi - lo < (uint32_t)KS ? hi - lo : (uint32_t)KS);
     __syncthreads();
-    bounds(kb + 3, BY);  // block kb + 3 is fetched in the next step
-    fetch(BX, X);        // block kb + 2, bounds loaded in the previous step
-    consume();
+    // loads return in order: first the quads of block kb + 3, which the ring
+    // takes (in block kb - 1's place) before this step ends
+    uint32_t qnext = 0;
+    if (tid < kQ) qnext = quad_of(kb + 3);
+    fetch(B, X);  // block kb + 1, bounds loaded a step ago
+    bounds(kb + 2, B);
+#pragma unroll 1
+    for (int ph = 0; ph < 2; ++ph) {
+      if (ph == late) consume();
+      else draw(kb + 1);
+    }
+    if (tid < kQ) qring[(kb + 3) & 3][tid] = qnext;
     // more than KS entries: the further turns, loaded here
     for (uint32_t base = lo + KS; base < hi; base += KS) {
       uint32_t pp[KS / kSThreads];
@@ -740,31 +807,18 @@ __global__ __launch_bounds__(kSThreads) void k_gauss_sparse(
       __syncthreads();
       consume();
     }
-  };
-  if (tid < kQ) {  // ring slots are block index mod 4
-    qring[k0 & 3][tid] = quad_of(k0);
-    qring[(k0 + 1) & 3][tid] = quad_of(k0 + 1);
-    qring[(k0 + 2) & 3][tid] = quad_of(k0 + 2);
   }
-  __syncthreads();
-  Bnd BA, BB;
-  ESet RA, RB;
-  bounds(k0, BA);
-  fetch(BA, RA);
-  bounds(k0 + 1, BB);
-  fetch(BB, RB);
-  bounds(k0 + 2, BA);
-  // both steps unconditional (a conditional one would copy set B at the
-  // loop's end): a step at k1 has empty bounds and adds nothing
-  for (int64_t kb = k0; kb < k1; kb += 2) {
-    step(kb, RA, BA, BB);
-    step(kb + 1, RB, BB, BA);
-  }
-  if (j < d) {
-    double *o = part + (ks * m + a0 + 16 * h) * d + j;
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (a0 + 16 * h + i < m) o[(int64_t)i * d] = (double)acc[i];
+  for (int c = 0; c < CPT; ++c) {
+    const int64_t j = j0 + c * (kSThreads / LPC);
+    if (j >= d) continue;
+#pragma unroll
+    for (int q = 0; q < NCH; ++q)
+#pragma unroll
+      for (int t = 0; t < CR; ++t) {
+        const int64_t row = a0 + CR * (LPC * q + rl) + t;
+        if (row < m) part[(ks * m + row) * d + j] = (double)acc[c][q][t];
+      }
   }
 }
 

@@ -1,14 +1,15 @@
 """LSQR with the sketch's preconditioner sharpened by A's Gram matrix: the
 solution against LAPACK (residual and normal equations to 1e-10, the bar of
-every least-squares test here), and which preconditioner ran, read off the
-iteration count (a sharpened one takes a handful, the sketch's own tens)."""
+every least-squares test here, plus what rounding x to FP64 moves them by),
+and which preconditioner ran, read off the iteration count (a sharpened one
+takes a handful, the sketch's own tens)."""
 import ctypes
 
 import numpy as np
 import pytest
 
 import synth
-from helpers import to_device
+from helpers import U64, to_device
 from oracle import lsq as olsq
 
 torch = pytest.importorskip("torch")
@@ -23,10 +24,14 @@ def api():
 
 
 def _check(a, b, x, info):
-    rn, ne = olsq.lsq_quality(a, b, x.cpu().numpy())
+    x = x.cpu().numpy()
+    rn, ne = olsq.lsq_quality(a, b, x)
     rs, _ = olsq.lsq_quality(a, b, olsq.lstsq(a, b))
     print(f"iters {info['iters']} excess {(rn - rs) / rs:.2e} normal eq {ne:.2e}", flush=True)
-    assert info["status"] == "PSK_OK" and (rn - rs) / rs <= 1e-10 and ne <= 1e-10
+    # |A^T A dx| <= ||A||^2 u ||x||: beyond 1e-10 only at cond 1e9, where the
+    # exact solution rounded to FP64 reads 1.5e-10 and LAPACK's 2.2e-10
+    floor = U64 * np.linalg.norm(a) * np.linalg.norm(x) / rn
+    assert info["status"] == "PSK_OK" and (rn - rs) / rs <= 1e-10 and ne <= 1e-10 + floor
 
 
 # one and more 64-column blocks of the factorization, full and ragged; a
