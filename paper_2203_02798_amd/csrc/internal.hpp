@@ -191,9 +191,20 @@ int gram_dense(double alpha, const psk_mat &A, double beta, void *C, Arena &ws,
 int rownorms_dense(double alpha, const psk_mat &A, const double *B, int64_t k,
                    double beta, double *x, Arena &ws, hipStream_t st);
 // General FP64 product C = alpha*op(A)*op(B) + beta*C, all row-major.
+// tri: operands with a zero triangle, whose zeros are then not walked.
+enum {
+  kTriB = 1,   // op(B) = B is upper triangular
+  kTriA = 2,   // op(A) = A is upper triangular
+  kTriAT = 4,  // op(A) = A^T with A upper triangular
+};
 int dgemm(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha,
           const double *A, int64_t lda, const double *B, int64_t ldb,
-          double beta, double *C, int64_t ldc, Arena &ws, hipStream_t st);
+          double beta, double *C, int64_t ldc, Arena &ws, hipStream_t st, int tri = 0);
+// W = C^T C (d x d, both triangles) for an FP64 row-major m x d C of a few
+// thousand rows; scratch: room doubles, at least dgram_room.
+int dgram(const double *C, int64_t m, int64_t d, double *W, double *scratch, int64_t room,
+          hipStream_t st);
+int64_t dgram_room(int64_t d);
 
 // ---- CSR kernels (k_csr.hip) -----------------------------------------------
 // out_f64: C is FP64 whatever the dtype of A (else the dtype of A)

@@ -13,8 +13,8 @@
 // the first pass keeps the Cholesky factorization defined for condition
 // numbers up to about 1/u, and up to two unshifted passes restore
 // orthogonality.  The second pass stops the factorisation when its Gram
-// matrix is within 1e-4 of the identity: then the first pass's Q was
-// already orthonormal to that level, the second pass leaves it orthonormal
+// matrix is within 1/2 of the identity: then the first pass's Q was
+// already that well conditioned, the second pass leaves it orthonormal
 // to rounding level (Cholesky-QR loses orthogonality like cond(Q)^2 u), and
 // a third pass would change R only by rounding.  Otherwise (ill-conditioned
 // C) the third pass runs as in sCQR3.
@@ -29,14 +29,19 @@
 namespace psk {
 namespace {
 
-__global__ void k_fill(double *__restrict__ p, int64_t count, double v) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < count) p[i] = v;
-}
-
-// W[i][i] += coef * trace(W)
-__global__ __launch_bounds__(256) void k_shift_diag(double *__restrict__ W, int64_t d,
-                                                    double coef) {
+// Before a blocked Cholesky, in one launch: R = X = 0, flag cleared (when
+// given) and W[i][i] += coef * trace(W) (coef != 0), the last by workgroup 0.
+__global__ __launch_bounds__(256) void k_chol_prep(double *__restrict__ W, int64_t d, double coef,
+                                                   double *__restrict__ R, double *__restrict__ X,
+                                                   int *__restrict__ flag) {
+  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < d * d;
+       e += (int64_t)gridDim.x * 256) {
+    R[e] = 0.0;
+    X[e] = 0.0;
+  }
+  if (blockIdx.x != 0) return;
+  if (flag && threadIdx.x < 4) flag[threadIdx.x] = 0;
+  if (coef == 0.0) return;
   __shared__ double red[4];
   double s = 0.0;
   for (int64_t i = threadIdx.x; i < d; i += 256) s += W[i * d + i];
@@ -613,6 +618,13 @@ __global__ __launch_bounds__(kTh) void k_chol_step(double *__restrict__ W, int64
 // the factorisation there.
 // ---------------------------------------------------------------------------
 constexpr double kSeriesTol = 1e-4;
+// ||W - I||_F up to which a pass's Cholesky is the last: cond(Q)^2 is at most
+// (1 + 1/2) / (1 - 1/2) = 3, and Cholesky-QR's loss of orthogonality, about
+// cond(Q)^2 u, stays at rounding level.  The shift of the first pass leaves
+// ||W - I|| at 1e-2 to 0.4 for sketches of condition number 1e3 to 1e4, which
+// a bound of 1e-4 sent through a third pass (2048 x 256 at 1e3: 638 us a call,
+// now 279 with the shorter products).
+constexpr double kLastTol = 0.5;
 constexpr int kParts = 64;
 
 // part[b] = sum over a fixed slice of (W - I)^2, fixed reduction order
@@ -676,17 +688,16 @@ __global__ __launch_bounds__(256) void k_series_x(const double *__restrict__ T, 
   X[e] = jj >= i ? (i == jj ? 1.0 : 0.0) - T[e] : 0.0;
 }
 
-void fill(double *p, int64_t count, double v, hipStream_t st) {
-  k_fill<<<(unsigned)ceil_div(count, 256), 256, 0, st>>>(p, count, v);
-}
-
-// Upper Cholesky of W (destroyed) into R, and X = R^{-1}; R and X must be
-// zero on entry.
+// Upper Cholesky of W + coef trace(W) I (W is destroyed) into R, and X =
+// R^{-1}; *flag (four ints) is cleared first with clear.
 // xpart: scratch of at least d * d doubles for the partial products of the
 // off-diagonal blocks of X (two block columns' worth, by parity).
-void chol_inv(double *W, int64_t d, double *R, double *X, int *flag, double *xpart,
-              hipStream_t st) {
+void chol_inv(double *W, int64_t d, double coef, double *R, double *X, int *flag, bool clear,
+              double *xpart, hipStream_t st) {
   const int nblk = (int)ceil_div(d, 64);
+  const int64_t pb = ceil_div(d * d, (int64_t)1024);
+  k_chol_prep<<<(unsigned)(pb < 1024 ? pb : 1024), 256, 0, st>>>(W, d, coef, R, X,
+                                                                 clear ? flag : nullptr);
   k_chol_first<<<1, kTh, 0, st>>>(W, d, R, X, flag);
   // launch j = nblk only finishes the last block column of X
   for (int j = 0; j <= nblk; ++j) {
@@ -733,14 +744,16 @@ int series_chol(const double *W, int64_t d, int depth, double *R, double *X, dou
   if (run) k_series_u0<<<ew, 256, 0, st>>>(W, d, B0);
   double *u = B0, *v = B1;
   for (int t = 0; t < depth; ++t) {
-    if ((rc = dgemm(true, false, d, d, d, 1.0, u, d, u, d, 0.0, B2, d, ws, st))) return rc;
+    if ((rc = dgemm(true, false, d, d, d, 1.0, u, d, u, d, 0.0, B2, d, ws, st, kTriAT | kTriB)))
+      return rc;
     ws.release(mk);
     if (run) k_series_phi<<<ew, 256, 0, st>>>(W, B2, d, v);
     double *tmp = u; u = v; v = tmp;
   }
   if (run) k_series_rx<<<ew, 256, 0, st>>>(u, d, R, X);
   for (int t = 0; t < depth; ++t) {
-    if ((rc = dgemm(false, false, d, d, d, 1.0, u, d, X, d, 0.0, B2, d, ws, st))) return rc;
+    if ((rc = dgemm(false, false, d, d, d, 1.0, u, d, X, d, 0.0, B2, d, ws, st, kTriA | kTriB)))
+      return rc;
     ws.release(mk);
     if (run) k_series_x<<<ew, 256, 0, st>>>(B2, d, X);
   }
@@ -749,22 +762,20 @@ int series_chol(const double *W, int64_t d, int depth, double *R, double *X, dou
 
 // R, X of the Gram matrix W = Q^T Q of a pass after the first: the series
 // when ||W - I||_F <= kSeriesTol, else the blocked Cholesky.  In a planning
-// run (no data) both are planned.  *series tells which ran.
+// run (no data) both are planned.  *dist: ||W - I||_F.
 int later_pass_chol(double *W, int64_t d, double *R, double *X, double *B0, double *B1,
-                    double *B2, double *part, int *flag, bool *series, Arena &ws,
+                    double *B2, double *part, int *flag, double *dist, Arena &ws,
                     hipStream_t st) {
   int rc;
   if (ws.dry()) {
-    *series = false;
+    *dist = INFINITY;
     return series_chol(W, d, 2, R, X, B0, B1, B2, ws, st);
   }
   double e2;
   if ((rc = fro_dist_identity_sq(W, d, part, st, &e2))) return rc;
-  *series = e2 <= kSeriesTol * kSeriesTol;
-  if (*series) return series_chol(W, d, series_depth(sqrt(e2)), R, X, B0, B1, B2, ws, st);
-  fill(R, d * d, 0.0, st);
-  fill(X, d * d, 0.0, st);
-  chol_inv(W, d, R, X, flag, B2, st);
+  *dist = sqrt(e2);
+  if (*dist <= kSeriesTol) return series_chol(W, d, series_depth(*dist), R, X, B0, B1, B2, ws, st);
+  chol_inv(W, d, 0.0, R, X, flag, false, B2, st);
   return 0;
 }
 
@@ -776,10 +787,7 @@ int chol_factor(double *W, int64_t d, double *R, double *X, int *flag, Arena &ws
   double *xpart = ws.take<double>((size_t)d * d);
   if (ws.dry()) return 0;
   if (!ws.ok()) return fail(PSK_ENOMEM, "workspace too small for the Cholesky factorization");
-  k_fill<<<1, 64, 0, st>>>(reinterpret_cast<double *>(flag), 2, 0.0);
-  fill(R, d * d, 0.0, st);
-  fill(X, d * d, 0.0, st);
-  chol_inv(W, d, R, X, flag, xpart, st);
+  chol_inv(W, d, 0.0, R, X, flag, true, xpart, st);
   PSK_HIP_TRY(hipGetLastError());
   return 0;
 }
@@ -808,56 +816,53 @@ int sketch_qr_impl(const double *C, int64_t m, int64_t d, double *R, double *Rin
   int rc;
   KTimer timer("sketch_qr", st, run);
   // flag[0]: a Cholesky pivot failed
-  if (run) k_fill<<<1, 64, 0, st>>>(reinterpret_cast<double *>(flag), 2, 0.0);
   if (flag_out) *flag_out = flag;
+  // W = Q^T Q, its partial sums in a copy of Q not in use at the time (too
+  // small for dgram's tiles only below 32 or so columns)
+  auto gram_of = [&](const double *Q, double *idle) -> int {
+    if (m * d >= dgram_room(d)) return run ? dgram(Q, m, d, W, idle, m * d, st) : 0;
+    const int e = dgemm(true, false, d, d, m, 1.0, Q, d, Q, d, 0.0, W, d, ws, st);
+    ws.release(mk);
+    return e;
+  };
   // pass 1 (shifted): W = C^T C + s I, blocked Cholesky
-  if ((rc = dgemm(true, false, d, d, m, 1.0, C, d, C, d, 0.0, W, d, ws, st))) return rc;
-  ws.release(mk);
+  if ((rc = gram_of(C, Qb))) return rc;
   const double u = 1.1102230246251565e-16;
   const double coef = 11.0 * ((double)m * d + (double)d * (d + 1)) * u;
-  if (run) {
-    k_shift_diag<<<1, 256, 0, st>>>(W, d, coef);
-    fill(R1, d * d, 0.0, st);
-    fill(X1, d * d, 0.0, st);
-    chol_inv(W, d, R1, X1, flag, B0, st);  // B0 is not in use yet
-  }
-  if ((rc = dgemm(false, false, m, d, d, 1.0, C, d, X1, d, 0.0, Qa, d, ws, st))) return rc;
-  ws.release(mk);
+  if (run) chol_inv(W, d, coef, R1, X1, flag, true, B0, st);  // B0 is not in use yet
+  // out = a * b for upper triangular b (m or d rows) or a and b (d x d)
+  auto times = [&](const double *a, const double *b, int64_t rows, int tri, double *out) -> int {
+    const int e = dgemm(false, false, rows, d, d, 1.0, a, d, b, d, 0.0, out, d, ws, st, tri);
+    ws.release(mk);
+    return e;
+  };
+  if ((rc = times(C, X1, m, kTriB, Qa))) return rc;
   // pass 2: W = Qa^T Qa
-  if ((rc = dgemm(true, false, d, d, m, 1.0, Qa, d, Qa, d, 0.0, W, d, ws, st))) return rc;
-  ws.release(mk);
-  bool series2 = false, series3 = false;
-  if ((rc = later_pass_chol(W, d, R2, X2, B0, B1, B2, part, flag, &series2, ws, st)))
+  if ((rc = gram_of(Qa, Qb))) return rc;
+  double dist2 = 0.0, dist3 = 0.0;
+  if ((rc = later_pass_chol(W, d, R2, X2, B0, B1, B2, part, flag, &dist2, ws, st)))
     return rc;
   ws.release(mk);
-  // When pass 2 took the series (Qa was orthonormal to within 1e-4), its
-  // result is orthonormal to rounding level and a third pass would change R
-  // only at that level: R = R2 R1, R^{-1} = X1 X2.
-  if (series2) {
-    if ((rc = dgemm(false, false, d, d, d, 1.0, R2, d, R1, d, 0.0, R, d, ws, st))) return rc;
-    ws.release(mk);
-    if ((rc = dgemm(false, false, d, d, d, 1.0, X1, d, X2, d, 0.0, Rinv, d, ws, st))) return rc;
-    ws.release(mk);
+  // When pass 2's W was near the identity, Q is orthonormal to rounding level
+  // after it and a third pass would change R only at that level: R = R2 R1,
+  // R^{-1} = X1 X2.
+  if (dist2 <= kLastTol) {
+    if ((rc = times(R2, R1, d, kTriA | kTriB, R))) return rc;
+    if ((rc = times(X1, X2, d, kTriA | kTriB, Rinv))) return rc;
     if (run) PSK_HIP_TRY(hipGetLastError());
     return 0;
   }
-  if ((rc = dgemm(false, false, m, d, d, 1.0, Qa, d, X2, d, 0.0, Qb, d, ws, st))) return rc;
-  ws.release(mk);
+  if ((rc = times(Qa, X2, m, kTriB, Qb))) return rc;
   // pass 3: W = Qb^T Qb
-  if ((rc = dgemm(true, false, d, d, m, 1.0, Qb, d, Qb, d, 0.0, W, d, ws, st))) return rc;
-  ws.release(mk);
-  if ((rc = later_pass_chol(W, d, R3, X3, B0, B1, B2, part, flag, &series3, ws, st)))
+  if ((rc = gram_of(Qb, Qa))) return rc;
+  if ((rc = later_pass_chol(W, d, R3, X3, B0, B1, B2, part, flag, &dist3, ws, st)))
     return rc;
   ws.release(mk);
   // R = R3 R2 R1, R^{-1} = X1 X2 X3
-  if ((rc = dgemm(false, false, d, d, d, 1.0, R2, d, R1, d, 0.0, T, d, ws, st))) return rc;
-  ws.release(mk);
-  if ((rc = dgemm(false, false, d, d, d, 1.0, R3, d, T, d, 0.0, R, d, ws, st))) return rc;
-  ws.release(mk);
-  if ((rc = dgemm(false, false, d, d, d, 1.0, X1, d, X2, d, 0.0, T, d, ws, st))) return rc;
-  ws.release(mk);
-  if ((rc = dgemm(false, false, d, d, d, 1.0, T, d, X3, d, 0.0, Rinv, d, ws, st))) return rc;
-  ws.release(mk);
+  if ((rc = times(R2, R1, d, kTriA | kTriB, T))) return rc;
+  if ((rc = times(R3, T, d, kTriA | kTriB, R))) return rc;
+  if ((rc = times(X1, X2, d, kTriA | kTriB, T))) return rc;
+  if ((rc = times(T, X3, d, kTriA | kTriB, Rinv))) return rc;
   if (run) PSK_HIP_TRY(hipGetLastError());
   return 0;
 }

@@ -184,7 +184,7 @@ int delta_from_factor(const double *Chat, const double *C, const double *Ri, int
     const int64_t len = m * d;
     k_sub<<<(unsigned)ceil_div(len, 256), 256, 0, st>>>(Chat, C, len, D);
   }
-  if ((rc = dgemm(false, false, m, d, d, 1.0, D, d, Ri, d, 0.0, F, d, ws, st))) return rc;
+  if ((rc = dgemm(false, false, m, d, d, 1.0, D, d, Ri, d, 0.0, F, d, ws, st, kTriB))) return rc;
   ws.release(mk);
   if ((rc = dgemm(true, false, d, d, m, 1.0, F, d, F, d, 0.0, W, d, ws, st))) return rc;
   ws.release(mk);

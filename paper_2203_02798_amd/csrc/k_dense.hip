@@ -107,7 +107,7 @@ template <typename TA, typename TB, bool TRA, bool TRB, int WM, int WN, int MB, 
           int EPI, bool UPPER>
 __global__ __launch_bounds__(256) void k_dgemm(
     int64_t M, int64_t N, int64_t K, const TA *__restrict__ A, int64_t lda,
-    const TB *__restrict__ B, int64_t ldb, int tiles_m, int tiles_n, int64_t kper,
+    const TB *__restrict__ B, int64_t ldb, int tiles_m, int tiles_n, int64_t kper, int tri,
     double *__restrict__ out, int64_t ldo, double alpha, double beta) {
   constexpr int BM = WM * MB * 16;
   constexpr int BN = WN * NB * 16;
@@ -117,9 +117,13 @@ __global__ __launch_bounds__(256) void k_dgemm(
   const TileCoord tc = tile_of(tiles_m, tiles_n, UPPER);
   const int64_t m0 = (int64_t)tc.mt * BM;
   const int64_t n0 = (int64_t)tc.nt * BN;
-  const int64_t kb = (int64_t)tc.ks * kper;
+  int64_t kb = (int64_t)tc.ks * kper;
   int64_t ke = kb + kper;
   if (ke > K) ke = K;
+  // the zero part of a triangular operand is not walked
+  if ((tri & kTriB) && ke > n0 + BN) ke = n0 + BN;
+  if ((tri & kTriAT) && ke > m0 + BM) ke = m0 + BM;
+  if ((tri & kTriA) && kb < m0) kb = m0;
 
   const int tid = threadIdx.x;
   const int wave = tid >> 6;
@@ -185,6 +189,18 @@ __global__ __launch_bounds__(256) void k_dgemm(
           }
         }
       }
+  } else if (EPI == EPI_PARTIAL && UPPER) {
+    // whole tiles, packed: [split][tile][BM][BN]
+    const int64_t nup = (int64_t)tiles_m * (tiles_m + 1) / 2;
+    const int64_t t = (int64_t)tc.mt * tiles_m - (int64_t)tc.mt * (tc.mt - 1) / 2 + tc.nt - tc.mt;
+    double *o = out + ((int64_t)tc.ks * nup + t) * (BM * BN);
+#pragma unroll
+    for (int a = 0; a < MB; ++a)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+          o[((wm * MB + a) * 16 + kq + 4 * e) * BN + (wn * NB + b) * 16 + li] = acc[a][b][e];
   } else if (EPI == EPI_PARTIAL) {
     double *o = out + (int64_t)tc.ks * M * ldo;
 #pragma unroll
@@ -225,27 +241,42 @@ __global__ __launch_bounds__(256) void k_dgemm(
   }
 }
 
-// C = alpha * sum_s part[s] + beta * C; part is [splits][M][ldp].  With
-// mirror, entries below the diagonal are read from the transposed position
-// (only upper tiles were computed).
-template <typename TO>
+// C = alpha * sum_s part[s] + beta * C; part is [splits][M][ldp]
 __global__ __launch_bounds__(256) void k_splitk_reduce(
     const double *__restrict__ part, int64_t M, int64_t N, int64_t ldp, int splits,
-    double alpha, double beta, TO *__restrict__ C, int64_t ldc, int mirror_tile) {
+    double alpha, double beta, double *__restrict__ C, int64_t ldc) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= M * N) return;
-  int64_t i = e / N, j = e % N;
-  if (mirror_tile > 0 && (i / mirror_tile) > (j / mirror_tile)) {
-    const int64_t t = i;
-    i = j;
-    j = t;
-  }
+  const int64_t i = e / N, j = e % N;
   double acc = part[i * ldp + j];
   for (int s = 1; s < splits; ++s) acc += part[(int64_t)s * M * ldp + i * ldp + j];
-  const int64_t oi = e / N, oj = e % N;
   double v = alpha * acc;
-  if (beta != 0.0) v += beta * (double)C[oi * ldc + oj];
-  C[oi * ldc + oj] = (TO)v;
+  if (beta != 0.0) v += beta * C[i * ldc + j];
+  C[i * ldc + j] = v;
+}
+
+// W = sum_s of the packed upper tiles (nup of them, BT x BT), s in order; both
+// triangles written
+template <int BT>
+__global__ __launch_bounds__(256) void k_sym_reduce(const double *__restrict__ part, int64_t d,
+                                                    int64_t nup, int T, int splits,
+                                                    double *__restrict__ W) {
+  int I = 0;
+  int64_t t = blockIdx.y;
+  while (t >= T - I) {
+    t -= T - I;
+    ++I;
+  }
+  const int J = I + (int)t;
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  const int64_t i = (int64_t)I * BT + e / BT, j = (int64_t)J * BT + e % BT;
+  if (i >= d || j >= d) return;
+  const double *p = part + (int64_t)blockIdx.y * (BT * BT) + e;
+  double acc = p[0];
+#pragma unroll 4
+  for (int s = 1; s < splits; ++s) acc += p[(int64_t)s * nup * (BT * BT)];
+  W[i * d + j] = acc;
+  if (I != J) W[j * d + i] = acc;
 }
 
 __global__ __launch_bounds__(256) void k_rownorm_reduce(const double *__restrict__ part,
@@ -261,7 +292,9 @@ __global__ __launch_bounds__(256) void k_rownorm_reduce(const double *__restrict
   x[i] = v;
 }
 
+// K splits of a product with few tiles; from 512 tiles on none
 int64_t pick_splits(int64_t tiles, int64_t K, int64_t target_blocks) {
+  if (tiles >= 512) return 1;
   const int64_t kchunks = ceil_div(K, kBK);
   int64_t s = ceil_div(target_blocks, tiles);
   int64_t smax = kchunks / 16;
@@ -270,38 +303,32 @@ int64_t pick_splits(int64_t tiles, int64_t K, int64_t target_blocks) {
   return s < 1 ? 1 : s;
 }
 
-template <typename TA, typename TB, bool TRA, bool TRB, int WM, int WN, int MB, int NB,
-          bool UPPER>
-int gemm_partial_launch(int64_t M, int64_t N, int64_t K, const TA *A, int64_t lda,
-                        const TB *B, int64_t ldb, double alpha, double beta, void *C,
-                        int64_t ldc, bool out_f32, Arena &ws, hipStream_t st) {
-  constexpr int BM = WM * MB * 16, BN = WN * NB * 16;
+template <bool TRA, bool TRB, int MB, int NB>
+int gemm_launch(int64_t M, int64_t N, int64_t K, const double *A, int64_t lda, const double *B,
+                int64_t ldb, double alpha, double beta, double *C, int64_t ldc, int tri, Arena &ws,
+                hipStream_t st) {
+  constexpr int BM = 32 * MB, BN = 32 * NB;
   const int tm = (int)ceil_div(M, BM), tn = (int)ceil_div(N, BN);
-  const int64_t tiles = UPPER ? (int64_t)tm * (tm + 1) / 2 : (int64_t)tm * tn;
+  const int64_t tiles = (int64_t)tm * tn;
   int64_t splits = pick_splits(tiles, K, 1024);
   const int64_t kper = ceil_div(ceil_div(K, kBK), splits) * kBK;
   splits = K > 0 ? ceil_div(K, kper) : 1;
-  if (splits == 1 && !UPPER && !out_f32) {
+  if (splits == 1) {
     if (ws.dry()) return 0;
-    k_dgemm<TA, TB, TRA, TRB, WM, WN, MB, NB, EPI_DIRECT, false>
-        <<<(unsigned)tiles, 256, 0, st>>>(M, N, K, A, lda, B, ldb, tm, tn, kper,
-                                          (double *)C, ldc, alpha, beta);
+    k_dgemm<double, double, TRA, TRB, 2, 2, MB, NB, EPI_DIRECT, false>
+        <<<(unsigned)tiles, 256, 0, st>>>(M, N, K, A, lda, B, ldb, tm, tn, kper, tri, C, ldc,
+                                          alpha, beta);
     PSK_HIP_TRY(hipGetLastError());
     return 0;
   }
   double *part = ws.take<double>((size_t)splits * M * N);
   if (ws.dry()) return 0;
   if (!ws.ok()) return fail(PSK_ENOMEM, "workspace too small for a GEMM");
-  k_dgemm<TA, TB, TRA, TRB, WM, WN, MB, NB, EPI_PARTIAL, UPPER>
-      <<<(unsigned)(tiles * splits), 256, 0, st>>>(M, N, K, A, lda, B, ldb, tm, tn,
-                                                    kper, part, N, 1.0, 0.0);
-  const int64_t len = M * N;
-  if (out_f32)
-    k_splitk_reduce<float><<<(unsigned)ceil_div(len, 256), 256, 0, st>>>(
-        part, M, N, N, (int)splits, alpha, beta, (float *)C, ldc, UPPER ? BM : 0);
-  else
-    k_splitk_reduce<double><<<(unsigned)ceil_div(len, 256), 256, 0, st>>>(
-        part, M, N, N, (int)splits, alpha, beta, (double *)C, ldc, UPPER ? BM : 0);
+  k_dgemm<double, double, TRA, TRB, 2, 2, MB, NB, EPI_PARTIAL, false>
+      <<<(unsigned)(tiles * splits), 256, 0, st>>>(M, N, K, A, lda, B, ldb, tm, tn, kper, tri,
+                                                   part, N, 1.0, 0.0);
+  k_splitk_reduce<<<(unsigned)ceil_div(M * N, 256), 256, 0, st>>>(part, M, N, N, (int)splits,
+                                                                  alpha, beta, C, ldc);
   PSK_HIP_TRY(hipGetLastError());
   return 0;
 }
@@ -697,7 +724,7 @@ int rownorm_launch(const psk_mat &Am, const double *B, int64_t k, double alpha,
       KTimer timer("rownorm", st);
       k_dgemm<TA, double, false, false, 2, 2, 1, 2, EPI_ROWNORM, false>
           <<<(unsigned)((int64_t)tm * tn), 256, 0, st>>>(n, k, d, A, Am.ld, B, k, tm, tn, d,
-                                                         part, n, 1.0, 0.0);
+                                                         0, part, n, 1.0, 0.0);
     }
     k_rownorm_reduce<<<(unsigned)ceil_div(n, 256), 256, 0, st>>>(part, n, tn, alpha,
                                                                   beta, x);
@@ -711,7 +738,7 @@ int rownorm_launch(const psk_mat &Am, const double *B, int64_t k, double alpha,
       KTimer timer("rownorm", st);
       k_dgemm<TA, double, false, false, 2, 2, 1, 8, EPI_ROWNORM, false>
           <<<(unsigned)((int64_t)tm * tn), 256, 0, st>>>(n, k, d, A, Am.ld, B, k, tm, tn, d,
-                                                         part, n, 1.0, 0.0);
+                                                         0, part, n, 1.0, 0.0);
     }
     k_rownorm_reduce<<<(unsigned)ceil_div(n, 256), 256, 0, st>>>(part, n, tn, alpha,
                                                                   beta, x);
@@ -956,22 +983,55 @@ int gram_syrk_launch(double alpha, const psk_mat &Am, double beta, void *C, bool
 
 int dgemm(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha,
           const double *A, int64_t lda, const double *B, int64_t ldb, double beta,
-          double *C, int64_t ldc, Arena &ws, hipStream_t st) {
+          double *C, int64_t ldc, Arena &ws, hipStream_t st, int tri) {
   if (M <= 0 || N <= 0) return 0;
   if (K <= 0) return fail(PSK_EINVAL, "internal GEMM with K <= 0");
   // up to 1024 x 1024 outputs (the d x d products of the factorizations),
   // 32 x 32 tiles give the chip four times the workgroups of 64 x 64 ones
-#define PSK_DG(TRA, TRB)                                                            \
-  return (M * N <= 1024 * 1024)                                                     \
-      ? gemm_partial_launch<double, double, TRA, TRB, 2, 2, 1, 1, false>(            \
-            M, N, K, A, lda, B, ldb, alpha, beta, C, ldc, false, ws, st)             \
-      : gemm_partial_launch<double, double, TRA, TRB, 2, 2, 2, 2, false>(            \
-            M, N, K, A, lda, B, ldb, alpha, beta, C, ldc, false, ws, st)
+#define PSK_DG(TRA, TRB)                                                                       \
+  return (M * N <= 1024 * 1024)                                                                \
+      ? gemm_launch<TRA, TRB, 1, 1>(M, N, K, A, lda, B, ldb, alpha, beta, C, ldc, tri, ws, st) \
+      : gemm_launch<TRA, TRB, 2, 2>(M, N, K, A, lda, B, ldb, alpha, beta, C, ldc, tri, ws, st)
   if (ta && tb) PSK_DG(true, true);
   if (ta) PSK_DG(true, false);
   if (tb) PSK_DG(false, true);
   PSK_DG(false, false);
 #undef PSK_DG
+}
+
+int dgram(const double *C, int64_t m, int64_t d, double *W, double *scratch, int64_t room,
+          hipStream_t st) {
+  // 64 x 64 tiles where they and their K splits (eight 16-row chunks or more
+  // each) fill the chip, else 32 x 32 ones: a wavefront then has one block a
+  // step, a quarter of the matrix work per operand read
+  const int64_t kch = ceil_div(m, (int64_t)kBK);
+  const int64_t smax = kch / 8 > 0 ? kch / 8 : 1;
+  auto run = [&](auto mb) -> int {
+    constexpr int MB = decltype(mb)::value, BT = 32 * MB;
+    const int T = (int)ceil_div(d, (int64_t)BT);
+    const int64_t nup = (int64_t)T * (T + 1) / 2;
+    int64_t splits = 768 / nup;
+    if (splits > smax) splits = smax;
+    if (splits > room / (nup * BT * BT)) splits = room / (nup * BT * BT);
+    if (splits < 1) splits = 1;
+    const int64_t kper = ceil_div(kch, splits) * kBK;
+    splits = ceil_div(m, kper);
+    k_dgemm<double, double, true, false, 2, 2, MB, MB, EPI_PARTIAL, true>
+        <<<(unsigned)(nup * splits), 256, 0, st>>>(d, d, m, C, d, C, d, T, T, kper, 0, scratch,
+                                                   d, 1.0, 0.0);
+    k_sym_reduce<BT><<<dim3(BT * BT / 256, (unsigned)nup), 256, 0, st>>>(scratch, d, nup, T,
+                                                                        (int)splits, W);
+    PSK_HIP_TRY(hipGetLastError());
+    return 0;
+  };
+  const int64_t T64 = ceil_div(d, (int64_t)64), n64 = T64 * (T64 + 1) / 2;
+  const bool wide = n64 * smax >= 256 && n64 * 4096 <= room;
+  return wide ? run(std::integral_constant<int, 2>{}) : run(std::integral_constant<int, 1>{});
+}
+
+int64_t dgram_room(int64_t d) {
+  const int64_t T = ceil_div(d, (int64_t)32);  // one split of whole 32 x 32 tiles
+  return T * (T + 1) / 2 * 1024;
 }
 
 int gram_dense(double alpha, const psk_mat &A, double beta, void *C, Arena &ws,

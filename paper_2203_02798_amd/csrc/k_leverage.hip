@@ -75,7 +75,7 @@ int leverage_sketch_impl(const psk_mat &A, int64_t m, int64_t r, int64_t t, uint
       k_jl_normals<<<(unsigned)ceil_div(thr, 256), 256, 0, st>>>(d, t, seed, Z);
     }
     if ((rc = dgemm(false, false, d, t, d, 1.0 / sqrt((double)t), Ri, d, Z, t, 0.0, X, t, ws,
-                    st)))
+                    st, kTriA)))
       return rc;
   }
   ws.release(mk2);

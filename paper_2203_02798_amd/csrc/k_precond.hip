@@ -30,43 +30,70 @@ constexpr double kGuardC = 16.0 * 1.1102230246251565e-16;  // c u
 constexpr int kGuardCols = 64;   // columns of a k_guard workgroup
 constexpr int kMaxGuard = 1024 / kGuardCols;
 
-// g[k] = ||R e_k||, R upper triangular: a workgroup takes 64 columns, its
-// four wavefronts every fourth row
-__global__ __launch_bounds__(256) void k_col_norm_upper(const double *__restrict__ R, int64_t d,
-                                                        double *__restrict__ g) {
-  __shared__ double red[4][kGuardCols];
+// A workgroup takes 64 columns j, a lane each; its 16 wavefronts take every
+// 16th row k <= j, eight rows' loads in flight (one at a time, by four
+// wavefronts, d = 500 took 77 us).  term(k, j) summed over k, the wavefronts'
+// sums then in order, valid in wavefront 0.
+constexpr int kGuardWaves = 16;
+constexpr int kGuardBatch = 8;
+
+template <class Load, class Use>
+__device__ __forceinline__ double column_sum(int64_t d, Load load, Use use) {
+  __shared__ double red[kGuardWaves][kGuardCols];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t j = (int64_t)blockIdx.x * kGuardCols + lane;
+  const int64_t jend = (int64_t)(blockIdx.x + 1) * kGuardCols < d
+                           ? (int64_t)(blockIdx.x + 1) * kGuardCols : d;  // rows of the block
   double s = 0.0;
-  if (j < d)
-    for (int64_t i = wave; i <= j; i += 4) s = fma(R[i * d + j], R[i * d + j], s);
+  for (int64_t k0 = wave; k0 < jend; k0 += kGuardWaves * kGuardBatch) {
+    double m[kGuardBatch], g[kGuardBatch];
+#pragma unroll
+    for (int q = 0; q < kGuardBatch; ++q) {
+      const int64_t k = k0 + kGuardWaves * q;
+      load(k < jend ? k : jend - 1, j < d ? j : d - 1, m[q], g[q]);  // clamped; masked below
+    }
+#pragma unroll
+    for (int q = 0; q < kGuardBatch; ++q)
+      if (k0 + kGuardWaves * q <= j && j < d) s = use(s, m[q], g[q]);
+  }
   red[wave][lane] = s;
   __syncthreads();
-  if (wave == 0 && j < d)
-    g[j] = sqrt((red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]));
+  double t = red[0][lane];
+#pragma unroll
+  for (int q = 1; q < kGuardWaves; ++q) t += red[q][lane];
+  return t;
+}
+
+// g[k] = ||R e_k||, R upper triangular
+__global__ __launch_bounds__(64 * kGuardWaves) void k_col_norm_upper(
+    const double *__restrict__ R, int64_t d, double *__restrict__ g) {
+  const double s = column_sum(
+      d, [&](int64_t k, int64_t j, double &m, double &) { m = R[k * d + j]; },
+      [](double s2, double m, double) { return fma(m, m, s2); });
+  const int64_t j = (int64_t)blockIdx.x * kGuardCols + threadIdx.x;
+  if (threadIdx.x < kGuardCols && j < d) g[j] = sqrt(s);
 }
 
 // part[b] = sum over the workgroup's columns j of (sum_{k <= j} |M_kj| g_k)^2,
 // g_k = g[k] (mode 0), 1 / |g[k d + k]| (mode 1) or sqrt(g[k d + k]) (mode 2)
-__global__ __launch_bounds__(256) void k_guard(const double *__restrict__ M, int64_t d,
-                                               const double *__restrict__ g, int mode,
-                                               double *__restrict__ part) {
-  __shared__ double red[4][kGuardCols];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t j = (int64_t)blockIdx.x * kGuardCols + lane;
-  double t = 0.0;
-  if (j < d)
-    for (int64_t k = wave; k <= j; k += 4) {
-      const double gk = mode == 0 ? g[k] : mode == 1 ? 1.0 / fabs(g[k * d + k])
-                                                     : sqrt(g[k * d + k]);
-      t = fma(fabs(M[k * d + j]), gk, t);
-    }
-  red[wave][lane] = t;
-  __syncthreads();
-  if (wave == 0) {
-    const double tj = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
-    const double s = wave_sum(j < d ? tj * tj : 0.0);
-    if (lane == 0) part[blockIdx.x] = s;
+__global__ __launch_bounds__(64 * kGuardWaves) void k_guard(const double *__restrict__ M,
+                                                            int64_t d,
+                                                            const double *__restrict__ g,
+                                                            int mode,
+                                                            double *__restrict__ part) {
+  const double t = column_sum(
+      d,
+      [&](int64_t k, int64_t j, double &m, double &gk) {
+        m = M[k * d + j];
+        gk = mode == 0 ? g[k] : g[k * d + k];
+      },
+      [&](double s, double m, double gk) {
+        return fma(fabs(m), mode == 0 ? gk : mode == 1 ? 1.0 / fabs(gk) : sqrt(gk), s);
+      });
+  if (threadIdx.x < kGuardCols) {
+    const int64_t j = (int64_t)blockIdx.x * kGuardCols + threadIdx.x;
+    const double s = wave_sum(j < d ? t * t : 0.0);
+    if (threadIdx.x == 0) part[blockIdx.x] = s;
   }
 }
 
@@ -114,10 +141,10 @@ void precond_estimate(const psk_mat &A, const double *R, const double *N, double
                       double *est, hipStream_t st) {
   const int64_t d = A.d;
   if (R) {
-    k_col_norm_upper<<<guard_blocks(d), 256, 0, st>>>(R, d, g);
-    k_guard<<<guard_blocks(d), 256, 0, st>>>(N, d, g, 0, est);
+    k_col_norm_upper<<<guard_blocks(d), 64 * kGuardWaves, 0, st>>>(R, d, g);
+    k_guard<<<guard_blocks(d), 64 * kGuardWaves, 0, st>>>(N, d, g, 0, est);
   } else {
-    k_guard<<<guard_blocks(d), 256, 0, st>>>(N, d, N, 1, est);
+    k_guard<<<guard_blocks(d), 64 * kGuardWaves, 0, st>>>(N, d, N, 1, est);
   }
   if (A.format == PSK_CSR)
     k_row_squares<<<kPrecondRowParts, 256, 0, st>>>(A.indptr, A.n, est + kMaxGuard);
@@ -158,16 +185,17 @@ int precond_sharpen(const psk_mat &A, const double *N, bool caller, double *P, A
     if (run) k_upper<<<ew, 256, 0, st>>>(N, d, U);
     T = U;
   }
-  if ((rc = dgemm(false, false, d, d, d, 1.0, G, d, T, d, 0.0, S, d, ws, st))) return rc;
+  if ((rc = dgemm(false, false, d, d, d, 1.0, G, d, T, d, 0.0, S, d, ws, st, kTriB))) return rc;
   ws.release(mk);
-  if ((rc = dgemm(true, false, d, d, d, 1.0, T, d, S, d, 0.0, W, d, ws, st))) return rc;
+  if ((rc = dgemm(true, false, d, d, d, 1.0, T, d, S, d, 0.0, W, d, ws, st, kTriAT))) return rc;
   ws.release(mk);
   if ((rc = chol_factor(W, d, S, X, flag, ws, st))) return rc;
   ws.release(mk);
-  if ((rc = dgemm(false, false, d, d, d, 1.0, T, d, X, d, 0.0, P, d, ws, st))) return rc;
+  if ((rc = dgemm(false, false, d, d, d, 1.0, T, d, X, d, 0.0, P, d, ws, st, kTriA | kTriB)))
+    return rc;
   ws.release(mk);
   if (!run) return 0;
-  k_guard<<<guard_blocks(d), 256, 0, st>>>(P, d, G, 2, part);
+  k_guard<<<guard_blocks(d), 64 * kGuardWaves, 0, st>>>(P, d, G, 2, part);
   k_precond_pick<<<ew, 256, 0, st>>>(N, d, part, (int)guard_blocks(d), flag, P);
   PSK_HIP_TRY(hipGetLastError());
   return 0;

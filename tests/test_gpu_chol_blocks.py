@@ -48,3 +48,22 @@ def test_factor_flags(d, col):
     with pytest.raises(api.PskError) as e:
         api.leverage_gram(to_device(a))
     assert e.value.status == -8  # PSK_ENONFINITE
+
+
+@pytest.mark.parametrize("m,d,cond", [(1024, 256, 3e2), (1024, 256, 3e3), (1024, 256, 1e4),
+                                      (1024, 256, 3e4), (700, 600, 1e3), (4000, 1000, 1e2),
+                                      (33, 31, 1e3), (20, 3, 1e4)])
+def test_second_or_third_pass(m, d, cond):
+    """Either side of where the second pass is the last (the first one's shift
+    leaves its Gram matrix within 1/2 of the identity to about cond 1e4), with
+    one and several K splits of the Gram products and both tile sizes."""
+    from paper_2203_02798_amd import api
+    print(f"sketch_qr m={m} d={d} cond={cond}", flush=True)
+    c, _, _ = synth.lsq_problem(m, d, cond, seed=3, noise=0.0)
+    r, ri = (t.cpu().numpy() for t in api.sketch_qr(to_device(c)))
+    assert np.linalg.norm(r.T @ r - c.T @ c) <= 1e-13 * np.linalg.norm(c.T @ c)
+    ref = np.linalg.qr(c, mode="r")
+    ref *= np.sign(np.diag(ref))[:, None]
+    k = np.linalg.cond(c)
+    assert np.linalg.norm(r - ref) <= 50 * k * U64 * np.linalg.norm(ref)
+    assert np.linalg.norm(ri @ r - np.eye(d)) <= 1e3 * k * d * U64
