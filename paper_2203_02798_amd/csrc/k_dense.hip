@@ -17,6 +17,8 @@
 // multiplied.  FP32 inputs are widened to FP64 when staged.
 #include <type_traits>
 
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace psk {
@@ -105,7 +107,7 @@ __device__ __forceinline__ TileCoord tile_of(int tiles_m, int tiles_n, bool uppe
 
 template <typename TA, typename TB, bool TRA, bool TRB, int WM, int WN, int MB, int NB,
           int EPI, bool UPPER>
-__global__ __launch_bounds__(256) void k_dgemm(
+__global__ __launch_bounds__(256, 2) void k_dgemm(
     int64_t M, int64_t N, int64_t K, const TA *__restrict__ A, int64_t lda,
     const TB *__restrict__ B, int64_t ldb, int tiles_m, int tiles_n, int64_t kper, int tri,
     double *__restrict__ out, int64_t ldo, double alpha, double beta) {
@@ -751,230 +753,366 @@ int rownorm_launch(const psk_mat &Am, const double *B, int64_t k, double alpha,
 // ---------------------------------------------------------------------------
 // Gram matrix of a dense tall A: C = A^T A as a sum over row slabs
 // ---------------------------------------------------------------------------
-// Each wavefront owns one 64 x 64 tile (I, J), I <= J, of the upper block
-// triangle of C and one slab of consecutive rows of A, and accumulates that
-// slab's contribution in registers (4 x 4 blocks of 16 x 16 FP64
-// accumulators).  Lane (li, kq) = (lane % 16, lane / 16) reads, for row
-// k0 + kq, the four consecutive columns 64 I + 4 li .. + 3 (one vector load)
-// and the same four of the tile's J columns: component a of that load is
-// row li of the MFMA operand block a, so block a of the tile holds the
-// columns 64 I + 4 i + a, i = 0 .. 15 (and likewise for J).  Block (a, b)
-// then accumulates C[64 I + 4 i + a][64 J + 4 j + b].  On a diagonal tile
-// (I = J) block (b, a) is the transpose of block (a, b), so only a <= b are
-// multiplied (10 of 16) and the others are mirrored when the tile is
-// written: the executed products are those of the upper triangle at the
-// 16 x 16 block level, n d (d + 16) flops for d a multiple of 64.
-// Rows past the slab and columns past d read as zero.
-// A diagonal tile does 10 of the 16 block products per row step, so its
-// slabs are 1.6 times as long (rows_d against rows_o rows): every work item
-// then costs about the same, and no SIMD waits on a pair of off-diagonal
-// items while others finish early.  The off-diagonal items come first,
-// (slab g / Uo, off-diagonal tile g % Uo), then the diagonal ones (slab,
-// tile (g' % T, g' % T)); four per workgroup, and workgroups of the same
-// XCD (linear ids equal mod 8) take consecutive items, so the tiles of one
-// slab read its rows through one L2.  Slab s of tile t writes its 64 x 64
-// partial (both triangles of a diagonal tile) to part at gram_part_off(t)
-// + s 4096; k_gram_reduce1 sums each tile's slabs in order (no atomics).
-// Row steps whose loads are in flight.  Four keep a wavefront at 208
-// registers (its 128 accumulators and 80 VGPRs), so beside the kernel's two
-// wavefronts per SIMD 96 registers stay free for the smaller kernels of a
-// stream beside it (the sketch's binning, the QR's GEMMs at 54).  Eight run
-// the Gram alone 4% faster (FP32 4e6 x 256: 4.71 ms at 4, 4.54 at 8) but
-// take 240 and leave 32: the sketch-beside-Gram step then takes 11.33 ms
-// against 11.17.
-constexpr int kGramPF = 4;
+// A work item is one 64 x 64 tile (I, J), I <= J, of the upper block triangle
+// of C and one slab of consecutive rows of A.  WPT wavefronts share it, each
+// accumulating every WPT-th group of the slab's rows in registers (4 x 4
+// blocks of 16 x 16 FP64 accumulators); with four (a whole workgroup) the
+// sums are added in LDS, in wavefront order, before the tile is written.  Lane (li, kq) = (lane % 16, lane / 16) reads, of row k0 + kq,
+// element li of each 16-column block.  On a diagonal tile (I = J) only the
+// blocks a <= b are multiplied (10 of 16).  The last tile of a d that is not
+// a multiple of 64 has fewer blocks (NBT of 4): the blocks past d are neither
+// read nor multiplied (d = 97: 28 blocks a step, not 36).
+// What bounds it: the FP64 matrix cores and next to them every vector
+// instruction, since the two do not run side by side (a 16 x 16 x 4 product
+// takes 64 cycles, each vector instruction about 4 more).  So the loop holds
+// little else than loads, FP32 conversions and products: addresses are one
+// addition per row and side, columns past d are clamped to column d - 1 (they
+// reach only outputs past d, which nobody reads) and rows are counted, so no
+// element is masked except in a slab's last rows; and two wavefronts per SIMD
+// are stated to the compiler, which then keeps the accumulators where the
+// products use them (without it they moved between the two register files on
+// every step).
+// Past that it waits for its rows in the vector L1 (FP64 1e6 x 256: 55 TF/s
+// whatever the instruction count; FP32, half the bytes: 65).
+// Two arrangements.  WPT = 4, d <= 112: as above, a partial per workgroup;
+// narrow products are short of work, and the fewer partials matter most.
+// WPT = 1, wider: every wavefront has a tile and a slab of its own and
+// writes its own partial, so that the workgroup's wavefronts, mostly tiles of
+// one slab, find each other's rows in the L1.  Measured in us, before / one
+// wavefront / four: FP64 300,000 x 64: 91 / 55 / 48, 300,007 x 97: 162 / 116
+// / 97, 1e6 x 128: 456 / 416 / 547, 1e6 x 256: 1290 / 1266 / 1728; FP32
+// 1e6 x 128: 390 / 306 / 309, 1e6 x 256: 1255 / 1076 / 1104.  Before, the
+// loads were masked element by element, the accumulators moved every step
+// and a small A was cut into 2048 partials whatever its size (20,000 x 50:
+// 34 us with its reduction, now 21; 20,000 x 256: 111, now 45).
+// Work items: the classes of tiles (off-diagonal, off-diagonal in the last
+// tile column, diagonal, last diagonal) take 16, 4 NBT, 10 and
+// NBT (NBT + 1) / 2 block products a row step, and each class gets slabs in
+// proportion, so that every item costs about the same and all of them run in
+// one round, two wavefronts per SIMD.  Slab-major order inside a class, and
+// workgroups of one XCD (linear ids equal mod 8) take consecutive items: the
+// tiles of one slab read its rows through one L2.  No atomics.
+constexpr int kGramWaves = 4;
+// Row steps whose loads are in flight: six where a wavefront has its item to
+// itself (FP64 300,000 x 129: 239 us at four, 206 at six; 198 registers, so
+// the smaller kernels of a stream beside the Gram still find room), four
+// where the workgroup shares it and the rows are few (20,000 x 97: 25 us at
+// four, 30 at six).
+constexpr int gram_prefetch(int wpt) { return wpt == 1 ? 6 : 4; }
+constexpr int kGramLds = 64 + 16;  // row stride of the LDS sum: rows kq and kq + 1 in other banks
 
-// (I, J), I < J, of off-diagonal tile o in row-major order
-__device__ __forceinline__ void gram_offdiag_tile(int o, int T, int &I, int &J) {
-  I = 0;
-  int rest = o;
-  while (rest >= T - 1 - I) {
-    rest -= T - 1 - I;
-    ++I;
+// The four tile classes of a T-tile-wide upper triangle: count of tiles and
+// slabs of each, in item order.
+struct GramPlan {
+  int T;        // tiles across
+  int nbt;      // 16-column blocks of the last tile
+  int cnt[4];   // tiles: off-diagonal, off-diagonal last column, diagonal, last diagonal
+  int slabs[4];
+  int64_t rows[4];   // rows of a slab
+  int64_t first[5];  // first item of each class; [4]: items in all
+};
+
+// class of tile (I, J) and its index in the class
+__device__ __forceinline__ int gram_class(const GramPlan &p, int I, int J, int &idx) {
+  const bool tail = p.cnt[3] != 0 && J == p.T - 1;
+  if (I == J) {
+    idx = tail ? 0 : I;
+    return tail ? 3 : 2;
   }
-  J = I + 1 + rest;
+  idx = tail ? I : J * (J - 1) / 2 + I;
+  return tail ? 1 : 0;
 }
 
-// first partial of tile (I, J) (row-major upper triangle): the diagonal
-// tiles before it (I of them, one more when J > I) have sd slabs, the others
-// so slabs
-__host__ __device__ __forceinline__ int64_t gram_part_off(int I, int J, int T, int64_t so,
-                                                          int64_t sd) {
-  const int t = I * T - I * (I - 1) / 2 + (J - I);
-  const int nd = I + (J > I ? 1 : 0);
-  return ((int64_t)nd * sd + (int64_t)(t - nd) * so) * 4096;
+// One wavefront's share of the rows [k0, k1) of a tile (every kGramWaves-th
+// group of rows, the last rows to wavefront 0): NI x NJ blocks (DG: NI = NJ,
+// the upper ones).  CLAMP: the tile is the last one of a ragged d, whose last
+// block holds columns past d: they read column d - 1.
+template <typename TA, int WPT, bool DG, bool CLAMP, int NI, int NJ>
+__device__ __forceinline__ void gram_rows(const TA *__restrict__ A, int64_t ld, int64_t d,
+                                          int64_t k0, int64_t k1, int wave, int I, int J,
+                                          v4d (&acc)[4][4]) {
+  constexpr int PF = gram_prefetch(WPT);
+  const int lane = threadIdx.x & 63;
+  const int li = lane & 15, kq = lane >> 4;
+  const TA *pi = A + (int64_t)kq * ld + 64 * (int64_t)I + li;
+  const TA *pj = A + (int64_t)kq * ld + 64 * (int64_t)J + li;
+  // the last block of the J columns, relative to pj
+  int64_t lastj = 16 * (NJ - 1);
+  if (CLAMP) {
+    const int64_t left = d - 1 - 64 * (int64_t)J - li;
+    if (left < lastj) lastj = left;
+  }
+  auto load = [&](const TA *p, bool isj, int nb, TA (&x)[4]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      if (b >= nb) continue;
+      x[b] = CLAMP && isj && b == nb - 1 ? p[lastj] : p[16 * b];
+    }
+  };
+  auto mul = [&](const TA (&xi)[4], const TA (&xj)[4]) __attribute__((always_inline)) {
+    double av[4], bv[4];
+#pragma unroll
+    for (int a = 0; a < NI; ++a) av[a] = (double)xi[a];
+#pragma unroll
+    for (int b = 0; b < NJ; ++b) bv[b] = DG ? av[b] : (double)xj[b];
+#pragma unroll
+    for (int a = 0; a < NI; ++a)
+#pragma unroll
+      for (int b = 0; b < NJ; ++b)
+        if (!DG || a <= b)
+          acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
+  };
+  TA xi[PF][4], xj[PF][4];
+  auto fetch = [&](int p, int64_t row) __attribute__((always_inline)) {
+    load(pi + row * ld, DG, NI, xi[p]);
+    if constexpr (!DG) load(pj + row * ld, true, NJ, xj[p]);
+  };
+  // this wavefront's groups of PF steps, WPT groups apart; the
+  // loads past its last group repeat that group (in bounds, unused)
+  constexpr int64_t kGroup = 4 * PF;
+  const int64_t groups = (k1 - k0) / kGroup;
+  if (wave < groups) {
+#pragma unroll
+    for (int p = 0; p < PF; ++p) fetch(p, k0 + kGroup * wave + 4 * p);
+    for (int64_t g = wave; g < groups; g += WPT) {
+      const int64_t next = k0 + kGroup * (g + WPT < groups ? g + WPT : g);
+#pragma unroll
+      for (int p = 0; p < PF; ++p) {
+        TA ci[4], cj[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          ci[b] = xi[p][b];
+          cj[b] = xj[p][b];
+        }
+        mul(ci, cj);
+        fetch(p, next + 4 * p);
+      }
+    }
+  }
+  if (wave) return;
+  // the rest (fewer than 16 rows, at the end of A only): rows past k1 as zero
+  for (int64_t k = k0 + groups * kGroup; k < k1; k += 4) {
+    const bool ok = k + kq < k1;
+    const int64_t row = ok ? k : k1 - 1 - kq;  // relative to this lane's row kq
+    fetch(0, row);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      xi[0][b] = ok && b < NI ? xi[0][b] : (TA)0;
+      if constexpr (!DG) xj[0][b] = ok && b < NJ ? xj[0][b] : (TA)0;
+    }
+    mul(xi[0], xj[0]);
+  }
 }
 
-template <typename TA, bool VEC>
-__global__ __launch_bounds__(256) void k_gram_syrk(const TA *__restrict__ A, int64_t ld,
-                                                   int64_t n, int64_t d, int T,
-                                                   int64_t so, int64_t rows_o,
-                                                   int64_t sd, int64_t rows_d,
-                                                   double *__restrict__ part) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+template <typename TA, int WPT>
+__global__ __launch_bounds__(64 * kGramWaves, 2) void k_gram_syrk(const TA *__restrict__ A,
+                                                                  int64_t ld, int64_t n,
+                                                                  int64_t d, GramPlan pl,
+                                                                  double *__restrict__ part) {
+  static_assert(WPT == 1 || WPT == kGramWaves, "one wavefront or the workgroup per item");
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int li = lane & 15, kq = lane >> 4;
   const int64_t nblk = gridDim.x;
-  int64_t lin = blockIdx.x;
-  if ((nblk & 7) == 0) lin = (lin & 7) * (nblk >> 3) + (lin >> 3);
-  const int64_t g = lin * 4 + wave;
-  const int Uo = T * (T - 1) / 2;
-  const int64_t no = so * Uo;
-  if (g >= no + sd * T) return;
+  int64_t g = blockIdx.x;
+  if ((nblk & 7) == 0) g = (g & 7) * (nblk >> 3) + (g >> 3);
+  if (WPT == 1) g = g * kGramWaves + wave;
+  if (g >= pl.first[4]) return;
+  int cls = 0;
+  while (g >= pl.first[cls + 1]) ++cls;
+  const int64_t local = g - pl.first[cls];
+  const int64_t slab = local / pl.cnt[cls];
+  const int idx = (int)(local - slab * pl.cnt[cls]);
   int I, J;
-  int64_t slab, rows_per;
-  if (g < no) {
-    slab = g / Uo;
-    gram_offdiag_tile((int)(g - slab * Uo), T, I, J);
-    rows_per = rows_o;
+  if (cls == 0) {
+    J = 1;
+    while (J * (J + 1) / 2 <= idx) ++J;
+    I = idx - J * (J - 1) / 2;
   } else {
-    slab = (g - no) / T;
-    I = J = (int)(g - no - slab * T);
-    rows_per = rows_d;
+    I = cls == 3 ? pl.T - 1 : idx;
+    J = cls == 2 ? idx : pl.T - 1;
   }
-  const bool diag = I == J;
-  const int64_t k_begin = slab * rows_per;
-  int64_t k_end = k_begin + rows_per;
-  if (k_end > n) k_end = n;
-  const int64_t ci = (int64_t)I * 64 + 4 * li, cj = (int64_t)J * 64 + 4 * li;
+  const int64_t k0 = slab * pl.rows[cls];
+  int64_t k1 = k0 + pl.rows[cls];
+  if (k1 > n) k1 = n;
   v4d acc[4][4];
 #pragma unroll
   for (int a = 0; a < 4; ++a)
 #pragma unroll
     for (int b = 0; b < 4; ++b) acc[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
-  auto run = [&](auto dg) __attribute__((always_inline)) {
-    constexpr bool DG = decltype(dg)::value;
-    Raw4<TA> xa[kGramPF], xb[kGramPF];
-    auto fetch = [&](int p, int64_t k0) __attribute__((always_inline)) {
-      const int64_t row = k0 + kq;
-      const bool rok = row < k_end;
-      raw4_load<TA, VEC>(A, ld, d, rok ? row : 0, rok, ci, xa[p]);
-      if constexpr (!DG) raw4_load<TA, VEC>(A, ld, d, rok ? row : 0, rok, cj, xb[p]);
-    };
+  const int wt = WPT == 1 ? 0 : wave;  // wavefront of the item
+#define PSK_GR(DG, CL, NI, NJ) gram_rows<TA, WPT, DG, CL, NI, NJ>(A, ld, d, k0, k1, wt, I, J, acc)
+  if (cls == 0) PSK_GR(false, false, 4, 4);
+  else if (cls == 2) PSK_GR(true, false, 4, 4);
+  else if (cls == 1) {
+    if (pl.nbt == 4) PSK_GR(false, true, 4, 4);
+    else if (pl.nbt == 3) PSK_GR(false, true, 4, 3);
+    else if (pl.nbt == 2) PSK_GR(false, true, 4, 2);
+    else PSK_GR(false, true, 4, 1);
+  } else {
+    if (pl.nbt == 4) PSK_GR(true, true, 4, 4);
+    else if (pl.nbt == 3) PSK_GR(true, true, 3, 3);
+    else if (pl.nbt == 2) PSK_GR(true, true, 2, 2);
+    else PSK_GR(true, true, 1, 1);
+  }
+#undef PSK_GR
+  // lane (li, kq) holds rows kq + 4 e, column li of each block; the blocks
+  // not multiplied hold zeros and are not read from the sum
+  double *o = part + g * 4096;
+  if constexpr (WPT == 1) {
 #pragma unroll
-    for (int p = 0; p < kGramPF; ++p) fetch(p, k_begin + 4 * p);
-    for (int64_t k0 = k_begin; k0 < k_end; k0 += 4 * kGramPF) {
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
-      for (int p = 0; p < kGramPF; ++p) {
-        double av[4], bv[4];
+      for (int b = 0; b < 4; ++b)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          av[q] = raw4_get(xa[p], q);
-          bv[q] = DG ? av[q] : raw4_get(xb[p], q);
-        }
-        fetch(p, k0 + 4 * (p + kGramPF));
+        for (int e = 0; e < 4; ++e) o[(16 * a + kq + 4 * e) * 64 + 16 * b + li] = acc[a][b][e];
+  } else {
+    __shared__ __align__(16) double sum[64][kGramLds];
+#pragma unroll 1
+    for (int w = 0; w < kGramWaves; ++w) {
+      if (wave == w) {
 #pragma unroll
         for (int a = 0; a < 4; ++a)
 #pragma unroll
           for (int b = 0; b < 4; ++b)
-            if (!DG || a <= b)
-              acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              double *s = &sum[16 * a + kq + 4 * e][16 * b + li];
+              *s = w ? *s + acc[a][b][e] : acc[a][b][e];
+            }
       }
+      __syncthreads();
     }
-  };
-  if (diag) run(std::true_type{});
-  else run(std::false_type{});
-  // lane (li, kq) holds rows kq + 4 e, column li of each block: the tile's
-  // local element (4 (kq + 4 e) + a, 4 li + b)
-  double *o = part + gram_part_off(I, J, T, so, sd) + slab * 4096;
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      if (diag && a > b) continue;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int pr = 4 * (kq + 4 * e) + a, pc = 4 * li + b;
-        o[pr * 64 + pc] = acc[a][b][e];
-        if (diag && a < b) o[pc * 64 + pr] = acc[a][b][e];
-      }
+    for (int q = 0; q < 8; ++q) {
+      const int e = 2 * (threadIdx.x + 256 * q);
+      *reinterpret_cast<double2 *>(o + e) =
+          *reinterpret_cast<const double2 *>(&sum[e >> 6][e & 63]);
     }
+  }
 }
 
-// First level of the slab sum: group q of kGramGroups sums its slabs in
-// order, gpart[q][p][c] for the d x d output, taken from the upper tile
-// (transposed for p > c).
+// C = alpha * sum over a tile's slabs + beta * C (beta == 0 ignores C): one
+// workgroup per tile row of 64 columns, blockDim.y groups of slabs summed
+// side by side (eight loads at once) and then in order.  The element (p, c),
+// p <= c, of the tile also gives (c, p).
 constexpr int kGramGroups = 16;
 
-__global__ __launch_bounds__(256) void k_gram_reduce1(const double *__restrict__ part,
-                                                      int64_t d, int T, int64_t so, int64_t sd,
-                                                      double *__restrict__ gpart) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t q = blockIdx.y;
-  if (e >= d * d) return;
-  int64_t p = e / d, c = e % d;
-  if (p / 64 > c / 64) {
-    const int64_t x = p;
-    p = c;
-    c = x;
-  }
-  const int I = (int)(p / 64), J = (int)(c / 64);
-  const int64_t slabs = I == J ? sd : so;
-  const int64_t off = gram_part_off(I, J, T, so, sd) + (p % 64) * 64 + (c % 64);
-  const int64_t s0 = slabs * q / kGramGroups, s1 = slabs * (q + 1) / kGramGroups;
-  double acc = 0.0;
-  for (int64_t s = s0; s < s1; ++s) acc += part[off + s * 4096];
-  gpart[q * d * d + e] = acc;
-}
-
-// C = alpha * sum of the groups (in order) + beta * C (beta == 0 ignores C)
 template <typename TO>
-__global__ __launch_bounds__(256) void k_gram_reduce2(const double *__restrict__ gpart,
-                                                      int64_t dd, double alpha, double beta,
-                                                      TO *__restrict__ C) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= dd) return;
-  double acc = gpart[e];
+__global__ __launch_bounds__(64 * kGramGroups) void k_gram_reduce(
+    const double *__restrict__ part, int64_t d, GramPlan pl, double alpha, double beta,
+    TO *__restrict__ C) {
+  __shared__ double sum[kGramGroups][64];
+  const int x = threadIdx.x, y = threadIdx.y, ny = blockDim.y;
+  const int row = blockIdx.x & 63, tile = blockIdx.x >> 6;
+  int J = 0;
+  while ((J + 1) * (J + 2) / 2 <= tile) ++J;
+  const int I = tile - J * (J + 1) / 2;
+  const int64_t p = 64 * (int64_t)I + row, c = 64 * (int64_t)J + x;
+  if (p >= d) return;  // the whole workgroup
+  int idx;
+  const int cls = gram_class(pl, I, J, idx);
+  const int64_t slabs = pl.slabs[cls], step = (int64_t)pl.cnt[cls] * 4096;
+  const int64_t s0 = slabs * y / ny, s1 = slabs * (y + 1) / ny;
+  const bool on = c < d && (I != J || row / 16 <= x / 16);
+  double acc = 0.0;
+  if (on) {
+    const double *q = part + (pl.first[cls] + idx) * 4096 + row * 64 + x;
+    int64_t s = s0;
+    for (; s + 8 <= s1; s += 8) {
+      double v[8];
 #pragma unroll
-  for (int q = 1; q < kGramGroups; ++q) acc += gpart[q * dd + e];
+      for (int u = 0; u < 8; ++u) v[u] = q[(s + u) * step];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc += v[u];
+    }
+    for (; s < s1; ++s) acc += q[s * step];
+  }
+  if (ny > 1) {
+    sum[y][x] = acc;
+    __syncthreads();
+    if (y) return;
+    for (int u = 1; u < ny; ++u) acc += sum[u][x];
+  }
+  if (!on || y) return;
   double v = alpha * acc;
+  const int64_t e = p * d + c, m = c * d + p;
+  // the mirrored element; inside a diagonal 16 x 16 block both are computed
+  const bool mirror = I != J || row / 16 < x / 16;
+  if (mirror) C[m] = (TO)(beta != 0.0 ? v + beta * (double)C[m] : v);
   if (beta != 0.0) v += beta * (double)C[e];
   C[e] = (TO)v;
+}
+
+GramPlan gram_plan(int64_t n, int64_t d, int wpt) {
+  GramPlan p{};
+  p.T = (int)ceil_div(d, (int64_t)64);
+  p.nbt = (int)ceil_div(d - 64 * (int64_t)(p.T - 1), (int64_t)16);
+  const bool tail = d % 64 != 0;
+  const int F = tail ? p.T - 1 : p.T;  // full tiles across
+  p.cnt[0] = F * (F - 1) / 2;
+  p.cnt[1] = tail ? F : 0;
+  p.cnt[2] = F;
+  p.cnt[3] = tail ? 1 : 0;
+  // a step costs its block products, or twice the blocks it loads where those
+  // are more: a narrow last tile waits for its rows (300,000 x 200 in FP64,
+  // whose last tile is one block wide: 420 us before, 605 by products alone,
+  // 372 by this rule)
+  const double nbt = p.nbt;
+  const double cost[4] = {16.0, std::max(4.0 * nbt, 2.0 * (4.0 + nbt)), 10.0,
+                          std::max(0.5 * nbt * (nbt + 1.0), 2.0 * nbt)};
+  double total = 0.0;
+  for (int c = 0; c < 4; ++c) total += p.cnt[c] * cost[c];
+  // two wavefronts per SIMD in one round, at least two groups of rows each
+  const int64_t kRound = 4 * gram_prefetch(wpt) * wpt;
+  const double slots = 512.0 * kGramWaves / wpt;
+  for (int c = 0; c < 4; ++c) {
+    if (!p.cnt[c]) continue;
+    int64_t s = (int64_t)(slots * cost[c] / total);
+    if (s < 2) s = 2;
+    int64_t rows = ceil_div(ceil_div(n, s), kRound) * kRound;
+    if (rows < 2 * kRound) rows = 2 * kRound;
+    p.rows[c] = rows;
+    p.slabs[c] = (int)ceil_div(n, rows);
+    if (p.slabs[c] < 1) p.slabs[c] = 1;
+  }
+  for (int c = 0; c < 4; ++c)
+    p.first[c + 1] = p.first[c] + (int64_t)p.cnt[c] * p.slabs[c];
+  return p;
 }
 
 template <typename TA>
 int gram_syrk_launch(double alpha, const psk_mat &Am, double beta, void *C, bool out_f32,
                      Arena &ws, hipStream_t st) {
   const int64_t n = Am.n, d = Am.d;
-  const int T = (int)ceil_div(d, (int64_t)64);
-  const int Uo = T * (T - 1) / 2;
-  const uintptr_t addr = (uintptr_t)Am.values;
-  const bool vec = (Am.ld % 4 == 0) && (d % 4 == 0) && (addr % 16 == 0);
-  // about two wavefronts per SIMD in one round: 2048 work items of equal
-  // cost, a diagonal item 10/16 of an off-diagonal one per row; slabs of
-  // whole loop iterations
-  constexpr int64_t kStep = 4 * kGramPF;
-  int64_t so = (int64_t)(2048.0 / (Uo + 0.625 * T));
-  if (so < 8) so = 8;
-  const int64_t rows_o = ceil_div(ceil_div(n, so), kStep) * kStep;
-  so = ceil_div(n, rows_o);
-  const int64_t rows_d = ceil_div((rows_o * 16) / 10, kStep) * kStep;
-  const int64_t sd = ceil_div(n, rows_d);
-  double *part = ws.take<double>((size_t)(so * Uo + sd * T) * 4096);
-  double *gpart = ws.take<double>((size_t)kGramGroups * d * d);
+  const int wpt = d <= 112 ? kGramWaves : 1;  // measured beside the kernel
+  const GramPlan pl = gram_plan(n, d, wpt);
+  const int64_t items = pl.first[4];
+  double *part = ws.take<double>((size_t)items * 4096);
   if (ws.dry()) return 0;
   if (!ws.ok()) return fail(PSK_ENOMEM, "workspace too small for the Gram matrix");
-  const int64_t items = so * Uo + sd * T;
-  int64_t nblk = ceil_div(items, (int64_t)4);
-  nblk = ceil_div(nblk, (int64_t)8) * 8;  // whole XCD rounds for the remap
+  // whole XCD rounds for the remap
+  const int64_t nblk = ceil_div(ceil_div(items * wpt, (int64_t)kGramWaves), (int64_t)8) * 8;
   {
     KTimer timer("gram", st);
-    if (vec)
-      k_gram_syrk<TA, true><<<(unsigned)nblk, 256, 0, st>>>((const TA *)Am.values, Am.ld, n, d,
-                                                            T, so, rows_o, sd, rows_d, part);
+    if (wpt == 1)
+      k_gram_syrk<TA, 1><<<(unsigned)nblk, 64 * kGramWaves, 0, st>>>((const TA *)Am.values, Am.ld,
+                                                                    n, d, pl, part);
     else
-      k_gram_syrk<TA, false><<<(unsigned)nblk, 256, 0, st>>>((const TA *)Am.values, Am.ld, n, d,
-                                                             T, so, rows_o, sd, rows_d, part);
+      k_gram_syrk<TA, kGramWaves><<<(unsigned)nblk, 64 * kGramWaves, 0, st>>>(
+          (const TA *)Am.values, Am.ld, n, d, pl, part);
   }
   KTimer rtimer("gram_reduce", st);
-  const int64_t dd = d * d;
-  dim3 g1((unsigned)ceil_div(dd, (int64_t)256), kGramGroups);
-  k_gram_reduce1<<<g1, 256, 0, st>>>(part, d, T, so, sd, gpart);
+  int most = 1, groups = 1;
+  for (int c = 0; c < 4; ++c) most = pl.slabs[c] > most ? pl.slabs[c] : most;
+  while (groups < kGramGroups && groups * 8 < most) groups *= 2;
+  const unsigned rgrid = (unsigned)(pl.T * (pl.T + 1) / 2 * 64);
   if (out_f32)
-    k_gram_reduce2<float><<<(unsigned)ceil_div(dd, (int64_t)256), 256, 0, st>>>(
-        gpart, dd, alpha, beta, (float *)C);
+    k_gram_reduce<float><<<rgrid, dim3(64, groups), 0, st>>>(part, d, pl, alpha, beta,
+                                                             (float *)C);
   else
-    k_gram_reduce2<double><<<(unsigned)ceil_div(dd, (int64_t)256), 256, 0, st>>>(
-        gpart, dd, alpha, beta, (double *)C);
+    k_gram_reduce<double><<<rgrid, dim3(64, groups), 0, st>>>(part, d, pl, alpha, beta,
+                                                              (double *)C);
   PSK_HIP_TRY(hipGetLastError());
   return 0;
 }

@@ -29,7 +29,7 @@ __global__ __launch_bounds__(256) void k_probe_copy(const float4 *__restrict__ s
     dst[i] = src[i];
 }
 
-__global__ __launch_bounds__(256) void k_probe_mfma_f64(int64_t iters, double *__restrict__ out) {
+__global__ __launch_bounds__(256, 2) void k_probe_mfma_f64(int64_t iters, double *__restrict__ out) {
   v4d acc[8];
 #pragma unroll
   for (int c = 0; c < 8; ++c) acc[c] = v4d{0.0, 0.0, 0.0, 0.0};
