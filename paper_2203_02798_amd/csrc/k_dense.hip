@@ -335,55 +335,26 @@ int gemm_launch(int64_t M, int64_t N, int64_t K, const double *A, int64_t lda, c
   return 0;
 }
 
-// Four consecutive elements of one row as loaded (raw, in the dtype of A)
-// and whether they are inside the matrix.  The load is branch-free: the
-// address is clamped to a valid element and the values are selected and
-// widened only when used, so the load stays in flight meanwhile (a load
-// inside a branch, or converted right away, is waited for on the spot).
-// VEC: one 16-byte FP32 load / two FP64 ones; needs d % 4 == 0 so that a
-// column group is wholly inside or outside.
-template <typename TA>
-struct Raw4 {
-  TA x[4];
-  bool ok[4];
-};
-
-template <typename TA, bool VEC>
-__device__ __forceinline__ void raw4_load(const TA *__restrict__ A, int64_t ld, int64_t d,
-                                          int64_t row, bool rok, int64_t c, Raw4<TA> &v) {
-  if constexpr (VEC) {
-    const bool ok = rok && c < d;
-    const TA *p = A + (ok ? row * ld + c : 0);
-    if constexpr (sizeof(TA) == 4) {
-      const float4 x = *reinterpret_cast<const float4 *>(p);
-      v.x[0] = x.x; v.x[1] = x.y; v.x[2] = x.z; v.x[3] = x.w;
-    } else {
-      const double2 x = *reinterpret_cast<const double2 *>(p);
-      const double2 y = *reinterpret_cast<const double2 *>(p + 2);
-      v.x[0] = x.x; v.x[1] = x.y; v.x[2] = y.x; v.x[3] = y.y;
-    }
+// KW consecutive elements of a row in 16-byte loads that need no more than
+// the element's own alignment, as loaded (raw, in the dtype of A: widened
+// when used, so the loads stay in flight meanwhile).
+template <typename TA, int KW>
+__device__ __forceinline__ void row_load(const TA *p, TA (&x)[KW]) {
+  constexpr int VE = 16 / sizeof(TA);
+  typedef TA vec __attribute__((ext_vector_type(VE), aligned(sizeof(TA))));
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v.ok[q] = ok;
-  } else {
+  for (int q = 0; q < KW / VE; ++q) {
+    const vec v = *reinterpret_cast<const vec *>(p + VE * q);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const bool ok = rok && c + q < d;
-      v.x[q] = A[ok ? row * ld + c + q : 0];
-      v.ok[q] = ok;
-    }
+    for (int e = 0; e < VE; ++e) x[VE * q + e] = v[e];
   }
 }
 
-template <typename TA>
-__device__ __forceinline__ double raw4_get(const Raw4<TA> &v, int q) {
-  return v.ok[q] ? (double)v.x[q] : 0.0;
-}
-
 // Fused row norms with a column tile of B resident in LDS.  A workgroup
-// holds 32-column tiles of B: one (PAIR false), or two, tiles p and
-// T - 1 - p of the T = ceil(k / 32) tiles (PAIR true; one when they
-// coincide).  Its B columns (rows padded to a multiple of the K chunk with
-// zeros, row stride BNC + 4) are staged once; the 12 wavefronts then stream
+// works on tiles p and T - 1 - p of the T = ceil(k / 32) 32-column tiles of B
+// (one when they coincide): both at once when they fit in LDS (PAIR true),
+// else one after the other.  Its B columns (rows padded to a multiple of the
+// K chunk with zeros, row stride BNC + 4) are staged; the 8 wavefronts then stream
 // row tiles of A (kBresMB blocks of 16 rows) straight from memory into the
 // MFMA operand registers (no LDS round trip and no barrier in the main loop)
 // and keep kBresMB x BNC/16 accumulator blocks.
@@ -394,6 +365,20 @@ __device__ __forceinline__ double raw4_get(const Raw4<TA> &v, int q) {
 // and pairing tile t with tile T - 1 - t gives every workgroup the same
 // work.  (Skipped products are a * 0 with a finite: the sums are the same
 // bits as the full product's.)
+// What bounds it: the FP64 matrix cores and the vector instructions between
+// their products, which do not run beside them (about 64 + 4 v cycles for a
+// product and v vector instructions).  So a chunk inside d is loaded in
+// vector loads of whatever alignment the rows have and multiplied unmasked;
+// RAG holds the code for the last chunk of a d that is not a multiple of 32
+// (without it 1e6 x 256 takes 1226 us, with it 1278).  The first chunk of a
+// phase or row tile is loaded while the one before it is multiplied.  Two
+// wavefronts per SIMD: with three (168 registers each) the paired form spilled
+// 30 to 130 of them (FP64 1e6 x 256: 1815 us at three, 1263 at two).
+// Measured in us, before (masked element loads, three wavefronts, single
+// tiles unpaired) and now: FP64 20,000 x 50 36 -> 19, 300,007 x 97 253 ->
+// 140, 1e6 x 128 738 -> 439, 1e6 x 256 2696 -> 1226, 200,000 x 500 3175 ->
+// 1052; FP32 1e6 x 128 383 -> 357, 4e6 x 256 4769 -> 4588 (2.9e11 flops: 62
+// TF/s of the 76 that bare products reach).
 // Inside a K chunk of 4 kBresKW columns, lane (li, kq) feeds column
 // k0 + kBresKW kq + s of A at step s, and B row k0 + kBresKW kq + s: the same
 // permutation of the chunk on both operands, so one lane reads kBresKW
@@ -411,18 +396,17 @@ __device__ __forceinline__ double raw4_get(const Raw4<TA> &v, int q) {
 // Workgroups form row groups of tn (one per slot) that sit on one XCD
 // (linear ids equal mod 8) and walk the same rows, so A is fetched into that
 // XCD's L2 about once for all tn slots.
-constexpr int kBresThreads = 768;  // 12 wavefronts: three per SIMD
+constexpr int kBresThreads = 512;  // 8 wavefronts: two per SIMD
 constexpr int kBresWaves = kBresThreads / 64;
 constexpr int kBresMB = 2;  // 16-row blocks per wavefront tile
 constexpr int kBresRows = 16 * kBresMB;
 constexpr int kBresKW = 8;
 constexpr int kBresTile = 32;  // columns of B per tile
 
-template <typename TA, bool PAIR, bool VEC>
+template <typename TA, bool PAIR, bool RAG>
 __global__ __launch_bounds__(kBresThreads) void k_rownorm_bres(
     const TA *__restrict__ A, int64_t ld, int64_t n, int64_t d, const double *__restrict__ B,
     int64_t k, int tn, double *__restrict__ part) {
-  static_assert(!VEC || sizeof(TA) == 4, "vector loads are for FP32 A");
   extern __shared__ double Bs[];
   __shared__ int ext[2];
   __shared__ int nzq[2];  // a nonzero in the lower-left quarter of the tile's diagonal block
@@ -441,214 +425,285 @@ __global__ __launch_bounds__(kBresThreads) void k_rownorm_bres(
   const int64_t ngroups = nblk / tn;
   const int64_t group = (slot / tn) * 8 + (lin & 7);
   const int64_t ntile = ceil_div(k, (int64_t)kBresTile);
-  // first columns of the (one or two) tiles; -1: no second tile
-  const int64_t c0a = (int64_t)nt * kBresTile;
-  const int64_t tb = PAIR ? ntile - 1 - nt : -1;
-  const int64_t c0b = (PAIR && tb != nt) ? tb * kBresTile : -1;
   const int64_t kch = (d + CK - 1) / CK;
   const int64_t drows = kch * CK;
-  if (tid < 2) {
-    ext[tid] = 0;
-    nzq[tid] = 0;
-  }
-  __syncthreads();
-  int exa = 0, exb = 0;
-  bool qa = false, qb = false;
-  for (int64_t e = tid; e < drows * BNC; e += kBresThreads) {
-    const int64_t kk = e / BNC;
-    const int jj = (int)(e - kk * BNC);
-    const bool hb = jj >= kBresTile;
-    const int64_t cb = hb ? c0b : c0a;
-    const int jt = hb ? jj - kBresTile : jj;
-    const int64_t col = cb + jt;
-    const double v = (cb >= 0 && kk < d && col < k) ? B[kk * k + col] : 0.0;
-    Bs[kk * LDB + jj] = v;
-    if (v != 0.0) {  // NaN counts as nonzero
-      const bool quarter = jt < 16 && kk >= cb + 16 && kk < cb + kBresTile;
-      if (hb) {
-        exb = (int)kk + 1;
-        qb = qb || quarter;
-      } else {
-        exa = (int)kk + 1;
-        qa = qa || quarter;
+  const int64_t ntiles = (n + kBresRows - 1) / kBresRows;
+  const int64_t t0 = wave * ngroups + group, tstep = ngroups * kBresWaves;
+  for (int pass = 0; pass < (PAIR ? 1 : 2); ++pass) {
+    const int64_t ta = pass ? ntile - 1 - nt : nt;  // the tile, or the first of the two
+    if (pass) {
+      if (ta == nt) break;
+      __syncthreads();  // the first pass is done with the LDS tile
+    }
+    // first columns of the (one or two) tiles; -1: no second tile
+    const int64_t c0a = ta * kBresTile;
+    const int64_t tb = PAIR ? ntile - 1 - nt : -1;
+    const int64_t c0b = (PAIR && tb != nt) ? tb * kBresTile : -1;
+    if (tid < 2) {
+      ext[tid] = 0;
+      nzq[tid] = 0;
+    }
+    __syncthreads();
+    int exa = 0, exb = 0;
+    bool qa = false, qb = false;
+    // four loads at once (clamped address, then a select): one after another
+    // they would cost a memory latency each
+    for (int64_t e0 = tid; e0 < drows * BNC; e0 += 4 * kBresThreads) {
+      double bv[4];
+      bool in[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t e = e0 + u * kBresThreads;
+        const int64_t kk = e / BNC;
+        const int jj = (int)(e - kk * BNC);
+        const int64_t cb = jj >= kBresTile ? c0b : c0a;
+        const int64_t col = cb + (jj & (kBresTile - 1));
+        in[u] = cb >= 0 && kk < d && col < k;
+        bv[u] = B[in[u] ? kk * k + col : 0];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t e = e0 + u * kBresThreads;
+        if (e >= drows * BNC) break;
+        const int64_t kk = e / BNC;
+        const int jj = (int)(e - kk * BNC);
+        const bool hb = jj >= kBresTile;
+        const int64_t cb = hb ? c0b : c0a;
+        const int jt = jj & (kBresTile - 1);
+        const double v = in[u] ? bv[u] : 0.0;
+        Bs[kk * LDB + jj] = v;
+        if (v != 0.0) {  // NaN counts as nonzero
+          const bool quarter = jt < 16 && kk >= cb + 16 && kk < cb + kBresTile;
+          if (hb) {
+            exb = (int)kk + 1;
+            qb = qb || quarter;
+          } else {
+            exa = (int)kk + 1;
+            qa = qa || quarter;
+          }
+        }
       }
     }
-  }
-  if (exa) atomicMax(&ext[0], exa);
-  if (exb) atomicMax(&ext[1], exb);
-  if (qa) atomicOr(&nzq[0], 1);
-  if (qb) atomicOr(&nzq[1], 1);
-  __syncthreads();
-  // K chunks each tile needs (uniform over the workgroup)
-  const int64_t kca = __builtin_amdgcn_readfirstlane((ext[0] + CK - 1) / CK);
-  const int64_t kcb = __builtin_amdgcn_readfirstlane((ext[1] + CK - 1) / CK);
-  // the diagonal chunk of each tile (chunk index = tile index, a chunk
-  // spanning one tile's rows) when its quarter is zero and its columns of A
-  // are inside d; -1: none
-  static_assert(CK == kBresTile, "a K chunk spans one tile's rows");
-  const int64_t dga =
-      (__builtin_amdgcn_readfirstlane(nzq[0]) || c0a + kBresTile > d) ? -1 : (int64_t)nt;
-  const int64_t dgb =
-      (c0b < 0 || __builtin_amdgcn_readfirstlane(nzq[1]) || c0b + kBresTile > d) ? -1 : tb;
-  const int64_t ntiles = (n + kBresRows - 1) / kBresRows;
-  for (int64_t t = group * kBresWaves + wave; t < ntiles; t += ngroups * kBresWaves) {
-    const int64_t r0 = t * kBresRows;
-    const TA *arow[MB];
-    bool rin[MB];
+    if (exa) atomicMax(&ext[0], exa);
+    if (exb) atomicMax(&ext[1], exb);
+    if (qa) atomicOr(&nzq[0], 1);
+    if (qb) atomicOr(&nzq[1], 1);
+    __syncthreads();
+    // K chunks each tile needs (uniform over the workgroup)
+    const int64_t kca = __builtin_amdgcn_readfirstlane((ext[0] + CK - 1) / CK);
+    const int64_t kcb = __builtin_amdgcn_readfirstlane((ext[1] + CK - 1) / CK);
+    // the diagonal chunk of each tile (chunk index = tile index, a chunk
+    // spanning one tile's rows) when its quarter is zero and its columns of A
+    // are inside d; -1: none
+    static_assert(CK == kBresTile, "a K chunk spans one tile's rows");
+    const int64_t dga =
+        (__builtin_amdgcn_readfirstlane(nzq[0]) || c0a + kBresTile > d) ? -1 : ta;
+    const int64_t dgb =
+        (c0b < 0 || __builtin_amdgcn_readfirstlane(nzq[1]) || c0b + kBresTile > d) ? -1 : tb;
+    // The chunks of a row tile, in the order they are taken: the phase that
+    // feeds both tiles (HM 3; the only one of a single tile is HM 1), then the
+    // rest of the tile with the larger extent (HM 1 or 2).  A phase's last chunk
+    // comes first when it is a special one: the diagonal chunk of the phase's
+    // tile (of its first tile in HM 3), or the ragged end of d (never a
+    // diagonal chunk: those are inside d).
+    const int64_t kone = PAIR && kcb < kca ? kcb : kca;  // end of the first phase
+    const int64_t k1 = PAIR ? kone : kca;
+    const int64_t k2 = PAIR ? (kca > kcb ? kca : kcb) : k1;
+    const bool hb2 = PAIR && kcb > kca;  // the second phase is the second tile's
+    const bool dg1 = k1 > 0 && k1 - 1 == dga;
+    const bool dg2 = k2 > k1 && k2 - 1 == (hb2 ? dgb : dga);
+    const bool sp1 = dg1 || (RAG && k1 * CK > d), sp2 = dg2 || (RAG && k2 * CK > d);
+    const int64_t f1 = sp1 ? k1 - 1 : 0, f2 = sp2 ? k2 - 1 : k1;  // first chunk of each phase
+    const int64_t ffirst = k1 > 0 ? f1 : f2;
+    // KW elements of each of the lane's rows, as loaded: a whole chunk in
+    // vector loads; of the ragged chunk the columns inside d (the others read
+    // the row's first element and are masked when used).  A row past n reads
+    // row 0 and feeds only its own outputs, which are not stored.
+    typedef TA RawChunk[MB][KW];
+    auto load_whole = [&](const TA *const (&row)[MB], int64_t c, RawChunk &a)
+                          __attribute__((always_inline)) {
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      const int64_t row = r0 + mb * 16 + li;
-      rin[mb] = row < n;
-      arow[mb] = A + (rin[mb] ? row : 0) * ld;
-    }
-    v4d acc[MB][NB];
+      for (int mb = 0; mb < MB; ++mb) row_load<TA, KW>(row[mb] + c * CK, a[mb]);
+    };
+    auto load = [&](const TA *const (&row)[MB], int64_t c, RawChunk &a)
+                    __attribute__((always_inline)) {
+      if (!RAG || (c + 1) * CK <= d) {
+        load_whole(row, c, a);
+      } else {
+        const int64_t left = d - (c * CK + KW * kq);  // this lane's columns inside d
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = v4d{0.0, 0.0, 0.0, 0.0};
-    // the chunk's KW elements of each of the lane's rows, loaded raw and
-    // branch-free (Raw4: clamped address, values selected and widened in
-    // step), so the next chunk's loads stay in flight during this one's
-    // matrix instructions
-    typedef Raw4<TA> RawChunk[MB][KW / 4];
-    auto load = [&](int64_t c, RawChunk &a) __attribute__((always_inline)) {
-      const int64_t kb = c * CK + KW * kq;
+          for (int s = 0; s < KW; ++s)
+            a[mb][s] = row[mb][s < left ? c * CK + s : -(int64_t)(KW * kq)];
+      }
+    };
+    auto rows_of = [&](int64_t t, const TA *(&row)[MB]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        const int64_t r = t * kBresRows + mb * 16 + li;
+        row[mb] = A + (r < n ? r : 0) * ld + KW * kq;
+      }
+    };
+    // a0: the chunk taken next, loading since the one before it was multiplied
+    // (across phases and row tiles)
+    RawChunk a0, a1;
+    const TA *arow[MB], *nrow[MB];
+    rows_of(t0 < ntiles ? t0 : 0, arow);
+    if (k2 > 0) load(arow, ffirst, a0);
+    for (int64_t t = t0; t < ntiles; t += tstep) {
+      const int64_t r0 = t * kBresRows;
+      rows_of(t + tstep < ntiles ? t + tstep : t, nrow);
+      v4d acc[MB][NB];
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int q = 0; q < KW / 4; ++q)
-          raw4_load<TA, VEC>(arow[mb], 0, d, 0, rin[mb], kb + 4 * q, a[mb][q]);
-    };
-    // one K chunk for the blocks of the tiles in HM (bit 0: first tile,
-    // bit 1: second tile); DG 1 / 2: a diagonal chunk in the swapped order,
-    // the first column block of the first / second tile skipping steps 4 .. 7
-    // (every element inside A: no masks; a row past n reads row 0 and
-    // feeds only its own outputs, which are not stored)
-    auto step = [&](auto hm, auto dg, int64_t c, const RawChunk &raw)
-                    __attribute__((always_inline)) {
-      constexpr int HM = decltype(hm)::value;
-      constexpr int DG = decltype(dg)::value;
-      double a[MB][KW];
-      if constexpr (DG == 0) {
+        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = v4d{0.0, 0.0, 0.0, 0.0};
+      using D0 = std::integral_constant<int, 0>;
+      // one K chunk for the blocks of the tiles in HM (bit 0: first tile,
+      // bit 1: second tile); DG 1 / 2: a diagonal chunk in the swapped order,
+      // the first column block of the first / second tile skipping steps 4 .. 7
+      auto step = [&](auto hm, auto dg, int64_t c, const RawChunk &raw)
+                      __attribute__((always_inline)) {
+        constexpr int HM = decltype(hm)::value;
+        constexpr int DG = decltype(dg)::value;
+        double a[MB][KW];
+        if constexpr (DG == 0) {
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+          for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-          for (int s = 0; s < KW; ++s) a[mb][s] = raw4_get(raw[mb][s / 4], s % 4);
-      } else {
-        static_assert(KW == 8, "the swap pairs elements s and s + 4");
+            for (int s = 0; s < KW; ++s) a[mb][s] = (double)raw[mb][s];
+        } else {
+          static_assert(KW == 8, "the swap pairs elements s and s + 4");
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+          for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-          for (int s = 0; s < 4; ++s) {
-            const TA x = raw[mb][0].x[s], y = raw[mb][1].x[s];
-            if constexpr (sizeof(TA) == 4) {
-              const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x),
-                                                              __float_as_uint(y), false, false);
-              a[mb][s] = (double)__uint_as_float(r[0]);
-              a[mb][4 + s] = (double)__uint_as_float(r[1]);
-            } else {
-              const uint64_t xb = (uint64_t)__double_as_longlong(x);
-              const uint64_t yb = (uint64_t)__double_as_longlong(y);
-              const auto rl = __builtin_amdgcn_permlane32_swap((uint32_t)xb, (uint32_t)yb, false,
-                                                               false);
-              const auto rh = __builtin_amdgcn_permlane32_swap((uint32_t)(xb >> 32),
-                                                               (uint32_t)(yb >> 32), false, false);
-              a[mb][s] = __longlong_as_double((long long)(((uint64_t)rh[0] << 32) | rl[0]));
-              a[mb][4 + s] = __longlong_as_double((long long)(((uint64_t)rh[1] << 32) | rl[1]));
+            for (int s = 0; s < 4; ++s) {
+              const TA x = raw[mb][s], y = raw[mb][s + 4];
+              if constexpr (sizeof(TA) == 4) {
+                const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x),
+                                                                __float_as_uint(y), false, false);
+                a[mb][s] = (double)__uint_as_float(r[0]);
+                a[mb][4 + s] = (double)__uint_as_float(r[1]);
+              } else {
+                const uint64_t xb = (uint64_t)__double_as_longlong(x);
+                const uint64_t yb = (uint64_t)__double_as_longlong(y);
+                const auto rl = __builtin_amdgcn_permlane32_swap((uint32_t)xb, (uint32_t)yb, false,
+                                                                 false);
+                const auto rh = __builtin_amdgcn_permlane32_swap(
+                    (uint32_t)(xb >> 32), (uint32_t)(yb >> 32), false, false);
+                a[mb][s] = __longlong_as_double((long long)(((uint64_t)rh[0] << 32) | rl[0]));
+                a[mb][4 + s] = __longlong_as_double((long long)(((uint64_t)rh[1] << 32) | rl[1]));
+              }
             }
-          }
-      }
+        }
 #pragma unroll
-      for (int s = 0; s < KW; ++s) {
-        const int64_t kr = DG == 0 ? c * CK + KW * kq + s
-                                   : c * CK + 16 * (s / 4) + 8 * (kq & 1) + 4 * (kq >> 1) + s % 4;
-        const double *brow = Bs + kr * LDB + li;
-        auto on = [&](int nb) {
-          return ((HM >> (nb / NBH)) & 1) && !(DG && s >= 4 && nb == (DG - 1) * NBH);
-        };
-        double bv[NB];
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-          if (on(nb)) bv[nb] = brow[nb * 16];
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+        for (int s = 0; s < KW; ++s) {
+          const int64_t kr = DG == 0 ? c * CK + KW * kq + s
+                                     : c * CK + 16 * (s / 4) + 8 * (kq & 1) + 4 * (kq >> 1) + s % 4;
+          const double *brow = Bs + kr * LDB + li;
+          auto on = [&](int nb) {
+            return ((HM >> (nb / NBH)) & 1) && !(DG && s >= 4 && nb == (DG - 1) * NBH);
+          };
+          double bv[NB];
 #pragma unroll
           for (int nb = 0; nb < NB; ++nb)
-            if (on(nb))
-              acc[mb][nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[mb][s], bv[nb], acc[mb][nb],
-                                                                 0, 0, 0);
-      }
-    };
-    using D0 = std::integral_constant<int, 0>;
-    // chunks c0 .. c1 - 1, the next chunk's A loaded while one is multiplied.
-    // The loads are unconditional (past the last chunk they reload it, and
-    // the copy goes unused): with the same loads in flight on every path,
-    // a step waits for its own chunk only, not for the one loading behind it.
-    // A phase whose last chunk is the diagonal chunk of its first tile
-    // (HM 3, 1) or of its second (HM 2) takes that chunk last, loaded in the
-    // same pipeline (its loads are those of any chunk).
-    auto run = [&](auto hm, int64_t c0, int64_t c1) __attribute__((always_inline)) {
-      constexpr int HM = decltype(hm)::value;
-      using DGT = std::integral_constant<int, HM == 2 ? 2 : 1>;
-      if (c0 >= c1) return;
-      const bool dg = c1 - 1 == (HM == 2 ? dgb : dga);
-      const int64_t ce = dg ? c1 - 1 : c1;  // chunks before ce: all products
-      const int64_t cl = c1 - 1;
-      RawChunk a0, a1;
-      load(c0, a0);
-      int64_t c = c0;
-      for (; c + 1 < ce; c += 2) {
-        load(c + 1, a1);
-        __builtin_amdgcn_sched_barrier(0);  // keep the next chunk's loads ahead of this step
-        step(hm, D0{}, c, a0);
-        load(c + 2 < c1 ? c + 2 : cl, a0);
-        __builtin_amdgcn_sched_barrier(0);
-        step(hm, D0{}, c + 1, a1);
-      }
-      // c = ce - 1: one more chunk (a0), the next one (the diagonal chunk,
-      // or a reload) loading into a1 meanwhile; c = ce: a0 holds the
-      // diagonal chunk when there is one
-      const bool in1 = c < ce;
-      if (in1) {
-        load(c + 1 < c1 ? c + 1 : cl, a1);
-        __builtin_amdgcn_sched_barrier(0);
-        step(hm, D0{}, c, a0);
-      }
-      if (dg) {
-        RawChunk ad;
+            if (on(nb)) bv[nb] = brow[nb * 16];
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+          for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-          for (int q = 0; q < KW / 4; ++q)
+            for (int nb = 0; nb < NB; ++nb)
+              if (on(nb))
+                acc[mb][nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[mb][s], bv[nb], acc[mb][nb],
+                                                                   0, 0, 0);
+        }
+      };
+      // chunks c0 .. c1 - 1, the next chunk's A loaded while one is multiplied:
+      // unconditional loads, so that with the same loads in flight on every path
+      // a step waits for its own chunk only, not for the one loading behind it.
+      // After the last comes chunk cn of the rows in rn.
+      auto run = [&](auto hm, bool dg, bool special, int64_t c0, int64_t c1,
+                     const TA *const (&rn)[MB], int64_t cn) __attribute__((always_inline)) {
+        constexpr int HM = decltype(hm)::value;
+        using DGT = std::integral_constant<int, HM == 2 ? 2 : 1>;
+        if (c0 >= c1) return;
+        int64_t ce = c1;
+        if (special) {
+          --ce;
+          if (c0 < ce) load_whole(arow, c0, a1);
+          else load(rn, cn, a1);
+          if (!RAG || dg) {
+            step(hm, DGT{}, ce, a0);
+          } else {
+            const int64_t left = d - (ce * CK + KW * kq);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) ad[mb][q].x[e] = in1 ? a1[mb][q].x[e] : a0[mb][q].x[e];
-        step(hm, DGT{}, ce, ad);
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+              for (int s = 0; s < KW; ++s) a0[mb][s] = s < left ? a0[mb][s] : (TA)0;
+            step(hm, D0{}, ce, a0);
+          }
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int s = 0; s < KW; ++s) a0[mb][s] = a1[mb][s];
+        }
+        int64_t c = c0;
+        for (; c + 2 < ce; c += 2) {
+          load_whole(arow, c + 1, a1);
+          __builtin_amdgcn_sched_barrier(0);  // keep the next chunk's loads ahead of this step
+          step(hm, D0{}, c, a0);
+          load_whole(arow, c + 2, a0);
+          __builtin_amdgcn_sched_barrier(0);
+          step(hm, D0{}, c + 1, a1);
+        }
+        if (c >= ce) return;
+        if (c + 1 < ce) {
+          load_whole(arow, c + 1, a1);
+          __builtin_amdgcn_sched_barrier(0);
+          step(hm, D0{}, c, a0);
+          load(rn, cn, a0);
+          __builtin_amdgcn_sched_barrier(0);
+          step(hm, D0{}, c + 1, a1);
+        } else {
+          load(rn, cn, a1);
+          __builtin_amdgcn_sched_barrier(0);
+          step(hm, D0{}, c, a0);
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int s = 0; s < KW; ++s) a0[mb][s] = a1[mb][s];
+        }
+      };
+      using HBoth = std::integral_constant<int, 3>;
+      using HA = std::integral_constant<int, 1>;
+      using HB = std::integral_constant<int, 2>;
+      if constexpr (PAIR) {
+        const bool two = k2 > k1;
+        const TA *prow[MB];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) prow[mb] = two ? arow[mb] : nrow[mb];
+        run(HBoth{}, dg1, sp1, 0, k1, prow, two ? f2 : ffirst);
+        if (two && !hb2) run(HA{}, dg2, sp2, k1, k2, nrow, ffirst);
+        if (two && hb2) run(HB{}, dg2, sp2, k1, k2, nrow, ffirst);
+      } else {
+        run(HA{}, dg1, sp1, 0, k1, nrow, ffirst);
       }
-    };
-    using HBoth = std::integral_constant<int, 3>;
-    using HA = std::integral_constant<int, 1>;
-    using HB = std::integral_constant<int, 2>;
-    if constexpr (PAIR) {
-      const int64_t kboth = kca < kcb ? kca : kcb;
-      run(HBoth{}, 0, kboth);
-      if (kca > kboth) run(HA{}, kboth, kca);
-      else if (kcb > kboth) run(HB{}, kboth, kcb);
-    } else {
-      run(HA{}, 0, kca);
+      // lane (li, kq) holds rows kq + 4 e, column li of each 16 x 16 block
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          double s2 = 0.0;
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) s2 += acc[mb][nb][e] * acc[mb][nb][e];
+#pragma unroll
+          for (int off = 1; off < 16; off <<= 1) s2 += __shfl_xor(s2, off, 64);
+          const int64_t row = r0 + mb * 16 + kq + 4 * e;
+          if (li == 0 && row < n) part[(PAIR ? nt : ta) * n + row] = s2;
+        }
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) arow[mb] = nrow[mb];
     }
-    // lane (li, kq) holds rows kq + 4 e, column li of each 16 x 16 block
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        double s2 = 0.0;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) s2 += acc[mb][nb][e] * acc[mb][nb][e];
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) s2 += __shfl_xor(s2, off, 64);
-        const int64_t row = r0 + mb * 16 + kq + 4 * e;
-        if (li == 0 && row < n) part[(int64_t)nt * n + row] = s2;
-      }
   }
 }
 
@@ -661,14 +716,14 @@ int bres_width(int64_t d, int64_t k) {
   return 0;
 }
 
-template <typename TA, bool PAIR, bool VEC>
-int bres_launch(const psk_mat &Am, const double *B, int64_t k, double *part, int tn,
+template <typename TA, bool PAIR, bool RAG>
+int bres_launch_as(const psk_mat &Am, const double *B, int64_t k, double *part, int tn,
                 hipStream_t st) {
   const int64_t n = Am.n, d = Am.d;
   constexpr int BNC = PAIR ? 2 * kBresTile : kBresTile;
   const size_t lds =
       (size_t)ceil_div(d, (int64_t)(4 * kBresKW)) * (4 * kBresKW) * (BNC + 4) * sizeof(double);
-  PSK_HIP_TRY(hipFuncSetAttribute((const void *)k_rownorm_bres<TA, PAIR, VEC>,
+  PSK_HIP_TRY(hipFuncSetAttribute((const void *)k_rownorm_bres<TA, PAIR, RAG>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   // one workgroup per CU (the LDS tile), row groups of tn workgroups per XCD
   const int64_t tiles = ceil_div(n, (int64_t)kBresRows);
@@ -681,9 +736,16 @@ int bres_launch(const psk_mat &Am, const double *B, int64_t k, double *part, int
   while (groups > 8 && groups / 16 * 8 >= need) groups = groups / 16 * 8;
   const unsigned nblk = (unsigned)(groups * tn);
   KTimer timer("rownorm", st);
-  k_rownorm_bres<TA, PAIR, VEC><<<nblk, kBresThreads, lds, st>>>(
+  k_rownorm_bres<TA, PAIR, RAG><<<nblk, kBresThreads, lds, st>>>(
       (const TA *)Am.values, Am.ld, n, d, B, k, tn, part);
   return 0;
+}
+
+template <typename TA, bool PAIR>
+int bres_launch(const psk_mat &Am, const double *B, int64_t k, double *part, int tn,
+                hipStream_t st) {
+  return Am.d % (4 * kBresKW) ? bres_launch_as<TA, PAIR, true>(Am, B, k, part, tn, st)
+                              : bres_launch_as<TA, PAIR, false>(Am, B, k, part, tn, st);
 }
 
 template <typename TA>
@@ -693,29 +755,18 @@ int rownorm_launch(const psk_mat &Am, const double *B, int64_t k, double alpha,
   const TA *A = (const TA *)Am.values;
   const int bw = bres_width(d, k);
   if (bw > 0) {
-    // slots: pairs of 32-column tiles (bw 2) or single tiles (bw 1)
+    // a workgroup's two 32-column tiles give one sum per row together (bw 2,
+    // both in LDS at once) or one each (bw 1, one after the other)
     const int64_t ntile = ceil_div(k, (int64_t)kBresTile);
-    const int tn = (int)(bw == 2 ? ceil_div(ntile, (int64_t)2) : ntile);
-    double *part = ws.take<double>((size_t)tn * n);
+    const int tn = (int)ceil_div(ntile, (int64_t)2);
+    const int slots = bw == 2 ? tn : (int)ntile;  // sums per row
+    double *part = ws.take<double>((size_t)slots * n);
     if (ws.dry()) return 0;
     if (!ws.ok()) return fail(PSK_ENOMEM, "workspace too small for row norms");
-    // FP32 rows read four elements at a time when every such group is aligned
-    const bool vec = Am.ld % 4 == 0 && d % 4 == 0 && ((uintptr_t)Am.values & 15) == 0;
-    int rc;
-    if constexpr (sizeof(TA) == 4) {
-      if (bw == 2)
-        rc = vec ? bres_launch<TA, true, true>(Am, B, k, part, tn, st)
-                 : bres_launch<TA, true, false>(Am, B, k, part, tn, st);
-      else
-        rc = vec ? bres_launch<TA, false, true>(Am, B, k, part, tn, st)
-                 : bres_launch<TA, false, false>(Am, B, k, part, tn, st);
-    } else {
-      (void)vec;
-      rc = bw == 2 ? bres_launch<TA, true, false>(Am, B, k, part, tn, st)
-                   : bres_launch<TA, false, false>(Am, B, k, part, tn, st);
-    }
+    const int rc = bw == 2 ? bres_launch<TA, true>(Am, B, k, part, tn, st)
+                           : bres_launch<TA, false>(Am, B, k, part, tn, st);
     if (rc) return rc;
-    k_rownorm_reduce<<<(unsigned)ceil_div(n, 256), 256, 0, st>>>(part, n, tn, alpha, beta, x);
+    k_rownorm_reduce<<<(unsigned)ceil_div(n, 256), 256, 0, st>>>(part, n, slots, alpha, beta, x);
   } else if (k <= 64) {
     constexpr int BM = 32, BN = 64;
     const int tm = (int)ceil_div(n, BM), tn = (int)ceil_div(k, BN);
@@ -757,8 +808,9 @@ int rownorm_launch(const psk_mat &Am, const double *B, int64_t k, double alpha,
 // of C and one slab of consecutive rows of A.  WPT wavefronts share it, each
 // accumulating every WPT-th group of the slab's rows in registers (4 x 4
 // blocks of 16 x 16 FP64 accumulators); with four (a whole workgroup) the
-// sums are added in LDS, in wavefront order, before the tile is written.  Lane (li, kq) = (lane % 16, lane / 16) reads, of row k0 + kq,
-// element li of each 16-column block.  On a diagonal tile (I = J) only the
+// sums are added in LDS, in wavefront order, before the tile is written.
+// Lane (li, kq) = (lane % 16, lane / 16) reads, of row k0 + kq, element li of
+// each 16-column block.  On a diagonal tile (I = J) only the
 // blocks a <= b are multiplied (10 of 16).  The last tile of a d that is not
 // a multiple of 64 has fewer blocks (NBT of 4): the blocks past d are neither
 // read nor multiplied (d = 97: 28 blocks a step, not 36).
