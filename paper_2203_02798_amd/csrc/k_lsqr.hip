@@ -108,6 +108,12 @@ __device__ __forceinline__ void block_rows(int64_t n, int64_t &r0, int64_t &r1) 
   if (r1 > n) r1 = n;
 }
 
+// What a pass forms: kStep u_i <- A_i vhat - alpha u_i; kInit u_i = b_i; kResid
+// u_i = b_i - A_i x (x in place of vhat), the start of a refinement pass: the
+// residual and its A^T u in one pass over A (1e6 x 256: 421 us, 518 more when
+// a kernel of its own formed the residual).
+constexpr int kStep = 0, kInit = 1, kResid = 2;
+
 // partial A^T u and ||u||^2 of this workgroup's rows, u_i updated in place.
 // vhat is staged in LDS, so the gathers vhat[col] are LDS reads; the first
 // kRegEntries entries of every short row are loaded at once and kept in
@@ -115,14 +121,14 @@ __device__ __forceinline__ void block_rows(int64_t n, int64_t &r0, int64_t &r1) 
 // dependent global loads (row pointers, then entries) whatever its length up
 // to kRegEntries.  Additions keep the order: entries in sequence within a
 // row; rows r, then lanes, into a wavefront's LDS accumulator row.
-template <typename T, bool INIT>
+template <typename T, int MODE>
 __global__ __launch_bounds__(64 * kCsrWaves, 4) void k_pass_csr(
     const T *__restrict__ vals, const int64_t *__restrict__ indptr,
     const int32_t *__restrict__ indices, int64_t n, int64_t d,
     const double *__restrict__ vhat, const double *__restrict__ rhs,
     double *__restrict__ u, const LsqrState *__restrict__ st,
     double *__restrict__ part_t, double *__restrict__ part_b2) {
-  const int stop = INIT ? 0 : st->done;  // tested after the first barrier
+  const int stop = MODE == kStep ? st->done : 0;  // tested after the first barrier
   extern __shared__ __align__(16) unsigned char smem_raw[];
   double *tl = reinterpret_cast<double *>(smem_raw);  // kCsrWaves x d accumulators
   double *vh = tl + kCsrWaves * d;                     // vhat, d
@@ -146,19 +152,19 @@ __global__ __launch_bounds__(64 * kCsrWaves, 4) void k_pass_csr(
       if (i < rb1) {
         fq0[r] = indptr[i];
         fq1[r] = indptr[i + 1];
-        fu[r] = INIT ? rhs[i] : u[i];
+        fu[r] = MODE == kStep ? u[i] : rhs[i];
       }
     }
   };
   int64_t base = rb0 + wave * 64 * kRowsPerLane;
   fetch(base);
   for (int64_t c = threadIdx.x; c < kCsrWaves * d; c += 64 * kCsrWaves) tl[c] = 0.0;
-  if (!INIT)
+  if (MODE != kInit)
     for (int64_t c = threadIdx.x; c < d; c += 64 * kCsrWaves) vh[c] = vhat[c];
   __syncthreads();
   if (stop) return;  // uniform per workgroup; nothing global written yet
   double *tw = tl + (int64_t)wave * d;
-  const double au = INIT ? 0.0 : st->alpha * st->ufac;
+  const double au = MODE == kStep ? st->alpha * st->ufac : 0.0;
   double b2 = 0.0;
   for (; base < rb1; base += 64 * kCsrWaves * kRowsPerLane) {
     int64_t p0[kRowsPerLane];
@@ -191,7 +197,7 @@ __global__ __launch_bounds__(64 * kCsrWaves, 4) void k_pass_csr(
         }
       }
     double ui[kRowsPerLane];
-    if (INIT) {
+    if (MODE == kInit) {
 #pragma unroll
       for (int r = 0; r < kRowsPerLane; ++r) ui[r] = ux[r];
     } else {
@@ -211,7 +217,8 @@ __global__ __launch_bounds__(64 * kCsrWaves, 4) void k_pass_csr(
         }
       }
 #pragma unroll
-      for (int r = 0; r < kRowsPerLane; ++r) ui[r] = dot[r] - au * ux[r];
+      for (int r = 0; r < kRowsPerLane; ++r)
+        ui[r] = MODE == kStep ? dot[r] - au * ux[r] : ux[r] - dot[r];
     }
 #pragma unroll
     for (int r = 0; r < kRowsPerLane; ++r) {
@@ -245,12 +252,13 @@ __global__ __launch_bounds__(64 * kCsrWaves, 4) void k_pass_csr(
         const int64_t q0 = indptr[row];
         const int64_t q1 = indptr[row + 1];
         double uv;
-        if (INIT) {
+        if (MODE == kInit) {
           uv = rhs[row];
         } else {
           double dt = 0.0;
           for (int64_t p = q0 + lane; p < q1; p += 64) dt += (double)vals[p] * vh[indices[p]];
-          uv = wave_sum(dt) - au * u[row];
+          dt = wave_sum(dt);
+          uv = MODE == kStep ? dt - au * u[row] : rhs[row] - dt;
         }
         if (lane == 0) {
           u[row] = uv;
@@ -285,7 +293,7 @@ __global__ __launch_bounds__(64 * kCsrWaves, 4) void k_pass_csr(
 // time, with their entries of u, so that short rows still keep a few KiB
 // per wavefront in flight (launch_dense_pass picks RB).  A row past the
 // workgroup's reads the batch's first row and counts as zero.
-template <typename T, bool INIT, int KC, int RB>
+template <typename T, int MODE, int KC, int RB>
 __global__ __launch_bounds__(256) void k_pass_dense(
     const T *__restrict__ A, int64_t ld, int64_t n, int64_t d,
     const double *__restrict__ vhat, const double *__restrict__ rhs,
@@ -293,19 +301,19 @@ __global__ __launch_bounds__(256) void k_pass_dense(
     double *__restrict__ part_t, double *__restrict__ part_b2) {
   // the stop flag is read now and tested once vhat and the first batch of
   // rows are in flight (nothing is written before the test)
-  const int stop = INIT ? 0 : st->done;
+  const int stop = MODE == kStep ? st->done : 0;
   __shared__ double tl[4][64 * KC];
   __shared__ double b2s[4];
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
-  const double au = INIT ? 0.0 : st->alpha * st->ufac;
+  const double au = MODE == kStep ? st->alpha * st->ufac : 0.0;
   int64_t rb0, rb1;
   block_rows(n, rb0, rb1);
   double vh[KC], tacc[KC];
 #pragma unroll
   for (int k = 0; k < KC; ++k) {
     const int64_t c = lane + 64 * k;
-    vh[k] = (!INIT && c < d) ? vhat[c] : 0.0;
+    vh[k] = (MODE != kInit && c < d) ? vhat[c] : 0.0;
     tacc[k] = 0.0;
   }
   double x[RB][KC], uo[RB];
@@ -321,7 +329,7 @@ __global__ __launch_bounds__(256) void k_pass_dense(
         const int64_t c = lane + 64 * k;
         x[r][k] = (ok[r] && c < d) ? (double)ra[c] : 0.0;
       }
-      uo[r] = INIT ? rhs[row] : u[row];
+      uo[r] = MODE == kStep ? u[row] : rhs[row];
     }
   };
   int64_t i = rb0 + wave;
@@ -330,7 +338,7 @@ __global__ __launch_bounds__(256) void k_pass_dense(
   double b2 = 0.0;
   for (; i < rb1; i += 4 * RB) {
     double uu[RB];
-    if (INIT) {
+    if (MODE == kInit) {
 #pragma unroll
       for (int r = 0; r < RB; ++r) uu[r] = ok[r] ? uo[r] : 0.0;
     } else {
@@ -346,7 +354,10 @@ __global__ __launch_bounds__(256) void k_pass_dense(
 #pragma unroll
         for (int r = 0; r < RB; ++r) dt[r] += __shfl_xor(dt[r], off, 64);
 #pragma unroll
-      for (int r = 0; r < RB; ++r) uu[r] = ok[r] ? dt[r] - au * uo[r] : 0.0;
+      for (int r = 0; r < RB; ++r) {
+        const double v = MODE == kStep ? dt[r] - au * uo[r] : uo[r] - dt[r];
+        uu[r] = ok[r] ? v : 0.0;
+      }
     }
     if (lane == 0) {
 #pragma unroll
@@ -647,53 +658,6 @@ __global__ __launch_bounds__(256) void k_diag_ratio(const double *__restrict__ R
   }
 }
 
-// res_i = b_i - A_i x.  Dense: one wavefront per row.  CSR: one lane per
-// row, and rows longer than kShortRow are taken by the whole wavefront.
-template <typename T, bool CSR>
-__global__ __launch_bounds__(256) void k_resid(const T *__restrict__ vals,
-                                               const int64_t *__restrict__ indptr,
-                                               const int32_t *__restrict__ indices,
-                                               int64_t n, int64_t d, int64_t ld,
-                                               const double *__restrict__ x,
-                                               const double *__restrict__ b,
-                                               double *__restrict__ res) {
-  const int lane = threadIdx.x & 63;
-  if (CSR) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool have = i < n;
-    int64_t p0 = 0, p1 = 0;
-    if (have) {
-      p0 = indptr[i];
-      p1 = indptr[i + 1];
-    }
-    const bool longrow = have && (p1 - p0) > kShortRow;
-    if (have && !longrow) {
-      double dot = 0.0;
-      for (int64_t p = p0; p < p1; ++p) dot += (double)vals[p] * x[indices[p]];
-      res[i] = b[i] - dot;
-    }
-    uint64_t pending = __ballot(longrow);
-    while (pending) {
-      const int src = __ffsll((unsigned long long)pending) - 1;
-      pending &= pending - 1;
-      const int64_t q0 = __shfl(p0, src, 64);
-      const int64_t q1 = __shfl(p1, src, 64);
-      const int64_t row = __shfl(i, src, 64);
-      double dot = 0.0;
-      for (int64_t p = q0 + lane; p < q1; p += 64) dot += (double)vals[p] * x[indices[p]];
-      dot = wave_sum(dot);
-      if (lane == 0) res[row] = b[row] - dot;
-    }
-    return;
-  }
-  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  if (i >= n) return;
-  double dot = 0.0;
-  for (int64_t c = lane; c < d; c += 64) dot += (double)vals[i * ld + c] * x[c];
-  dot = wave_sum(dot);
-  if (lane == 0) res[i] = b[i] - dot;
-}
-
 // The second half of an iteration in one launch: every workgroup computes
 // v of the previous iteration is read from v_in and the new one written to
 // v_out (the two alternate), since every workgroup reads v while the extra
@@ -815,16 +779,16 @@ struct LsqBufs {
   LsqrState *st;
 };
 
-template <typename T, bool INIT>
+template <typename T, int MODE>
 void launch_dense_pass(const psk_mat &A, const LsqBufs &B, const double *rhs,
-                       hipStream_t s) {
+                       const double *vhat, hipStream_t s) {
   const T *a = (const T *)A.values;
   const int64_t d = A.d;
   // rows per wavefront batch (FP64, n = 1e6: d = 32 135 us a pass with 8
   // against 166 with 2; n = 2e4, d = 50: 10.1 us with 2 against 11.4 with
   // 8, a wavefront then holding about ten rows; d = 128: 4 better than 2)
 #define PSK_DP(KC, RB)                                                                  \
-  k_pass_dense<T, INIT, KC, RB><<<kPassBlocks, 256, 0, s>>>(a, A.ld, A.n, d, B.vhat, rhs, \
+  k_pass_dense<T, MODE, KC, RB><<<kPassBlocks, 256, 0, s>>>(a, A.ld, A.n, d, vhat, rhs, \
                                                             B.u, B.st, B.part_t, B.part_b2)
   if (d <= 64) {
     if (A.n >= 65536) PSK_DP(1, 8);
@@ -841,39 +805,36 @@ void launch_dense_pass(const psk_mat &A, const LsqBufs &B, const double *rhs,
 #undef PSK_DP
 }
 
-template <typename T>
-void launch_pass(const psk_mat &A, bool init, const LsqBufs &B, const double *rhs,
+template <typename T, int MODE>
+void launch_pass(const psk_mat &A, const LsqBufs &B, const double *rhs, const double *vhat,
                  hipStream_t s) {
   if (A.format == PSK_CSR) {
     const size_t lds = (size_t)(kCsrWaves + 1) * A.d * sizeof(double);
-    const T *vals = (const T *)A.values;
-    if (init)
-      k_pass_csr<T, true><<<kPassBlocks, 64 * kCsrWaves, lds, s>>>(vals, A.indptr, A.indices, A.n, A.d,
-                                                        B.vhat, rhs, B.u, B.st, B.part_t,
-                                                        B.part_b2);
-    else
-      k_pass_csr<T, false><<<kPassBlocks, 64 * kCsrWaves, lds, s>>>(vals, A.indptr, A.indices, A.n, A.d,
-                                                         B.vhat, rhs, B.u, B.st, B.part_t,
-                                                         B.part_b2);
+    k_pass_csr<T, MODE><<<kPassBlocks, 64 * kCsrWaves, lds, s>>>(
+        (const T *)A.values, A.indptr, A.indices, A.n, A.d, vhat, rhs, B.u, B.st, B.part_t,
+        B.part_b2);
   } else {
-    if (init)
-      launch_dense_pass<T, true>(A, B, rhs, s);
-    else
-      launch_dense_pass<T, false>(A, B, rhs, s);
+    launch_dense_pass<T, MODE>(A, B, rhs, vhat, s);
   }
 }
 
-// step k of a solve reads v[k & 1] and writes v[(k + 1) & 1]
-void one_step(const psk_mat &A, bool init, int k, const LsqBufs &B, const double *Rinv,
-              const double *rhs, const psk_lsq_opts &o, hipStream_t s) {
+// step k of a solve reads v[k & 1] and writes v[(k + 1) & 1]; rhs and (kResid)
+// x are read by the first step of a pass only
+void one_step(const psk_mat &A, int mode, int k, const LsqBufs &B, const double *Rinv,
+              const double *rhs, const double *x, const psk_lsq_opts &o, hipStream_t s) {
+  const bool init = mode != kStep;
   const int64_t d = A.d;
   const unsigned nb16 = (unsigned)ceil_div(d, kColsPerBlk);
   {
     KTimer t("lsqr_pass", s);
-    if (A.dtype == PSK_F64)
-      launch_pass<double>(A, init, B, rhs, s);
-    else
-      launch_pass<float>(A, init, B, rhs, s);
+    auto run = [&](auto t) {
+      typedef decltype(t) T;
+      if (mode == kInit) launch_pass<T, kInit>(A, B, rhs, nullptr, s);
+      else if (mode == kResid) launch_pass<T, kResid>(A, B, rhs, x, s);
+      else launch_pass<T, kStep>(A, B, nullptr, B.vhat, s);
+    };
+    if (A.dtype == PSK_F64) run(double{});
+    else run(float{});
   }
   const unsigned nbv = (unsigned)ceil_div(d, kVRows);
   k_vnew_rows<<<nbv, kVThreads, 0, s>>>(B.part_t, B.part_b2, Rinv, d, B.st, B.vpart,
@@ -934,7 +895,6 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
   B.w = ws.take<double>((size_t)d);
   B.y = ws.take<double>((size_t)d);
   B.vhat = ws.take<double>((size_t)d);
-  double *res = ws.take<double>((size_t)n);  // residual of the refinement passes
   B.st = ws.take<LsqrState>(1);
   double *ratio = ws.take<double>(2 + kPrecondEst);  // max |R_ii|, min |R_ii|; precond_estimate's
   // the reduced-precision sketch's perturbation against the FP64 one, on
@@ -1114,30 +1074,9 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
   LsqrState hs{};
   double rate = 0.0;  // d log(stopping margin) / d iteration, from the last pass
   for (int pass = 0; pass <= o.refine; ++pass) {
-    const double *rhs = b;
-    if (pass > 0) {
-      // CSR: a lane per row; dense: a wavefront per row
-      const unsigned rb = (unsigned)ceil_div(A.format == PSK_CSR ? n : n * 64, 256);
-      if (A.format == PSK_CSR) {
-        if (A.dtype == PSK_F64)
-          k_resid<double, true><<<rb, 256, 0, st>>>((const double *)A.values, A.indptr,
-                                                     A.indices, n, d, A.ld, x, b, res);
-        else
-          k_resid<float, true><<<rb, 256, 0, st>>>((const float *)A.values, A.indptr,
-                                                   A.indices, n, d, A.ld, x, b, res);
-      } else {
-        if (A.dtype == PSK_F64)
-          k_resid<double, false><<<rb, 256, 0, st>>>((const double *)A.values, nullptr,
-                                                      nullptr, n, d, A.ld, x, b, res);
-        else
-          k_resid<float, false><<<rb, 256, 0, st>>>((const float *)A.values, nullptr,
-                                                    nullptr, n, d, A.ld, x, b, res);
-      }
-      rhs = res;
-    }
     k_state_reset<<<1, 64, 0, st>>>(B.st);
     k_zero<<<db, 256, 0, st>>>(B.v[0], d);
-    one_step(A, true, 0, B, N, rhs, o, st);
+    one_step(A, pass > 0 ? kResid : kInit, 0, B, N, b, x, o, st);
     int kstep = 1;
     // Groups of at most check_every iterations; after each, the state is
     // copied to pinned memory and the host reads the previous group's copy
@@ -1192,7 +1131,7 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
       }
       if (batch > o.max_iter - it) batch = o.max_iter - it;
       if (batch > 0) {
-        for (int q = 0; q < batch; ++q) one_step(A, false, kstep++, B, N, rhs, o, st);
+        for (int q = 0; q < batch; ++q) one_step(A, kStep, kstep++, B, N, nullptr, nullptr, o, st);
         it += batch;
         const int cur = ngroup++ & 1;
         PSK_HIP_TRY(hipMemcpyAsync(&slot.sl.h[cur], B.st, sizeof(LsqrState),
