@@ -26,6 +26,22 @@
 // no launch reads what it writes; column p is only read during its step.
 // Sums run over lanes in a fixed order and then a fixed butterfly, so the
 // selection is deterministic.
+//
+// A launch per pivot is bound by the launch (1000 x 500: 6.3 us a pivot, two
+// of them work), and the choice itself needs inner products only.  So the
+// pivots are first looked for in the Gram matrix of the sketch: the pivoted
+// Cholesky factorization of G = B^T B meets the same columns, its remaining
+// diagonal being the squared norms that the QR recomputes.  One workgroup
+// takes a panel of up to 16 pivots with its rows of the factor in LDS
+// (k_pivot_panel: 23 us for 16 at d = 500), the whole chip then takes the
+// panel out of G (k_schur: 5 us), and 100 pivots of 1000 x 500 take 0.23 ms
+// with G, not 0.63.  What squaring loses is watched: a pivot counts only if it leads the
+// next candidate by more than kPivotGap of the largest squared norm, some
+// 1e5 times what rounding can have moved either; at the first that does not
+// (equal columns, norms near rounding level, nothing left) the whole
+// selection is made by the QR steps instead.
+#include <type_traits>
+
 #include "internal.hpp"
 
 namespace psk {
@@ -190,6 +206,204 @@ __global__ __launch_bounds__(256) void k_qrcp_step(double *__restrict__ Bt, int6
   if (lane == 0) nout[c] = nn;
 }
 
+// ---------------------------------------------------------------------------
+// pivots from the Gram matrix
+// ---------------------------------------------------------------------------
+constexpr int kPanel = 16;  // pivots a panel at most
+constexpr double kPivotGap = 1e-10;
+constexpr double kPivotTiny = 1e-290;  // squared norms down here have lost their digits
+
+// The largest value of a wavefront in every lane: four shifts inside rows of
+// 16 lanes and two row broadcasts leave it in lane 63 (register moves, where
+// a shuffle goes through LDS).
+__device__ __forceinline__ double wave_max(double v) {
+  auto step = [&](auto ctrl, auto rows) __attribute__((always_inline)) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)b, hi = (uint32_t)(b >> 32);
+    const uint32_t l2 = (uint32_t)__builtin_amdgcn_update_dpp((int)lo, (int)lo, decltype(ctrl)::value,
+                                                              decltype(rows)::value, 0xf, false);
+    const uint32_t h2 = (uint32_t)__builtin_amdgcn_update_dpp((int)hi, (int)hi, decltype(ctrl)::value,
+                                                              decltype(rows)::value, 0xf, false);
+    v = fmax(v, __longlong_as_double((long long)(((uint64_t)h2 << 32) | l2)));
+  };
+  using std::integral_constant;
+  step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});  // row_shr 1
+  step(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});  // row_shr 2
+  step(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});  // row_shr 4
+  step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});  // row_shr 8
+  step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});  // row_bcast 15
+  step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});  // row_bcast 31
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, 63);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 63);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// The best and second best of the candidates: value and column of the best,
+// value of the second (equal to the best where two tie).
+struct Top2 {
+  double v1, v2;
+  int i1;
+};
+
+__device__ __forceinline__ void top2_merge(Top2 &a, double v1, int i1, double v2) {
+  if (v1 > a.v1) {
+    a.v2 = fmax(a.v1, v2);
+    a.v1 = v1;
+    a.i1 = i1;
+  } else {
+    a.v2 = fmax(a.v2, v1);
+  }
+}
+
+// res[c] = G[c, c], state: pivots found, 1 once the search has stopped
+__global__ __launch_bounds__(256) void k_pivot_start(const double *__restrict__ G, int64_t d,
+                                                     double *__restrict__ res,
+                                                     int *__restrict__ state) {
+  const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (c < d) res[c] = G[c * d + c];
+  if (c == 0) state[0] = state[1] = 0;
+}
+
+// Pivots j0 .. j0 + nb - 1 of G, from which the factor rows before j0 are
+// taken out.  Thread t owns columns t, t + blockDim.x, .. (OWN of them) and
+// keeps its entries of the panel's factor rows in registers; LDS holds the
+// rows too, for the pivot column's entries.  res: remaining squared norms, -1
+// for chosen columns; L: the panel's rows of the factor (nb x d).  top[0]: the
+// largest squared norm of all (written by the first panel).  One barrier a
+// pivot: the reductions alternate between two buffers, and a factor row
+// written before the barrier is read after it.  Bound by latencies in a row
+// (the reduction, the barrier, the row of G): 0.8 us a pivot at d = 500.
+template <int OWN, int NP>
+__global__ __launch_bounds__(1024) void k_pivot_panel(const double *__restrict__ G, int64_t d,
+                                                      int64_t j0, int nb,
+                                                      double *__restrict__ res,
+                                                      double *__restrict__ top,
+                                                      double *__restrict__ L,
+                                                      int *__restrict__ state,
+                                                      int32_t *__restrict__ cols) {
+  extern __shared__ double Ls[];  // NP x d
+  __shared__ double r1[2][16], r2[2][16];
+  __shared__ int ri[2][16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nw = blockDim.x >> 6;
+  if (state[1]) return;
+  double rv[OWN], l[OWN][NP];
+#pragma unroll
+  for (int u = 0; u < OWN; ++u) {
+    const int c = tid + u * (int)blockDim.x;
+    rv[u] = c < d ? res[c] : -1.0;
+  }
+  double gap = j0 ? fmax(kPivotGap * top[0], kPivotTiny) : 0.0;
+  int done = 0;
+  bool stop = false;
+#pragma unroll
+  for (int t = 0; t < NP; ++t) {
+    if (t >= nb || stop) continue;  // uniform
+    Top2 b = {-1.0, -1.0, 0x7fffffff};
+#pragma unroll
+    for (int u = 0; u < OWN; ++u)  // a chosen column, or a NaN, is no candidate
+      if (rv[u] >= 0.0) top2_merge(b, rv[u], tid + u * (int)blockDim.x, -1.0);
+    const double m1 = wave_max(b.v1);
+    const uint64_t at = __ballot(b.v1 == m1);  // never empty: no candidate is a NaN
+    const int src = __ffsll((unsigned long long)at) - 1;
+    const double m2 = wave_max(lane == src ? b.v2 : b.v1);
+    const int i1 = __builtin_amdgcn_readlane(b.i1, src);
+    if (lane == 0) {
+      r1[t & 1][wave] = m1;
+      r2[t & 1][wave] = m2;
+      ri[t & 1][wave] = i1;
+    }
+    __syncthreads();
+    b = {r1[t & 1][0], r2[t & 1][0], ri[t & 1][0]};
+    for (int w = 1; w < nw; ++w) top2_merge(b, r1[t & 1][w], ri[t & 1][w], r2[t & 1][w]);
+    if (j0 == 0 && t == 0) {
+      gap = fmax(kPivotGap * b.v1, kPivotTiny);
+      if (tid == 0) top[0] = b.v1;
+    }
+    // no clear leader (uniform; also true for NaN): leave the rest to the QR
+    if (!(b.v1 > gap && b.v1 - fmax(b.v2, 0.0) > gap)) {
+      stop = true;
+      continue;
+    }
+    const int p = __builtin_amdgcn_readfirstlane(b.i1);
+    const double *gp = G + (int64_t)p * d;
+    double g[OWN], lp[NP];
+#pragma unroll
+    for (int u = 0; u < OWN; ++u) {
+      const int c = tid + u * (int)blockDim.x;
+      g[u] = gp[c < d ? c : 0];
+    }
+#pragma unroll
+    for (int q = 0; q < t; ++q) lp[q] = Ls[q * d + p];
+    const double inv = 1.0 / sqrt(b.v1);
+#pragma unroll
+    for (int u = 0; u < OWN; ++u) {
+      const int c = tid + u * (int)blockDim.x;
+#pragma unroll
+      for (int q = 0; q < t; ++q) g[u] = fma(-lp[q], l[u][q], g[u]);
+      l[u][t] = rv[u] >= 0.0 ? g[u] * inv : 0.0;
+      if (c < d) Ls[t * d + c] = l[u][t];
+      if (c == p) {
+        rv[u] = -1.0;
+        cols[j0 + t] = (int32_t)c;
+      } else if (rv[u] >= 0.0) {
+        rv[u] = fmax(fma(-l[u][t], l[u][t], rv[u]), 0.0);
+      }
+    }
+    done = t + 1;
+  }
+  if (tid == 0) {
+    state[0] = (int)j0 + done;
+    state[1] = stop ? 1 : 0;
+  }
+  if (stop) return;
+#pragma unroll
+  for (int u = 0; u < OWN; ++u) {
+    const int c = tid + u * (int)blockDim.x;
+    if (c >= d) continue;
+    res[c] = rv[u];
+#pragma unroll
+    for (int q = 0; q < NP; ++q)
+      if (q < nb) L[(int64_t)q * d + c] = l[u][q];
+  }
+}
+
+// G -= L^T L for the nb rows of a panel (all of G: rows and columns of chosen
+// pivots are not read again): 16 x 64 elements a workgroup, its columns of L
+// loaded together
+__global__ __launch_bounds__(256) void k_schur(double *__restrict__ G, int64_t d, int nb,
+                                               const double *__restrict__ L,
+                                               const int *__restrict__ state) {
+  __shared__ double la[kPanel][16];
+  const int stopped = state[1];
+  const int x = threadIdx.x & 63, y = threadIdx.x >> 6;
+  const int64_t c = (int64_t)blockIdx.x * 64 + x, a0 = (int64_t)blockIdx.y * 16;
+  const int64_t cc = c < d ? c : d - 1;
+  double lc[kPanel], g[4];
+#pragma unroll
+  for (int q = 0; q < kPanel; ++q) lc[q] = q < nb ? L[(int64_t)q * d + cc] : 0.0;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int64_t a = a0 + 4 * y + u;
+    g[u] = G[(a < d ? a : d - 1) * d + cc];
+  }
+  {
+    const int q = threadIdx.x >> 4;
+    const int64_t a = a0 + (threadIdx.x & 15);
+    la[q][threadIdx.x & 15] = q < nb ? L[(int64_t)q * d + (a < d ? a : d - 1)] : 0.0;
+  }
+  __syncthreads();
+  if (stopped || c >= d) return;
+#pragma unroll
+  for (int q = 0; q < kPanel; ++q)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) g[u] = fma(-la[q][4 * y + u], lc[q], g[u]);
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    if (a0 + 4 * y + u < d) G[(a0 + 4 * y + u) * d + c] = g[u];
+}
+
 // W[a, b] = G[cols[a], cols[b]] (k x k block of the d x d Gram matrix).
 __global__ __launch_bounds__(256) void k_gather_block(const double *__restrict__ G, int64_t d,
                                                       const int32_t *__restrict__ cols, int64_t k,
@@ -232,7 +446,8 @@ int css_select_impl(const psk_mat &A, int64_t m, int64_t r, int64_t k, uint64_t 
   double *Bt = ws.take<double>((size_t)rows * d);
   double *na = ws.take<double>((size_t)d);
   double *nb = ws.take<double>((size_t)d);
-  int *flag = ws.take<int>(2);
+  double *L = ws.take<double>((size_t)kPanel * d);
+  int *flag = ws.take<int>(4);  // [0]: non-finite sketch; [2], [3]: the pivot search's state
   const bool run = !ws.dry();
   if (run && !ws.ok()) return fail(PSK_ENOMEM, "workspace too small for css_select");
   const size_t mk = ws.mark();
@@ -242,12 +457,51 @@ int css_select_impl(const psk_mat &A, int64_t m, int64_t r, int64_t k, uint64_t 
   if (!run) return 0;
   // pivots chosen by norms with a NaN in them are meaningless: the sketch is
   // checked first and read back before the selection runs
-  k_zero<<<1, 64, 0, st>>>(reinterpret_cast<double *>(flag), 1);
+  k_zero<<<1, 64, 0, st>>>(reinterpret_cast<double *>(flag), 2);
   flag_nonfinite(C, rows * d, flag, st);
-  int h = 0;
-  PSK_HIP_TRY(hipMemcpyAsync(&h, flag, sizeof(int), hipMemcpyDeviceToHost, st));
+  // The search in the Gram matrix, where that is the shorter way (in us: G at
+  // 40 TFLOP/s, four launches, two a panel and 1.5 a pivot or more, against 5
+  // a pivot and the sketch read and written at 4 TB/s for each) and the
+  // transposed sketch's room holds G and the partial sums of it.  Measured
+  // whole calls, 20,000 rows, steps / search: d = 32, k = 16 352 / 159; d =
+  // 500, k = 20 636 / 325; d = 1000, k = 100 1992 / 1045.
+  const double gram_us = 20.0 + (double)rows * d * d / 40e6 + 10.0 * ceil_div(k, (int64_t)kPanel) +
+                         (double)k * (1.5 + (double)d * 1e-3);
+  const double steps_us = (double)k * (5.0 + (double)rows * d * 16.0 / 4e6);
+  const int64_t room = rows * d - d * d;
+  const bool search = k > 1 && gram_us < steps_us && room >= dgram_room(d);
+  int h[4] = {0, 0, 0, 1};
+  if (search) {
+    KTimer timer("pivots", st);
+    double *G = Bt;
+    if ((rc = dgram(C, rows, d, G, Bt + d * d, room, st))) return rc;
+    k_pivot_start<<<(unsigned)ceil_div(d, (int64_t)256), 256, 0, st>>>(G, d, na, flag + 2);
+    const dim3 sg((unsigned)ceil_div(d, (int64_t)64), (unsigned)ceil_div(d, (int64_t)16));
+    // a column a thread while 1024 threads suffice; the factor rows of a panel
+    // fit LDS (128 KiB)
+    auto panels = [&](auto own, auto np) -> int {
+      constexpr int OWN = decltype(own)::value, NP = decltype(np)::value;
+      const unsigned threads = (unsigned)(ceil_div(d, (int64_t)(64 * OWN)) * 64);
+      const size_t lds = (size_t)NP * d * sizeof(double);
+      PSK_HIP_TRY(hipFuncSetAttribute((const void *)k_pivot_panel<OWN, NP>,
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+      for (int64_t j = 0; j < k; j += NP) {
+        const int n1 = (int)(k - j < NP ? k - j : NP);
+        k_pivot_panel<OWN, NP><<<1, threads, lds, st>>>(G, d, j, n1, na, nb, L, flag + 2, cols);
+        if (j + n1 < k) k_schur<<<sg, 256, 0, st>>>(G, d, n1, L, flag + 2);
+      }
+      return 0;
+    };
+    using std::integral_constant;
+    if (d <= 1024) rc = panels(integral_constant<int, 1>{}, integral_constant<int, kPanel>{});
+    else if (d <= 2048) rc = panels(integral_constant<int, 2>{}, integral_constant<int, 8>{});
+    else rc = panels(integral_constant<int, 4>{}, integral_constant<int, 4>{});
+    if (rc) return rc;
+  }
+  PSK_HIP_TRY(hipMemcpyAsync(h, flag, (search ? 4 : 1) * sizeof(int), hipMemcpyDeviceToHost, st));
   PSK_HIP_TRY(hipStreamSynchronize(st));
-  if ((rc = factor_status(h, ""))) return rc;
+  if ((rc = factor_status(h[0], ""))) return rc;
+  if (search && !h[3]) return 0;
   KTimer timer("qrcp", st);
   const dim3 tg((unsigned)ceil_div(rows, (int64_t)kTile), (unsigned)ceil_div(d, (int64_t)kTile));
   k_transpose<<<tg, 256, 0, st>>>(C, rows, d, Bt);
