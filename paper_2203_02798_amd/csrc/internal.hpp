@@ -67,8 +67,8 @@ struct KTimer {
 // only below bptr[r].  Returns 0 or a status.
 int cs_bin(const psk_mat &A, uint32_t r, uint64_t seed, Arena &ws, hipStream_t st,
            uint32_t **perm, uint32_t **bptr);
-// Stable LSD radix sort (8-bit digits) of (key, val) pairs with keys < r;
-// keys/vals are consumed (used as the first ping-pong buffers).  On return
+// Stable LSD radix sort of (key, val) pairs with keys < r; keys/vals are
+// consumed (a second pass writes over them).  On return
 // *skeys/*svals point at the sorted arrays; with ptr != NULL, ptr[0..r] gets
 // the start of each key's run (ptr[r] = n).  With dn != NULL only the first
 // dn[0] <= n pairs (a count on the device) are sorted.
