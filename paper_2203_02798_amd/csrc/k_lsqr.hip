@@ -502,54 +502,59 @@ __global__ __launch_bounds__(kVThreads) void k_vnew_rows(
 // nothing here waits on memory but the few entries of d > 256 kUpdPre.
 constexpr int kUpdPre = 4;
 
+// The scalars of one step, by one thread: the state's new values and sh =
+// {1 / alpha, phi / rho, theta / rho, done}.
+__device__ __forceinline__ void lsqr_scalars(LsqrState *__restrict__ st, const LsqrState &ss,
+                                             double beta, double alpha, double atol, double btol,
+                                             int init, double (&sh)[4]) {
+  double phi = 0.0, rho = 1.0, theta = 0.0;
+  int done = 0;
+  if (init) {
+    st->bnorm = beta;
+    st->phibar = beta;
+    st->rhobar = alpha;
+    st->anorm2 = 0.0;
+    st->iters = 0;
+    if (beta == 0.0 || alpha == 0.0) done = 1;
+  } else {
+    const double anorm2 = ss.anorm2 + ss.alpha * ss.alpha + beta * beta;
+    st->anorm2 = anorm2;
+    const double rhobar = ss.rhobar;
+    rho = sqrt(rhobar * rhobar + beta * beta);
+    const double c = rhobar / rho;
+    const double s = beta / rho;
+    theta = s * alpha;
+    st->rhobar = -c * alpha;
+    phi = c * ss.phibar;
+    const double phibar = s * ss.phibar;
+    st->phibar = phibar;
+    st->iters = ss.iters + 1;
+    const double anorm = sqrt(anorm2);
+    const double rnorm = phibar;
+    const double arnorm = rnorm * alpha * fabs(c);
+    st->rnorm = rnorm;
+    st->arnorm = arnorm;
+    st->test2 = (anorm > 0.0 && rnorm > 0.0) ? arnorm / (anorm * rnorm) : 0.0;
+    if (arnorm <= atol * anorm * rnorm) done = 1;
+    if (rnorm <= btol * ss.bnorm + atol * anorm * sqrt(ss.ynorm2)) done = 1;
+    if (alpha == 0.0 || beta == 0.0) done = 1;
+  }
+  st->alpha = alpha;
+  st->ufac = beta > 0.0 ? 1.0 / beta : 0.0;
+  sh[0] = alpha > 0.0 ? 1.0 / alpha : 0.0;
+  sh[1] = init ? 0.0 : phi / rho;
+  sh[2] = init ? 0.0 : theta / rho;
+  sh[3] = done;
+}
+
 __device__ void lsqr_update(LsqrState *__restrict__ st, const LsqrState &ss, int64_t d,
                             double *__restrict__ v, const double *__restrict__ vnew,
                             double *__restrict__ w, double *__restrict__ y,
                             const double (&wp)[kUpdPre], const double (&yp)[kUpdPre],
                             double alpha, double atol, double btol, int init) {
-  __shared__ double sh[8];
+  __shared__ double sh[4];
   __shared__ double red[4];
-  if (threadIdx.x == 0) {
-    const double beta = ss.beta_new;
-    double phi = 0.0, rho = 1.0, theta = 0.0;
-    int done = 0;
-    if (init) {
-      st->bnorm = beta;
-      st->phibar = beta;
-      st->rhobar = alpha;
-      st->anorm2 = 0.0;
-      st->iters = 0;
-      if (beta == 0.0 || alpha == 0.0) done = 1;
-    } else {
-      const double anorm2 = ss.anorm2 + ss.alpha * ss.alpha + beta * beta;
-      st->anorm2 = anorm2;
-      const double rhobar = ss.rhobar;
-      rho = sqrt(rhobar * rhobar + beta * beta);
-      const double c = rhobar / rho;
-      const double s = beta / rho;
-      theta = s * alpha;
-      st->rhobar = -c * alpha;
-      phi = c * ss.phibar;
-      const double phibar = s * ss.phibar;
-      st->phibar = phibar;
-      st->iters = ss.iters + 1;
-      const double anorm = sqrt(anorm2);
-      const double rnorm = phibar;
-      const double arnorm = rnorm * alpha * fabs(c);
-      st->rnorm = rnorm;
-      st->arnorm = arnorm;
-      st->test2 = (anorm > 0.0 && rnorm > 0.0) ? arnorm / (anorm * rnorm) : 0.0;
-      if (arnorm <= atol * anorm * rnorm) done = 1;
-      if (rnorm <= btol * ss.bnorm + atol * anorm * sqrt(ss.ynorm2)) done = 1;
-      if (alpha == 0.0 || beta == 0.0) done = 1;
-    }
-    st->alpha = alpha;
-    st->ufac = beta > 0.0 ? 1.0 / beta : 0.0;
-    sh[0] = alpha > 0.0 ? 1.0 / alpha : 0.0;
-    sh[1] = init ? 0.0 : phi / rho;
-    sh[2] = init ? 0.0 : theta / rho;
-    sh[3] = done;
-  }
+  if (threadIdx.x == 0) lsqr_scalars(st, ss, ss.beta_new, alpha, atol, btol, init, sh);
   __syncthreads();
   const double ainv = sh[0], fx = sh[1], fw = sh[2];
   double y2 = 0.0;
@@ -617,8 +622,16 @@ __global__ __launch_bounds__(256) void k_trmv(const double *__restrict__ Rinv, i
   }
 }
 
-__global__ void k_state_reset(LsqrState *st) {
-  if (threadIdx.x == 0) {
+// The start of a pass: a fresh state, v = 0 and (x not NULL: the first pass)
+// x = 0, in one launch.
+__global__ __launch_bounds__(256) void k_start(LsqrState *st, int64_t d, double *__restrict__ v,
+                                               double *__restrict__ x) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < d) {
+    v[i] = 0.0;
+    if (x) x[i] = 0.0;
+  }
+  if (i == 0) {
     st->alpha = st->beta_new = st->rhobar = st->phibar = 0.0;
     st->anorm2 = st->bnorm = st->ufac = st->ynorm2 = 0.0;
     st->rnorm = st->arnorm = st->test2 = 0.0;
@@ -627,14 +640,12 @@ __global__ void k_state_reset(LsqrState *st) {
   }
 }
 
-__global__ void k_zero(double *p, int64_t count) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < count) p[i] = 0.0;
-}
-
-// out[0] = max_i |R_ii|, out[1] = min_i |R_ii| (one workgroup, fixed order)
+// out[0] = max_i |R_ii|, out[1] = min_i |R_ii| (one workgroup, fixed order),
+// and the factorization's flag at status, to be read back with them
 __global__ __launch_bounds__(256) void k_diag_ratio(const double *__restrict__ R, int64_t d,
-                                                    double *__restrict__ out) {
+                                                    const int *__restrict__ flag,
+                                                    double *__restrict__ out,
+                                                    double *__restrict__ status) {
   __shared__ double mx[256], mn[256];
   double a = 0.0, b = INFINITY;
   for (int64_t i = threadIdx.x; i < d; i += 256) {
@@ -653,6 +664,7 @@ __global__ __launch_bounds__(256) void k_diag_ratio(const double *__restrict__ R
     __syncthreads();
   }
   if (threadIdx.x == 0) {
+    status[0] = (double)flag[0];
     out[0] = mx[0];
     out[1] = mn[0];
   }
@@ -774,6 +786,112 @@ __global__ __launch_bounds__(256) void k_update(const double *__restrict__ Rinv,
   }
 }
 
+// Both halves of an iteration for d <= DP <= 64 by one workgroup: with R^{-1}
+// in LDS the products are a few thousand multiply-adds, and two launches with
+// their partial results through memory cost more than the chip's width gives
+// (1e4 x 32: 6 + 6 us, with this 5).  1024 threads sum the pass partials
+// (thread (g, c): column c, partials g, g + 1024 / DP, ...; the groups then in
+// order); the first wavefront does the rest, lane j owning column j, then row
+// j, of R^{-1}: no barrier after the sums.
+template <int DP>
+__global__ __launch_bounds__(1024) void k_small_step(
+    const double *__restrict__ part_t, const double *__restrict__ part_b2,
+    const double *__restrict__ Rinv, int64_t d, LsqrState *__restrict__ st,
+    const double *__restrict__ v_in, double *__restrict__ v_out, double *__restrict__ w,
+    double *__restrict__ y, double *__restrict__ vhat, double atol, double btol, int init) {
+  constexpr int kGroups = 1024 / DP, kPer = kPassBlocks / kGroups;
+  __shared__ double Rs[DP][DP + 1];
+  __shared__ double red[kGroups][DP + 1];
+  __shared__ double b2s[kPassBlocks / 64];
+  __shared__ double tv[DP], vn[DP];
+  const int stop = init ? 0 : st->done;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c = tid % DP, g = tid / DP;
+  // all loads first (clamped, masked afterwards)
+  double pt[kPer], rr[DP * DP / 1024];
+#pragma unroll
+  for (int q = 0; q < kPer; ++q)
+    pt[q] = part_t[(int64_t)(g + kGroups * q) * d + (c < d ? c : 0)];
+#pragma unroll
+  for (int q = 0; q < DP * DP / 1024; ++q) {
+    const int i = g + kGroups * q;
+    rr[q] = Rinv[i < d && c < d ? i * d + c : 0];
+  }
+  double s = part_b2[tid < kPassBlocks ? tid : 0];
+  const LsqrState ss = *st;
+  const int j = lane < d ? lane : 0;
+  const double vj0 = init ? 0.0 : v_in[j], wj = init ? 0.0 : w[j], yj = init ? 0.0 : y[j];
+#pragma unroll
+  for (int q = 0; q < DP * DP / 1024; ++q) {
+    const int i = g + kGroups * q;
+    Rs[i][c] = i <= c && c < d ? rr[q] : 0.0;
+  }
+  double ts = 0.0;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) ts += pt[q];
+  red[g][c] = c < d ? ts : 0.0;
+  if (tid < kPassBlocks) {  // whole wavefronts
+    s = wave_sum(s);
+    if (lane == 0) b2s[wave] = s;
+  }
+  __syncthreads();
+  if (stop || wave) return;
+  double b2 = b2s[0];
+#pragma unroll
+  for (int q = 1; q < kPassBlocks / 64; ++q) b2 += b2s[q];
+  const double beta = sqrt(b2);
+  const double binv = beta > 0.0 ? 1.0 / beta : 0.0;
+  const int col = lane < DP ? lane : 0;
+  double t = 0.0;
+#pragma unroll 16
+  for (int q = 0; q < kGroups; ++q) t += red[q][col];
+  auto settle = [] {  // this wavefront's LDS writes, to its own reads
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  if (lane < DP) tv[lane] = t * binv;
+  settle();
+  // vnew = R^{-T} t - beta v, alpha = ||vnew||, vhat = R^{-1} vnew / alpha
+  double a0 = 0.0, a1 = 0.0;
+#pragma unroll 8
+  for (int i = 0; i < DP; i += 2) {
+    a0 += Rs[i][col] * tv[i];
+    a1 += Rs[i + 1][col] * tv[i + 1];
+  }
+  const double val = lane < d ? (a0 + a1) - beta * vj0 : 0.0;
+  if (lane < DP) vn[lane] = val;
+  const double alpha = sqrt(wave_sum(val * val));
+  settle();
+  a0 = a1 = 0.0;
+#pragma unroll 8
+  for (int i = 0; i < DP; i += 2) {
+    a0 += Rs[col][i] * vn[i];
+    a1 += Rs[col][i + 1] * vn[i + 1];
+  }
+  double sh[4];
+  if (lane == 0) {
+    st->beta_new = beta;
+    lsqr_scalars(st, ss, beta, alpha, atol, btol, init, sh);
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) sh[q] = __shfl(sh[q], 0, 64);
+  double y2 = 0.0;
+  if (lane < d) {
+    const double vj = val * sh[0];
+    const double yn = init ? 0.0 : yj + sh[1] * wj;
+    v_out[lane] = vj;
+    y[lane] = yn;
+    w[lane] = init ? vj : vj - sh[2] * wj;
+    vhat[lane] = (a0 + a1) * sh[0];
+    y2 = yn * yn;
+  }
+  y2 = wave_sum(y2);
+  if (lane == 0) {
+    st->ynorm2 = y2;
+    if (sh[3] != 0.0) st->done = 1;
+  }
+}
+
 struct LsqBufs {
   double *u, *part_t, *part_b2, *vpart, *v[2], *w, *y, *vhat;
   LsqrState *st;
@@ -836,6 +954,17 @@ void one_step(const psk_mat &A, int mode, int k, const LsqBufs &B, const double 
     if (A.dtype == PSK_F64) run(double{});
     else run(float{});
   }
+  if (d <= 64) {
+    if (d <= 32)
+      k_small_step<32><<<1, 1024, 0, s>>>(B.part_t, B.part_b2, Rinv, d, B.st, B.v[k & 1],
+                                          B.v[(k + 1) & 1], B.w, B.y, B.vhat, o.atol, o.btol,
+                                          init ? 1 : 0);
+    else
+      k_small_step<64><<<1, 1024, 0, s>>>(B.part_t, B.part_b2, Rinv, d, B.st, B.v[k & 1],
+                                          B.v[(k + 1) & 1], B.w, B.y, B.vhat, o.atol, o.btol,
+                                          init ? 1 : 0);
+    return;
+  }
   const unsigned nbv = (unsigned)ceil_div(d, kVRows);
   k_vnew_rows<<<nbv, kVThreads, 0, s>>>(B.part_t, B.part_b2, Rinv, d, B.st, B.vpart,
                                         init ? 1 : 0);
@@ -896,7 +1025,8 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
   B.y = ws.take<double>((size_t)d);
   B.vhat = ws.take<double>((size_t)d);
   B.st = ws.take<LsqrState>(1);
-  double *ratio = ws.take<double>(2 + kPrecondEst);  // max |R_ii|, min |R_ii|; precond_estimate's
+  // max |R_ii|, min |R_ii|; precond_estimate's; the factorization's flag
+  double *ratio = ws.take<double>(3 + kPrecondEst);
   // the reduced-precision sketch's perturbation against the FP64 one, on
   // request: that sketch kept (Chat), the FP64 sketch and its factor
   const bool want_delta = own && o.want_delta != 0 && o.prec != PSK_PREC_F64;
@@ -1000,16 +1130,15 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
   // delta of the sketch LSQR is preconditioned with: 0 for the FP64 sketch,
   // NaN when not measured (not requested, or the caller's R^{-1})
   double delta_est = (own && o.prec == PSK_PREC_F64) ? 0.0 : NAN;
-  double hr[2 + kPrecondEst] = {1.0, 1.0};
+  double hr[3 + kPrecondEst] = {1.0, 1.0};
   if (own) {
-    int hflag = 0;
-    k_diag_ratio<<<1, 256, 0, st>>>(R, d, ratio);
+    k_diag_ratio<<<1, 256, 0, st>>>(R, d, flag, ratio, ratio + 2 + kPrecondEst);
     if (may_sharpen) precond_estimate(A, R, Rinv, B.vhat, ratio + 2, st);
-    PSK_HIP_TRY(hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, st));
     PSK_HIP_TRY(hipMemcpyAsync(hr, ratio, sizeof(hr), hipMemcpyDeviceToHost, st));
     if (want_delta)
       PSK_HIP_TRY(hipMemcpyAsync(&delta_est, dl, sizeof(double), hipMemcpyDeviceToHost, st));
     PSK_HIP_TRY(hipStreamSynchronize(st));
+    int hflag = (int)hr[2 + kPrecondEst];
     // A reduced-precision sketch only preconditions well while its relative
     // error (about 1e-5 for the BF16 GEMM) times cond(A) stays small; the
     // diagonal ratio of R is a cheap lower estimate of cond(A).
@@ -1068,14 +1197,12 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
   SlotGuard slot;
   if ((rc = take_slot(&slot.sl))) return rc;
   slot.held = true;
-  k_zero<<<db, 256, 0, st>>>(x, d);
   int total_iters = 0;
   bool converged = true, nonfinite = false;
   LsqrState hs{};
   double rate = 0.0;  // d log(stopping margin) / d iteration, from the last pass
   for (int pass = 0; pass <= o.refine; ++pass) {
-    k_state_reset<<<1, 64, 0, st>>>(B.st);
-    k_zero<<<db, 256, 0, st>>>(B.v[0], d);
+    k_start<<<db, 256, 0, st>>>(B.st, d, B.v[0], pass > 0 ? nullptr : x);
     one_step(A, pass > 0 ? kResid : kInit, 0, B, N, b, x, o, st);
     int kstep = 1;
     // Groups of at most check_every iterations; after each, the state is
