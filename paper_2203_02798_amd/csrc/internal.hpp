@@ -42,6 +42,10 @@ struct Arena {
   bool ok() const { return measure || peak <= cap; }
 };
 
+// dst = bytes (4 KiB at most) at src on the device, once st has reached this
+// point: synchronises st (k_check.hip).
+int read_back(void *dst, const void *src, size_t bytes, hipStream_t st);
+
 inline size_t elem_size(int dtype) { return dtype == PSK_F64 ? 8 : 4; }
 
 // Event bracket around a launch (or region) when timing is enabled:

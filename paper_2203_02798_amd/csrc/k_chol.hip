@@ -716,8 +716,8 @@ int fro_dist_identity_sq(const double *W, int64_t d, double *part, hipStream_t s
                          double *out) {
   k_fro_partials<<<kParts, 256, 0, st>>>(W, d, part);
   double h[kParts];
-  PSK_HIP_TRY(hipMemcpyAsync(h, part, sizeof(h), hipMemcpyDeviceToHost, st));
-  PSK_HIP_TRY(hipStreamSynchronize(st));
+  int rc;
+  if ((rc = read_back(h, part, sizeof(h), st))) return rc;
   double sum = 0.0;
   for (int b = 0; b < kParts; ++b) sum += h[b];
   *out = sum;

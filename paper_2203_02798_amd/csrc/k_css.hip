@@ -498,8 +498,7 @@ int css_select_impl(const psk_mat &A, int64_t m, int64_t r, int64_t k, uint64_t 
     else rc = panels(integral_constant<int, 4>{}, integral_constant<int, 4>{});
     if (rc) return rc;
   }
-  PSK_HIP_TRY(hipMemcpyAsync(h, flag, (search ? 4 : 1) * sizeof(int), hipMemcpyDeviceToHost, st));
-  PSK_HIP_TRY(hipStreamSynchronize(st));
+  if ((rc = read_back(h, flag, (search ? 4 : 1) * sizeof(int), st))) return rc;
   if ((rc = factor_status(h[0], ""))) return rc;
   if (search && !h[3]) return 0;
   KTimer timer("qrcp", st);
@@ -552,8 +551,7 @@ int leverage_css_impl(const psk_mat &A, int64_t m, int64_t r, int64_t k, uint64_
   PSK_HIP_TRY(hipGetLastError());
   flag_nonfinite(theta, A.n, flag, st);
   int h = 0;
-  PSK_HIP_TRY(hipMemcpyAsync(&h, flag, sizeof(int), hipMemcpyDeviceToHost, st));
-  PSK_HIP_TRY(hipStreamSynchronize(st));
+  if ((rc = read_back(&h, flag, sizeof(int), st))) return rc;
   return factor_status(h, "a Cholesky pivot was not positive: the selected columns are numerically rank deficient");
 }
 

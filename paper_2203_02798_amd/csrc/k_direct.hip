@@ -256,9 +256,8 @@ int gram_f64(const psk_mat &A, double *B, Arena &ws, hipStream_t st) {
 // result, count values at out), read back once the stream reaches it
 int rank_check(int *flag, const double *out, int64_t count, hipStream_t st) {
   flag_nonfinite(out, count, flag, st);
-  int h = 0;
-  PSK_HIP_TRY(hipMemcpyAsync(&h, flag, sizeof(int), hipMemcpyDeviceToHost, st));
-  PSK_HIP_TRY(hipStreamSynchronize(st));
+  int h = 0, rc;
+  if ((rc = read_back(&h, flag, sizeof(int), st))) return rc;
   return factor_status(h, "a Cholesky pivot was not positive: A is numerically rank deficient");
 }
 

@@ -90,8 +90,7 @@ int leverage_sketch_impl(const psk_mat &A, int64_t m, int64_t r, int64_t t, uint
   // still reaches its row's score
   flag_nonfinite(theta, A.n, flag, st);
   int h = 0;
-  PSK_HIP_TRY(hipMemcpyAsync(&h, flag, sizeof(int), hipMemcpyDeviceToHost, st));
-  PSK_HIP_TRY(hipStreamSynchronize(st));
+  if ((rc = read_back(&h, flag, sizeof(int), st))) return rc;
   return factor_status(h, "a Cholesky pivot was not positive: the sketch is numerically rank deficient");
 }
 

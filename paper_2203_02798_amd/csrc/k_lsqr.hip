@@ -1134,10 +1134,8 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
   if (own) {
     k_diag_ratio<<<1, 256, 0, st>>>(R, d, flag, ratio, ratio + 2 + kPrecondEst);
     if (may_sharpen) precond_estimate(A, R, Rinv, B.vhat, ratio + 2, st);
-    PSK_HIP_TRY(hipMemcpyAsync(hr, ratio, sizeof(hr), hipMemcpyDeviceToHost, st));
-    if (want_delta)
-      PSK_HIP_TRY(hipMemcpyAsync(&delta_est, dl, sizeof(double), hipMemcpyDeviceToHost, st));
-    PSK_HIP_TRY(hipStreamSynchronize(st));
+    if ((rc = read_back(hr, ratio, sizeof(hr), st))) return rc;
+    if (want_delta && (rc = read_back(&delta_est, dl, sizeof(double), st))) return rc;
     int hflag = (int)hr[2 + kPrecondEst];
     // A reduced-precision sketch only preconditions well while its relative
     // error (about 1e-5 for the BF16 GEMM) times cond(A) stays small; the
@@ -1159,10 +1157,9 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
       ws.release(mk2);
       if (may_sharpen) {
         precond_estimate(A, R, Rinv, B.vhat, ratio + 2, st);
-        PSK_HIP_TRY(hipMemcpyAsync(hr, ratio, sizeof(hr), hipMemcpyDeviceToHost, st));
+        if ((rc = read_back(hr, ratio, sizeof(hr), st))) return rc;
       }
-      PSK_HIP_TRY(hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, st));
-      PSK_HIP_TRY(hipStreamSynchronize(st));
+      if ((rc = read_back(&hflag, flag, sizeof(int), st))) return rc;
       prec_used = PSK_PREC_F64;
       delta_est = 0.0;  // LSQR runs on the FP64 sketch now
     }
@@ -1176,8 +1173,7 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
   if (may_sharpen && o.max_iter >= kSharpenMinIter) {
     if (!own) {
       precond_estimate(A, nullptr, Rinv, B.vhat, ratio + 2, st);
-      PSK_HIP_TRY(hipMemcpyAsync(hr, ratio, sizeof(hr), hipMemcpyDeviceToHost, st));
-      PSK_HIP_TRY(hipStreamSynchronize(st));
+      if ((rc = read_back(hr, ratio, sizeof(hr), st))) return rc;
     }
     const double err = precond_error(hr + 2, d);
     const double rsq = A.format == PSK_CSR ? precond_row_squares(hr + 2) : 0.0;
