@@ -23,7 +23,8 @@
 // with one launch per block step (k_chol_step, below): the panel, the
 // trailing update, the partial products of R^{-1} and the factorization of
 // the next diagonal block all happen in the same launch, so a pass costs
-// ceil(d/64) + 2 launches besides its two GEMMs with C.
+// ceil(d/64) + 2 launches besides its two GEMMs with C.  Up to 64 columns a
+// pass is one workgroup's launch (k_chol_small, k_later_small).
 #include "internal.hpp"
 
 namespace psk {
@@ -692,8 +693,16 @@ __global__ __launch_bounds__(256) void k_series_x(const double *__restrict__ T, 
 // R^{-1}; *flag (four ints) is cleared first with clear.
 // xpart: scratch of at least d * d doubles for the partial products of the
 // off-diagonal blocks of X (two block columns' worth, by parity).
+__global__ void k_chol_small(const double *__restrict__ W, int64_t d, double coef,
+                             double *__restrict__ R, double *__restrict__ X,
+                             int *__restrict__ flag, int clear);
+
 void chol_inv(double *W, int64_t d, double coef, double *R, double *X, int *flag, bool clear,
               double *xpart, hipStream_t st) {
+  if (d <= 64) {
+    k_chol_small<<<1, kTh, 0, st>>>(W, d, coef, R, X, flag, clear ? 1 : 0);
+    return;
+  }
   const int nblk = (int)ceil_div(d, 64);
   const int64_t pb = ceil_div(d * d, (int64_t)1024);
   k_chol_prep<<<(unsigned)(pb < 1024 ? pb : 1024), 256, 0, st>>>(W, d, coef, R, X,
@@ -726,10 +735,139 @@ int fro_dist_identity_sq(const double *W, int64_t d, double *part, hipStream_t s
 
 // Products of the series for ||E||_F = eps: after t fixed-point steps U is
 // off by about 2^t eps^(t+2), and I - U + ... + (-U)^(t+1) by eps^(t+2).
-int series_depth(double eps) {
+__host__ __device__ inline int series_depth(double eps) {
   if (eps <= 1e-8) return 0;
   if (eps <= 3e-6) return 1;
   return 2;
+}
+
+// The whole of a first pass's Cholesky for d <= 64 in one launch: W + coef
+// trace(W) I factored in LDS into R and X = R^{-1} (*flag cleared first with
+// clear).
+__global__ __launch_bounds__(kTh) void k_chol_small(const double *__restrict__ W, int64_t d,
+                                                    double coef, double *__restrict__ R,
+                                                    double *__restrict__ X,
+                                                    int *__restrict__ flag, int clear) {
+  __shared__ CholSmem S;
+  __shared__ double shift;
+  if (clear && threadIdx.x < 4) atomicExch(&flag[threadIdx.x], 0);
+  Tile64 t;
+  t.load(W, d, 0, 0, (int)d, (int)d);
+  t.store(S.PJ);
+  __threadfence();  // the cleared flag, ahead of what the factorization reports
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    const int i = threadIdx.x;
+    const double tr = wave_sum(i < d ? S.PJ[i * kLd + i] : 0.0);
+    if (i == 0) shift = coef * tr;
+  }
+  __syncthreads();
+  if (coef != 0.0 && threadIdx.x < (unsigned)d) S.PJ[threadIdx.x * (kLd + 1)] += shift;
+  __syncthreads();
+  factor_diag(S.PJ, S.X, S, (int)d, d, 0, R, X, flag);
+}
+
+// A pass after the first for d <= 64 in one launch: from W = Q^T Q and the
+// factors R1, X1 = R1^{-1} so far, R = R2 R1 and X = X1 X2 with R2 the
+// Cholesky factor of W and X2 its inverse, by the series where ||W - I||_F <=
+// kSeriesTol (as series_chol) and by factor_diag otherwise; dist = ||W -
+// I||_F.  R2 and X2 are written by the second way only.  The d x d steps and
+// products were up to 13 launches with nothing to do but start (a solve of 1e4
+// x 32: 334 us with them, 309 now).
+__global__ __launch_bounds__(kTh) void k_later_small(
+    const double *__restrict__ W, int64_t d, const double *__restrict__ R1,
+    const double *__restrict__ X1, double *__restrict__ R, double *__restrict__ X,
+    double *__restrict__ R2, double *__restrict__ X2, double *__restrict__ dist,
+    int *__restrict__ flag) {
+  __shared__ CholSmem S;
+  __shared__ double red[4];
+  const int nb = (int)d;
+  const int w = threadIdx.x >> 6, li = threadIdx.x & 15, kq = (threadIdx.x >> 4) & 3;
+  const int j = threadIdx.x & 63, i0 = threadIdx.x >> 6;
+  Tile64 t, r1, x1;
+  t.load(W, d, 0, 0, nb, nb);
+  r1.load(R1, d, 0, 0, nb, nb);
+  x1.load(X1, d, 0, 0, nb, nb);
+  double s = 0.0;
+#pragma unroll
+  for (int p = 0; p < 16; ++p) {
+    const int i = i0 + 4 * p;
+    const double v = i < nb && j < nb ? t.v[p] - (i == j ? 1.0 : 0.0) : 0.0;
+    s = fma(v, v, s);
+  }
+  s = wave_sum(s);
+  if (j == 0) red[i0] = s;
+  t.store(S.PJ);
+  __syncthreads();
+  const double eps = sqrt((red[0] + red[1]) + (red[2] + red[3]));
+  if (threadIdx.x == 0) dist[0] = eps;
+  v4d acc[4];
+  // element e of block a of this wavefront's strip
+  auto each = [&](auto f) __attribute__((always_inline)) {
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f(a, e, 16 * a + kq + 4 * e, 16 * w + li);
+  };
+  if (eps <= kSeriesTol) {
+    const int depth = series_depth(eps);
+    // U = Phi(W - I - T) in PI (W is zero outside d; so is U there)
+    auto phi = [&](bool first) __attribute__((always_inline)) {
+      each([&](int a, int e, int i, int c) {
+        const double id = i == c && i < nb ? 1.0 : 0.0;
+        const double m = S.PJ[i * kLd + c] - id - (first ? 0.0 : acc[a][e]);
+        S.PI[i * kLd + c] = c > i ? m : (c == i ? 0.5 * m : 0.0);
+      });
+      __syncthreads();
+    };
+    phi(true);
+    for (int q = 0; q < depth; ++q) {
+      strip_zero(acc);
+      strip_mul<true, 0>(acc, S.PI, S.PI, w, 1.0);
+      __syncthreads();
+      phi(false);
+    }
+    // X2 = I - U, then I - U X2
+    each([&](int, int, int i, int c) {
+      S.X[i * kLd + c] = (i == c ? 1.0 : 0.0) - S.PI[i * kLd + c];
+    });
+    __syncthreads();
+    for (int q = 0; q < depth; ++q) {
+      strip_zero(acc);
+      strip_mul<false, 2>(acc, S.PI, S.X, w, 1.0);
+      __syncthreads();
+      each([&](int a, int e, int i, int c) {
+        S.X[i * kLd + c] = c >= i ? (i == c ? 1.0 : 0.0) - acc[a][e] : 0.0;
+      });
+      __syncthreads();
+    }
+    // R2 = I + U
+    if (threadIdx.x < 64) S.PI[threadIdx.x * (kLd + 1)] += 1.0;
+  } else {
+    factor_diag(S.PJ, S.X, S, nb, d, 0, R2, X2, flag);
+    __syncthreads();
+    each([&](int, int, int i, int c) {
+      S.PI[i * kLd + c] = c >= i ? S.PJ[i * kLd + c] : 0.0;
+      if (c < i) S.X[i * kLd + c] = 0.0;
+    });
+  }
+  __syncthreads();
+  auto put = [&](double *__restrict__ out) __attribute__((always_inline)) {
+    each([&](int a, int e, int i, int c) {
+      if (i < nb && c < nb) out[i * d + c] = c >= i ? acc[a][e] : 0.0;
+    });
+  };
+  r1.store(S.PJ);
+  __syncthreads();
+  strip_zero(acc);
+  strip_mul<false, 2>(acc, S.PI, S.PJ, w, 1.0);
+  put(R);
+  __syncthreads();
+  x1.store(S.PJ);
+  __syncthreads();
+  strip_zero(acc);
+  strip_mul<false, 2>(acc, S.PJ, S.X, w, 1.0);
+  put(X);
 }
 
 // R = I + U, X = R^{-1} of W = I + E with ||E||_F <= kSeriesTol: U_0 =
@@ -840,6 +978,24 @@ int sketch_qr_impl(const double *C, int64_t m, int64_t d, double *R, double *Rin
   // pass 2: W = Qa^T Qa
   if ((rc = gram_of(Qa, Qb))) return rc;
   double dist2 = 0.0, dist3 = 0.0;
+  if (d <= 64) {
+    // (planned by what follows, whose scratch is larger)
+    if (run) {
+      k_later_small<<<1, kTh, 0, st>>>(W, d, R1, X1, R, Rinv, R2, X2, part, flag);
+      if ((rc = read_back(&dist2, part, sizeof(double), st))) return rc;
+      if (dist2 <= kLastTol) return 0;
+      if ((rc = times(Qa, X2, m, kTriB, Qb))) return rc;
+      if ((rc = gram_of(Qb, Qa))) return rc;
+      // so far R2 R1 = R and X1 X2 = Rinv, both replaced by the last pass's
+      PSK_HIP_TRY(hipMemcpyAsync(T, R, (size_t)d * d * sizeof(double), hipMemcpyDeviceToDevice,
+                                 st));
+      PSK_HIP_TRY(hipMemcpyAsync(B0, Rinv, (size_t)d * d * sizeof(double),
+                                 hipMemcpyDeviceToDevice, st));
+      k_later_small<<<1, kTh, 0, st>>>(W, d, T, B0, R, Rinv, R3, X3, part, flag);
+      PSK_HIP_TRY(hipGetLastError());
+      return 0;
+    }
+  }
   if ((rc = later_pass_chol(W, d, R2, X2, B0, B1, B2, part, flag, &dist2, ws, st)))
     return rc;
   ws.release(mk);

@@ -67,3 +67,23 @@ def test_second_or_third_pass(m, d, cond):
     k = np.linalg.cond(c)
     assert np.linalg.norm(r - ref) <= 50 * k * U64 * np.linalg.norm(ref)
     assert np.linalg.norm(ri @ r - np.eye(d)) <= 1e3 * k * d * U64
+
+
+@pytest.mark.parametrize("m,d", [(8, 1), (40, 2), (64, 17), (1024, 32), (300, 50), (4096, 63),
+                                 (512, 64)])
+@pytest.mark.parametrize("cond", [1.0, 1e2, 3e3, 1e5, 1e8])
+def test_later_passes_up_to_64_columns(m, d, cond):
+    """The passes after the first in one workgroup: by the series (no, one and
+    two steps), by the Cholesky factorization, and with a third pass.  The
+    bounds are those of test_second_or_third_pass."""
+    from paper_2203_02798_amd import api
+    print(f"sketch_qr m={m} d={d} cond={cond}", flush=True)
+    c, _, _ = synth.lsq_problem(m, d, cond, seed=5, noise=0.0)
+    r, ri = (t.cpu().numpy() for t in api.sketch_qr(to_device(c)))
+    assert np.linalg.norm(r.T @ r - c.T @ c) <= 1e-13 * np.linalg.norm(c.T @ c)
+    ref = np.linalg.qr(c, mode="r")
+    ref *= np.sign(np.diag(ref))[:, None]
+    k = np.linalg.cond(c)
+    assert not np.tril(r, -1).any() and not np.tril(ri, -1).any()
+    assert np.linalg.norm(r - ref) <= 50 * k * U64 * np.linalg.norm(ref)
+    assert np.linalg.norm(ri @ r - np.eye(d)) <= 1e3 * k * d * U64
