@@ -407,12 +407,14 @@ int sketch_cs(const psk_mat *A, int64_t r, uint64_t seed, void *SA, void *wsp,
   if (!SA) return fail(PSK_EINVAL, "SA is NULL");
   Arena plan;
   if ((rc = validate_csr(*A, plan, nullptr))) return rc;
-  if ((rc = do_sketch_cs(*A, r, seed, nullptr, plan, nullptr))) return rc;
+  auto work = [&](Arena &ws) { return do_sketch_cs(*A, r, seed, SA, ws, as_stream(stream)); };
+  if ((rc = plan_work(plan, ws_bytes, work))) return rc;
   if (!wsp || ws_bytes < plan.peak)
     return fail(PSK_ENOMEM, "workspace smaller than psk_workspace_size(PSK_OP_SKETCH_CS)");
   Arena ws = Arena::over(wsp, ws_bytes);
   if ((rc = validate_csr(*A, ws, as_stream(stream)))) return rc;
-  return do_sketch_cs(*A, r, seed, SA, ws, as_stream(stream));
+  ws.lean = plan.lean;
+  return work(ws);
 }
 
 int sketch_gcs(const psk_mat *A, int64_t m, int64_t r, uint64_t seed, int prec,
@@ -502,12 +504,14 @@ int leverage_gram(const psk_mat *A, double *theta, void *wsp, size_t ws_bytes, v
   if (!theta) return fail(PSK_EINVAL, "theta is NULL");
   Arena plan;
   if ((rc = validate_csr(*A, plan, nullptr))) return rc;
-  if ((rc = leverage_gram_impl(*A, nullptr, plan, nullptr))) return rc;
+  auto work = [&](Arena &ws) { return leverage_gram_impl(*A, theta, ws, as_stream(stream)); };
+  if ((rc = plan_work(plan, ws_bytes, work))) return rc;
   if (!wsp || ws_bytes < plan.peak)
     return fail(PSK_ENOMEM, "workspace smaller than psk_workspace_size(PSK_OP_LEVERAGE_GRAM)");
   Arena ws = Arena::over(wsp, ws_bytes);
   if ((rc = validate_csr(*A, ws, as_stream(stream)))) return rc;
-  return leverage_gram_impl(*A, theta, ws, as_stream(stream));
+  ws.lean = plan.lean;
+  return work(ws);
 }
 
 int lsq_gram(const psk_mat *A, const double *b, double *x, void *wsp, size_t ws_bytes,
@@ -517,12 +521,14 @@ int lsq_gram(const psk_mat *A, const double *b, double *x, void *wsp, size_t ws_
   if (!b || !x) return fail(PSK_EINVAL, "b and x must be non-NULL");
   Arena plan;
   if ((rc = validate_csr(*A, plan, nullptr))) return rc;
-  if ((rc = lsq_gram_impl(*A, nullptr, nullptr, plan, nullptr))) return rc;
+  auto work = [&](Arena &ws) { return lsq_gram_impl(*A, b, x, ws, as_stream(stream)); };
+  if ((rc = plan_work(plan, ws_bytes, work))) return rc;
   if (!wsp || ws_bytes < plan.peak)
     return fail(PSK_ENOMEM, "workspace smaller than psk_workspace_size(PSK_OP_LSQ_GRAM)");
   Arena ws = Arena::over(wsp, ws_bytes);
   if ((rc = validate_csr(*A, ws, as_stream(stream)))) return rc;
-  return lsq_gram_impl(*A, b, x, ws, as_stream(stream));
+  ws.lean = plan.lean;
+  return work(ws);
 }
 
 int lsq_sketch_solve(const psk_mat *A, const double *b, double *x, int64_t m, int64_t r,
@@ -618,15 +624,17 @@ int gram(double alpha, const psk_mat *A, double beta, void *C, void *wsp,
   if (!C) return fail(PSK_EINVAL, "C is NULL");
   Arena plan;
   if ((rc = validate_csr(*A, plan, nullptr))) return rc;
-  rc = A->format == PSK_DENSE ? gram_dense(alpha, *A, beta, nullptr, plan, nullptr)
-                              : gram_csr(alpha, *A, beta, nullptr, plan, nullptr);
-  if (rc) return rc;
+  auto work = [&](Arena &ws) {
+    return A->format == PSK_DENSE ? gram_dense(alpha, *A, beta, C, ws, as_stream(stream))
+                                  : gram_csr(alpha, *A, beta, C, ws, as_stream(stream));
+  };
+  if ((rc = plan_work(plan, ws_bytes, work))) return rc;
   if (ws_bytes < plan.peak || (plan.peak > 0 && !wsp))
     return fail(PSK_ENOMEM, "workspace smaller than psk_workspace_size(PSK_OP_GRAM)");
   Arena ws = Arena::over(wsp, ws_bytes);
   if ((rc = validate_csr(*A, ws, as_stream(stream)))) return rc;
-  return A->format == PSK_DENSE ? gram_dense(alpha, *A, beta, C, ws, as_stream(stream))
-                                : gram_csr(alpha, *A, beta, C, ws, as_stream(stream));
+  ws.lean = plan.lean;
+  return work(ws);
 }
 
 int rownorms_sq(double alpha, const psk_mat *A, const double *B, int64_t k,
@@ -637,17 +645,18 @@ int rownorms_sq(double alpha, const psk_mat *A, const double *B, int64_t k,
   if (!B || !x) return fail(PSK_EINVAL, "B and x must be non-NULL");
   Arena plan;
   if ((rc = validate_csr(*A, plan, nullptr))) return rc;
-  rc = A->format == PSK_DENSE
-           ? rownorms_dense(alpha, *A, nullptr, k, beta, nullptr, plan, nullptr)
-           : rownorms_csr(alpha, *A, nullptr, k, beta, nullptr, plan, nullptr);
-  if (rc) return rc;
+  auto work = [&](Arena &ws) {
+    return A->format == PSK_DENSE
+               ? rownorms_dense(alpha, *A, B, k, beta, x, ws, as_stream(stream))
+               : rownorms_csr(alpha, *A, B, k, beta, x, ws, as_stream(stream));
+  };
+  if ((rc = plan_work(plan, ws_bytes, work))) return rc;
   if (ws_bytes < plan.peak || (plan.peak > 0 && !wsp))
     return fail(PSK_ENOMEM, "workspace smaller than psk_workspace_size(PSK_OP_ROWNORMS)");
   Arena ws = Arena::over(wsp, ws_bytes);
   if ((rc = validate_csr(*A, ws, as_stream(stream)))) return rc;
-  return A->format == PSK_DENSE
-             ? rownorms_dense(alpha, *A, B, k, beta, x, ws, as_stream(stream))
-             : rownorms_csr(alpha, *A, B, k, beta, x, ws, as_stream(stream));
+  ws.lean = plan.lean;
+  return work(ws);
 }
 
 int psk_check(const psk_mat *A, int check_values, void *wsp, size_t ws_bytes, void *stream) {

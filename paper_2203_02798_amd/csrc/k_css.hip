@@ -446,7 +446,6 @@ int css_select_impl(const psk_mat &A, int64_t m, int64_t r, int64_t k, uint64_t 
   double *Bt = ws.take<double>((size_t)rows * d);
   double *na = ws.take<double>((size_t)d);
   double *nb = ws.take<double>((size_t)d);
-  double *L = ws.take<double>((size_t)kPanel * d);
   int *flag = ws.take<int>(4);  // [0]: non-finite sketch; [2], [3]: the pivot search's state
   const bool run = !ws.dry();
   if (run && !ws.ok()) return fail(PSK_ENOMEM, "workspace too small for css_select");
@@ -469,11 +468,12 @@ int css_select_impl(const psk_mat &A, int64_t m, int64_t r, int64_t k, uint64_t 
                          (double)k * (1.5 + (double)d * 1e-3);
   const double steps_us = (double)k * (5.0 + (double)rows * d * 16.0 / 4e6);
   const int64_t room = rows * d - d * d;
-  const bool search = k > 1 && gram_us < steps_us && room >= dgram_room(d);
+  const bool search =
+      k > 1 && gram_us < steps_us && room >= dgram_room(d) && room >= kPanel * d;
   int h[4] = {0, 0, 0, 1};
   if (search) {
     KTimer timer("pivots", st);
-    double *G = Bt;
+    double *G = Bt, *L = Bt + d * d;  // L where the partial sums of G were
     if ((rc = dgram(C, rows, d, G, Bt + d * d, room, st))) return rc;
     k_pivot_start<<<(unsigned)ceil_div(d, (int64_t)256), 256, 0, st>>>(G, d, na, flag + 2);
     const dim3 sg((unsigned)ceil_div(d, (int64_t)64), (unsigned)ceil_div(d, (int64_t)16));

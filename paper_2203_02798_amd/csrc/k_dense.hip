@@ -1096,7 +1096,7 @@ __global__ __launch_bounds__(64 * kGramGroups) void k_gram_reduce(
   C[e] = (TO)v;
 }
 
-GramPlan gram_plan(int64_t n, int64_t d, int wpt) {
+GramPlan gram_plan(int64_t n, int64_t d, int wpt, bool lean) {
   GramPlan p{};
   p.T = (int)ceil_div(d, (int64_t)64);
   p.nbt = (int)ceil_div(d - 64 * (int64_t)(p.T - 1), (int64_t)16);
@@ -1115,9 +1115,10 @@ GramPlan gram_plan(int64_t n, int64_t d, int wpt) {
                           std::max(0.5 * nbt * (nbt + 1.0), 2.0 * nbt)};
   double total = 0.0;
   for (int c = 0; c < 4; ++c) total += p.cnt[c] * cost[c];
-  // two wavefronts per SIMD in one round, at least two groups of rows each
+  // two wavefronts per SIMD in one round (a lean workspace: one), at least
+  // two groups of rows each
   const int64_t kRound = 4 * gram_prefetch(wpt) * wpt;
-  const double slots = 512.0 * kGramWaves / wpt;
+  const double slots = (lean ? 256.0 : 512.0) * kGramWaves / wpt;
   for (int c = 0; c < 4; ++c) {
     if (!p.cnt[c]) continue;
     int64_t s = (int64_t)(slots * cost[c] / total);
@@ -1138,7 +1139,7 @@ int gram_syrk_launch(double alpha, const psk_mat &Am, double beta, void *C, bool
                      Arena &ws, hipStream_t st) {
   const int64_t n = Am.n, d = Am.d;
   const int wpt = d <= 112 ? kGramWaves : 1;  // measured beside the kernel
-  const GramPlan pl = gram_plan(n, d, wpt);
+  const GramPlan pl = gram_plan(n, d, wpt, ws.lean);
   const int64_t items = pl.first[4];
   double *part = ws.take<double>((size_t)items * 4096);
   if (ws.dry()) return 0;

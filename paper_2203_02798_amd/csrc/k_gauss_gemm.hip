@@ -274,6 +274,8 @@ int gauss_gemm(int64_t m, int64_t r, int64_t d, uint64_t seed, int prec,
     max_splits = std::max(max_splits, r / (2 * m));
     max_splits = std::max(whole, std::min(max_splits, std::max(kchunks / 4, (int64_t)1)));
   }
+  // (lean: no more than one round of 256-column tiles would have, twice over)
+  if (ws.lean) max_splits = std::min(max_splits, 512 / (tiles_m * ceil_div(d, (int64_t)256)));
   if (splits > max_splits) splits = max_splits;
   if (splits < 1) splits = 1;
   const int64_t kper = ceil_div(kchunks, splits) * kBK;

@@ -1025,8 +1025,10 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
   B.y = ws.take<double>((size_t)d);
   B.vhat = ws.take<double>((size_t)d);
   B.st = ws.take<LsqrState>(1);
-  // max |R_ii|, min |R_ii|; precond_estimate's; the factorization's flag
-  double *ratio = ws.take<double>(3 + kPrecondEst);
+  // max |R_ii|, min |R_ii|, the factorization's flag; precond_estimate's (a
+  // lean workspace, never sharpened, has no room for those)
+  const size_t nratio = ws.lean ? 3 : 3 + kPrecondEst;
+  double *ratio = ws.take<double>(nratio);
   // the reduced-precision sketch's perturbation against the FP64 one, on
   // request: that sketch kept (Chat), the FP64 sketch and its factor
   const bool want_delta = own && o.want_delta != 0 && o.prec != PSK_PREC_F64;
@@ -1132,11 +1134,11 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
   double delta_est = (own && o.prec == PSK_PREC_F64) ? 0.0 : NAN;
   double hr[3 + kPrecondEst] = {1.0, 1.0};
   if (own) {
-    k_diag_ratio<<<1, 256, 0, st>>>(R, d, flag, ratio, ratio + 2 + kPrecondEst);
-    if (may_sharpen) precond_estimate(A, R, Rinv, B.vhat, ratio + 2, st);
-    if ((rc = read_back(hr, ratio, sizeof(hr), st))) return rc;
+    k_diag_ratio<<<1, 256, 0, st>>>(R, d, flag, ratio, ratio + 2);
+    if (may_sharpen) precond_estimate(A, R, Rinv, B.vhat, ratio + 3, st);
+    if ((rc = read_back(hr, ratio, nratio * sizeof(double), st))) return rc;
     if (want_delta && (rc = read_back(&delta_est, dl, sizeof(double), st))) return rc;
-    int hflag = (int)hr[2 + kPrecondEst];
+    int hflag = (int)hr[2];
     // A reduced-precision sketch only preconditions well while its relative
     // error (about 1e-5 for the BF16 GEMM) times cond(A) stays small; the
     // diagonal ratio of R is a cheap lower estimate of cond(A).
@@ -1156,8 +1158,8 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
       if ((rc = sketch_qr_impl(C, m, d, R, Rinv, ws, st, &flag))) return rc;
       ws.release(mk2);
       if (may_sharpen) {
-        precond_estimate(A, R, Rinv, B.vhat, ratio + 2, st);
-        if ((rc = read_back(hr, ratio, sizeof(hr), st))) return rc;
+        precond_estimate(A, R, Rinv, B.vhat, ratio + 3, st);
+        if ((rc = read_back(hr, ratio, nratio * sizeof(double), st))) return rc;
       }
       if ((rc = read_back(&hflag, flag, sizeof(int), st))) return rc;
       prec_used = PSK_PREC_F64;
@@ -1172,11 +1174,11 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
   int first = 0;  // iterations of the first group when sharpened
   if (may_sharpen && o.max_iter >= kSharpenMinIter) {
     if (!own) {
-      precond_estimate(A, nullptr, Rinv, B.vhat, ratio + 2, st);
-      if ((rc = read_back(hr, ratio, sizeof(hr), st))) return rc;
+      precond_estimate(A, nullptr, Rinv, B.vhat, ratio + 3, st);
+      if ((rc = read_back(hr, ratio, nratio * sizeof(double), st))) return rc;
     }
-    const double err = precond_error(hr + 2, d);
-    const double rsq = A.format == PSK_CSR ? precond_row_squares(hr + 2) : 0.0;
+    const double err = precond_error(hr + 3, d);
+    const double rsq = A.format == PSK_CSR ? precond_row_squares(hr + 3) : 0.0;
     if (err <= kPrecondMax && precond_pays(A, own ? m : 0, tol, rsq)) {
       double *P = ws.take<double>((size_t)d * d);
       const size_t mkp = ws.mark();

@@ -756,13 +756,31 @@ int cs_hash_export(int64_t row0, int64_t count, uint32_t r, uint64_t seed,
 
 namespace {
 
+// One bucket: the pairs as they come.
+template <class SRC>
+__global__ __launch_bounds__(256) void k_write_pairs(SRC src, int64_t n,
+                                                     const uint32_t *__restrict__ dn,
+                                                     uint32_t *__restrict__ k,
+                                                     uint32_t *__restrict__ v,
+                                                     uint32_t *__restrict__ ptr) {
+  n = keys_in_use(n, dn);
+  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (j == 0 && ptr) {
+    ptr[0] = 0u;
+    ptr[1] = (uint32_t)n;
+  }
+  if (j < n && k) src.get(j, k[j], v[j]);
+}
+
 // The sort of n pairs from src (dn: their count on the device, n at most)
 // by keys below r.  The first pass reads src and writes (k0, v0); later ones
 // go back and forth between (k0, v0) and (k1, v1), which are only needed then.
-int sort_passes(uint32_t r) {
+// A lean workspace keeps to 8-bit digits (a quarter of the counts).
+int sort_passes(uint32_t r, bool lean) {
   int bits = 0;
   while (bits < 32 && ((uint64_t)1 << bits) < (uint64_t)r) ++bits;
-  return bits > kDigitBits ? (bits + kDigitBits - 1) / kDigitBits : 1;
+  const int most = lean ? 8 : kDigitBits;
+  return bits > most ? (bits + most - 1) / most : 1;
 }
 
 template <class SRC>
@@ -771,7 +789,17 @@ int sort_run(SRC src, int64_t n, uint32_t r, uint32_t *k0, uint32_t *v0, uint32_
              uint32_t *ptr, const uint32_t *dn) {
   int bits = 0;
   while (bits < 32 && ((uint64_t)1 << bits) < (uint64_t)r) ++bits;
-  const int passes = sort_passes(r);
+  if (r == 1) {
+    if (ws.dry()) return 0;
+    if (!ws.ok()) return fail(PSK_ENOMEM, "workspace too small for a radix sort");
+    k_write_pairs<<<(unsigned)(n > 0 ? ceil_div(n, (int64_t)256) : 1), 256, 0, st>>>(
+        src, n, dn, k0, v0, ptr);
+    PSK_HIP_TRY(hipGetLastError());
+    *skeys = k0;
+    *svals = v0;
+    return 0;
+  }
+  const int passes = sort_passes(r, ws.lean);
   const int nbits = (bits + passes - 1) / passes;  // equal digits: fewer counts to scan
   const int D = 1 << nbits;
   const int64_t ntiles = ceil_div(n, kSortTile);
@@ -812,10 +840,16 @@ int sort_run(SRC src, int64_t n, uint32_t r, uint32_t *k0, uint32_t *v0, uint32_
 int sort_pairs(uint32_t *keys, uint32_t *vals, int64_t n, uint32_t r, Arena &ws,
                hipStream_t st, uint32_t **skeys, uint32_t **svals, uint32_t *ptr,
                const uint32_t *dn) {
-  uint32_t *k0 = ws.take<uint32_t>(n);
-  uint32_t *v0 = ws.take<uint32_t>(n);
-  return sort_run(StoredPairs{keys, vals}, n, r, k0, v0, keys, vals, ws, st, skeys, svals, ptr,
-                  dn);
+  // one bucket: the pairs stay where they are
+  uint32_t *k0 = r > 1 ? ws.take<uint32_t>(n) : nullptr;
+  uint32_t *v0 = r > 1 ? ws.take<uint32_t>(n) : nullptr;
+  const int rc =
+      sort_run(StoredPairs{keys, vals}, n, r, k0, v0, keys, vals, ws, st, skeys, svals, ptr, dn);
+  if (r == 1 && !rc) {
+    *skeys = keys;
+    *svals = vals;
+  }
+  return rc;
 }
 
 int osnap_hash_export(int64_t row0, int64_t count, uint32_t s, uint32_t r, uint64_t seed,
@@ -837,7 +871,7 @@ static int bin_pairs(const psk_mat &A, uint32_t s, uint32_t r, uint64_t seed, Ar
   const int64_t n = A.n;
   const int64_t pairs = n * (int64_t)s;
   const bool compact = A.format == PSK_CSR;
-  const bool two = sort_passes(r) > 1;
+  const bool two = sort_passes(r, ws.lean) > 1;
   uint32_t *k0 = ws.take<uint32_t>(pairs);
   uint32_t *v0 = ws.take<uint32_t>(pairs);
   uint32_t *k1 = two ? ws.take<uint32_t>(pairs) : nullptr;
