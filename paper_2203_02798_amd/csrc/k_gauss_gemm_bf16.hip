@@ -15,18 +15,27 @@
 // contiguous bytes at Lq[kc][q][n][0..7]; a B fragment of the 16x16x32
 // instruction (lane l: column l%16, buckets 8(l/16)..+7) is then one 16-byte
 // load, and the 16 columns of one quad are 256 contiguous bytes (no LDS bank
-// conflicts).  Columns are padded to a multiple of 512 with zeros.
+// conflicts).  Columns are padded to a multiple of the tile with zeros.
 //
-// Tiling: 512 threads = 8 wavefronts; workgroup tile 128 rows x 512 columns,
-// so every Gaussian value is drawn once per 512 columns.  A chunk is 32
-// buckets: the workgroup draws the chunk's 128 x 32 block of G (FP32
-// Box-Muller, rounded to bfloat16) into LDS once, and the limb chunk of S*A
-// (2 x 32 KiB) is copied into double-buffered LDS by buffer loads one chunk
-// ahead.  Each wavefront owns 64 rows x 128 columns (4 x 8 blocks of 16 x
-// 16, 128 FP32 accumulators per lane): it reads 4 A fragments and 16 B
-// fragments per chunk and issues 64 matrix instructions, so every B
-// fragment read from LDS feeds four of them (LDS bandwidth, not the matrix
-// cores, bounded the one-row-block layout).
+// Tiling: 512 threads = 8 wavefronts.  A chunk is 32 buckets: the workgroup
+// draws the chunk's rows x 32 block of G (FP32 Box-Muller, rounded to
+// bfloat16) into LDS once, and the limb chunk of S*A is copied into
+// double-buffered LDS by buffer loads one chunk ahead.
+//   d > 256: 128 rows x 512 columns, so that every Gaussian value is drawn once per
+//   512 columns.  Each wavefront owns 64 rows x 128 columns (4 x 8 blocks of
+//   16 x 16, 128 FP32 accumulators per lane): it reads 4 A fragments and 16
+//   B fragments per chunk and issues 64 matrix instructions, so every B
+//   fragment read from LDS feeds four of them.
+//   d <= 256: 64 rows x 256 columns (d <= 128: 128), a wavefront owning 64 rows x 32 (16)
+//   columns.  Half the rows and half the columns leave room for two (three)
+//   workgroups on a CU, one drawing while the other multiplies, and finer
+//   pieces for the last round; columns past d are neither copied nor
+//   multiplied.  Columns are padded to the tile.
+// What bounds it: the vector instructions that draw G, some 45 for a value
+// and lane, where the phases overlap.  With 512-column tiles for every d, one
+// workgroup a CU: m = 804, r = 40,000, d = 201 246 us (266 workgroups on 256
+// CUs), now 105; m = 1024, r = 16,384, d = 128 122 us (128 workgroups), now 62.
+// The K splits, and so the order of every FP32 sum, do not depend on the tile.
 #include "internal.hpp"
 
 namespace psk {
@@ -38,19 +47,27 @@ typedef __attribute__((address_space(3))) void *lds_ptr_t;
 
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
-constexpr int kBM = 16 * kWaves;  // 128
-constexpr int kBN = 512;
+constexpr int kBM = 16 * kWaves;  // 128: the rows and
+constexpr int kBN = 512;          // columns that the K splits are counted by
 constexpr int kBK = 32;
-constexpr int kQuadBytes = kBN * 8 * 2;         // 8 KiB: one quad of one chunk-tile
-constexpr int kLimbBytes = 4 * kQuadBytes;      // 32 KiB per limb per chunk
-constexpr int kChunkBytes = 2 * kLimbBytes;     // 64 KiB (hi + lo)
-constexpr int kRB = 4;          // 16-row blocks per wavefront (64 rows)
-constexpr int kCB = 8;          // 16-column blocks per wavefront (128 columns)
-constexpr int kWR = kBM / 16 / kRB;   // wavefront rows of the tile
-constexpr int kWC = kWaves / kWR;     // wavefront columns of the tile
-static_assert(kWC * kCB * 16 == kBN, "wavefront tiles cover the block");
 constexpr int kGRow = 80;       // LDS row stride of the Gaussian tile (64 B + pad)
-constexpr int kGBytes = kBM * kGRow;  // 10 KiB per Gaussian tile
+
+// A workgroup's tile: RB x CB blocks of 16 x 16 per wavefront, WR x WC wavefronts.
+template <int RB_, int CB_, int WR_>
+struct Tile {
+  static constexpr int RB = RB_, CB = CB_, WR = WR_, WC = kWaves / WR_;
+  static constexpr int BM = 16 * RB * WR, BN = 16 * CB * WC;
+  static constexpr int kQuadBytes = BN * 8 * 2;      // one quad of one chunk-tile
+  static constexpr int kLimbBytes = 4 * kQuadBytes;  // a limb of a chunk
+  static constexpr int kChunkBytes = 2 * kLimbBytes; // hi + lo
+  static constexpr int kGBytes = BM * kGRow;         // one Gaussian tile
+  static constexpr int kLds = 2 * kChunkBytes + 2 * kGBytes;
+  static constexpr int kPerCu = kLds <= 50 * 1024 ? 3 : kLds <= 80 * 1024 ? 2 : 1;
+};
+typedef Tile<4, 8, 2> Tile512;  // 128 x 512
+typedef Tile<4, 2, 1> Tile256;  // 64 x 256
+typedef Tile<4, 1, 1> Tile128;  // 64 x 128
+static_assert(Tile512::BM == kBM && Tile512::BN == kBN, "the widest tile");
 
 __device__ __forceinline__ uint16_t bf16_bits(float x) {
   return __builtin_bit_cast(uint16_t, (__bf16)x);  // v_cvt_pk_bf16_f32, RNE
@@ -162,11 +179,15 @@ __global__ __launch_bounds__(512) void k_scatter_csr_limbs(
   }
 }
 
-__global__ __launch_bounds__(kThreads) void k_gauss_gemm_bf16(
+template <class TL>
+__global__ __launch_bounds__(kThreads, 2 * TL::kPerCu) void k_gauss_gemm_bf16(
     int64_t m, int64_t d, int64_t npad, uint64_t seed, const uint16_t *__restrict__ hi,
     const uint16_t *__restrict__ lo, int tiles_m, int tiles_n, int64_t kchunks,
     int64_t cper, float *__restrict__ out /* [splits][m][d] */) {
-  __shared__ __align__(16) unsigned char smem[2 * kChunkBytes + 2 * kGBytes];
+  constexpr int kRB = TL::RB, kCB = TL::CB, kWC = TL::WC;
+  constexpr int kQuadBytes = TL::kQuadBytes, kLimbBytes = TL::kLimbBytes;
+  constexpr int kChunkBytes = TL::kChunkBytes, kGBytes = TL::kGBytes;
+  __shared__ __align__(16) unsigned char smem[TL::kLds];
 
   const int64_t nblk = (int64_t)gridDim.x;
   int64_t lin = blockIdx.x;
@@ -175,8 +196,8 @@ __global__ __launch_bounds__(kThreads) void k_gauss_gemm_bf16(
   const int64_t rest = lin / tiles_m;
   const int nt = (int)(rest % tiles_n);
   const int ks = (int)(rest / tiles_n);
-  const int64_t m0 = (int64_t)mt * kBM;
-  const int64_t n0 = (int64_t)nt * kBN;
+  const int64_t m0 = (int64_t)mt * TL::BM;
+  const int64_t n0 = (int64_t)nt * TL::BN;
   const int64_t cb = (int64_t)ks * cper;
   int64_t ce = cb + cper;
   if (ce > kchunks) ce = kchunks;
@@ -203,15 +224,15 @@ __global__ __launch_bounds__(kThreads) void k_gauss_gemm_bf16(
       (void *)(hi + cb * chunk_stride), (short)0, nbytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc(
       (void *)(lo + cb * chunk_stride), (short)0, nbytes, 0x00020000);
-  // a chunk tile is 4 quads x 8 KiB per limb; wave w copies 1 KiB pieces
-  // w, w+8, ... (8 per limb per chunk: 64 KiB / 8 waves / 1 KiB)
+  // a chunk tile is 4 quads per limb; wave w copies 1 KiB pieces w, w+8, ...
   auto copy_chunk = [&](int64_t crel, int buf) {
     unsigned char *base = smem + buf * kChunkBytes;
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      const int piece = wave + kWaves * p;      // 0..31 within one limb
-      const int quad = piece >> 3;              // 8 pieces of 1 KiB per quad
-      const int off_in_quad = (piece & 7) * 1024;
+    for (int p = 0; p < kLimbBytes / 1024 / kWaves; ++p) {
+      constexpr int kPieces = kQuadBytes / 1024;  // of a quad
+      const int piece = wave + kWaves * p;
+      const int quad = piece / kPieces;
+      const int off_in_quad = (piece % kPieces) * 1024;
       const int gsrc = (int)((crel * chunk_stride + (int64_t)quad * npad * 8 + n0 * 8) * 2) +
                        off_in_quad + lane * 16;
       const int ldst = quad * kQuadBytes + off_in_quad;
@@ -221,23 +242,25 @@ __global__ __launch_bounds__(kThreads) void k_gauss_gemm_bf16(
     }
   };
 
-  // The Gaussian block of a chunk (128 rows x 32 buckets) is drawn once per
-  // workgroup: thread t takes row t / 4 and buckets 8 (t % 4) .. +7 (two
-  // Philox blocks), rounds them to bfloat16 and stores 16 bytes in the LDS
-  // G tile (row stride kGRow bytes, padded against bank conflicts), from
-  // which the wavefronts read their A fragments.
-  const int grow = tid >> 2, goct = tid & 3;
+  // The Gaussian block of a chunk (BM rows x 32 buckets) is drawn once per
+  // workgroup: a thread takes kBlk Philox blocks in a row (4 buckets each) of
+  // one row, rounds them to bfloat16 and stores them in the LDS G tile (row
+  // stride kGRow bytes, padded against bank conflicts), from which the
+  // wavefronts read their A fragments.
+  constexpr int kBlk = TL::BM * 8 / kThreads;
+  typedef __bf16 vbf __attribute__((ext_vector_type(4 * kBlk)));
+  const int grow = tid / (8 / kBlk), gpart = tid % (8 / kBlk);
   const uint32_t row_g = (uint32_t)(m0 + grow);
   auto gen_g = [&](int64_t c_abs, int gbuf) {
-    float z[8];  // bfloat16 values (each the rounding of the FP64 normal)
-    const uint64_t qb = (uint64_t)c_abs * 8u + 2u * (uint64_t)goct;
-    gauss4_bf16(qb, row_g, seed, z);
-    gauss4_bf16(qb + 1, row_g, seed, z + 4);
-    v8bf a;
+    float z[4 * kBlk];  // bfloat16 values (each the rounding of the FP64 normal)
+    const uint64_t qb = (uint64_t)c_abs * 8u + (uint64_t)(kBlk * gpart);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) a[e] = (__bf16)z[e];
-    *reinterpret_cast<v8bf *>(smem + 2 * kChunkBytes + gbuf * kGBytes + grow * kGRow +
-                              goct * 16) = a;
+    for (int k = 0; k < kBlk; ++k) gauss4_bf16(qb + k, row_g, seed, z + 4 * k);
+    vbf a;
+#pragma unroll
+    for (int e = 0; e < 4 * kBlk; ++e) a[e] = (__bf16)z[e];
+    *reinterpret_cast<vbf *>(smem + 2 * kChunkBytes + gbuf * kGBytes + grow * kGRow +
+                             gpart * 8 * kBlk) = a;
   };
 
   if (nch > 0) {
@@ -307,26 +330,27 @@ namespace {
 
 // Tiling, K split and workspace of one BF16 product (limbs, FP32 partials).
 struct Bf16Plan {
-  int tiles_m, tiles_n;
-  int64_t npad, kchunks, tiles, splits, cper;
+  int bn, tiles_m, tiles_n;  // columns of a workgroup's tile; tiles
+  int64_t npad, kchunks, splits, cper;
   uint16_t *hi, *lo;
   float *part;
 };
 
 int bf16_plan(int64_t m, int64_t r, int64_t d, Arena &ws, Bf16Plan &P) {
-  P.tiles_m = (int)ceil_div(m, kBM);
-  P.tiles_n = (int)ceil_div(d, kBN);
-  P.npad = (int64_t)P.tiles_n * kBN;
   P.kchunks = ceil_div(r, kBK);
-  P.tiles = (int64_t)P.tiles_m * P.tiles_n;
-  int64_t splits = ceil_div(512, P.tiles);
+  const int64_t wide = ceil_div(d, kBN) * kBN;
+  int64_t splits = ceil_div(512, ceil_div(m, kBM) * (wide / kBN));
   const int64_t max_splits = P.kchunks / 32 > 0 ? P.kchunks / 32 : 1;
   if (splits > max_splits) splits = max_splits;
   if (splits < 1) splits = 1;
   P.cper = ceil_div(P.kchunks, splits);
   P.splits = ceil_div(P.kchunks, P.cper);
+  P.bn = d <= 128 ? 128 : d <= 256 ? 256 : kBN;
+  P.tiles_m = (int)ceil_div(m, P.bn == kBN ? kBM : 64);
+  P.tiles_n = (int)ceil_div(d, (int64_t)P.bn);
+  P.npad = (int64_t)P.tiles_n * P.bn;
   const int64_t limb_elems = P.kchunks * 4 * P.npad * 8;
-  if ((P.cper + 1) * 4 * P.npad * 8 * 2 + 65536 >= ((int64_t)1 << 31))
+  if ((P.cper + 1) * 4 * wide * 8 * 2 + 65536 >= ((int64_t)1 << 31))
     return fail(PSK_EUNSUPPORTED, "BF16 Gaussian GEMM: K slice too large for one descriptor");
   P.hi = ws.take<uint16_t>((size_t)limb_elems);
   P.lo = ws.take<uint16_t>((size_t)limb_elems);
@@ -341,8 +365,14 @@ int bf16_run(const Bf16Plan &P, int64_t m, int64_t d, uint64_t seed, double *C,
              hipStream_t st) {
   {
     KTimer t("gauss_gemm", st);
-    k_gauss_gemm_bf16<<<(unsigned)(P.tiles * P.splits), kThreads, 0, st>>>(
-        m, d, P.npad, seed, P.hi, P.lo, P.tiles_m, P.tiles_n, P.kchunks, P.cper, P.part);
+    auto run = [&](auto tile) {
+      k_gauss_gemm_bf16<decltype(tile)>
+          <<<(unsigned)((int64_t)P.tiles_m * P.tiles_n * P.splits), kThreads, 0, st>>>(
+              m, d, P.npad, seed, P.hi, P.lo, P.tiles_m, P.tiles_n, P.kchunks, P.cper, P.part);
+    };
+    if (P.bn == 128) run(Tile128{});
+    else if (P.bn == 256) run(Tile256{});
+    else run(Tile512{});
   }
   {
     KTimer t("gemm_reduce", st);
@@ -354,7 +384,7 @@ int bf16_run(const Bf16Plan &P, int64_t m, int64_t d, uint64_t seed, double *C,
   return 0;
 }
 
-// FP64 bucket sums of 8 buckets over the padded columns
+// FP64 bucket sums of 8 buckets over the widest tile's columns
 size_t csr_limbs_lds(const psk_mat &A, int64_t d) {
   (void)A;
   return (size_t)8 * ceil_div(d, kBN) * kBN * sizeof(double);
@@ -395,7 +425,7 @@ int gauss_gemm_bf16_csr(int64_t m, int64_t r, const psk_mat &A, const uint32_t *
   {
     KTimer t("cs_scatter_limbs", st);
     const unsigned quads = (unsigned)(P.kchunks * 4);
-    const size_t lds = csr_limbs_lds(A, A.d);
+    const size_t lds = (size_t)8 * P.npad * sizeof(double);
     if (A.dtype == PSK_F64)
       k_scatter_csr_limbs<double><<<quads, 512, lds, st>>>(
           (const double *)A.values, A.indptr, A.indices, P.npad, r, perm, bptr, P.hi, P.lo);
