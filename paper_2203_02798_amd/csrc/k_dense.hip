@@ -335,18 +335,18 @@ int gemm_launch(int64_t M, int64_t N, int64_t K, const double *A, int64_t lda, c
   return 0;
 }
 
-// KW consecutive elements of a row in 16-byte loads that need no more than
-// the element's own alignment, as loaded (raw, in the dtype of A: widened
-// when used, so the loads stay in flight meanwhile).
+// Groups of four consecutive elements of a row, 16 apart, in 16-byte loads
+// that need no more than the element's own alignment, as loaded (raw, in the
+// dtype of A: widened when used, so the loads stay in flight meanwhile).
 template <typename TA, int KW>
 __device__ __forceinline__ void row_load(const TA *p, TA (&x)[KW]) {
   constexpr int VE = 16 / sizeof(TA);
   typedef TA vec __attribute__((ext_vector_type(VE), aligned(sizeof(TA))));
 #pragma unroll
-  for (int q = 0; q < KW / VE; ++q) {
-    const vec v = *reinterpret_cast<const vec *>(p + VE * q);
+  for (int s = 0; s < KW; s += VE) {
+    const vec v = *reinterpret_cast<const vec *>(p + 16 * (s / 4) + s % 4);
 #pragma unroll
-    for (int e = 0; e < VE; ++e) x[VE * q + e] = v[e];
+    for (int e = 0; e < VE; ++e) x[s + e] = v[e];
   }
 }
 
@@ -375,23 +375,23 @@ __device__ __forceinline__ void row_load(const TA *p, TA (&x)[KW]) {
 // wavefronts per SIMD: with three (168 registers each) the paired form spilled
 // 30 to 130 of them (FP64 1e6 x 256: 1815 us at three, 1263 at two).
 // Measured in us, before (masked element loads, three wavefronts, single
-// tiles unpaired) and now: FP64 20,000 x 50 36 -> 19, 300,007 x 97 253 ->
-// 140, 1e6 x 128 738 -> 439, 1e6 x 256 2696 -> 1226, 200,000 x 500 3175 ->
-// 1052; FP32 1e6 x 128 383 -> 357, 4e6 x 256 4769 -> 4588 (2.9e11 flops: 62
+// tiles unpaired) and now: FP64 20,000 x 50 36 -> 18, 300,007 x 97 253 ->
+// 134, 1e6 x 128 738 -> 427, 1e6 x 256 2696 -> 1214, 200,000 x 500 3175 ->
+// 1032; FP32 1e6 x 128 383 -> 349, 4e6 x 256 4769 -> 4563 (2.9e11 flops: 62
 // TF/s of the 76 that bare products reach).
-// Inside a K chunk of 4 kBresKW columns, lane (li, kq) feeds column
-// k0 + kBresKW kq + s of A at step s, and B row k0 + kBresKW kq + s: the same
-// permutation of the chunk on both operands, so one lane reads kBresKW
-// consecutive elements of its row.
+// Inside a K chunk of 32 columns, lane (li, kq) feeds column k0 + 16 (s / 4) +
+// 4 kq + s % 4 of A at step s = 0 .. 7, and that row of B: the same permutation
+// of the chunk on both operands.  A lane reads four consecutive elements at a
+// time and the four lanes of a row 16 in a row, so a load touches a cache line
+// a row, and the chunk's first 16 rows are steps 0 .. 3 (with eight
+// consecutive elements a lane it touched four lines, and a diagonal chunk
+// needed lane halves swapped: 300,007 x 97 140 us, now 134; 200,000 x 256 in
+// FP64 269, now 260).
 // The diagonal 32 x 32 block of a triangular B is half zeros.  When the
 // staging finds the lower-left 16 x 16 quarter of a tile's diagonal block
 // zero (its rows 16 .. 31 in the tile's first 16 columns) and that block is
-// the tile's last chunk (and inside the d columns), the chunk is taken in
-// another order: one swap of lane halves per pair of elements (lanes
-// kq = 0, 1 exchange element s + 4 for element s of kq = 2, 3) gives steps
-// 0 .. 3 the chunk's first 16 rows and steps 4 .. 7 its last 16, row
-// 16 h + 8 (kq & 1) + 4 (kq >> 1) + s at step 4 h + s, so the products of
-// the tile's first column block skip steps 4 .. 7 there.
+// the tile's last chunk (and inside the d columns), the products of the tile's
+// first column block skip steps 4 .. 7, which are that chunk's last 16 rows.
 // part[slot * n + row] = the row's squared norm over the slot's columns.
 // Workgroups form row groups of tn (one per slot) that sit on one XCD
 // (linear ids equal mod 8) and walk the same rows, so A is fetched into that
@@ -530,19 +530,21 @@ __global__ __launch_bounds__(kBresThreads) void k_rownorm_bres(
       if (!RAG || (c + 1) * CK <= d) {
         load_whole(row, c, a);
       } else {
-        const int64_t left = d - (c * CK + KW * kq);  // this lane's columns inside d
+        const int64_t left = d - (c * CK + 4 * kq);  // this lane's columns inside d
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-          for (int s = 0; s < KW; ++s)
-            a[mb][s] = row[mb][s < left ? c * CK + s : -(int64_t)(KW * kq)];
+          for (int s = 0; s < KW; ++s) {
+            const int k = 16 * (s / 4) + s % 4;
+            a[mb][s] = row[mb][k < left ? c * CK + k : -(int64_t)(4 * kq)];
+          }
       }
     };
     auto rows_of = [&](int64_t t, const TA *(&row)[MB]) __attribute__((always_inline)) {
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) {
         const int64_t r = t * kBresRows + mb * 16 + li;
-        row[mb] = A + (r < n ? r : 0) * ld + KW * kq;
+        row[mb] = A + (r < n ? r : 0) * ld + 4 * kq;
       }
     };
     // a0: the chunk taken next, loading since the one before it was multiplied
@@ -561,46 +563,20 @@ __global__ __launch_bounds__(kBresThreads) void k_rownorm_bres(
         for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = v4d{0.0, 0.0, 0.0, 0.0};
       using D0 = std::integral_constant<int, 0>;
       // one K chunk for the blocks of the tiles in HM (bit 0: first tile,
-      // bit 1: second tile); DG 1 / 2: a diagonal chunk in the swapped order,
-      // the first column block of the first / second tile skipping steps 4 .. 7
+      // bit 1: second tile); DG 1 / 2: a diagonal chunk, the first
+      // column block of the first / second tile skipping steps 4 .. 7
       auto step = [&](auto hm, auto dg, int64_t c, const RawChunk &raw)
                       __attribute__((always_inline)) {
         constexpr int HM = decltype(hm)::value;
         constexpr int DG = decltype(dg)::value;
         double a[MB][KW];
-        if constexpr (DG == 0) {
 #pragma unroll
-          for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int s = 0; s < KW; ++s) a[mb][s] = (double)raw[mb][s];
-        } else {
-          static_assert(KW == 8, "the swap pairs elements s and s + 4");
-#pragma unroll
-          for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-              const TA x = raw[mb][s], y = raw[mb][s + 4];
-              if constexpr (sizeof(TA) == 4) {
-                const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x),
-                                                                __float_as_uint(y), false, false);
-                a[mb][s] = (double)__uint_as_float(r[0]);
-                a[mb][4 + s] = (double)__uint_as_float(r[1]);
-              } else {
-                const uint64_t xb = (uint64_t)__double_as_longlong(x);
-                const uint64_t yb = (uint64_t)__double_as_longlong(y);
-                const auto rl = __builtin_amdgcn_permlane32_swap((uint32_t)xb, (uint32_t)yb, false,
-                                                                 false);
-                const auto rh = __builtin_amdgcn_permlane32_swap(
-                    (uint32_t)(xb >> 32), (uint32_t)(yb >> 32), false, false);
-                a[mb][s] = __longlong_as_double((long long)(((uint64_t)rh[0] << 32) | rl[0]));
-                a[mb][4 + s] = __longlong_as_double((long long)(((uint64_t)rh[1] << 32) | rl[1]));
-              }
-            }
-        }
+          for (int s = 0; s < KW; ++s) a[mb][s] = (double)raw[mb][s];
 #pragma unroll
         for (int s = 0; s < KW; ++s) {
-          const int64_t kr = DG == 0 ? c * CK + KW * kq + s
-                                     : c * CK + 16 * (s / 4) + 8 * (kq & 1) + 4 * (kq >> 1) + s % 4;
+          const int64_t kr = c * CK + 16 * (s / 4) + 4 * kq + s % 4;
           const double *brow = Bs + kr * LDB + li;
           auto on = [&](int nb) {
             return ((HM >> (nb / NBH)) & 1) && !(DG && s >= 4 && nb == (DG - 1) * NBH);
@@ -635,11 +611,12 @@ __global__ __launch_bounds__(kBresThreads) void k_rownorm_bres(
           if (!RAG || dg) {
             step(hm, DGT{}, ce, a0);
           } else {
-            const int64_t left = d - (ce * CK + KW * kq);
+            const int64_t left = d - (ce * CK + 4 * kq);
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-              for (int s = 0; s < KW; ++s) a0[mb][s] = s < left ? a0[mb][s] : (TA)0;
+              for (int s = 0; s < KW; ++s)
+                a0[mb][s] = 16 * (s / 4) + s % 4 < left ? a0[mb][s] : (TA)0;
             step(hm, D0{}, ce, a0);
           }
 #pragma unroll
