@@ -802,18 +802,23 @@ int rownorm_launch(const psk_mat &Am, const double *B, int64_t k, double alpha,
 // products use them (without it they moved between the two register files on
 // every step).
 // Past that it waits for its rows in the vector L1 (FP64 1e6 x 256: 55 TF/s
-// whatever the instruction count; FP32, half the bytes: 65).
+// whatever the instruction count, before the wavefronts kept step; FP32, half
+// the bytes: 65).
 // Two arrangements.  WPT = 4, d <= 112: as above, a partial per workgroup;
 // narrow products are short of work, and the fewer partials matter most.
 // WPT = 1, wider: every wavefront has a tile and a slab of its own and
 // writes its own partial, so that the workgroup's wavefronts, mostly tiles of
-// one slab, find each other's rows in the L1.  Measured in us, before / one
-// wavefront / four: FP64 300,000 x 64: 91 / 55 / 48, 300,007 x 97: 162 / 116
-// / 97, 1e6 x 128: 456 / 416 / 547, 1e6 x 256: 1290 / 1266 / 1728; FP32
-// 1e6 x 128: 390 / 306 / 309, 1e6 x 256: 1255 / 1076 / 1104.  Before, the
-// loads were masked element by element, the accumulators moved every step
-// and a small A was cut into 2048 partials whatever its size (20,000 x 50:
-// 34 us with its reduction, now 21; 20,000 x 256: 111, now 45).
+// one slab, find each other's rows in the L1; a barrier every group of rows
+// keeps the off-diagonal ones in step, without which they drift apart and
+// find nothing (us, without / with: FP64 1e6 x 256 1267 / 1190, 200,000 x 500
+// 913 / 865; FP32 1e6 x 256 1076 / 1025, 300,000 x 200 302 / 274).  Measured
+// in us, before / one wavefront, out of step / four: FP64 300,000 x 64: 91 /
+// 55 / 48, 300,007 x 97: 162 / 116 / 97, 1e6 x 128: 456 / 416 / 547, 1e6 x
+// 256: 1290 / 1266 / 1728; FP32 1e6 x 128: 390 / 306 / 309, 1e6 x 256: 1255 /
+// 1076 / 1104.  Before, the loads were masked element by element, the
+// accumulators moved every step and a small A was cut into 2048 partials
+// whatever its size (20,000 x 50: 34 us with its reduction, now 21; 20,000 x
+// 256: 111, now 46).
 // Work items: the classes of tiles (off-diagonal, off-diagonal in the last
 // tile column, diagonal, last diagonal) take 16, 4 NBT, 10 and
 // NBT (NBT + 1) / 2 block products a row step, and each class gets slabs in
@@ -859,7 +864,8 @@ __device__ __forceinline__ int gram_class(const GramPlan &p, int I, int J, int &
 template <typename TA, int WPT, bool DG, bool CLAMP, int NI, int NJ>
 __device__ __forceinline__ void gram_rows(const TA *__restrict__ A, int64_t ld, int64_t d,
                                           int64_t k0, int64_t k1, int wave, int I, int J,
-                                          v4d (&acc)[4][4]) {
+                                          int64_t stepped, v4d (&acc)[4][4]) {
+  constexpr bool kStepped = WPT == 1;
   constexpr int PF = gram_prefetch(WPT);
   const int lane = threadIdx.x & 63;
   const int li = lane & 15, kq = lane >> 4;
@@ -916,8 +922,13 @@ __device__ __forceinline__ void gram_rows(const TA *__restrict__ A, int64_t ld, 
         mul(ci, cj);
         fetch(p, next + 4 * p);
       }
+      if (kStepped && stepped) __builtin_amdgcn_s_barrier();
     }
   }
+  // (a shorter slab waits out its fellows' groups: every wavefront meets the
+  // barrier `stepped` times)
+  if (kStepped)
+    for (int64_t g = groups; g < stepped; ++g) __builtin_amdgcn_s_barrier();
   if (wave) return;
   // the rest (fewer than 16 rows, at the end of A only): rows past k1 as zero
   for (int64_t k = k0 + groups * kGroup; k < k1; k += 4) {
@@ -970,7 +981,18 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void k_gram_syrk(const TA *__re
 #pragma unroll
     for (int b = 0; b < 4; ++b) acc[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
   const int wt = WPT == 1 ? 0 : wave;  // wavefront of the item
-#define PSK_GR(DG, CL, NI, NJ) gram_rows<TA, WPT, DG, CL, NI, NJ>(A, ld, d, k0, k1, wt, I, J, acc)
+  // The groups that the workgroup's wavefronts take in step, 0: none.  In step
+  // where all four are tiles of one off-diagonal class, so that a step costs
+  // them the same, and three or more of those share a slab: the first one's
+  // slab is the longest.
+  int64_t stepped = 0;
+  const int64_t g0 = g - wave;
+  if (WPT == 1 && cls < 2 && g0 >= pl.first[cls] && g0 + kGramWaves <= pl.first[cls + 1] &&
+      pl.cnt[cls] >= 3) {
+    const int64_t r0 = (g0 - pl.first[cls]) / pl.cnt[cls] * pl.rows[cls];
+    stepped = (n - r0 < pl.rows[cls] ? n - r0 : pl.rows[cls]) / (4 * gram_prefetch(1));
+  }
+#define PSK_GR(DG, CL, NI, NJ) gram_rows<TA, WPT, DG, CL, NI, NJ>(A, ld, d, k0, k1, wt, I, J, stepped, acc)
   if (cls == 0) PSK_GR(false, false, 4, 4);
   else if (cls == 2) PSK_GR(true, false, 4, 4);
   else if (cls == 1) {
