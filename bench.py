@@ -63,15 +63,15 @@ HEAD = dict(n=4_000_000, d=256, r=65536, m=1024, smin=1e-6)
 PMC_TRAFFIC = {
     "k_gram_syrk": {
         "source": "paper_2203_02798_amd/csrc/k_dense.hip",
-        "sha256_prefix": "be36c3e0e668d061",
-        "fetch_kib": 4068896.1, "write_kib": 69821.0,
+        "sha256_prefix": "b63e300e92ca95d7",
+        "fetch_kib": 4577120.2, "write_kib": 65280.0,
         "fetch_scale": 2.000, "write_scale": 1.000,
         "profile": "profiles/step_dense-4e6x256_pmc.md",
     },
     "k_rownorm_bres": {
         "source": "paper_2203_02798_amd/csrc/k_dense.hip",
-        "sha256_prefix": "be36c3e0e668d061",
-        "fetch_kib": 6241491.0, "write_kib": 329335.0,
+        "sha256_prefix": "b63e300e92ca95d7",
+        "fetch_kib": 3398222.1, "write_kib": 125028.5,
         "fetch_scale": 2.000, "write_scale": 1.000,
         "profile": "profiles/step_dense-4e6x256_pmc.md",
     },

@@ -828,10 +828,12 @@ int rownorm_launch(const psk_mat &Am, const double *B, int64_t k, double alpha,
 // tiles of one slab read its rows through one L2.  No atomics.
 constexpr int kGramWaves = 4;
 // Row steps whose loads are in flight: six where a wavefront has its item to
-// itself (FP64 300,000 x 129: 239 us at four, 206 at six; 198 registers, so
-// the smaller kernels of a stream beside the Gram still find room), four
-// where the workgroup shares it and the rows are few (20,000 x 97: 25 us at
-// four, 30 at six).
+// itself (FP64 300,000 x 129: 239 us at four, 206 at six; 244 registers, 252
+// with FP32 rows, so kernels of another stream run before and after it rather
+// than beside it: 4e6 x 256 in FP32 with its sketch on a second stream takes
+// 10.50 ms a step, 10.59 on one stream; 11.05 and 11.98 while it held 208 and
+// ran slower), four where the workgroup shares it and the rows are few (20,000
+// x 97: 25 us at four, 30 at six).
 constexpr int gram_prefetch(int wpt) { return wpt == 1 ? 6 : 4; }
 constexpr int kGramLds = 64 + 16;  // row stride of the LDS sum: rows kq and kq + 1 in other banks
 

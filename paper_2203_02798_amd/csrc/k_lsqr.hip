@@ -9,9 +9,10 @@
 //
 // Where it pays, R^{-1} is first sharpened by A's own Gram matrix
 // (precond_sharpen): LSQR then stops after two or three iterations instead of
-// 30 to 50 (1e6 x 256 at condition number 1e3, m = 8 d: 16.1 -> 6.8 ms a
-// solve; 1e4 x 32: 982 -> 518 us; CSR 1e6 x 500 by the caller's R^{-1}: the
-// solve's 1.48 ms became 0.95).
+// 30 to 50 (when it was added, with the other kernels as they were then: 1e6 x
+// 256 at condition number 1e3, m = 8 d: 16.1 -> 6.8 ms a solve; 1e4 x 32: 982
+// -> 518 us; CSR 1e6 x 500 by the caller's R^{-1}: the solve's 1.48 ms became
+// 0.95).
 //
 // One LSQR iteration reads A once: for every row, u_i <- A_i vhat - alpha u_i
 // and A_i^T u_i is accumulated immediately (the normalisation by beta is a
@@ -985,7 +986,8 @@ void one_step(const psk_mat &A, int mode, int k, const LsqBufs &B, const double 
 // matrix and the d x d factorization.  Times in us from single kernels on
 // the largest and smallest shapes: a dense pass reads 5 TB/s and its two
 // small kernels take 12; the Gram matrix runs at 55 TFLOP/s; a 64-column step of the
-// factorization takes 40.  CSR: a pass is about 20 B a row and 12 an entry
+// factorization takes 40 (both on the safe side: 1e6 x 256 now runs at 57 in
+// FP64, 66 in FP32, and a step takes 20).  CSR: a pass is about 20 B a row and 12 an entry
 // at 3 TB/s, and the Gram matrix half a us for every 64 d multiply-adds (a wavefront
 // per column, one dependent load after another).
 bool precond_pays(const psk_mat &A, int64_t m, double tol, double row_squares) {
