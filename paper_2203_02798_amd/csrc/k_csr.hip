@@ -210,7 +210,8 @@ __global__ __launch_bounds__(256) void k_row_first(const double *__restrict__ B,
 // batches as long as the longest row.  Its entries are staged in LDS TH at a
 // time, so that a batch waits for B alone, and a triangular B's leading zeros
 // (up to first[c]) are not read, their lanes taking the row's last element
-// instead; an entry that is not finite takes the whole row, zeros too.  1900
+// instead; an entry that is not finite takes the whole row, zeros too, and a
+// place past the row's end takes none of B (its row 0 may not be finite).  1900
 // rows of 350 entries, k = 1000: 592 us with 8 entries and 4 columns a thread,
 // 486 with staging and without the zeros, 446 with 16 entries and 2 columns
 // of 512 threads (1024 threads: 456; a launch per 256 columns, which an XCD's
@@ -273,10 +274,10 @@ __global__ __launch_bounds__(TH) void k_rownorm_csr_listed(
         __syncthreads();  // the entries before have been used
         ev[tid] = ve;
         ec[tid] = c;
-        ef[tid] = fabs(ve) <= 1.7976931348623157e308 ? f : 0u;
+        ef[tid] = p >= p1 ? UINT32_MAX : fabs(ve) <= 1.7976931348623157e308 ? f : 0u;
         __syncthreads();
         const int m = (int)(p1 - s0 < TH ? p1 - s0 : TH);
-        for (int e0 = 0; e0 < m; e0 += kRnU) {  // past m: zero entries
+        for (int e0 = 0; e0 < m; e0 += kRnU) {  // past m: 0 times 0
           double b[kRnU][Q];
 #pragma unroll
           for (int u = 0; u < kRnU; ++u) {
