@@ -269,15 +269,22 @@ int leverage_css_impl(const psk_mat &A, int64_t m, int64_t r, int64_t k, uint64_
 // est (kPrecondEst doubles, device): what the host needs to decide, read
 // back by the caller and passed to the two functions after it: the bound of
 // the rounding error of N^T A^T A N (kPrecondMax and above: not worth
-// forming) and, CSR A, the sum of squared row lengths (the Gram matrix's
-// multiply-adds).  R: N's inverse, or NULL; g: d doubles of scratch.
+// forming) and, CSR A (d <= 1024), what the times of its Gram matrix and of a
+// pass depend on.  R: N's inverse, or NULL; g: d doubles of scratch.
 constexpr double kPrecondMax = 0.1;
-constexpr int kPrecondRowParts = 256;
-constexpr int kPrecondEst = 16 + kPrecondRowParts;
+constexpr int kPrecondRowParts = 64;
+constexpr int kPrecondEst = 16 + 4 * kPrecondRowParts;
+struct RowStats {
+  double squares, cubes;  // sums of squared and cubed row lengths
+  double pass_us;         // what a pass's longer rows take
+  double share;           // the fullest column's share of the entries
+};
 void precond_estimate(const psk_mat &A, const double *R, const double *N, double *g,
                       double *est, hipStream_t st);
 double precond_error(const double *est, int64_t d);
-double precond_row_squares(const double *est);
+RowStats precond_row_stats(const double *est, int64_t d);
+// the stats of an A of this size for which sharpening pays most
+RowStats precond_row_bounds(const psk_mat &A);
 // P (d x d, whole, d <= 1024) = N S^{-1} with S^T S = N^T A^T A N, or N itself
 // where that is not accurate.  caller: N is the caller's, its lower triangle
 // is not read.

@@ -981,29 +981,43 @@ void one_step(const psk_mat &A, int mode, int k, const LsqBufs &B, const double 
 }
 
 // Whether the preconditioner of an m-row sketch is worth sharpening with A's
-// Gram matrix: the passes over A it saves (those LSQR takes at the rate
-// sqrt(d / m) to the tighter tolerance, less about five) against the Gram
-// matrix and the d x d factorization.  Times in us from single kernels on
-// the largest and smallest shapes: a dense pass reads 5 TB/s and its two
-// small kernels take 12; the Gram matrix runs at 55 TFLOP/s; a 64-column step of the
-// factorization takes 40 (both on the safe side: 1e6 x 256 now runs at 57 in
-// FP64, 66 in FP32, and a step takes 20).  CSR: a pass is about 20 B a row and 12 an entry
-// at 3 TB/s, and the Gram matrix half a us for every 64 d multiply-adds (a wavefront
-// per column, one dependent load after another).
-bool precond_pays(const psk_mat &A, int64_t m, double tol, double row_squares) {
-  const double n = (double)A.n, d = (double)A.d;
+// Gram matrix: the passes over A it saves against the Gram matrix and the d x d
+// factorization.  Times in us.
+// Dense: LSQR's passes at the rate sqrt(d / m) to the tighter tolerance, less
+// about five; a pass reads 5 TB/s and its two small kernels take 12; the Gram
+// matrix runs at 55 TFLOP/s; a 64-column step of the factorization takes 40
+// (both on the safe side: 1e6 x 256 now runs at 57 in FP64, 66 in FP32, and a
+// step takes 20).
+// CSR: constants fitted to 620 solves (5e3 to 2e6 rows, 10 to 1000 columns, 1 to 30
+// entries a row, even and Zipf lengths, a full column; m = 2 d, 8 d and a
+// caller's factor), each timed both ways.  LSQR takes a third more than
+// that rate (the refinement pass) while d is large, and 1.6 d where that is
+// fewer: it ends after d steps or so.  Beside its longer rows a pass takes 13
+// us and one for every 48 columns and 250,000 entries.  The Gram matrix sorts
+// the entries and then has one wavefront a column, 64 of its entries at a time,
+// each turn as long as the longest row of the 64 (about the cubes over the
+// squares of the row lengths, 0.33 us an entry): one full column makes its
+// wavefront the whole time.  With an even share of the multiply-adds, half a
+// us for 64 d, and no more said of the passes, tall matrices of few columns
+// and those with a full column were sharpened at a loss (2e6 x 10, an entry a row,
+// m = 2 d: 1.54 ms plain, 5.20 sharpened).
+bool precond_pays(const psk_mat &A, int64_t m, double tol, const RowStats &rows) {
+  const double n = (double)A.n, d = (double)A.d, blocks = std::ceil(d / 64.0);
   const double es = A.dtype == PSK_F64 ? 8.0 : 4.0;
   const double e = m > 0 ? std::fmin(std::sqrt(d / (double)m), 0.9) : 0.5;
-  const double saved = std::log(1.0 / std::fmax(tol, 1e-16)) / std::log(1.0 / e) - 5.0;
-  double pass = 12.0, gram = 100.0 + 40.0 * std::ceil(d / 64.0);
+  const double plain = std::log(1.0 / std::fmax(tol, 1e-16)) / std::log(1.0 / e);
   if (A.format == PSK_DENSE) {
-    pass += n * d * es / 5e6;
-    gram += n * d * (d + 64.0) / 55e6;
-  } else {
-    pass += 12.0 + (n * 20.0 + (double)A.nnz * (es + 4.0)) / 3e6;
-    gram += 100.0 + 0.5 * row_squares / (64.0 * d);
+    const double pass = 12.0 + n * d * es / 5e6;
+    const double gram = 100.0 + 40.0 * blocks + n * d * (d + 64.0) / 55e6;
+    return (plain - 5.0) * pass > gram;
   }
-  return saved * pass > gram;
+  const double nnz = (double)A.nnz;
+  const double iters = std::pow(std::pow(1.6 * d, -1.5) + std::pow(1.33 * plain, -1.5), -1.0 / 1.5);
+  const double pass = 12.6 + d / 48.0 + (d > 64.0 ? 3.2 : 0.0) + nnz / 2.5e5 + rows.pass_us;
+  const double longest = rows.squares > 0.0 ? rows.cubes / rows.squares : 0.0;
+  const double gram = 30.0 + 25.0 * blocks + nnz / 5e3 +
+                      std::ceil(nnz * rows.share / 64.0) * (0.76 + 0.33 * longest);
+  return (iters - 3.0) * pass > gram;
 }
 
 }  // namespace
@@ -1116,14 +1130,13 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
       ws.release(mk2);
     }
   }
-  // sharpening: planned where it pays at the least row_squares that A can
-  // have (equal rows); with an iteration limit below the tens of passes that
-  // the sketch's own preconditioner takes, the limit is meant for that method
+  // sharpening: planned where it can pay; with an iteration limit below the
+  // tens of passes that the sketch's own preconditioner takes, the limit is
+  // meant for that method
   const double tol = std::fmax(o.atol, o.btol);
-  const double mean_len = (double)A.nnz / (double)n;
   const bool may_sharpen =
       !ws.lean && n >= d && (A.format == PSK_DENSE || A.nnz < ((int64_t)1 << 31)) &&
-      precond_pays(A, own ? m : 0, tol, (double)A.nnz * std::fmax(mean_len, 1.0));
+      precond_pays(A, own ? m : 0, tol, precond_row_bounds(A));
   if (ws.dry() && may_sharpen) {
     ws.release(mk);
     ws.take<double>((size_t)d * d);
@@ -1180,8 +1193,8 @@ int lsq_impl(const psk_mat &A, const double *b, double *x, const psk_lsq_opts &o
       if ((rc = read_back(hr, ratio, nratio * sizeof(double), st))) return rc;
     }
     const double err = precond_error(hr + 3, d);
-    const double rsq = A.format == PSK_CSR ? precond_row_squares(hr + 3) : 0.0;
-    if (err <= kPrecondMax && precond_pays(A, own ? m : 0, tol, rsq)) {
+    const RowStats rows = A.format == PSK_CSR ? precond_row_stats(hr + 3, d) : RowStats{};
+    if (err <= kPrecondMax && precond_pays(A, own ? m : 0, tol, rows)) {
       double *P = ws.take<double>((size_t)d * d);
       const size_t mkp = ws.mark();
       if ((rc = precond_sharpen(A, Rinv, !own, P, ws, st))) return rc;

@@ -21,6 +21,8 @@
 // when E is too large or a pivot failed, so a bad P never reaches LSQR.
 #include <math.h>
 
+#include <cmath>
+
 #include "internal.hpp"
 
 namespace psk {
@@ -118,19 +120,74 @@ __global__ __launch_bounds__(256) void k_precond_pick(const double *__restrict__
   if (e < d * d) P[e] = N[e];
 }
 
-// part[b] = sum of (entries of row i)^2 over the workgroup's rows
-__global__ __launch_bounds__(256) void k_row_squares(const int64_t *__restrict__ indptr,
-                                                     int64_t n, double *__restrict__ part) {
-  __shared__ double red[4];
-  double s = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += 256 * kPrecondRowParts) {
-    const double c = (double)(indptr[i + 1] - indptr[i]);
-    s = fma(c, c, s);
+// What the times of a CSR LSQR pass and Gram matrix depend on, from workgroup b
+// in part[b + kPrecondRowParts q]: sums of squared (q 0) and cubed (q 1) row
+// lengths, what the pass's longer rows take (q 2, us), and the largest share of one
+// column in up to kSample of the entries (q 3), less two standard deviations
+// of a count (even columns are not to look like fewer).  Every workgroup's
+// sample is spread over all the rows, an entry at a scattered place of every
+// stretch of `step` (a fixed place could meet the same column of every row).
+constexpr int kSample = 1024;  // one a thread: 64 x 1024 in all (4096 took 8 us more at 1e6 rows)
+// us of a pass: a row past 16 entries takes a wavefront of its own (4.8 us, 4096
+// wavefronts side by side), an entry past the fourth of a shorter one is not
+// held in registers (20 us a million); both fitted to whole passes of 5e3 to
+// 2e6 rows
+constexpr double kLongRowUs = 4.8 / 4096.0, kDeepEntryUs = 20e-6;
+
+__global__ __launch_bounds__(1024) void k_row_stats(const int64_t *__restrict__ indptr,
+                                                    const int32_t *__restrict__ indices,
+                                                    int64_t n, int64_t nnz, int d,
+                                                    double *__restrict__ part) {
+  __shared__ int hist[1024];
+  __shared__ double red[4][16];
+  const int tid = threadIdx.x;
+  hist[tid] = 0;
+  constexpr int64_t kAll = (int64_t)kSample * kPrecondRowParts;
+  const int64_t step = nnz > kAll ? nnz / kAll : 1;
+  int64_t taken = (nnz - blockIdx.x + kPrecondRowParts - 1) / kPrecondRowParts;
+  taken = taken < 0 ? 0 : taken > kSample ? kSample : taken;
+  int col = -1;  // used after the rows
+  if (tid < taken) {
+    const int64_t j = (int64_t)tid * kPrecondRowParts + blockIdx.x;  // j * step + step <= nnz
+    const uint32_t off = (((uint32_t)j * 2654435761u) >> 4) % (uint32_t)step;  // nnz < 2^31
+    col = indices[j * step + off];
   }
-  s = wave_sum(s);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  double s2 = 0.0, s3 = 0.0, us = 0.0;
+#pragma unroll 4
+  for (int64_t i = (int64_t)blockIdx.x * 1024 + tid; i < n; i += 1024 * kPrecondRowParts) {
+    const double c = (double)(indptr[i + 1] - indptr[i]);
+    s2 = fma(c, c, s2);
+    s3 = fma(c * c, c, s3);
+    us += c > 16.0 ? kLongRowUs : c > 4.0 ? kDeepEntryUs * (c - 4.0) : 0.0;
+  }
   __syncthreads();
-  if (threadIdx.x == 0) part[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+  if (col >= 0) atomicAdd(&hist[col], 1);
+  s2 = wave_sum(s2);
+  s3 = wave_sum(s3);
+  us = wave_sum(us);
+  __syncthreads();
+  double most = tid < d ? (double)hist[tid] : 0.0;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) most = fmax(most, __shfl_xor(most, off, 64));
+  if ((tid & 63) == 0) {
+    red[0][tid >> 6] = s2;
+    red[1][tid >> 6] = s3;
+    red[2][tid >> 6] = us;
+    red[3][tid >> 6] = most;
+  }
+  __syncthreads();
+  if (tid) return;
+  for (int w = 1; w < 16; ++w) {
+    s2 += red[0][w];
+    s3 += red[1][w];
+    us += red[2][w];
+    most = fmax(most, red[3][w]);
+  }
+  part[blockIdx.x] = s2;
+  part[kPrecondRowParts + blockIdx.x] = s3;
+  part[2 * kPrecondRowParts + blockIdx.x] = us;
+  part[3 * kPrecondRowParts + blockIdx.x] =
+      taken > 0 ? fmax(most - 2.0 * sqrt(most), 0.0) / (double)taken : 0.0;
 }
 
 unsigned guard_blocks(int64_t d) { return (unsigned)ceil_div(d, (int64_t)kGuardCols); }
@@ -147,7 +204,8 @@ void precond_estimate(const psk_mat &A, const double *R, const double *N, double
     k_guard<<<guard_blocks(d), 64 * kGuardWaves, 0, st>>>(N, d, N, 1, est);
   }
   if (A.format == PSK_CSR)
-    k_row_squares<<<kPrecondRowParts, 256, 0, st>>>(A.indptr, A.n, est + kMaxGuard);
+    k_row_stats<<<kPrecondRowParts, 1024, 0, st>>>(A.indptr, A.indices, A.n, A.nnz, (int)d,
+                                                  est + kMaxGuard);
 }
 
 double precond_error(const double *est, int64_t d) {
@@ -156,10 +214,22 @@ double precond_error(const double *est, int64_t d) {
   return kGuardC * s;
 }
 
-double precond_row_squares(const double *est) {
-  double s = 0.0;
-  for (int b = 0; b < kPrecondRowParts; ++b) s += est[kMaxGuard + b];
-  return s;
+RowStats precond_row_stats(const double *est, int64_t d) {
+  RowStats r{0.0, 0.0, 0.0, 0.0};
+  for (int b = 0; b < kPrecondRowParts; ++b) {
+    r.squares += est[kMaxGuard + b];
+    r.cubes += est[kMaxGuard + kPrecondRowParts + b];
+    r.pass_us += est[kMaxGuard + 2 * kPrecondRowParts + b];
+    r.share += est[kMaxGuard + 3 * kPrecondRowParts + b] / kPrecondRowParts;
+  }
+  r.share = fmax(r.share, 1.0 / (double)d);
+  return r;
+}
+
+RowStats precond_row_bounds(const psk_mat &A) {
+  const double nnz = (double)A.nnz, len = std::fmax(nnz / (double)A.n, 1.0);
+  return RowStats{len, len * len, nnz / 17.0 * kLongRowUs + 0.75 * nnz * kDeepEntryUs,
+                  1.0 / (double)A.d};
 }
 
 int precond_sharpen(const psk_mat &A, const double *N, bool caller, double *P, Arena &ws,
