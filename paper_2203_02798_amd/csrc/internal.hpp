@@ -273,7 +273,8 @@ int leverage_css_impl(const psk_mat &A, int64_t m, int64_t r, int64_t k, uint64_
 // pass depend on.  R: N's inverse, or NULL; g: d doubles of scratch.
 constexpr double kPrecondMax = 0.1;
 constexpr int kPrecondRowParts = 64;
-constexpr int kPrecondEst = 16 + 4 * kPrecondRowParts;
+constexpr int kPrecondGuards = 16;  // the error comes in up to this many parts
+constexpr int kPrecondEst = kPrecondGuards + 4 * kPrecondRowParts;
 struct RowStats {
   double squares, cubes;  // sums of squared and cubed row lengths
   double pass_us;         // what a pass's longer rows take
@@ -282,6 +283,12 @@ struct RowStats {
 void precond_estimate(const psk_mat &A, const double *R, const double *N, double *g,
                       double *est, hipStream_t st);
 double precond_error(const double *est, int64_t d);
+// precond_estimate without R takes a lower bound, some 70 times short for A of
+// even columns: where the error read back is doubtful for that, the same again
+// (its first part of est) with g from a sample of A's rows
+bool precond_doubtful(const psk_mat &A, double err);
+void precond_estimate_rows(const psk_mat &A, const double *N, double *g, double *est,
+                           hipStream_t st);
 RowStats precond_row_stats(const double *est, int64_t d);
 // the stats of an A of this size for which sharpening pays most
 RowStats precond_row_bounds(const psk_mat &A);

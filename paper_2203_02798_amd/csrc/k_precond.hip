@@ -15,10 +15,11 @@
 // P^T G P is at most E = c u sum_j t_j^2, t_j = sum_k |P_kj| g_k, in
 // Frobenius norm, whatever the scaling of A's columns.  k_guard sums t_j^2.
 // It is asked twice: before G is formed, with N in P's place and g from R
-// (or a lower bound of it from N's diagonal), where E above kPrecondMax
-// leaves the sketch's N as it is (cond(A) beyond about 1e5); and afterwards
-// with P and G's diagonal, on the device: k_precond_pick puts N back into P
-// when E is too large or a pivot failed, so a bad P never reaches LSQR.
+// (or, for a caller's N, a lower bound of it from N's diagonal and, where that
+// leaves doubt, some of A's rows), where E above kPrecondMax leaves the sketch's N as it is (cond(A)
+// beyond about 1e6); and afterwards with P and G's diagonal, on the device:
+// k_precond_pick puts N back into P when E is too large or a pivot failed, so
+// a bad P never reaches LSQR.
 #include <math.h>
 
 #include <cmath>
@@ -31,6 +32,7 @@ namespace {
 constexpr double kGuardC = 16.0 * 1.1102230246251565e-16;  // c u
 constexpr int kGuardCols = 64;   // columns of a k_guard workgroup
 constexpr int kMaxGuard = 1024 / kGuardCols;
+static_assert(kMaxGuard == kPrecondGuards, "a part for every workgroup of k_guard");
 
 // A workgroup takes 64 columns j, a lane each; its 16 wavefronts take every
 // 16th row k <= j, eight rows' loads in flight (one at a time, by four
@@ -74,6 +76,39 @@ __global__ __launch_bounds__(64 * kGuardWaves) void k_col_norm_upper(
       [](double s2, double m, double) { return fma(m, m, s2); });
   const int64_t j = (int64_t)blockIdx.x * kGuardCols + threadIdx.x;
   if (threadIdx.x < kGuardCols && j < d) g[j] = sqrt(s);
+}
+
+// g[k], three quarters of about ||A e_k|| of a dense A from 256 of its rows, and
+// not below 1 / |N_kk| = |R_kk|: four groups of 64 rows, one row in every
+// stretch of n / 256, each group's sum of squares scaled to n rows, the least of the
+// four (a few heavy rows must not look like all of them).  Three quarters: P's
+// bound is about 0.75 of N's, and on the line a Gram matrix formed for nothing
+// costs a tenth of the solve, one not formed three quarters.
+constexpr int kNormRows = 256;
+
+template <typename T>
+__global__ __launch_bounds__(64 * kGuardWaves) void k_col_norm_sample(
+    const T *__restrict__ A, int64_t ld, int64_t n, int64_t d, const double *__restrict__ N,
+    double *__restrict__ g) {
+  __shared__ double red[kGuardWaves][kGuardCols];
+  constexpr int kEach = kNormRows / kGuardWaves;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t j = (int64_t)blockIdx.x * kGuardCols + lane;
+  T x[kEach];
+#pragma unroll
+  for (int q = 0; q < kEach; ++q)  // rows of one wavefront are spread over all of A
+    x[q] = A[(n * (q * kGuardWaves + wave) / kNormRows) * ld + (j < d ? j : d - 1)];
+  double s = 0.0;
+#pragma unroll
+  for (int q = 0; q < kEach; ++q) s = fma((double)x[q], (double)x[q], s);
+  red[wave][lane] = s;
+  __syncthreads();
+  if (wave || j >= d) return;
+  double least = INFINITY;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    least = fmin(least, (red[q][lane] + red[q + 4][lane]) + (red[q + 8][lane] + red[q + 12][lane]));
+  g[j] = fmax(0.75 * sqrt(least * (double)n * (4.0 / kNormRows)), 1.0 / fabs(N[j * d + j]));
 }
 
 // part[b] = sum over the workgroup's columns j of (sum_{k <= j} |M_kj| g_k)^2,
@@ -206,6 +241,21 @@ void precond_estimate(const psk_mat &A, const double *R, const double *N, double
   if (A.format == PSK_CSR)
     k_row_stats<<<kPrecondRowParts, 1024, 0, st>>>(A.indptr, A.indices, A.n, A.nnz, (int)d,
                                                   est + kMaxGuard);
+}
+
+bool precond_doubtful(const psk_mat &A, double err) {
+  return A.format == PSK_DENSE && A.n >= 4 * kNormRows && err > 1e-3 && err <= kPrecondMax;
+}
+
+void precond_estimate_rows(const psk_mat &A, const double *N, double *g, double *est,
+                           hipStream_t st) {
+  const int64_t d = A.d;
+  const unsigned nb = guard_blocks(d);
+  if (A.dtype == PSK_F64)
+    k_col_norm_sample<<<nb, 64 * kGuardWaves, 0, st>>>((const double *)A.values, A.ld, A.n, d, N, g);
+  else
+    k_col_norm_sample<<<nb, 64 * kGuardWaves, 0, st>>>((const float *)A.values, A.ld, A.n, d, N, g);
+  k_guard<<<nb, 64 * kGuardWaves, 0, st>>>(N, d, g, 0, est);
 }
 
 double precond_error(const double *est, int64_t d) {
