@@ -11,9 +11,9 @@
 //   column j: nnz_2(A) work in total.  Only k >= j is accumulated and the
 //   other triangle is mirrored, so C is exactly symmetric.
 // * Row norms: Algorithm squared_row_norms: Bt = B B^T once, then per row
-//   sum_{k,j} V_k V_j Bt[J_j, J_k].  Rows of up to 4 entries take one lane
-//   each, up to 16 a sixteenth of a wavefront, longer ones a wavefront (lanes
-//   over k) from a list.
+//   sum_{k,j} V_k V_j Bt[J_j, J_k].  Rows of up to 4 entries (6 to 9 where a
+//   wavefront has many) take one lane each, up to 16 a quarter of a wavefront, longer ones
+//   a wavefront (lanes over k) from a list.
 //   That costs a row nnz^2 scattered reads of Bt; a row with more than
 //   max(32, k/8) entries costs less as the product itself, ||V B[J, :]||^2
 //   (nnz contiguous rows of B, k values each): such rows are listed too and
@@ -90,14 +90,23 @@ __global__ __launch_bounds__(256) void k_gram_csc(
 // of them holding entries, Zipf lengths: 549 us; row pointers and x alone
 // take 33).  With the longer rows' lanes over k, their loads side by side, it
 // takes 89 and the listed rows of up to 125 entries 87.
-constexpr int kRowLane = 4, kRowGroup = 16;
+// Four rows of 5 to 16 entries side by side take 1.4 us, a wavefront full of
+// them 22; rows of up to 9 entries one lane each take half a us an entry of
+// the longest, whatever their number, so from 2.5 rows an entry on they do
+// (1e6 rows of 5 entries, d = 20: 196 us in fours, 61 by lanes).  Beyond 262,144
+// rows it is the scattered loads of Bt that count and not the chain: then up
+// to 8 entries for d up to 256 and up to 6 for more (1e6 rows of 8, lanes /
+// fours: d = 140 156 / 200 us, d = 500 255 / 211).
+constexpr int kRowLane = 4, kRowGroup = 16, kRowMany = 9;
+
+int row_many(int64_t n, int64_t d) { return n <= 262144 ? kRowMany : d <= 256 ? 8 : 6; }
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_rownorm_csr(
     const T *__restrict__ vals, const int64_t *__restrict__ indptr,
     const int32_t *__restrict__ indices, int64_t n, int64_t d,
     const double *__restrict__ Bt, double alpha, double beta, double *__restrict__ x,
-    int64_t tl, uint32_t *__restrict__ list, uint32_t *__restrict__ count) {
+    int64_t tl, int most, uint32_t *__restrict__ list, uint32_t *__restrict__ count) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int lane = threadIdx.x & 63;
   const bool have = i < n;
@@ -142,8 +151,31 @@ __global__ __launch_bounds__(256) void k_rownorm_csr(
     at = __shfl(at, 0, 64) + (uint32_t)__popcll(m & lt);
     if (mine) list[which ? (uint32_t)n - 1u - at : at] = (uint32_t)i;
   }
-  // rows of kRowLane + 1 .. kRowGroup entries, four at a time
-  uint64_t pending = __ballot(len > kRowLane && len <= kRowGroup);
+  // many rows of kRowLane + 1 .. most entries: a lane each
+  const bool some = len > kRowLane && len <= most;
+  int longest = most;
+  while (longest > kRowLane && !__ballot(len == longest)) --longest;
+  const bool many = longest > kRowLane && 2 * __popcll(__ballot(some)) >= 5 * longest;
+  if (many && some) {
+    double v[kRowMany], acc = 0.0;
+    int64_t c[kRowMany];
+#pragma unroll
+    for (int j = 0; j < kRowMany; ++j) {
+      v[j] = j < len ? (double)vals[p0 + j] : 0.0;
+      c[j] = j < len ? indices[p0 + j] : 0;
+    }
+    for (int k = 0; k < len; ++k) {
+      const int64_t ck = indices[p0 + k];
+      double t = 0.0;
+#pragma unroll
+      for (int j = 0; j < kRowMany; ++j)
+        if (j < len) t += v[j] * Bt[c[j] * d + ck];
+      acc += (double)vals[p0 + k] * t;
+    }
+    finish(i, acc);
+  }
+  // the others of kRowLane + 1 .. kRowGroup entries, four at a time
+  uint64_t pending = __ballot(len > (many ? most : kRowLane) && len <= kRowGroup);
   const int g = lane >> 4, l = lane & 15;
   while (pending) {
     int src = -1;  // this group's row: the g-th pending one
@@ -381,7 +413,7 @@ int rownorms_csr(double alpha, const psk_mat &A, const double *B, int64_t k,
     typedef decltype(t) T;
     const T *vals = (const T *)A.values;
     k_rownorm_csr<T><<<blocks, 256, 0, st>>>(vals, A.indptr, A.indices, A.n, d, Bt, alpha, beta,
-                                             x, tl, list, count);
+                                             x, tl, row_many(A.n, d), list, count);
 #define PSK_RNL(TH, Q)                                                                       \
   k_rownorm_csr_listed<T, TH, Q><<<2048, TH, 0, st>>>(vals, A.indptr, A.indices, list, A.n, \
                                                       count, first, d, Bt, B, k, alpha, beta, x)
