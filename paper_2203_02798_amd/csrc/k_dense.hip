@@ -932,7 +932,7 @@ __device__ __forceinline__ void gram_rows(const TA *__restrict__ A, int64_t ld, 
   if (kStepped)
     for (int64_t g = groups; g < stepped; ++g) __builtin_amdgcn_s_barrier();
   if (wave) return;
-  // the rest (fewer than 16 rows, at the end of A only): rows past k1 as zero
+  // the rest (fewer than 4 PF rows, at the end of A only): rows past k1 as zero
   for (int64_t k = k0 + groups * kGroup; k < k1; k += 4) {
     const bool ok = k + kq < k1;
     const int64_t row = ok ? k : k1 - 1 - kq;  // relative to this lane's row kq
@@ -1097,7 +1097,7 @@ __global__ __launch_bounds__(64 * kGramGroups) void k_gram_reduce(
   C[e] = (TO)v;
 }
 
-GramPlan gram_plan(int64_t n, int64_t d, int wpt, bool lean) {
+GramPlan gram_plan(int64_t n, int64_t d, int wpt, bool f64, bool lean) {
   GramPlan p{};
   p.T = (int)ceil_div(d, (int64_t)64);
   p.nbt = (int)ceil_div(d - 64 * (int64_t)(p.T - 1), (int64_t)16);
@@ -1109,11 +1109,14 @@ GramPlan gram_plan(int64_t n, int64_t d, int wpt, bool lean) {
   p.cnt[3] = tail ? 1 : 0;
   // a step costs its block products, or twice the blocks it loads where those
   // are more: a narrow last tile waits for its rows (300,000 x 200 in FP64,
-  // whose last tile is one block wide: 420 us before, 605 by products alone,
-  // 372 by this rule)
-  const double nbt = p.nbt;
+  // whose last tile is one block wide: 605 us by products alone, 302 by this
+  // rule).  The last diagonal tile of a wavefront of its own waits longest, its
+  // loads are all it does: two more in FP64, one in FP32 past 256 columns (without them 120,000 x 836 in FP64 took 2397 us,
+  // its last tile alone in two slabs of 60,000 rows, now 1428; 200,000 x 452 1068
+  // and 765, 300,000 x 220 375 and 323)
+  const double nbt = p.nbt, wait = wpt > 1 ? 0.0 : f64 ? 2.0 : p.T > 4 ? 1.0 : 0.0;
   const double cost[4] = {16.0, std::max(4.0 * nbt, 2.0 * (4.0 + nbt)), 10.0,
-                          std::max(0.5 * nbt * (nbt + 1.0), 2.0 * nbt)};
+                          std::max(0.5 * nbt * (nbt + 1.0), 2.0 * nbt + wait)};
   double total = 0.0;
   for (int c = 0; c < 4; ++c) total += p.cnt[c] * cost[c];
   // two wavefronts per SIMD in one round (a lean workspace: one), at least
@@ -1140,7 +1143,7 @@ int gram_syrk_launch(double alpha, const psk_mat &Am, double beta, void *C, bool
                      Arena &ws, hipStream_t st) {
   const int64_t n = Am.n, d = Am.d;
   const int wpt = d <= 112 ? kGramWaves : 1;  // measured beside the kernel
-  const GramPlan pl = gram_plan(n, d, wpt, ws.lean);
+  const GramPlan pl = gram_plan(n, d, wpt, sizeof(TA) == 8, ws.lean);
   const int64_t items = pl.first[4];
   double *part = ws.take<double>((size_t)items * 4096);
   if (ws.dry()) return 0;
