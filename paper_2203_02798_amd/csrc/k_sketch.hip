@@ -775,18 +775,23 @@ __global__ __launch_bounds__(256) void k_write_pairs(SRC src, int64_t n,
 // The sort of n pairs from src (dn: their count on the device, n at most)
 // by keys below r.  The first pass reads src and writes (k0, v0); later ones
 // go back and forth between (k0, v0) and (k1, v1), which are only needed then.
-// A lean workspace keeps to 8-bit digits (a quarter of the counts).
-int sort_passes(uint32_t r, bool lean) {
+// A lean workspace keeps to 8-bit digits (a quarter of the counts), unless a
+// single pass of the pairs is the smaller one: with `arrays`, where the caller
+// takes (k1, v1) only for a second pass, 8 bytes a pair against the counts.
+int sort_passes(uint32_t r, bool lean, int64_t n, bool arrays) {
   int bits = 0;
   while (bits < 32 && ((uint64_t)1 << bits) < (uint64_t)r) ++bits;
   const int most = lean ? 8 : kDigitBits;
-  return bits > most ? (bits + most - 1) / most : 1;
+  const int passes = bits > most ? (bits + most - 1) / most : 1;
+  if (!lean || !arrays || passes == 1 || bits > kDigitBits) return passes;
+  const int64_t more = ((int64_t)1 << bits) - ((int64_t)1 << (bits + 1) / 2);  // digits
+  return more * ceil_div(n, (int64_t)kSortTile) * 4 <= 8 * n ? 1 : passes;
 }
 
 template <class SRC>
 int sort_run(SRC src, int64_t n, uint32_t r, uint32_t *k0, uint32_t *v0, uint32_t *k1,
-             uint32_t *v1, Arena &ws, hipStream_t st, uint32_t **skeys, uint32_t **svals,
-             uint32_t *ptr, const uint32_t *dn) {
+             uint32_t *v1, int passes, Arena &ws, hipStream_t st, uint32_t **skeys,
+             uint32_t **svals, uint32_t *ptr, const uint32_t *dn) {
   int bits = 0;
   while (bits < 32 && ((uint64_t)1 << bits) < (uint64_t)r) ++bits;
   if (r == 1) {
@@ -799,7 +804,6 @@ int sort_run(SRC src, int64_t n, uint32_t r, uint32_t *k0, uint32_t *v0, uint32_
     *svals = v0;
     return 0;
   }
-  const int passes = sort_passes(r, ws.lean);
   const int nbits = (bits + passes - 1) / passes;  // equal digits: fewer counts to scan
   const int D = 1 << nbits;
   const int64_t ntiles = ceil_div(n, kSortTile);
@@ -843,8 +847,8 @@ int sort_pairs(uint32_t *keys, uint32_t *vals, int64_t n, uint32_t r, Arena &ws,
   // one bucket: the pairs stay where they are
   uint32_t *k0 = r > 1 ? ws.take<uint32_t>(n) : nullptr;
   uint32_t *v0 = r > 1 ? ws.take<uint32_t>(n) : nullptr;
-  const int rc =
-      sort_run(StoredPairs{keys, vals}, n, r, k0, v0, keys, vals, ws, st, skeys, svals, ptr, dn);
+  const int rc = sort_run(StoredPairs{keys, vals}, n, r, k0, v0, keys, vals,
+                          sort_passes(r, ws.lean, n, false), ws, st, skeys, svals, ptr, dn);
   if (r == 1 && !rc) {
     *skeys = keys;
     *svals = vals;
@@ -871,7 +875,8 @@ static int bin_pairs(const psk_mat &A, uint32_t s, uint32_t r, uint64_t seed, Ar
   const int64_t n = A.n;
   const int64_t pairs = n * (int64_t)s;
   const bool compact = A.format == PSK_CSR;
-  const bool two = sort_passes(r, ws.lean) > 1;
+  const int passes = sort_passes(r, ws.lean, pairs, true);
+  const bool two = passes > 1;
   uint32_t *k0 = ws.take<uint32_t>(pairs);
   uint32_t *v0 = ws.take<uint32_t>(pairs);
   uint32_t *k1 = two ? ws.take<uint32_t>(pairs) : nullptr;
@@ -897,13 +902,14 @@ static int bin_pairs(const psk_mat &A, uint32_t s, uint32_t r, uint64_t seed, Ar
   int rc;
   // for CSR A the pairs of the listed rows (cnt[1]) bound the sort
   if (compact)
-    rc = sort_run(HashedList{rows, s, r / s, seed}, pairs, r, k0, v0, k1, v1, ws, st, &sk, perm,
-                  bp, cnt + 1);
+    rc = sort_run(HashedList{rows, s, r / s, seed}, pairs, r, k0, v0, k1, v1, passes, ws, st,
+                  &sk, perm, bp, cnt + 1);
   else if (s == 1)
-    rc = sort_run(HashedRows{r, seed}, pairs, r, k0, v0, k1, v1, ws, st, &sk, perm, bp, nullptr);
-  else
-    rc = sort_run(HashedOsnap{s, r / s, seed}, pairs, r, k0, v0, k1, v1, ws, st, &sk, perm, bp,
+    rc = sort_run(HashedRows{r, seed}, pairs, r, k0, v0, k1, v1, passes, ws, st, &sk, perm, bp,
                   nullptr);
+  else
+    rc = sort_run(HashedOsnap{s, r / s, seed}, pairs, r, k0, v0, k1, v1, passes, ws, st, &sk, perm,
+                  bp, nullptr);
   if (rc) return rc;
   *bptr = bp;
   return 0;
