@@ -804,10 +804,10 @@ int rownorm_launch(const psk_mat &Am, const double *B, int64_t k, double alpha,
 // Past that it waits for its rows in the vector L1 (FP64 1e6 x 256: 55 TF/s
 // whatever the instruction count, before the wavefronts kept step; FP32, half
 // the bytes: 65).
-// Two arrangements.  WPT = 4, d <= 112: as above, a partial per workgroup;
-// narrow products are short of work, and the fewer partials matter most.
-// WPT = 1, wider: every wavefront has a tile and a slab of its own and
-// writes its own partial, so that the workgroup's wavefronts, mostly tiles of
+// Two arrangements.  WPT = 4, d <= 112 and many rows: as above, a partial per
+// workgroup; narrow products are short of work, and the fewer partials matter
+// most.  WPT = 1, wider or few rows: every wavefront has a tile and a slab of
+// its own and writes its own partial, so that the workgroup's wavefronts, mostly tiles of
 // one slab, find each other's rows in the L1; a barrier every group of rows
 // keeps the off-diagonal ones in step, without which they drift apart and
 // find nothing (us, without / with: FP64 1e6 x 256 1267 / 1190, 200,000 x 500
@@ -1097,6 +1097,15 @@ __global__ __launch_bounds__(64 * kGramGroups) void k_gram_reduce(
   C[e] = (TO)v;
 }
 
+// Wavefronts that share an item, for d <= 112 as said beside the kernel.  Up to
+// 24,000 rows such a product is a launch, a few groups of rows and the reduction,
+// and summing four wavefronts in LDS is most of it (us, four / one: 100 x 64
+// 34.8 / 29.9, 4000 x 97 37.1 / 35.1, 16,000 x 97 44.0 / 41.8, 32,000 x 97 48.3 /
+// 49.8).  A lean workspace has no room for the partials of one.
+int gram_wpt(int64_t n, int64_t d, bool lean) {
+  return d <= 112 && (n > 24000 || lean) ? kGramWaves : 1;
+}
+
 GramPlan gram_plan(int64_t n, int64_t d, int wpt, bool f64, bool lean) {
   GramPlan p{};
   p.T = (int)ceil_div(d, (int64_t)64);
@@ -1111,9 +1120,10 @@ GramPlan gram_plan(int64_t n, int64_t d, int wpt, bool f64, bool lean) {
   // are more: a narrow last tile waits for its rows (300,000 x 200 in FP64,
   // whose last tile is one block wide: 605 us by products alone, 302 by this
   // rule).  The last diagonal tile of a wavefront of its own waits longest, its
-  // loads are all it does: two more in FP64, one in FP32 past 256 columns (without them 120,000 x 836 in FP64 took 2397 us,
-  // its last tile alone in two slabs of 60,000 rows, now 1428; 200,000 x 452 1068
-  // and 765, 300,000 x 220 375 and 323)
+  // loads are all it does: two more in FP64, one in FP32 past 256 columns
+  // (without them 120,000 x 836 in FP64 took 2397 us, its last tile alone in two
+  // slabs of 60,000 rows, now 1428; 200,000 x 452 1068 and 765, 300,000 x 220 375
+  // and 323)
   const double nbt = p.nbt, wait = wpt > 1 ? 0.0 : f64 ? 2.0 : p.T > 4 ? 1.0 : 0.0;
   const double cost[4] = {16.0, std::max(4.0 * nbt, 2.0 * (4.0 + nbt)), 10.0,
                           std::max(0.5 * nbt * (nbt + 1.0), 2.0 * nbt + wait)};
@@ -1142,7 +1152,7 @@ template <typename TA>
 int gram_syrk_launch(double alpha, const psk_mat &Am, double beta, void *C, bool out_f32,
                      Arena &ws, hipStream_t st) {
   const int64_t n = Am.n, d = Am.d;
-  const int wpt = d <= 112 ? kGramWaves : 1;  // measured beside the kernel
+  const int wpt = gram_wpt(n, d, ws.lean);
   const GramPlan pl = gram_plan(n, d, wpt, sizeof(TA) == 8, ws.lean);
   const int64_t items = pl.first[4];
   double *part = ws.take<double>((size_t)items * 4096);
