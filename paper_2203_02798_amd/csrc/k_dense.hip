@@ -517,7 +517,7 @@ __global__ __launch_bounds__(kBresThreads) void k_rownorm_bres(
     const int64_t ffirst = k1 > 0 ? f1 : f2;
     // KW elements of each of the lane's rows, as loaded: a whole chunk in
     // vector loads; of the ragged chunk the columns inside d (the others read
-    // the row's first element and are masked when used).  A row past n reads
+    // the row's first element or four and are masked when used).  A row past n reads
     // row 0 and feeds only its own outputs, which are not stored.
     typedef TA RawChunk[MB][KW];
     auto load_whole = [&](const TA *const (&row)[MB], int64_t c, RawChunk &a)
@@ -531,13 +531,26 @@ __global__ __launch_bounds__(kBresThreads) void k_rownorm_bres(
         load_whole(row, c, a);
       } else {
         const int64_t left = d - (c * CK + 4 * kq);  // this lane's columns inside d
+        // Groups of four are inside or past d as a whole where d is a multiple of
+        // four (FP32, k = 16, element / vector loads: 300,000 x 28 51.5 / 46.2 us,
+        // 300,000 x 100 80.7 / 78.5).
+        if (d % 4 == 0) {
+          typedef TA Four[4];
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+          for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-          for (int s = 0; s < KW; ++s) {
-            const int k = 16 * (s / 4) + s % 4;
-            a[mb][s] = row[mb][k < left ? c * CK + k : -(int64_t)(4 * kq)];
-          }
+            for (int g = 0; g < KW / 4; ++g)
+              row_load<TA, 4>(row[mb] + (16 * g < left ? c * CK + 16 * g : -(int64_t)(4 * kq)),
+                              *reinterpret_cast<Four *>(&a[mb][4 * g]));
+        } else {
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int s = 0; s < KW; ++s) {
+              const int k = 16 * (s / 4) + s % 4;
+              a[mb][s] = row[mb][k < left ? c * CK + k : -(int64_t)(4 * kq)];
+            }
+        }
       }
     };
     auto rows_of = [&](int64_t t, const TA *(&row)[MB]) __attribute__((always_inline)) {
