@@ -353,8 +353,9 @@ __device__ __forceinline__ void row_load(const TA *p, TA (&x)[KW]) {
 // Fused row norms with a column tile of B resident in LDS.  A workgroup
 // works on tiles p and T - 1 - p of the T = ceil(k / 32) 32-column tiles of B
 // (one when they coincide): both at once when they fit in LDS (PAIR true),
-// else one after the other.  Its B columns (rows padded to a multiple of the
-// K chunk with zeros, row stride BNC + 4) are staged; the 8 wavefronts then stream
+// else one after the other, or on one tile only (tn = T) where that ends
+// sooner.  Its B columns (rows padded to a multiple of the K chunk with zeros,
+// row stride BNC + 4) are staged; the 8 wavefronts then stream
 // row tiles of A (kBresMB blocks of 16 rows) straight from memory into the
 // MFMA operand registers (no LDS round trip and no barrier in the main loop)
 // and keep kBresMB x BNC/16 accumulator blocks.
@@ -429,7 +430,7 @@ __global__ __launch_bounds__(kBresThreads) void k_rownorm_bres(
   const int64_t drows = kch * CK;
   const int64_t ntiles = (n + kBresRows - 1) / kBresRows;
   const int64_t t0 = wave * ngroups + group, tstep = ngroups * kBresWaves;
-  for (int pass = 0; pass < (PAIR ? 1 : 2); ++pass) {
+  for (int pass = 0; pass < (PAIR || tn == ntile ? 1 : 2); ++pass) {
     const int64_t ta = pass ? ntile - 1 - nt : nt;  // the tile, or the first of the two
     if (pass) {
       if (ta == nt) break;
@@ -706,6 +707,37 @@ int bres_width(int64_t d, int64_t k) {
   return 0;
 }
 
+// Row groups of tn workgroups: one workgroup per CU (the LDS tile), so that each
+// XCD holds whole groups.
+int64_t bres_groups(int64_t n, int tn) {
+  const int64_t tiles = ceil_div(n, (int64_t)kBresRows);
+  int64_t groups = 256 / tn;
+  if (groups < 8) groups = 8;
+  groups = (groups / 8) * 8;
+  const int64_t need = ceil_div(tiles, (int64_t)kBresWaves);  // row tiles per wavefront round
+  // fewer groups for few rows, still whole eights (the kernel deals groups to
+  // XCDs by linear id mod 8; 80 halved to 20 or 10 left rows without a group)
+  while (groups > 8 && groups / 16 * 8 >= need) groups = groups / 16 * 8;
+  return groups;
+}
+
+// Workgroups per row group, single tiles (bw 1): a workgroup takes two tiles in
+// turn, T / 2 workgroups a group, or one, T a group and so fewer groups.  The
+// costs compared are rounds of row tiles times the tiles' extents: two tiles of a
+// B with fewer columns than rows are two whole ones, those of a square B are
+// taken for a triangular one's, which together are one and a little (T + 1) / T.
+// Few rows leave CUs idle when paired (FP64, k = 64, two / one in us: 3000 x 320
+// 75.8 / 49.7, 30,000 x 320 80.0 / 52.7), many are the same either way (100,000 x
+// 320: 125.9).
+int bres_single_tn(int64_t n, int64_t d, int64_t k) {
+  const int64_t ntile = ceil_div(k, (int64_t)kBresTile);
+  const int pair = (int)ceil_div(ntile, (int64_t)2);
+  const int64_t tiles = ceil_div(n, (int64_t)kBresRows);
+  auto rounds = [&](int tn) { return ceil_div(tiles, bres_groups(n, tn) * kBresWaves); };
+  const int64_t two = rounds(pair) * (k < d ? 2 * ntile : ntile + 1);
+  return rounds((int)ntile) * ntile < two ? (int)ntile : pair;
+}
+
 template <typename TA, bool PAIR, bool RAG>
 int bres_launch_as(const psk_mat &Am, const double *B, int64_t k, double *part, int tn,
                 hipStream_t st) {
@@ -715,16 +747,7 @@ int bres_launch_as(const psk_mat &Am, const double *B, int64_t k, double *part, 
       (size_t)ceil_div(d, (int64_t)(4 * kBresKW)) * (4 * kBresKW) * (BNC + 4) * sizeof(double);
   PSK_HIP_TRY(hipFuncSetAttribute((const void *)k_rownorm_bres<TA, PAIR, RAG>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  // one workgroup per CU (the LDS tile), row groups of tn workgroups per XCD
-  const int64_t tiles = ceil_div(n, (int64_t)kBresRows);
-  int64_t groups = 256 / tn;
-  if (groups < 8) groups = 8;
-  groups = (groups / 8) * 8;
-  const int64_t need = ceil_div(tiles, (int64_t)kBresWaves);  // row tiles per wavefront round
-  // fewer groups for few rows, still whole eights (the kernel deals groups to
-  // XCDs by linear id mod 8; 80 halved to 20 or 10 left rows without a group)
-  while (groups > 8 && groups / 16 * 8 >= need) groups = groups / 16 * 8;
-  const unsigned nblk = (unsigned)(groups * tn);
+  const unsigned nblk = (unsigned)(bres_groups(n, tn) * tn);
   KTimer timer("rownorm", st);
   k_rownorm_bres<TA, PAIR, RAG><<<nblk, kBresThreads, lds, st>>>(
       (const TA *)Am.values, Am.ld, n, d, B, k, tn, part);
@@ -748,7 +771,7 @@ int rownorm_launch(const psk_mat &Am, const double *B, int64_t k, double alpha,
     // a workgroup's two 32-column tiles give one sum per row together (bw 2,
     // both in LDS at once) or one each (bw 1, one after the other)
     const int64_t ntile = ceil_div(k, (int64_t)kBresTile);
-    const int tn = (int)ceil_div(ntile, (int64_t)2);
+    const int tn = bw == 2 ? (int)ceil_div(ntile, (int64_t)2) : bres_single_tn(n, d, k);
     const int slots = bw == 2 ? tn : (int)ntile;  // sums per row
     double *part = ws.take<double>((size_t)slots * n);
     if (ws.dry()) return 0;
