@@ -46,6 +46,23 @@ struct Arena {
 // point: synchronises st (k_check.hip).
 int read_back(void *dst, const void *src, size_t bytes, hipStream_t st);
 
+// The same in parts: start() and mark() put the copy on st, wait() waits for it
+// and not for what was put on st since.  A buffer that was not taken back, since
+// something failed and its copy may be pending, is not used again.
+struct ReadBack {
+  void *p = nullptr;
+  size_t bytes = 0;
+  hipEvent_t done = nullptr;
+  int start(const void *src, size_t n, hipStream_t st);
+  int mark(hipStream_t st);
+  int wait(void *dst);
+  void take(void *dst);
+  ReadBack() = default;
+  ReadBack(const ReadBack &) = delete;
+  ReadBack &operator=(const ReadBack &) = delete;
+  ~ReadBack();
+};
+
 inline size_t elem_size(int dtype) { return dtype == PSK_F64 ? 8 : 4; }
 
 // Event bracket around a launch (or region) when timing is enabled:

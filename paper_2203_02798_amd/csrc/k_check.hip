@@ -27,8 +27,16 @@ std::vector<void *> g_back;
 // host twice: a kernel, this copy and the wait take 23 us that way, 14 with
 // the copy into pinned memory (11 without a copy).
 int read_back(void *dst, const void *src, size_t bytes, hipStream_t st) {
-  if (bytes > kBackBytes) return fail(PSK_EINVAL, "read_back of more than 4 KiB");
-  void *p = nullptr;
+  ReadBack rb;
+  if (const int rc = rb.start(src, bytes, st)) return rc;
+  const hipError_t e = hipStreamSynchronize(st);
+  if (e == hipSuccess) rb.take(dst);
+  PSK_HIP_TRY(e);
+  return 0;
+}
+
+int ReadBack::start(const void *src, size_t n, hipStream_t st) {
+  if (n > kBackBytes) return fail(PSK_EINVAL, "read_back of more than 4 KiB");
   {
     std::lock_guard<std::mutex> lk(g_back_mu);
     if (!g_back.empty()) {
@@ -37,15 +45,32 @@ int read_back(void *dst, const void *src, size_t bytes, hipStream_t st) {
     }
   }
   if (!p) PSK_HIP_TRY(hipHostMalloc(&p, kBackBytes, hipHostMallocPortable));
-  hipError_t e = hipMemcpyAsync(p, src, bytes, hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  // after an error the copy may still be pending: the buffer is not used again
-  PSK_HIP_TRY(e);
+  bytes = n;
+  PSK_HIP_TRY(hipMemcpyAsync(p, src, n, hipMemcpyDeviceToHost, st));
+  return 0;
+}
+
+int ReadBack::mark(hipStream_t st) {
+  PSK_HIP_TRY(hipEventCreateWithFlags(&done, hipEventDisableTiming));
+  PSK_HIP_TRY(hipEventRecord(done, st));
+  return 0;
+}
+
+int ReadBack::wait(void *dst) {
+  PSK_HIP_TRY(hipEventSynchronize(done));
+  take(dst);
+  return 0;
+}
+
+void ReadBack::take(void *dst) {
   memcpy(dst, p, bytes);
   std::lock_guard<std::mutex> lk(g_back_mu);
   if (g_back.size() < kBackKept) g_back.push_back(p);
   else (void)hipHostFree(p);
-  return 0;
+}
+
+ReadBack::~ReadBack() {
+  if (done) (void)hipEventDestroy(done);
 }
 
 namespace {

@@ -37,9 +37,15 @@
 // panel out of G (k_schur: 5 us), and 100 pivots of 1000 x 500 take 0.23 ms
 // with G, not 0.63.  What squaring loses is watched: a pivot counts only if it leads the
 // next candidate by more than kPivotGap of the largest squared norm, some
-// 1e5 times what rounding can have moved either; at the first that does not
-// (equal columns, norms near rounding level, nothing left) the whole
-// selection is made by the QR steps instead.
+// 1e5 times what rounding can have moved either.  At the first that does not
+// (equal columns, norms near rounding level, nothing left) the QR steps take
+// over.  They need the sketch as the steps before would have left it, and with
+// the pivots known that is made sixteen steps a pass (k_replay_panel and
+// k_replay_rest: 24 + 18 us for 16 at 1000 x 500, 2.6 a pivot), in the steps' own
+// arithmetic: the rest of the selection is, bit for bit, what steps from the
+// start choose.  Whole calls in us, steps alone / search and steps: 1000 x 500,
+// k = 500, singular values over eight decades 2867 / 2620, equal columns near the
+// start 2910 / 2890; 2000 x 1000, k = 1000, eight decades 11,515 / 9080.
 #include <type_traits>
 
 #include "internal.hpp"
@@ -204,6 +210,203 @@ __global__ __launch_bounds__(256) void k_qrcp_step(double *__restrict__ Bt, int6
     if (lane == 0) col[j] = fma(-s, v0, cj);
   }
   if (lane == 0) nout[c] = nn;
+}
+
+// ---------------------------------------------------------------------------
+// steps whose pivots are known
+// ---------------------------------------------------------------------------
+// A column of Bt as a wavefront holds it from row 64 tb on: lane l has the rows
+// 64 (tb + u) + l, in registers (R > 0: u < R reaches the column's end) or in
+// memory (R = 0; a lane reads back only what it wrote itself).  Row j is in
+// u = 0 or 1 for the steps of one pass that starts in row block tb.
+// k_qrcp_step's lane i at step j sums the rows j + 1 + i, j + 1 + i + 64, ..: the
+// rows below j of this lane's (j + 1 + i) mod 64, in the same order.  So a sum
+// here takes zeros for the rows up to j, which leave it as it is, and its lanes
+// are rotated before they are added: the same additions.
+template <int R>
+struct QrColumn {
+  double *col;
+  int64_t rows, tb;
+  int lane;
+  double c[R > 0 ? R : 1];
+
+  __device__ __forceinline__ int64_t row(int64_t u) const { return 64 * (tb + u) + lane; }
+  __device__ __forceinline__ void load() {
+    if constexpr (R > 0) {
+#pragma unroll
+      for (int u = 0; u < R; ++u) c[u] = row(u) < rows ? col[row(u)] : 0.0;
+    }
+  }
+  __device__ __forceinline__ void store() {
+    if constexpr (R > 0) {
+#pragma unroll
+      for (int u = 0; u < R; ++u)
+        if (row(u) < rows) col[row(u)] = c[u];
+    }
+  }
+  // row j of the column (uniform)
+  __device__ __forceinline__ double at(int64_t j) const {
+    const int64_t u = (j >> 6) - tb;
+    double e;
+    if constexpr (R > 0) e = u == 0 ? c[0] : c[1];
+    else e = row(u) < rows ? col[row(u)] : 0.0;
+    return __shfl(e, (int)(j & 63), 64);
+  }
+  // sum over the lanes in the order of step j
+  __device__ __forceinline__ double sum(double part, int64_t j) const {
+    return wave_sum(__shfl(part, (int)((lane + j + 1) & 63), 64));
+  }
+  // The step j of this column, as k_qrcp_step makes it: x(u) is the reflector's
+  // column at row(u), zero up to row j and past the end.  Returns the squared
+  // norm of the rows below j when it is asked for.
+  template <class X>
+  __device__ __forceinline__ double step(X x, double v0, double vtv, int64_t j, bool norm) {
+    constexpr int N = R > 0 ? R : 16;  // R = 0: as many rows loaded at once
+    const int64_t end = R > 0 ? N : (rows + 63) / 64 - tb;
+    const double cj = at(j);
+    double s = 0.0, part = 0.0, part2 = 0.0;
+    for (int64_t b = 0; b < end; b += N) {
+      double xv[N], cv[N];
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        xv[u] = x(b + u);
+        cv[u] = R > 0 ? c[R > 0 ? u : 0] : row(b + u) < rows ? col[row(b + u)] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < N; ++u) part = fma(xv[u], cv[u], part);
+    }
+    if (vtv != 0.0) s = 2.0 * fma(v0, cj, sum(part, j)) / vtv;
+    for (int64_t b = 0; b < end; b += N) {
+      double xv[N], cv[N];
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        xv[u] = x(b + u);
+        cv[u] = R > 0 ? c[R > 0 ? u : 0] : row(b + u) < rows ? col[row(b + u)] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        const double y = fma(-s, xv[u], cv[u]);
+        if constexpr (R > 0) c[u] = y;
+        else if (row(b + u) < rows) col[row(b + u)] = y;
+        const double z = (R == 0 || u < 2) && row(b + u) <= j ? 0.0 : y;
+        part2 = fma(z, z, part2);
+      }
+    }
+    return norm ? sum(part2, j) : 0.0;
+  }
+};
+
+// The steps j0 .. j0 + nb - 1, nb <= W, of the columns that they choose
+// (cols[j0 ..]): one workgroup, a wavefront per column.  Column t is final after
+// t steps, is handed to the others through LDS (R = 0: through memory) and is
+// the reflector of the next.  refl[2 t], refl[2 t + 1]: v's first element and
+// v^T v, 0 for no reflection.  Two buffers, so one barrier a step.  Bound by the
+// chain of a step: two sums over the lanes, a square root and a division.
+template <int R, int W>
+__global__ __launch_bounds__(64 * W) void k_replay_panel(double *__restrict__ Bt, int64_t rows,
+                                                         int64_t j0, int nb,
+                                                         const double *__restrict__ norms,
+                                                         const int32_t *__restrict__ cols,
+                                                         double *__restrict__ refl) {
+  extern __shared__ double xs[];  // 2 x 64 R
+  __shared__ double vs[2][2];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const bool mine = wave < nb;
+  const int64_t p = mine ? cols[j0 + wave] : 0;
+  QrColumn<R> q{Bt + p * rows, rows, j0 >> 6, lane};
+  if (mine) q.load();
+  double n2 = mine ? norms[p] : 0.0;
+  for (int t = 0; t < nb; ++t) {
+    const int64_t j = j0 + t;
+    double *xt = xs + (t & 1) * 64 * R;
+    if (wave == t) {
+      double v0 = 0.0, vtv = 0.0;
+      if (n2 > 0.0) {
+        const double alpha = q.at(j);
+        const double nx = sqrt(n2);
+        const double beta = alpha >= 0.0 ? -nx : nx;
+        v0 = alpha - beta;
+        vtv = 2.0 * beta * (beta - alpha);
+      }
+      if constexpr (R > 0) {
+#pragma unroll
+        for (int u = 0; u < R; ++u) xt[64 * u + lane] = u < 2 && q.row(u) <= j ? 0.0 : q.c[u];
+      }
+      if (lane == 0) {
+        vs[t & 1][0] = refl[2 * t] = v0;
+        vs[t & 1][1] = refl[2 * t + 1] = vtv;
+      }
+    }
+    __syncthreads();
+    if (!mine || wave <= t) continue;
+    const double v0 = vs[t & 1][0], vtv = vs[t & 1][1];
+    const bool next = wave == t + 1;
+    double nn;
+    if constexpr (R > 0) {
+      nn = q.step([&](int64_t u) { return xt[64 * u + lane]; }, v0, vtv, j, next);
+    } else {
+      const double *x = Bt + (int64_t)cols[j] * rows;
+      nn = q.step([&](int64_t u) { return q.row(u) > j && q.row(u) < rows ? x[q.row(u)] : 0.0; },
+                  v0, vtv, j, next);
+    }
+    if (next) n2 = nn;
+  }
+  if (mine) q.store();
+}
+
+// The same steps of every other live column, a wavefront each; norms: theirs
+// after the last of them, -1 for the columns chosen.  A workgroup stages the
+// reflector of the next step in LDS beside a step (R = 0: reads it from memory).
+template <int R>
+__global__ __launch_bounds__(256) void k_replay_rest(double *__restrict__ Bt, int64_t rows,
+                                                     int64_t d, int64_t j0, int nb,
+                                                     const double *__restrict__ refl,
+                                                     const int32_t *__restrict__ cols,
+                                                     double *__restrict__ norms) {
+  extern __shared__ double xs[];  // 2 x 64 R
+  const int lane = threadIdx.x & 63;
+  const int64_t c = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const bool chosen =
+      __ballot(lane < nb && cols[j0 + (lane < nb ? lane : 0)] == c) != 0;
+  const bool live = c < d && !chosen && !(norms[c < d ? c : 0] < 0.0);
+  if (chosen && lane == 0) norms[c] = -1.0;
+  QrColumn<R> q{Bt + (live ? c : 0) * rows, rows, j0 >> 6, lane};
+  if (live) q.load();
+  double nn = 0.0;
+  if constexpr (R > 0) {
+    constexpr int M = R / 4;  // elements of a reflector a thread stages
+    const int64_t first = 64 * (j0 >> 6) + threadIdx.x;
+    double x[M];
+    auto fetch = [&](int t) __attribute__((always_inline)) {
+      const double *xp = Bt + (int64_t)cols[j0 + t] * rows;
+#pragma unroll
+      for (int u = 0; u < M; ++u) {
+        const int64_t i = first + 256 * u;
+        x[u] = i < rows && i > j0 + t ? xp[i] : 0.0;
+      }
+    };
+    fetch(0);
+    for (int t = 0; t < nb; ++t) {
+      double *xt = xs + (t & 1) * 64 * R;
+#pragma unroll
+      for (int u = 0; u < M; ++u) xt[threadIdx.x + 256 * u] = x[u];
+      __syncthreads();
+      if (t + 1 < nb) fetch(t + 1);
+      if (live)
+        nn = q.step([&](int64_t u) { return xt[64 * u + lane]; }, refl[2 * t], refl[2 * t + 1],
+                    j0 + t, t == nb - 1);
+    }
+  } else if (live) {
+    for (int t = 0; t < nb; ++t) {
+      const int64_t j = j0 + t;
+      const double *x = Bt + (int64_t)cols[j] * rows;
+      nn = q.step([&](int64_t u) { return q.row(u) > j && q.row(u) < rows ? x[q.row(u)] : 0.0; },
+                  refl[2 * t], refl[2 * t + 1], j, t == nb - 1);
+    }
+  }
+  if (!live) return;
+  q.store();
+  if (lane == 0) norms[c] = nn;
 }
 
 // ---------------------------------------------------------------------------
@@ -377,6 +580,7 @@ __global__ __launch_bounds__(256) void k_schur(double *__restrict__ G, int64_t d
                                                const int *__restrict__ state) {
   __shared__ double la[kPanel][16];
   const int stopped = state[1];
+  if (d > 1024 && stopped) return;  // (waited for: below, that is most of the launch)
   const int x = threadIdx.x & 63, y = threadIdx.x >> 6;
   const int64_t c = (int64_t)blockIdx.x * 64 + x, a0 = (int64_t)blockIdx.y * 16;
   const int64_t cc = c < d ? c : d - 1;
@@ -470,7 +674,7 @@ int css_select_impl(const psk_mat &A, int64_t m, int64_t r, int64_t k, uint64_t 
   const int64_t room = rows * d - d * d;
   const bool search =
       k > 1 && gram_us < steps_us && room >= dgram_room(d) && room >= kPanel * d;
-  int h[4] = {0, 0, 0, 1};
+  int h[4] = {0, 0, 0, 1};  // h[2]: pivots found, h[3]: some are left to the steps
   if (search) {
     KTimer timer("pivots", st);
     double *G = Bt, *L = Bt + d * d;  // L where the partial sums of G were
@@ -479,6 +683,7 @@ int css_select_impl(const psk_mat &A, int64_t m, int64_t r, int64_t k, uint64_t 
     const dim3 sg((unsigned)ceil_div(d, (int64_t)64), (unsigned)ceil_div(d, (int64_t)16));
     // a column a thread while 1024 threads suffice; the factor rows of a panel
     // fit LDS (128 KiB)
+    ReadBack early;
     auto panels = [&](auto own, auto np) -> int {
       constexpr int OWN = decltype(own)::value, NP = decltype(np)::value;
       const unsigned threads = (unsigned)(ceil_div(d, (int64_t)(64 * OWN)) * 64);
@@ -489,6 +694,17 @@ int css_select_impl(const psk_mat &A, int64_t m, int64_t r, int64_t k, uint64_t 
         const int n1 = (int)(k - j < NP ? k - j : NP);
         k_pivot_panel<OWN, NP><<<1, threads, lds, st>>>(G, d, j, n1, na, nb, L, flag + 2, cols);
         if (j + n1 < k) k_schur<<<sg, 256, 0, st>>>(G, d, n1, L, flag + 2);
+        // Panels after a stop find nothing to do, at two launches each.  A long
+        // search that has stopped in its first two panels is ended; the third runs
+        // while the host waits to know (1000 x 500, k = 500, the first two columns
+        // equal: 3230 us without, 2940 so).
+        if (j == NP && k > 14 * NP) {
+          if (int rb = early.start(flag + 2, 2 * sizeof(int), st)) return rb;
+          if (int rb = early.mark(st)) return rb;
+        } else if (j == 2 * NP && k > 14 * NP) {
+          if (int rb = early.wait(h + 2)) return rb;
+          if (h[3]) break;
+        }
       }
       return 0;
     };
@@ -506,7 +722,33 @@ int css_select_impl(const psk_mat &A, int64_t m, int64_t r, int64_t k, uint64_t 
   k_transpose<<<tg, 256, 0, st>>>(C, rows, d, Bt);
   const unsigned cb = (unsigned)ceil_div(d, (int64_t)4);
   k_col_norms<<<cb, 256, 0, st>>>(Bt, rows, d, na);
-  for (int64_t j = 0; j < k; ++j) {
+  // the steps whose pivots are known, a pass of 16 or 8 (the registers of a column)
+  auto replay = [&](auto regs, auto width, int64_t j) -> int {
+    constexpr int R = decltype(regs)::value, W = decltype(width)::value;
+    const int steps = (int)(h[2] - j < W ? h[2] - j : W);
+    const size_t lds = (size_t)2 * 64 * R * sizeof(double);
+    double *refl = C;  // the sketch is in Bt now
+    PSK_HIP_TRY(hipFuncSetAttribute((const void *)k_replay_panel<R, W>,
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    PSK_HIP_TRY(hipFuncSetAttribute((const void *)k_replay_rest<R>,
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    k_replay_panel<R, W><<<1, 64 * W, lds, st>>>(Bt, rows, j, steps, na, cols, refl);
+    k_replay_rest<R><<<cb, 256, lds, st>>>(Bt, rows, d, j, steps, refl, cols, na);
+    return steps;
+  };
+  for (int64_t j = 0; j < h[2];) {
+    using std::integral_constant;
+    using W16 = integral_constant<int, 16>;
+    using W8 = integral_constant<int, 8>;
+    const int64_t blocks = ceil_div(rows, (int64_t)64) - (j >> 6);
+    const int rc = blocks <= 16   ? replay(W16{}, W16{}, j)
+                   : blocks <= 32 ? replay(integral_constant<int, 32>{}, W8{}, j)
+                   : blocks <= 64 ? replay(integral_constant<int, 64>{}, W8{}, j)
+                                  : replay(integral_constant<int, 0>{}, W16{}, j);
+    if (rc < 0) return rc;
+    j += rc;
+  }
+  for (int64_t j = h[2]; j < k; ++j) {
     k_qrcp_step<<<cb, 256, 0, st>>>(Bt, rows, d, j, na, nb, cols);
     double *t = na;
     na = nb;
