@@ -1134,12 +1134,14 @@ __global__ __launch_bounds__(64 * kGramGroups) void k_gram_reduce(
 }
 
 // Wavefronts that share an item, for d <= 112 as said beside the kernel.  Up to
-// 24,000 rows such a product is a launch, a few groups of rows and the reduction,
+// 2000 rows such a product is a launch, a few groups of rows and the reduction,
 // and summing four wavefronts in LDS is most of it (us, four / one: 100 x 64
-// 34.8 / 29.9, 4000 x 97 37.1 / 35.1, 16,000 x 97 44.0 / 41.8, 32,000 x 97 48.3 /
-// 49.8).  A lean workspace has no room for the partials of one.
+// 34.8 / 29.9, 500 x 112 37.3 / 33.5).  Past that one is little faster (16,000 x
+// 97 44.0 / 41.8) and holds 2.5 times the partials, which narrow requests in a
+// small server pool would run fewer at once for (20,000 x 50 in 20 MB: 384 us
+// each, not 143).  A lean workspace has no room for them at all.
 int gram_wpt(int64_t n, int64_t d, bool lean) {
-  return d <= 112 && (n > 24000 || lean) ? kGramWaves : 1;
+  return d <= 112 && (n > 2000 || lean) ? kGramWaves : 1;
 }
 
 GramPlan gram_plan(int64_t n, int64_t d, int wpt, bool f64, bool lean) {

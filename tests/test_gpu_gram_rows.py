@@ -13,7 +13,7 @@ pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
 
 
-@pytest.mark.parametrize("n", [1, 47, 49, 1000, 24000, 24001, 50007])
+@pytest.mark.parametrize("n", [1, 47, 49, 1000, 2000, 2001, 24000, 50007])
 @pytest.mark.parametrize("d,dt", [(1, "f64"), (49, "f32"), (64, "f64"), (65, "f64"), (97, "f32"),
                                   (112, "f64"), (113, "f64")])
 def test_gram_rows(n, d, dt):
@@ -32,7 +32,7 @@ def test_gram_rows(n, d, dt):
     if dt == "f32":
         bar = bar + 2.0 ** -24 * np.abs(ref)
     # half the full plan's partials hold the lean plan of few rows (128 rows a slab, not 48)
-    for size in (full, full // 2 if d <= 112 and 4000 < n <= 24000 else full):
+    for size in (full, full // 2 if d <= 112 and n == 2000 else full):
         c = torch.zeros(d, d, dtype=dev.dtype, device="cuda")
         rc = L.lib().gram(1.0, ctypes.byref(mat), 0.0, c.data_ptr(), base, size,
                           torch.cuda.current_stream().cuda_stream)
