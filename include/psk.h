@@ -573,10 +573,14 @@ int psk_probe_valu_f32(int64_t iters, float *out, void *stream);
  * is admitted when a slot is free and its whole workspace fits in the
  * caller's device pool, which the server carves with a first-fit allocator,
  * so the workspace footprint of the requests in flight never exceeds
- * pool_bytes.  Admission is strictly first-in first-out.  Requests on
- * different slots run concurrently on the device; each request's result is
- * the same bit for bit as when it runs alone (its kernels read only its own
- * inputs and workspace).
+ * pool_bytes.  Admission is strictly first-in first-out.  A request takes
+ * what psk_workspace_size gives for its call (lsq_solve, or leverage_sketch
+ * without the JL step), in whole 256 bytes: a pool of that for each slot
+ * keeps all slots busy.  One that is larger than the whole pool runs with
+ * the smaller workspace that its call accepts, if the pool holds that.
+ * Requests on different slots run concurrently on the device; each
+ * request's result is the same bit for bit as when it runs alone (its
+ * kernels read only its own inputs and workspace).
  *
  * Requests:
  *   PSK_REQ_LSQ       x = argmin ||A x - b|| exactly as lsq_solve with
