@@ -672,14 +672,13 @@ __global__ __launch_bounds__(256) void k_diag_ratio(const double *__restrict__ R
 }
 
 // The second half of an iteration in one launch: every workgroup computes
-// v of the previous iteration is read from v_in and the new one written to
-// v_out (the two alternate), since every workgroup reads v while the extra
-// one writes it.
 // vnew_j = sum_{b <= j / kVRows} vpart[b][j] - beta v_j (partials in order),
 // alpha = ||vnew|| (one fixed order, so every workgroup has the same bits)
-// and rows of vhat = R^{-1} (vnew / alpha), 8 rows per workgroup.  The one
-// extra workgroup (index nb) runs the scalar recurrences, the v, w, y
-// updates and the stopping test, which no other workgroup of this launch
+// and rows of vhat = R^{-1} (vnew / alpha), 8 rows per workgroup.  v of the
+// previous iteration is read from v_in and the new one written to v_out (the
+// two alternate), since every workgroup reads v while the extra one writes
+// it.  The one extra workgroup (index nb) runs the scalar recurrences, the v,
+// w, y updates and the stopping test, which no other workgroup of this launch
 // reads; a stop it signals turns the following launches into no-ops.
 template <int NBV>  // bound on the number of vnew partials (ceil(d / kVRows))
 __global__ __launch_bounds__(256) void k_update(const double *__restrict__ Rinv, int64_t d,

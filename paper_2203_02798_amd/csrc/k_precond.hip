@@ -11,15 +11,19 @@
 // after two or three passes.  Forming W from G squares cond(A) where forming
 // A N would not, but costs half of A N's own products and no n x d scratch.
 //
-// The rounding: |dG_kl| <= c u g_k g_l with g_k = ||A e_k||, so the error of
-// P^T G P is at most E = c u sum_j t_j^2, t_j = sum_k |P_kj| g_k, in
-// Frobenius norm, whatever the scaling of A's columns.  k_guard sums t_j^2.
-// It is asked twice: before G is formed, with N in P's place and g from R
-// (or, for a caller's N, a lower bound of it from N's diagonal and, where that
-// leaves doubt, some of A's rows), where E above kPrecondMax leaves the sketch's N as it is (cond(A)
-// beyond about 1e6); and afterwards with P and G's diagonal, on the device:
-// k_precond_pick puts N back into P when E is too large or a pivot failed, so
-// a bad P never reaches LSQR.
+// The rounding is taken as |dG_kl| ~ c u g_k g_l with g_k = ||A e_k|| and c = 16,
+// which makes the error of P^T G P about E = c u sum_j t_j^2, t_j =
+// sum_k |P_kj| g_k, in Frobenius norm, whatever the scaling of A's columns.
+// That is an estimate and no bound: a sum's worst rounding grows with its
+// length (rows of a slab, entries of a column of a CSR A) and its typical one
+// with the root of it.  What it decides is only how many passes LSQR takes; its
+// stopping rule and the refinement do not rest on it.  k_guard sums t_j^2.
+// It is asked twice: before G is formed, with N in P's place and g from R (or,
+// for a caller's N, a lower bound of it from N's diagonal and, where that leaves
+// doubt, some of A's rows), where E above kPrecondMax leaves the sketch's N as
+// it is (cond(A) beyond about 7e6 / sqrt(d)); and afterwards with P and G's
+// diagonal, on the device: k_precond_pick puts N back into P when E is too large
+// or a pivot failed, so such a P never reaches LSQR.
 #include <math.h>
 
 #include <cmath>
