@@ -418,10 +418,11 @@ typedef struct psk_lsq_info {
  * operator A*R^{-1} (Paige & Saunders 1982) in FP64, x = R^{-1} y, then
  * `refine` passes that solve for the residual and add the correction.
  * Where it saves time and A is not too ill-conditioned for it (condition
- * numbers to about 1e6 at d = 50, 4e5 at d = 256), R^{-1} is first sharpened by A's Gram matrix, P =
- * R^{-1} S^{-1} with S^T S = R^{-T} A^T A R^{-1}, and takes R^{-1}'s place in
- * LSQR, which then stops after a few iterations; max_iter below 100 and a
- * workspace that only holds LSQR's vectors keep R^{-1} itself.
+ * numbers to about 1e6 at d = 50, 4e5 at d = 256), R^{-1} is first sharpened
+ * by A's Gram matrix, P = R^{-1} S^{-1} with S^T S = R^{-T} A^T A R^{-1}, and
+ * P takes R^{-1}'s place in LSQR, which then stops after a few iterations;
+ * max_iter below 100 and a workspace that only holds LSQR's vectors keep
+ * R^{-1} itself.
  *   b : n FP64 (device);  x : d FP64 (device, output).
  * The call enqueues LSQR iterations in groups of check_every; each group's
  * convergence flag is copied to pinned host memory (a few pinned bytes per
